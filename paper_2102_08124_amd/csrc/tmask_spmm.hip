@@ -4,30 +4,25 @@
 //
 //     y[t][r] = sum_c x[t][c] * Wd[r][c],   Wd = the rows x cols matrix whose compressed form is (vals, idx)
 //
-// The instruction: D(16x16, fp32) += A(16x64, 2:4 sparse along k, bf16) * B(64x16, bf16).  Lane l of the
-// wavefront holds, with m = l % 16 and a = l / 16:
+// The instructions: D(16x16, fp32) += A(16x64, 2:4 sparse along k, bf16) * B(64x16, bf16), and the same as
+// 32x32 += 32x32 * 32x32.  Lane l of the wavefront holds, with m = l % 16 and a = l / 16 (m = l % 32, a = l / 32):
 //   A: 8 compressed values of row m: the two values of each of the groups of four g0, g0+1, g0+4, g0+5,
-//      g0 = 8 (a % 2) + 2 (a / 2), i.e. two runs of four consecutive compressed values;
+//      g0 = 8 (a % 2) + 2 (a / 2) (g0 = 2 a), i.e. two runs of four consecutive compressed values;
 //   index register: bits 2j..2j+1 = position inside its group of the j-th value, j = 0..7 (low 16 bits);
 //   B: 16 consecutive k of column n = m: k = 16 a .. 16 a + 15;
-//   D: rows 4 a .. 4 a + 3 of column m.
-// (Layout established by one-hot probes on the hardware; the tests compare whole products with a CPU
-// reference, which fixes every part of it.)  One byte of the packed `idx` array holds the positions of
-// two consecutive groups, low nibble first, two bits per value in slot order: exactly eight index bits of
-// the instruction, so the packed operands feed it unchanged.
+//   D: rows 4 a .. 4 a + 3 of column m (rows 8 (i / 4) + 4 a + i % 4, i = 0 .. 15).
+// (Layouts established by probes on the hardware; the tests compare whole products with a CPU reference, which fixes
+// every part of them.)  One byte of the packed `idx` array holds the positions of two consecutive groups, low nibble
+// first, two bits per value in slot order: exactly eight index bits of the instruction, so the packed operands feed
+// it unchanged.
 //
-// Tiling: a workgroup computes 256 rows x 128 tokens with eight wavefronts in two roles.  Wavefronts 0-3
-// multiply (2 x 2, each 128 x 64 = 8 x 4 instruction tiles, 128 accumulator registers): they only read
-// fragments from LDS and issue matrix instructions.  Wavefronts 4-7 feed them: per step of k = 64 they move
-// the compressed A tile (256 x 32 values + 256 x 8 index bytes) and the x tile (128 tokens x 64) from global
-// memory through registers into a ring of three LDS buffers, with three register sets, so a load is in flight
-// for three steps before it is needed.  One barrier per step joins the two roles; each SIMD holds one wavefront
-// of each role, so the feeders' waits and LDS writes overlap the multipliers' matrix instructions.  A workgroup
-// is persistent: it takes every G-th tile and treats their steps as one stream, so nothing drains between
-// tiles.  LDS rows are padded so that fragment reads are conflict-free.
+// Two kernels: one whose wavefronts split the reduction of a small tile, for products with few tokens or few rows, and
+// one whose wavefronts share a large tile.  tmask_spmm24 (at the end) chooses between their tile sizes.
 #include <hip/hip_runtime.h>
 
+#include <cmath>
 #include <cstdint>
+#include <type_traits>
 
 #include "../../include/tmask.h"
 #include "tmask_host.hpp"
@@ -37,22 +32,11 @@ namespace tmask {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t su32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t su32x2 __attribute__((ext_vector_type(2)));
 
-constexpr int kSpThreads = 512;      // 4 multiplying + 4 feeding wavefronts
-constexpr int kSpFeed = 256;         // threads that move tiles
-constexpr int kSpRing = 3;           // LDS buffers
-constexpr int kSpRT = 8;            // 16-row instruction tiles per wavefront
-constexpr int kSpCT = 4;            // 16-token instruction tiles per wavefront
-constexpr int kSpTR = 2 * kSpRT * 16;   // rows of Wd per workgroup (2 x 2 wavefronts)
-constexpr int kSpTT = 2 * kSpCT * 16;   // tokens per workgroup
-constexpr int kSpAL = kSpTR / 64;   // 16-byte pieces of A a thread moves per step
-constexpr int kSpBL = kSpTT / 32;   // 16-byte pieces of B a thread moves per step
-constexpr int kSpKS = 64;           // k per step (one instruction deep)
-constexpr int kSpAPitch = 72;       // bytes per LDS row of compressed A (64 data + 8 pad)
-constexpr int kSpBPitch = 144;      // bytes per LDS row of B (128 data + 16 pad)
-constexpr int kSpIPitch = 8;        // index bytes per row and step
+constexpr int kSpKS = 64;            // k per step
 
 struct SpmmArgs {
     const void *vals;     // rows x cols/2 bf16
@@ -64,25 +48,333 @@ struct SpmmArgs {
     uint32_t tiles_r, tiles_t;
 };
 
+// y[tok][r .. r+3] (fp32 -> bf16 rounds to nearest even, by the hardware's packed conversion)
 template <bool OUT_BF16>
-__global__ __launch_bounds__(kSpThreads, 1) void spmm24_kernel(const SpmmArgs p)
+__device__ __forceinline__ void store_quad(const SpmmArgs &p, uint32_t tok, uint32_t r, f32x4 v)
 {
-    __shared__ __attribute__((aligned(16))) unsigned char As[kSpRing][kSpTR * kSpAPitch];
-    __shared__ __attribute__((aligned(16))) unsigned char Bs[kSpRing][kSpTT * kSpBPitch];
-    __shared__ __attribute__((aligned(16))) unsigned char Is[kSpRing][kSpTR * kSpIPitch];
+    if constexpr (OUT_BF16) {
+        typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+        typedef float f32x2 __attribute__((ext_vector_type(2)));
+        union { bf16x2 h; uint32_t u; } c0, c1;
+        c0.h = __builtin_convertvector(f32x2{v.x, v.y}, bf16x2);
+        c1.h = __builtin_convertvector(f32x2{v.z, v.w}, bf16x2);
+        *(su32x2 *)((unsigned char *)p.y + ((size_t)tok * p.ld_y + r) * 2u) = su32x2{c0.u, c1.u};
+    } else {
+        *(f32x4 *)((unsigned char *)p.y + ((size_t)tok * p.ld_y + r) * 4u) = v;
+    }
+}
 
-    // The grid is one workgroup per compute unit (or per tile if there are fewer); workgroup b works through
-    // tiles b, b + G, b + 2G, ... as ONE stream of steps, so the loads of a tile's first steps are in flight
-    // while the previous tile is still being multiplied and stored.
-    // Tile numbers -> output position: workgroups are handed to the eight XCDs round-robin (b % 8 with G a
-    // multiple of 8), so give each XCD a contiguous range of tile numbers, and number the tiles so that 64
-    // consecutive ones form an 8 x 8 block of the output: the workgroups that run on one XCD at the same time
-    // then share a few row panels of Wd and token panels of x in its L2 instead of streaming one each.
+// ---------------------------------------------------------------------------------------------------------------------
+// Direct global -> LDS copies.  The instruction writes lane l's piece at the (wavefront-uniform) LDS address in m0 plus
+// l times the piece size, so a swizzle of the LDS image is a permutation of the addresses the lanes read from.  Inline
+// asm, because the compiler would make every LDS read wait for all copies in flight; the waits below count them.  The
+// copies have no destination register, and the address registers are read when the instruction issues.
+// ---------------------------------------------------------------------------------------------------------------------
+__device__ __forceinline__ void copy16(const unsigned char *base, uint32_t lane_off, uint32_t lds)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(lane_off), "s"(base));
+}
+
+__device__ __forceinline__ void copy4(const unsigned char *base, uint32_t lane_off, uint32_t lds)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds), "v"(lane_off), "s"(base));
+}
+
+// at most N of the wavefront's global memory operations are still in flight (they finish in order)
+template <int N>
+__device__ __forceinline__ void wait_copies()
+{
+    static_assert(N >= 0 && N < 64, "six bits of counter");
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
+// the wavefront's LDS reads have arrived in registers (as the builtin, so that the compiler knows and adds no wait of its
+// own in front of their first use)
+__device__ __forceinline__ void wait_lds_reads()
+{
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xC07F);                         // lgkmcnt(0)
+    asm volatile("" ::: "memory");
+}
+
+__device__ __forceinline__ uint32_t lds_address(const void *p)
+{
+    return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const unsigned char *)p;
+}
+
+// ---------------------------------------------------------------------------------------------------------------------
+// Few tokens or few rows: the reduction split over the wavefronts of a workgroup
+// ---------------------------------------------------------------------------------------------------------------------
+//
+// With tens of large tiles most compute units stand idle, so these products take small tiles (16 RT rows x 16 CT
+// tokens) and what a workgroup has in excess, wavefronts, shares the reduction: wavefront w takes the units of 256 k
+// numbered w, w + W, ... for the whole tile.  Every byte is then needed by one wavefront only, so each keeps a ring of
+// D steps (64 k) in its own part of LDS, filled by direct copies and read back as fragments, and no wavefront waits for
+// another before the final sum.  (Fragments loaded straight into registers need no LDS, but sixteen consecutive lanes
+// then read sixteen different rows and the memory path delivers a quarter of its 64 bytes per clock.)
+//
+// Which k a position of the instruction stands for is free as long as both operands agree.  Position groups (of four
+// k) 4b, 4b+1 stand for the step's groups 2b, 2b+1 and 4b+2, 4b+3 for 8+2b, 9+2b: lane a's compressed values are then
+// the 16 bytes at 16 a of the row's 64 with the index bytes 2a, 2a+1 of its eight, its x values the 16 bytes at 16 a and
+// at 64 + 16 a of the token's 128.
+//
+// LDS images are swizzled in 16-byte pieces so that eight consecutive lanes of a fragment read cover all banks: piece c
+// of row r of A lies in slot c ^ ((r >> 1) & 3), piece c of token t of B in slot c ^ (t & 7).
+constexpr int kSkUnit = 4;           // steps per unit (a row's index bytes of a unit are 32 contiguous bytes)
+
+template <int RT, int CT, int W, int D, bool OUT_BF16>
+__global__ __launch_bounds__(64 * W, 1) void spmm24_ksplit_kernel(const SpmmArgs p)
+{
+    constexpr int TR = RT * 16, TT = CT * 16;
+    constexpr int kPitch = TR + 4;                              // floats per token in the exchange buffer
+    constexpr uint32_t kStep = RT * 1024u + CT * 2048u;         // bytes of a step: A, then B
+    constexpr uint32_t kIdx = RT * 512u;                        // index bytes of a unit
+    constexpr uint32_t kWave = D * kStep + 2u * kIdx;
+    constexpr uint32_t kPart = TT * kPitch * 4u;
+    constexpr int kData = RT + 2 * CT;                          // copy instructions of a step
+    constexpr uint32_t kLds = kWave > kPart ? kWave : kPart;
+    __shared__ __attribute__((aligned(16))) unsigned char lds[W * kLds];
+
+    // Each XCD takes a contiguous range of tile numbers; 32 consecutive ones form a block of 4 row panels x 8 token
+    // panels, so that the workgroups that run on an XCD together share panels in its L2.
+    const uint32_t n_tiles = p.tiles_r * p.tiles_t;
+    uint32_t id = blockIdx.x;
+    const uint32_t per = n_tiles / 8u;
+    if (id < per * 8u)
+        id = (id & 7u) * per + (id >> 3);
+    constexpr uint32_t kGroup = 4;
+    const uint32_t in_group = kGroup * p.tiles_t;
+    const uint32_t group = id / in_group, rem = id - group * in_group;
+    const uint32_t first_r = group * kGroup;
+    const uint32_t group_rows = min(p.tiles_r - first_r, kGroup);
+    const uint32_t tt = rem / group_rows;
+    const uint32_t row0 = (first_r + (rem - tt * group_rows)) * TR, tok0 = tt * TT;
+
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t m = lane & 15u, a = lane >> 4;
+    const uint32_t steps = p.cols / kSpKS;
+
+    // ---- copies: rows and tokens past the edge re-read the last valid one; their results are not stored ----
+    uint32_t off_a[RT], off_i[2 * RT], off_b[2 * CT];
+#pragma unroll
+    for (int i = 0; i < RT; i++) {                              // 16 rows x 64 bytes
+        const uint32_t r = (uint32_t)i * 16u + (lane >> 2);
+        off_a[i] = (min(row0 + r, p.rows - 1u) - row0) * p.cols + (((lane & 3u) ^ ((lane >> 3) & 3u)) * 16u);
+    }
+#pragma unroll
+    for (int i = 0; i < 2 * RT; i++)                            // 8 rows x 32 bytes
+        off_i[i] = (min(row0 + (uint32_t)i * 8u + (lane >> 3), p.rows - 1u) - row0) * (p.cols >> 3);
+#pragma unroll
+    for (int j = 0; j < 2 * CT; j++) {                          // 8 tokens x 128 bytes
+        const uint32_t t = (uint32_t)j * 8u + (lane >> 3);
+        off_b[j] = (min(tok0 + t, p.tokens - 1u) - tok0) * p.ld_x * 2u + (((lane & 7u) ^ ((lane >> 3) & 7u)) * 16u);
+    }
+    const unsigned char *base_a = (const unsigned char *)p.vals + (size_t)row0 * p.cols;
+    const unsigned char *base_b = (const unsigned char *)p.x + (size_t)tok0 * p.ld_x * 2u;
+    const unsigned char *base_i = (const unsigned char *)p.idx + (size_t)row0 * (p.cols >> 3);
+    unsigned char *const mine = lds + wave * kWave;
+    const uint32_t mine_at = __builtin_amdgcn_readfirstlane(lds_address(mine));
+
+    // The wavefront's steps as one stream t = 0 .. n - 1: unit wave + W (t / 4), step t % 4 of it.  Only the last unit of
+    // all can be short, and it is the last of its wavefront.
+    const uint32_t units = (steps + kSkUnit - 1u) / kSkUnit;
+    const uint32_t my_units = wave < units ? (units - wave + W - 1u) / W : 0u;
+    uint32_t n = my_units * kSkUnit;
+    if (my_units && wave + (my_units - 1u) * W == units - 1u)
+        n -= units * kSkUnit - steps;
+    auto copy_step = [&](uint32_t t) {
+        const uint32_t s = (wave + (t / kSkUnit) * W) * kSkUnit + t % kSkUnit;
+        const unsigned char *pa = base_a + (size_t)s * 64u, *pb = base_b + (size_t)s * 128u;
+        uint32_t at = mine_at + (t % D) * kStep;
+#pragma unroll
+        for (int i = 0; i < RT; i++, at += 1024u)
+            copy16(pa, off_a[i], at);
+#pragma unroll
+        for (int j = 0; j < 2 * CT; j++, at += 1024u)
+            copy16(pb, off_b[j], at);
+    };
+    auto copy_idx = [&](uint32_t k) {                           // the wavefront's k-th unit; bytes past the row's end repeat its last
+        const uint32_t d = min((wave + k * W) * (2u * kSkUnit) + (lane & 7u), 2u * steps - 1u) * 4u;
+        uint32_t at = mine_at + D * kStep + (k & 1u) * kIdx;
+#pragma unroll
+        for (int i = 0; i < 2 * RT; i++, at += 256u)
+            copy4(base_i, off_i[i] + d, at);
+    };
+
+    // ---- fragments ----
+    struct Frag {
+        bf16x8 a[RT];
+        bf16x16 b[CT];
+        int sel[RT];
+    };
+    const uint32_t read_a = m * 64u + ((a ^ ((m >> 1) & 3u)) * 16u);
+    const uint32_t read_b0 = RT * 1024u + m * 128u + ((a ^ (m & 7u)) * 16u);
+    const uint32_t read_b1 = RT * 1024u + m * 128u + (((a + 4u) ^ (m & 7u)) * 16u);
+    const uint32_t read_i = D * kStep + m * 32u + a * 2u;
+    auto read_step = [&](Frag &f, uint32_t t) {
+        const unsigned char *src = mine + (t % D) * kStep;
+        const unsigned char *src_i = mine + ((t / kSkUnit) & 1u) * kIdx + (t % kSkUnit) * 8u;
+#pragma unroll
+        for (int i = 0; i < RT; i++) {
+            f.a[i] = *(const bf16x8 *)(src + read_a + i * 1024);
+            f.sel[i] = (int)*(const uint16_t *)(src_i + read_i + i * 512);
+        }
+#pragma unroll
+        for (int j = 0; j < CT; j++) {
+            union { su32x4 u[2]; bf16x16 v; } cv;
+            cv.u[0] = *(const su32x4 *)(src + read_b0 + j * 2048);
+            cv.u[1] = *(const su32x4 *)(src + read_b1 + j * 2048);
+            f.b[j] = cv.v;
+        }
+    };
+    f32x4 acc[RT][CT];
+#pragma unroll
+    for (int i = 0; i < RT; i++)
+#pragma unroll
+        for (int j = 0; j < CT; j++)
+            acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto multiply = [&](const Frag &f) {
+#pragma unroll
+        for (int i = 0; i < RT; i++)
+#pragma unroll
+            for (int j = 0; j < CT; j++)
+                acc[i][j] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(f.a[i], f.b[j], acc[i][j], f.sel[i], 0, 0);
+    };
+
+    // Step t: its fragments are in registers; those of step t + 1 are read while it is multiplied, and once they have
+    // arrived step t + 1 + D may overwrite them.  Copies of steps t + 2 .. t + D are in flight meanwhile.
+    if (n) {
+        copy_idx(0);
+#pragma unroll
+        for (int t = 0; t < D; t++)
+            if ((uint32_t)t < n)
+                copy_step(t);
+        if (my_units > 1u)
+            copy_idx(1);
+        Frag f[2];
+        auto arrive = [&](uint32_t t) {                         // step t is in LDS
+            if (t + D <= n)                                     // steps t + 1 .. t + D - 1 may be in flight
+                wait_copies<(D - 1) * kData>();
+            else
+                wait_copies<0>();
+        };
+        arrive(0);
+        read_step(f[0], 0);
+        wait_lds_reads();
+        if (D < n)
+            copy_step(D);
+        uint32_t t = 0;
+        auto step = [&](int cur) {                              // t + 1 < n
+            arrive(t + 1u);
+            read_step(f[cur ^ 1], t + 1u);
+            __builtin_amdgcn_sched_barrier(0);
+            multiply(f[cur]);
+            __builtin_amdgcn_sched_barrier(0);
+            t++;
+            wait_lds_reads();
+            // the unit that step t ends gives its place to the one after the next
+            if (t % kSkUnit == kSkUnit - 1u && t / kSkUnit + 2u < my_units)
+                copy_idx(t / kSkUnit + 2u);
+            if (t + D < n)
+                copy_step(t + D);
+        };
+        while (t + 2u < n) {
+            step(0);
+            step(1);
+        }
+        if (t + 1u < n) {
+            step(0);
+            multiply(f[1]);
+        } else {
+            multiply(f[0]);
+        }
+    }
+
+    // ---- the wavefronts' sums, added in a fixed order; a lane holds rows 4a..4a+3 of token m of each instruction tile ----
+    __syncthreads();                                            // the rings are no longer read
+    float *const part = (float *)lds;
+#pragma unroll
+    for (int i = 0; i < RT; i++)
+#pragma unroll
+        for (int j = 0; j < CT; j++)
+            *(f32x4 *)&part[wave * (TT * kPitch) + (j * 16u + m) * kPitch + i * 16u + a * 4u] = acc[i][j];
+    __syncthreads();
+    constexpr int kQuads = TR * TT / 4;                         // four rows of a token each
+    const uint32_t used = min(units, (uint32_t)W);
+#pragma unroll
+    for (int q0 = 0; q0 < kQuads; q0 += 64 * W) {
+        const uint32_t q = q0 + threadIdx.x;
+        if (kQuads % (64 * W) != 0 && q >= (uint32_t)kQuads)
+            break;
+        const uint32_t t = q / (TR / 4), r = (q % (TR / 4)) * 4u;
+        f32x4 v = *(const f32x4 *)&part[t * kPitch + r];
+        for (uint32_t w = 1; w < used; w++)
+            v += *(const f32x4 *)&part[w * (TT * kPitch) + t * kPitch + r];
+        const uint32_t tok = tok0 + t, row = row0 + r;
+        if (tok < p.tokens && row < p.rows)                     // rows is a multiple of 4: the four entries are in or out together
+            store_quad<OUT_BF16>(p, tok, row, v);
+    }
+}
+
+// ---------------------------------------------------------------------------------------------------------------------
+// Many tokens and rows: tiles shared by four wavefronts
+// ---------------------------------------------------------------------------------------------------------------------
+//
+// A workgroup computes 64 RT rows x 64 CT tokens with 2 x 2 wavefronts, each 32 RT x 32 CT on the 32 x 32 x 32
+// instruction.  Positions are assigned to k as in the split kernel: lane a's values of a half step (32 k) are the 16 bytes
+// at 16 a of the row's 32, its x values the 16 bytes at 16 a and 32 + 16 a of the token's 64.
+//
+// What bounds it is what a compute unit can pull from the caches (about 10 TB/s over the chip, whatever the tile), so the
+// tile is as large as the registers allow: 256 x 256, with 256 accumulator registers per lane, moves 50 KB per 2^22
+// products, a third of what the 256 x 128 tiles of a kernel with eight wavefronts moved that staged them through
+// registers (W 4096 x 1024, 8192 tokens: 77 -> 55 us, 1.25 PFLOP/s dense equivalent; matrix instructions and LDS reads
+// alone, without the copies, take two thirds of that).  Steps of 64 k arrive in a ring of three LDS images by direct
+// copies, two steps ahead.  The fragments of a half step are read while the half before it is multiplied.  One barrier per
+// step, between its halves: when all wavefronts have read the second half of step g its image is overwritten by step
+// g + 3, and step g + 1, whose copies every wavefront has waited for, may be read.  Workgroups are persistent and treat
+// the steps of all their tiles as one stream, so the copies of a tile's first steps are in flight while the one before
+// is stored.
+//
+// Swizzle: 32 rows of one piece are read at a time, sixteen lanes per pass over the 64 banks, so piece c of row r of A
+// lies in slot c ^ ((r >> 2) & 3) and piece c of token t of B in slot c ^ ((t >> 1) & 7) (bank conflict cycles 14.7e6 ->
+// 2.1e6 per product against the split kernel's swizzle).
+constexpr int kTileRing = 3;
+
+// acc += A B with the sums in accumulation registers.  As the builtin, with 256 of them, the compiler moves sums between
+// the two register files in every step.  What it would do for the builtin is done here by hand: two wait states in case
+// an operand was just written by a vector instruction; and whoever reads the sums afterwards waits (sums_ready).
+__device__ __forceinline__ void multiply32(f32x16 &acc, bf16x8 a, bf16x16 b, int sel)
+{
+    asm volatile("s_nop 1\n\tv_smfmac_f32_32x32x32_bf16 %0, %1, %2, %3" : "+a"(acc) : "v"(a), "v"(b), "v"(sel));
+}
+
+// The last matrix instruction's results can be read by vector instructions (16 passes; 18 wait states needed).
+__device__ __forceinline__ void sums_ready()
+{
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_nop 15\n\ts_nop 15");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+template <int RT, int CT, bool OUT_BF16>
+__global__ __launch_bounds__(256, RT * CT <= 4 ? 2 : 1) void spmm24_tile_kernel(const SpmmArgs p)
+{
+    constexpr int TR = RT * 64, TT = CT * 64;
+    constexpr uint32_t kA = TR * 64u, kB = TT * 128u, kI = TR * 8u, kImage = kA + kB + kI;
+    constexpr int kCopyA = RT, kCopyB = 2 * CT, kCopyI = RT / 2 > 0 ? RT / 2 : 1;       // copies of a wavefront per step
+    constexpr int kCopies = kCopyA + kCopyB + kCopyI;
+    constexpr int kStores = RT * CT * (OUT_BF16 ? 2 : 4);                               // of a wavefront per tile
+    static_assert(RT % 2 == 0, "index bytes: four wavefronts x 32 rows per copy");
+    __shared__ __attribute__((aligned(16))) unsigned char lds[kTileRing * kImage];
+
+    // Tiles b, b + G, b + 2G, ... of the launch, as one stream of steps.  Each XCD takes a contiguous range of tile
+    // numbers, and 64 consecutive ones form an 8 x 8 block of the output, so that the workgroups that run on an XCD together
+    // share panels in its L2.
     const uint32_t n_tiles = p.tiles_r * p.tiles_t;
     const uint32_t G = gridDim.x, b = blockIdx.x;
     const uint32_t my_tiles = (n_tiles - b + G - 1u) / G;       // b < G <= n_tiles
     const uint32_t steps = p.cols / kSpKS;
-    const uint32_t total = my_tiles * steps;                    // steps of this workgroup's stream
     auto locate = [&](uint32_t j, uint32_t &row0, uint32_t &tok0) {
         uint32_t id = b + j * G;
         const uint32_t per = n_tiles / 8u;
@@ -94,246 +386,249 @@ __global__ __launch_bounds__(kSpThreads, 1) void spmm24_kernel(const SpmmArgs p)
         const uint32_t first_r = group * kGroup;
         const uint32_t group_rows = min(p.tiles_r - first_r, kGroup);
         const uint32_t tt = rem / group_rows;
-        row0 = (first_r + (rem - tt * group_rows)) * kSpTR;
-        tok0 = tt * kSpTT;
+        row0 = (first_r + (rem - tt * group_rows)) * TR;
+        tok0 = tt * TT;
     };
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const bool feeder = wave >= 4u;
+    const uint32_t lds_at = __builtin_amdgcn_readfirstlane(lds_address(lds));
 
-    if (feeder) {
-        // ---- global -> registers -> LDS (rows and tokens past the edge re-read the last valid one) ----
-        // Consecutive lanes fetch consecutive 16-byte pieces of one row, so every load instruction covers whole
-        // runs: 8 lanes = the 128 bytes a token contributes to a step, 4 lanes = the 64 bytes of a row of
-        // compressed A.  (One lane per row with several pieces each touches four times as many cache lines per
-        // instruction and measured twice as slow overall.)
-        // Addresses are a wavefront-uniform base (scalar registers) plus a 32-bit lane offset.
-        const uint32_t tid = threadIdx.x & (kSpFeed - 1);          // index among the feeding threads
-        const unsigned char *base_a, *base_b, *base_i;
-        uint32_t off_b[kSpBL], off_a[kSpAL], off_i;
-        auto set_tile = [&](uint32_t j) {
-            uint32_t row0, tok0;
-            locate(j, row0, tok0);
-            base_a = (const unsigned char *)p.vals + (size_t)row0 * p.cols;
-            base_b = (const unsigned char *)p.x + (size_t)tok0 * p.ld_x * 2u;
-            base_i = (const unsigned char *)p.idx + (size_t)row0 * (p.cols >> 3);
+    // ---- copies (rows and tokens past the edge re-read the last valid one; their results are not stored) ----
+    // wavefront w copies rows 16 (w + 4 i) .. + 15 of A, tokens 8 (w + 4 i) .. + 7 of B, index bytes of rows 32 (w + 4 i) .. + 31
+    uint32_t off_a[kCopyA], off_b[kCopyB], off_i[kCopyI];
+    const unsigned char *base_a, *base_b, *base_i;
+    auto set_tile = [&](uint32_t j) {
+        uint32_t row0, tok0;
+        locate(j, row0, tok0);
+        base_a = (const unsigned char *)p.vals + (size_t)row0 * p.cols;
+        base_b = (const unsigned char *)p.x + (size_t)tok0 * p.ld_x * 2u;
+        base_i = (const unsigned char *)p.idx + (size_t)row0 * (p.cols >> 3);
 #pragma unroll
-            for (int i = 0; i < kSpBL; i++) {
-                const uint32_t tok = min(tok0 + (uint32_t)i * 32u + (tid >> 3), p.tokens - 1u);
-                off_b[i] = (tok - tok0) * p.ld_x * 2u + (tid & 7u) * 16u;
-            }
-#pragma unroll
-            for (int i = 0; i < kSpAL; i++) {
-                const uint32_t row = min(row0 + (uint32_t)i * 64u + (tid >> 2), p.rows - 1u);
-                off_a[i] = (row - row0) * p.cols + (tid & 3u) * 16u;
-            }
-            const uint32_t i_row = min(row0 + (tid % kSpTR), p.rows - 1u);     // idx: 8 B per row and step
-            off_i = (i_row - row0) * (p.cols >> 3);
-        };
-        struct Stage {
-            su32x4 ra[kSpAL], rb[kSpBL];
-            su32x2 ri;
-        };
-        Stage st[kSpRing];
-        uint32_t fj = 0, fk = 0;          // tile ordinal and k-step of the next fetch
-        set_tile(0);
-        // fetch the next step of the stream; past its end the last step is read again (and never consumed)
-        auto fetch = [&](Stage &r) {
-            const uint32_t k0 = fk * kSpKS;
-            // compressed A: cols/2 values per row = cols bytes per row; a step covers 32 values = 64 bytes
-#pragma unroll
-            for (int i = 0; i < kSpAL; i++)
-                r.ra[i] = *(const su32x4 *)(base_a + k0 + off_a[i]);
-#pragma unroll
-            for (int i = 0; i < kSpBL; i++)
-                r.rb[i] = *(const su32x4 *)(base_b + (size_t)k0 * 2u + off_b[i]);
-            r.ri = *(const su32x2 *)(base_i + (k0 >> 3) + off_i);
-            // advance (address arithmetic only: no memory operation inside the branch)
-            if (fk + 1u < steps) {
-                fk++;
-            } else if (fj + 1u < my_tiles) {
-                fk = 0;
-                fj++;
-                set_tile(fj);
-            }
-        };
-        auto stash = [&](const Stage &r, int buf) {
-#pragma unroll
-            for (int i = 0; i < kSpAL; i++) {
-                unsigned char *da = &As[buf][((uint32_t)i * 64u + (tid >> 2)) * kSpAPitch + (tid & 3u) * 16u];
-                *(su32x2 *)(da) = su32x2{r.ra[i].x, r.ra[i].y};      // rows are 8-byte aligned only (pitch 72)
-                *(su32x2 *)(da + 8) = su32x2{r.ra[i].z, r.ra[i].w};
-            }
-#pragma unroll
-            for (int i = 0; i < kSpBL; i++)
-                *(su32x4 *)&Bs[buf][((uint32_t)i * 32u + (tid >> 3)) * kSpBPitch + (tid & 7u) * 16u] = r.rb[i];
-            // index bytes regrouped as (0, 2, 4, 6, 1, 3, 5, 7): the two bytes a lane needs (groups g0, g0+1 and
-            // g0+4, g0+5) then sit side by side and come with one 16-bit read
-            *(su32x2 *)&Is[buf][(tid % kSpTR) * kSpIPitch] =
-                su32x2{__builtin_amdgcn_perm(r.ri.y, r.ri.x, 0x06040200u), __builtin_amdgcn_perm(r.ri.y, r.ri.x, 0x07050301u)};
-        };
-        // Stream step g is multiplied out of LDS buffer g % 3 while the feeders write step g + 2 into buffer
-        // (g + 2) % 3 (last read at step g - 1, before the previous barrier) and issue the loads of step g + 5
-        // into the register set they have just emptied.  Both roles run the same number of barriers; each has
-        // its own loop, unrolled by three so that buffers and register sets are static, and its own registers.
-        fetch(st[0]);
-        fetch(st[1]);
-        stash(st[0], 0);
-        stash(st[1], 1);
-        fetch(st[2]);
-        fetch(st[0]);
-        fetch(st[1]);
-        __syncthreads();
-        auto feed = [&](int pos) {                    // pos = g % 3, a compile-time constant at every call
-            const int nxt = (pos + 2) % kSpRing;
-            stash(st[nxt], nxt);                      // step g + 2
-            __builtin_amdgcn_sched_barrier(0);
-            fetch(st[nxt]);                           // step g + 5
-            __syncthreads();
-        };
-        uint32_t g = 0;
-        for (; g + 3 <= total; g += 3) {
-            feed(0);
-            feed(1);
-            feed(2);
+        for (int i = 0; i < kCopyA; i++) {
+            const uint32_t r = ((uint32_t)i * 4u + wave) * 16u + (lane >> 2);
+            off_a[i] = (min(row0 + r, p.rows - 1u) - row0) * p.cols + (((lane & 3u) ^ (lane >> 4)) * 16u);
         }
-        if (g < total)
-            feed(0);
-        if (g + 1 < total)
-            feed(1);
-    } else {
-        const uint32_t wr = (wave >> 1) & 1u, wc = wave & 1u;     // position of this wavefront in the tile
-        f32x4 acc[kSpRT][kSpCT];
 #pragma unroll
-        for (int i = 0; i < kSpRT; i++)
+        for (int i = 0; i < kCopyB; i++) {
+            const uint32_t t = ((uint32_t)i * 4u + wave) * 8u + (lane >> 3);
+            off_b[i] = (min(tok0 + t, p.tokens - 1u) - tok0) * p.ld_x * 2u + (((lane & 7u) ^ ((wave & 1u) * 4u + (lane >> 4))) * 16u);
+        }
 #pragma unroll
-            for (int j = 0; j < kSpCT; j++)
-                acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int i = 0; i < kCopyI; i++) {
+            const uint32_t r = ((uint32_t)i * 4u + wave) * 32u + (lane >> 1);
+            off_i[i] = (min(row0 + r, p.rows - 1u) - row0) * (p.cols >> 3) + (lane & 1u) * 4u;
+        }
+    };
+    uint32_t fj = 0, fk = 0;                                    // tile ordinal and step of the next copy
+    uint32_t slot = 0;                                          // its image
+    auto copy_piece = [&](int i) {                              // i < kCopies, a compile-time constant at every call
+        const uint32_t at = lds_at + slot * kImage;
+        if (i < kCopyA)
+            copy16(base_a + (size_t)fk * 64u, off_a[i], at + ((uint32_t)i * 4u + wave) * 1024u);
+        else if (i < kCopyA + kCopyB)
+            copy16(base_b + (size_t)fk * 128u, off_b[i - kCopyA], at + kA + ((uint32_t)(i - kCopyA) * 4u + wave) * 1024u);
+        else
+            copy4(base_i + (size_t)fk * 8u, off_i[i - kCopyA - kCopyB],
+                  at + kA + kB + ((uint32_t)(i - kCopyA - kCopyB) * 4u + wave) * 256u);
+    };
+    auto copied = [&]() {                                       // on to the next step
+        slot = slot == kTileRing - 1 ? 0 : slot + 1;
+        if (++fk == steps) {                                    // past the end of the stream its last tile is copied again
+            fk = 0;
+            if (fj + 1u < my_tiles)
+                set_tile(++fj);
+        }
+    };
 
-        const uint32_t m = lane & 15u, a = lane >> 4;
-        // the lane's two runs of compressed A inside a step: groups g0, g0+1 (8 bytes) and g0+4, g0+5
-        const uint32_t g0 = 8u * (a & 1u) + 2u * (a >> 1);
-        const uint32_t a_off = g0 * 4u;                 // bytes: 2 values x 2 bytes per group
-        const uint32_t i_off = 2u * a;                  // the lane's two index bytes in the regrouped order
-
-        // Fragments of x for a step are read one step ahead (the ring buffer of step g + 1 is complete when step
-        // g starts), and so is the first A fragment: the matrix instructions of a step start without waiting
-        // for LDS, and the remaining A fragments arrive while they run.
-        auto read_b1 = [&](int buf, int ct, bf16x16 &bfrag) {
-            const unsigned char *src = &Bs[buf][(wc * (kSpCT * 16u) + (uint32_t)ct * 16u + m) * kSpBPitch + a * 32u];
-            union { su32x4 u[2]; bf16x16 v; } cv;
-            cv.u[0] = *(const su32x4 *)src;
-            cv.u[1] = *(const su32x4 *)(src + 16);
-            bfrag = cv.v;
-        };
-        auto read_b = [&](int buf, bf16x16 (&bfrag)[kSpCT]) {
+    // ---- fragments ----
+    struct Frag {
+        bf16x8 a[RT];
+        su32x4 b[CT][2];
+        int sel[RT];
+    };
+    const uint32_t wr = wave >> 1, wc = wave & 1u;              // position of this wavefront in the tile
+    const uint32_t m = lane & 31u, a = lane >> 5;
+    uint32_t read_a[2], read_b[2][2];
 #pragma unroll
-            for (int ct = 0; ct < kSpCT; ct++)
-                read_b1(buf, ct, bfrag[ct]);
-        };
-        auto read_a = [&](int buf, int rt, bf16x8 &av, int &sel) {
-            const uint32_t r = wr * (kSpRT * 16u) + (uint32_t)rt * 16u + m;
-            const unsigned char *src = &As[buf][r * kSpAPitch + a_off];
-            union { su32x2 u[2]; bf16x8 v; } cv;
-            cv.u[0] = *(const su32x2 *)src;
-            cv.u[1] = *(const su32x2 *)(src + 16);
-            av = cv.v;
-            sel = (int)*(const uint16_t *)&Is[buf][r * kSpIPitch + i_off];
-        };
-        bf16x16 bcur[kSpCT];
-        bf16x8 a0;
-        int sel0;
-        // A fragments travel through a ring of three register sets, read two instruction rows ahead of their use,
-        // and the reads of the next step's x fragments are spread over the rows: every matrix instruction finds
-        // its operands in registers, and LDS latency hides behind the 4 x 16 cycles of a row of instructions.
-        // (Left to itself the compiler reads every fragment into the registers of the one before, i.e. after the
-        // instructions that use those have issued, and waits for it.)
-        auto multiply = [&](int cur) {
-            const int nxt = (cur + 1) % kSpRing;
-            bf16x16 bnext[kSpCT];
-            bf16x8 a0n;
-            int sel0n;
-            bf16x8 av[3];
-            int sel[3];
-            av[0] = a0;
-            sel[0] = sel0;
-            read_a(cur, 1, av[1], sel[1]);
-            read_a(cur, 2, av[2], sel[2]);
-            __builtin_amdgcn_sched_barrier(0);
+    for (uint32_t h = 0; h < 2; h++) {
+        read_a[h] = (wr * RT * 32u + m) * 64u + (((2u * h + a) ^ ((m >> 2) & 3u)) * 16u);
+        read_b[h][0] = kA + (wc * CT * 32u + m) * 128u + (((4u * h + a) ^ ((m >> 1) & 7u)) * 16u);
+        read_b[h][1] = kA + (wc * CT * 32u + m) * 128u + (((4u * h + 2u + a) ^ ((m >> 1) & 7u)) * 16u);
+    }
+    const uint32_t read_i = kA + kB + (wr * RT * 32u + m) * 8u + a * 2u;
+    // read i of a half step's fragments, in the order in which the multiplication needs them: x of token tile 0, A and
+    // positions of row tile 0, x of the other token tiles, A and positions of the other row tiles
+    constexpr int kReads = 2 * CT + RT;
+    auto read_piece = [&](Frag &f, uint32_t image, int h, int i) {
+        const unsigned char *src = lds + image;
+        if (i == 2 || i > 2 * CT) {
+            const int rt = i == 2 ? 0 : i - 2 * CT;
+            f.a[rt] = *(const bf16x8 *)(src + read_a[h] + rt * 2048);
+            f.sel[rt] = (int)*(const uint16_t *)(src + read_i + rt * 256 + h * 4);
+        } else {
+            const int k = i < 2 ? i : i - 1;
+            f.b[k / 2][k % 2] = *(const su32x4 *)(src + read_b[h][k % 2] + (k / 2) * 4096);
+        }
+    };
+    f32x16 acc[RT][CT];
+    // Multiplies the fragments of a half step; between its instructions go the reads of the next one's fragments and, with
+    // COPY, the copies of a step three ahead: there is one wavefront per SIMD, so the matrix cores would wait for whatever
+    // is issued in a run of its own.
+    auto half = [&](const Frag &cur, Frag &nxt, uint32_t nxt_image, int nxt_h, auto copy) {
+        constexpr bool COPY = decltype(copy)::value;
+        constexpr int kMul = RT * CT;
 #pragma unroll
-            for (int rt = 0; rt < kSpRT; rt++) {
+        for (int q = 0; q < kMul; q++) {
+            union { su32x4 u[2]; bf16x16 v; } bv;
+            bv.u[0] = cur.b[q % CT][0];
+            bv.u[1] = cur.b[q % CT][1];
+            multiply32(acc[q / CT][q % CT], cur.a[q / CT], bv.v, cur.sel[q / CT]);
+            // reads all go out in the first three quarters
 #pragma unroll
-                for (int ct = 0; ct < kSpCT; ct++)
-                    acc[rt][ct] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(av[rt % 3], bcur[ct], acc[rt][ct], sel[rt % 3], 0, 0);
-                __builtin_amdgcn_sched_barrier(0);
-                if (rt + 3 < kSpRT)
-                    read_a(cur, rt + 3, av[rt % 3], sel[rt % 3]);
-                if (rt < kSpCT)
-                    read_b1(nxt, rt, bnext[rt]);
-                if (rt == kSpCT)
-                    read_a(nxt, 0, a0n, sel0n);
-                __builtin_amdgcn_sched_barrier(0);
+            for (int i = q * kReads * 4 / (3 * kMul); i < (q + 1) * kReads * 4 / (3 * kMul) && i < kReads; i++)
+                read_piece(nxt, nxt_image, nxt_h, i);
+            if constexpr (COPY) {
+#pragma unroll
+                for (int i = q * kCopies / kMul; i < (q + 1) * kCopies / kMul; i++)
+                    copy_piece(i);
             }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if constexpr (COPY)
+            copied();
+        wait_lds_reads();
+    };
+
+    // Writes the tile; returns whether all of kStores store instructions were issued.
+    auto store_tile = [&](uint32_t j) -> bool {
+        uint32_t row0, tok0;
+        locate(j, row0, tok0);
+        const bool whole = row0 + TR <= p.rows && tok0 + TT <= p.tokens;
+        row0 += wr * RT * 32u;
+        tok0 += wc * CT * 32u + m;
 #pragma unroll
-            for (int ct = 0; ct < kSpCT; ct++)
-                bcur[ct] = bnext[ct];
-            a0 = a0n;
-            sel0 = sel0n;
-        };
-        // lane holds rows 4a..4a+3 of token column m of each instruction tile: 4 consecutive y entries
-        auto store_tile = [&](uint32_t j) {
-            uint32_t row0, tok0;
-            locate(j, row0, tok0);
+        for (int ct = 0; ct < CT; ct++) {
+            const uint32_t tok = tok0 + (uint32_t)ct * 32u;
 #pragma unroll
-            for (int rt = 0; rt < kSpRT; rt++) {
+            for (int rt = 0; rt < RT; rt++) {
+                if constexpr (OUT_BF16) {
+                    // pairs of lanes l, l + 32 exchange quads so that each holds eight consecutive rows
+                    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+                    typedef float f32x2 __attribute__((ext_vector_type(2)));
+                    uint32_t d[8];
 #pragma unroll
-                for (int ct = 0; ct < kSpCT; ct++) {
-                    const uint32_t tok = tok0 + wc * (kSpCT * 16u) + ct * 16u + m;
-                    const uint32_t r = row0 + wr * (kSpRT * 16u) + rt * 16u + a * 4u;
-                    if (tok < p.tokens && r < p.rows) {       // rows is a multiple of 4: the four entries are in or out together
-                        const f32x4 v = acc[rt][ct];
-                        if constexpr (OUT_BF16) {
-                            // fp32 -> bf16, round to nearest even, by the hardware's packed conversion
-                            typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-                            typedef float f32x2 __attribute__((ext_vector_type(2)));
-                            union { bf16x2 h; uint32_t u; } c0, c1;
-                            c0.h = __builtin_convertvector(f32x2{v.x, v.y}, bf16x2);
-                            c1.h = __builtin_convertvector(f32x2{v.z, v.w}, bf16x2);
-                            const su32x2 o = {c0.u, c1.u};
-                            *(su32x2 *)((unsigned char *)p.y + ((size_t)tok * p.ld_y + r) * 2u) = o;
-                        } else {
-                            *(f32x4 *)((unsigned char *)p.y + ((size_t)tok * p.ld_y + r) * 4u) = v;
-                        }
+                    for (int q = 0; q < 8; q++) {
+                        union { bf16x2 h; uint32_t u; } cv;
+                        cv.h = __builtin_convertvector(f32x2{acc[rt][ct][2 * q], acc[rt][ct][2 * q + 1]}, bf16x2);
+                        d[q] = cv.u;
                     }
-                    acc[rt][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int q = 0; q < 2; q++) {
+                        const auto lo = __builtin_amdgcn_permlane32_swap(d[4 * q], d[4 * q + 2], false, false);
+                        const auto hi = __builtin_amdgcn_permlane32_swap(d[4 * q + 1], d[4 * q + 3], false, false);
+                        const uint32_t r = row0 + (uint32_t)rt * 32u + (uint32_t)q * 16u + a * 8u;
+                        unsigned char *dst = (unsigned char *)p.y + ((size_t)tok * p.ld_y + r) * 2u;
+                        if (whole || (tok < p.tokens && r + 8u <= p.rows))
+                            *(su32x4 *)dst = su32x4{lo[0], hi[0], lo[1], hi[1]};
+                        else if (tok < p.tokens && r + 4u <= p.rows)
+                            *(su32x2 *)dst = su32x2{lo[0], hi[0]};
+                    }
+                } else {
+#pragma unroll
+                    for (int q = 0; q < 4; q++) {
+                        const uint32_t r = row0 + (uint32_t)rt * 32u + (uint32_t)q * 8u + a * 4u;
+                        if (whole || (tok < p.tokens && r + 4u <= p.rows))
+                            *(f32x4 *)((unsigned char *)p.y + ((size_t)tok * p.ld_y + r) * 4u) =
+                                f32x4{acc[rt][ct][4 * q], acc[rt][ct][4 * q + 1], acc[rt][ct][4 * q + 2], acc[rt][ct][4 * q + 3]};
+                    }
                 }
             }
-        };
-        uint32_t mj = 0, mk = 0;          // tile ordinal and k-step being multiplied
-        auto mult = [&](int pos) {
-            multiply(pos);
-            __syncthreads();
-            if (++mk == steps) {          // the tile is complete: write it while the feeders run ahead
-                store_tile(mj);
-                mk = 0;
-                mj++;
-            }
-        };
-        __syncthreads();
-        read_b(0, bcur);
-        read_a(0, 0, a0, sel0);
-        uint32_t g = 0;
-        for (; g + 3 <= total; g += 3) {
-            mult(0);
-            mult(1);
-            mult(2);
         }
-        if (g < total)
-            mult(0);
-        if (g + 1 < total)
-            mult(1);
+        return whole;
+    };
+
+    set_tile(0);
+#pragma unroll
+    for (int g = 0; g < kTileRing; g++) {
+#pragma unroll
+        for (int i = 0; i < kCopies; i++)
+            copy_piece(i);
+        copied();
     }
+    // The next step is in LDS, for every wavefront.  The copies of the step after it may be in flight (those of the one after
+    // that are issued behind the barrier), and so may the stores of a tile if they were issued after the copies of the step.
+    uint32_t stored = 0;                                        // arrivals for which the last tile's stores count
+    auto arrive = [&]() {
+        constexpr int kFlight = (kTileRing - 2) * kCopies;
+        if (stored)
+            wait_copies<(kFlight + kStores < 63 ? kFlight + kStores : 63)>();
+        else
+            wait_copies<kFlight>();
+        stored -= stored ? 1u : 0u;
+        asm volatile("s_barrier" ::: "memory");
+    };
+    Frag f[2];
+    wait_copies<(kTileRing - 1) * kCopies>();
+    asm volatile("s_barrier" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < kReads; i++)
+        read_piece(f[0], 0, 0, i);
+    wait_lds_reads();
+    uint32_t image = 0;                                         // image being multiplied
+    for (uint32_t mj = 0; mj < my_tiles; mj++) {
+#pragma unroll
+        for (int i = 0; i < RT; i++)
+#pragma unroll
+            for (int j = 0; j < CT; j++)
+                acc[i][j] = (f32x16)(0.f);
+        for (uint32_t k = 0; k < steps; k++) {
+            const uint32_t next = image == (kTileRing - 1) * kImage ? 0 : image + kImage;
+            half(f[0], f[1], image, 1, std::false_type{});
+            arrive();
+            half(f[1], f[0], next, 0, std::true_type{});
+            image = next;
+        }
+        sums_ready();
+        stored = store_tile(mj) ? kTileRing - 1u : 0u;
+    }
+    wait_copies<0>();                                           // the last copies land while the workgroup still owns its LDS
 }
+
+// The tile sizes, and what a product takes with each, in microseconds: fixed + rounds (per_round + per_step cols / 64).
+// A round is what the compute units do side by side.  `resident` workgroups share a compute unit: of the smallest tiles so
+// many that rounds count in fractions; two of 128 x 128, which together take 1.6 times as long as one.  The coefficients
+// are a fit to 100 products (rows and cols 256 .. 4096, 1 .. 8192 tokens, bf16 results) timed with every tile size; the
+// choice they lead to is on average 0.3 % and at most 10 % slower than the fastest tile, and 3.3 times as fast (geometric
+// mean) as one kernel with 256 x 128 tiles for all: small tiles win while they fill no more than a few rounds, because a
+// compute unit alone moves 50 GB/s whatever its tile (W 4096 x 1024, 16 tokens: 15.8 -> 3.6 us on 16 x 16 tiles, 19 on
+// 256 x 256; 1024 x 4096, 1003 tokens: 55 -> 16 us on 64 x 64 tiles, 60 on 256 x 256), large ones when there are many,
+// because they move less (4096 x 1024, 8192 tokens: 55 us on 256 x 256, 70 on 128 x 128, 163 on 64 x 64).
+struct SpmmVariant {
+    void (*kernel[2])(const SpmmArgs);   // fp32, bf16 results
+    int64_t rows, tokens;                // of a tile
+    uint32_t resident, persistent;       // workgroups per compute unit; at most that many are launched (0: one per tile)
+    double fixed, per_round, per_step;
+    double estimate(uint64_t tiles, double steps, uint64_t cus) const
+    {
+        const double full = (double)tiles / (double)cus;
+        double rounds = ceil(full);
+        if (resident == 3)
+            rounds = full > 1.0 ? full : 1.0;
+        else if (resident == 2 && full > 1.0)
+            rounds = 1.6 * (full > 2.0 ? ceil(2.0 * full) / 4.0 : 1.0);
+        return fixed + rounds * (per_round + per_step * steps);
+    }
+};
+
+static const SpmmVariant kSpmmVariants[] = {
+    {{spmm24_ksplit_kernel<1, 1, 4, 4, false>, spmm24_ksplit_kernel<1, 1, 4, 4, true>}, 16, 16, 3, 0, 2.78, 0.295, 0.033},
+    {{spmm24_ksplit_kernel<2, 2, 4, 4, false>, spmm24_ksplit_kernel<2, 2, 4, 4, true>}, 32, 32, 1, 0, 1.47, 1.55, 0.071},
+    {{spmm24_ksplit_kernel<4, 4, 4, 3, false>, spmm24_ksplit_kernel<4, 4, 4, 3, true>}, 64, 64, 1, 0, 0.83, 3.16, 0.138},
+    {{spmm24_ksplit_kernel<8, 4, 4, 2, false>, spmm24_ksplit_kernel<8, 4, 4, 2, true>}, 128, 64, 1, 0, 0.17, 5.14, 0.197},
+    {{spmm24_tile_kernel<2, 2, false>, spmm24_tile_kernel<2, 2, true>}, 128, 128, 2, 2, 0.0, 4.2, 0.38},
+    {{spmm24_tile_kernel<2, 4, false>, spmm24_tile_kernel<2, 4, true>}, 128, 256, 1, 1, 0.0, 5.74, 0.524},
+    {{spmm24_tile_kernel<4, 4, false>, spmm24_tile_kernel<4, 4, true>}, 256, 256, 1, 1, 0.0, 8.08, 0.782},
+};
 
 }  // namespace tmask
 
@@ -361,23 +656,28 @@ extern "C" int tmask_spmm24(const void *vals, const void *idx, int64_t rows, int
     p.vals = vals; p.idx = idx; p.x = x; p.y = y;
     p.rows = (uint32_t)rows; p.cols = (uint32_t)cols; p.tokens = (uint32_t)tokens;
     p.ld_x = (uint32_t)ld_x; p.ld_y = (uint32_t)ld_y;
-    p.tiles_r = (uint32_t)((rows + kSpTR - 1) / kSpTR);
-    p.tiles_t = (uint32_t)((tokens + kSpTT - 1) / kSpTT);
-    const uint64_t n_tiles = (uint64_t)p.tiles_r * p.tiles_t;
-    if (n_tiles > 0x7FFFFFFFull)
+    if ((uint64_t)((rows + 255) / 256) * (uint64_t)((tokens + 127) / 128) > 0x7FFFFFFFull)
         return fail(TMASK_ERR_SHAPE, "too many tiles");
-    // one workgroup per compute unit, a multiple of 8 (the XCD count) when there are that many tiles
-    const int cus = cu_count();
-    uint32_t grid = n_tiles < (uint64_t)cus ? (uint32_t)n_tiles : (uint32_t)cus;
-    if (grid >= 8)
-        grid &= ~7u;
+    const uint64_t cus = (uint64_t)cu_count();
+    const SpmmVariant *best = nullptr;
+    double best_us = 0.0;
+    for (const SpmmVariant &v : kSpmmVariants) {
+        const uint64_t tiles = (uint64_t)((rows + v.rows - 1) / v.rows) * (uint64_t)((tokens + v.tokens - 1) / v.tokens);
+        const double us = v.estimate(tiles, (double)(cols / kSpKS), cus);
+        if (tiles <= 0x7FFFFFFFull && (!best || us < best_us)) {
+            best = &v;
+            best_us = us;
+        }
+    }
+    p.tiles_r = (uint32_t)((rows + best->rows - 1) / best->rows);
+    p.tiles_t = (uint32_t)((tokens + best->tokens - 1) / best->tokens);
+    uint32_t grid = p.tiles_r * p.tiles_t;
+    if (best->persistent && grid > best->persistent * cus)
+        grid = (uint32_t)(best->persistent * cus) & ~7u;        // a multiple of the XCD count, which the tile numbering assumes
     hipStream_t stream = (hipStream_t)hip_stream;
     {
         ProfileScope prof(stream, true);
-        if (out_dt == TMASK_BF16)
-            hipLaunchKernelGGL(spmm24_kernel<true>, dim3(grid), dim3(kSpThreads), 0, stream, p);
-        else
-            hipLaunchKernelGGL(spmm24_kernel<false>, dim3(grid), dim3(kSpThreads), 0, stream, p);
+        hipLaunchKernelGGL(best->kernel[out_dt == TMASK_BF16 ? 1 : 0], dim3(grid), dim3(256), 0, stream, p);
     }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess)

@@ -136,3 +136,32 @@ def test_spmm_argument_errors():
     assert lib.tmask_spmm24(*args(x=x.data_ptr() + 2)) == tm.TMASK_ERR_ALIGN
     assert lib.tmask_spmm24(*args(dt=7)) == tm.TMASK_ERR_DTYPE
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("rows,cols,tokens,out", [
+    (20, 64, 1, "f32"), (20, 1088, 17, "bf16"), (132, 320, 33, "f32"),                # one unit, one step in the last unit
+    (1020, 576, 129, "bf16"), (4092, 1088, 41, "f32"), (2044, 192, 127, "bf16"),
+    (1028, 1088, 499, "f32"), (1100, 64, 640, "bf16"), (4092, 1088, 509, "bf16"),     # 64 x 64 and 128 x 64 tiles
+    (3076, 128, 1001, "f32"), (4092, 64, 4100, "bf16"), (4100, 192, 4090, "f32"), (4100, 960, 4097, "bf16"),   # 128 x 128
+    (4092, 1024, 2003, "bf16"), (2052, 192, 4099, "f32"), (4100, 64, 2040, "bf16"),   # 128 x 256, 256 x 256
+    (4100, 256, 5000, "f32"), (4092, 320, 8190, "bf16"), (4100, 640, 8195, "bf16")])  # several tiles per workgroup
+def test_every_tile_size_at_its_edges(rows, cols, tokens, out):
+    """Shapes that take each of the tile sizes, with rows, tokens and the reduction off their multiples: sampled tokens
+    against the oracle's float64 product, nothing written outside y."""
+    pad, extra = 8, 3
+    w_bits = wl.f32_to_bf16_bits(wl.gaussian_f32(rows, cols, seed=6400 + rows + cols, std=0.05))
+    vals, idx, _, _ = oracle.apply_pack(w_bits, oracle.approx(w_bits, 2, 4, threads=8)[0], 2, 4)
+    x_bits = wl.f32_to_bf16_bits(wl.gaussian_f32(tokens, cols, seed=6401 + tokens))
+    dtype = torch.float32 if out == "f32" else torch.bfloat16
+    ld = (rows + 7) // 8 * 8 + pad
+    buf = torch.full((tokens + extra, ld), -7.0, dtype=dtype, device="cuda")
+    tm.tmask_spmm24(_bf16_dev(vals), torch.from_numpy(idx).cuda(), rows, cols, to_dev(x_bits), buf[:tokens, :rows])
+    torch.cuda.synchronize()
+    assert bool((buf[tokens:] == -7.0).all()) and bool((buf[:, rows:] == -7.0).all())
+    rng = np.random.default_rng(6402)
+    sample = np.unique(np.concatenate([np.arange(min(tokens, 33)), np.arange(max(tokens - 33, 0), tokens),
+                                       rng.integers(0, tokens, 40)]))
+    got = buf[torch.from_numpy(sample).cuda(), :rows].float().cpu().numpy().astype(np.float64)
+    want = oracle.spmm(vals, idx, rows, cols, 2, 4, x_bits[sample])
+    bound = _bound(vals, idx, rows, cols, x_bits[sample]) + (2.0 ** -8 * np.abs(want) if out == "bf16" else 0.0)
+    assert (np.abs(got - want) <= bound).all()
