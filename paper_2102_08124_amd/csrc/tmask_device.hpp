@@ -9,6 +9,8 @@
 //                          column-direction work is lane-local, row-direction work crosses the G
 //                          lanes with DPP quad permutes (G lanes are an aligned part of a quad)
 //   M*sizeof(elem)  < 16 : one lane = B = 2 adjacent blocks (bf16 M=4)
+// Narrow strips (kBF16N): bf16 at M = 4 in strips of 8 bytes, one block per lane, for matrices that are only 8-byte
+// aligned (a width that is a multiple of four, not of eight); everything past the load is as at fp32 M = 4.
 // Strips of a matrix are numbered block-row-major; a workgroup handles 256 consecutive strips.
 #pragma once
 #include <hip/hip_runtime.h>
@@ -30,6 +32,7 @@ __device__ __forceinline__ void stream_store(T v, T *p)
 
 constexpr int kF32 = 0;
 constexpr int kBF16 = 1;
+constexpr int kBF16N = 2;            // bf16 in strips of 8 bytes; exists at M = 4
 constexpr int kMaskU8 = 0;
 constexpr int kMaskBits = 1;
 constexpr int kThreads = 256;        // workgroup size of the streaming kernels
@@ -85,7 +88,7 @@ static_assert(sizeof(BatchArgs) <= 16384, "descriptor table is sized to stay a s
 template <int DT, int M>
 struct Geo {
     static constexpr int ES = (DT == kF32) ? 4 : 2;          // element bytes
-    static constexpr int C = 16 / ES;                        // columns per strip
+    static constexpr int C = DT == kBF16 ? 8 : 4;            // columns per strip
     static constexpr int G = (M > C) ? M / C : 1;            // lanes per block
     static constexpr int B = (M < C) ? C / M : 1;            // blocks per lane
     static constexpr int CL = C / B;                         // columns of one block inside a lane
@@ -265,7 +268,7 @@ __device__ __forceinline__ StripPos strip_pos(const MatDev &md, uint32_t s)
 // ---- strip load / store -------------------------------------------------------------------------
 
 // Loads the lane's strip: a[i][c] = |W| as an fp32 bit pattern (bf16 widened by << 16), i.e. the
-// magnitude ordering key, and raw[i] = the untouched 16 bytes of row i.
+// magnitude ordering key, and raw[i] = the untouched 16 (kBF16N: 8) bytes of row i.
 template <int DT, int M>
 __device__ __forceinline__ void load_strip(const MatDev &md, StripPos p, uint32_t (&a)[M][Geo<DT, M>::C],
                                            u32x4 (&raw)[M])
@@ -274,8 +277,14 @@ __device__ __forceinline__ void load_strip(const MatDev &md, StripPos p, uint32_
     const char *base = (const char *)md.w + ((size_t)p.br * M * md.ld + (size_t)p.sc * C) * Geo<DT, M>::ES;
     const size_t row_bytes = (size_t)md.ld * Geo<DT, M>::ES;
 #pragma unroll
-    for (int i = 0; i < M; i++)
-        raw[i] = __builtin_nontemporal_load((const u32x4 *)(base + i * row_bytes));
+    for (int i = 0; i < M; i++) {
+        if constexpr (DT == kBF16N) {
+            const u32x2 v = __builtin_nontemporal_load((const u32x2 *)(base + i * row_bytes));
+            raw[i] = u32x4{v.x, v.y, 0u, 0u};
+        } else {
+            raw[i] = __builtin_nontemporal_load((const u32x4 *)(base + i * row_bytes));
+        }
+    }
 #pragma unroll
     for (int i = 0; i < M; i++) {
         const uint32_t d[4] = {raw[i].x, raw[i].y, raw[i].z, raw[i].w};
@@ -285,7 +294,7 @@ __device__ __forceinline__ void load_strip(const MatDev &md, StripPos p, uint32_
                 a[i][c] = d[c] & 0x7FFFFFFFu;
         } else {
 #pragma unroll
-            for (int c = 0; c < 4; c++) {
+            for (int c = 0; c < C / 2; c++) {
                 a[i][2 * c] = (d[c] << 16) & 0x7FFF0000u;
                 a[i][2 * c + 1] = d[c] & 0x7FFF0000u;
             }

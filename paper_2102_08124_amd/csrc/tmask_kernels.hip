@@ -380,7 +380,7 @@ __global__ __launch_bounds__(kThreads) void approx_dense_kernel(const BatchArgs 
                     v[c] = __uint_as_float(d[c]);
             } else {
 #pragma unroll
-                for (int c = 0; c < 4; c++) {
+                for (int c = 0; c < C / 2; c++) {
                     v[2 * c] = __uint_as_float(d[c] << 16);
                     v[2 * c + 1] = __uint_as_float(d[c] & 0xFFFF0000u);
                 }
@@ -416,7 +416,7 @@ __global__ __launch_bounds__(kThreads) void approx_dense_kernel(const BatchArgs 
                 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
                 typedef float f32x2 __attribute__((ext_vector_type(2)));
 #pragma unroll
-                for (int c = 0; c < 4; c++) {
+                for (int c = 0; c < C / 2; c++) {
                     union { bf16x2 h; uint32_t w; } cv;
                     cv.h = __builtin_convertvector(f32x2{v[2 * c], v[2 * c + 1]}, bf16x2);   // round to nearest even
                     d[c] = cv.w;
@@ -424,14 +424,17 @@ __global__ __launch_bounds__(kThreads) void approx_dense_kernel(const BatchArgs 
             }
         } else {
 #pragma unroll
-            for (int q = 0; q < 4; q++) {
+            for (int q = 0; q < C * ES / 4; q++) {
                 if constexpr (DT == kF32)
                     d[q] &= 0u - ((bits[i] >> q) & 1u);
                 else
                     d[q] &= ((0u - ((bits[i] >> (2 * q)) & 1u)) & 0xFFFFu) | ((0u - ((bits[i] >> (2 * q + 1)) & 1u)) << 16);
             }
         }
-        stream_store(u32x4{d[0], d[1], d[2], d[3]}, (u32x4 *)(ob + i * out_row_bytes));
+        if constexpr (DT == kBF16N)
+            stream_store(u32x2{d[0], d[1]}, (u32x2 *)(ob + i * out_row_bytes));
+        else
+            stream_store(u32x4{d[0], d[1], d[2], d[3]}, (u32x4 *)(ob + i * out_row_bytes));
     }
 }
 
@@ -906,13 +909,32 @@ struct HostMat {
     double *objective;
 };
 
-// Validates one matrix for (dt, N, M, mf).  *aligned is cleared (never set) when the matrix misses what the strip
-// kernels read and write with -- w 16-byte aligned with ld and cols multiples of 16 bytes, a U8 mask and its pitch
-// multiples of the strip width -- in which case the call runs on the column-per-lane kernels instead.
-static int check_mat(const HostMat &h, int idx, int dt, int M, int mf, bool need_mask, bool *aligned)
+// What the matrices of a call let it run on: strips of 16 bytes, the 8-byte strips that exist for bf16 at M = 4, or only
+// the column-per-lane kernels (also M = 32).  Narrow strips move half the bytes per instruction, but a matrix whose width
+// is an odd multiple of four then runs at the speed of the others: 1000 x 2052 bf16 2:4, mask 20 -> 5 us, score 24 -> 5 us,
+// compression 13 -> 8 us (the three calls with their second stages 62.9 -> 32.2 us).
+enum Fit { kFitColumns, kFitNarrow, kFitWide };
+
+static Fit fit_at_best(int M) { return M == 32 ? kFitColumns : kFitWide; }
+
+// Lowers *fit to what addresses (or pitches in bytes) allow that are all multiples of the powers of two in `bits`, for
+// accesses of `wide` bytes, or `wide` / 2 with narrow strips.
+static void lower_fit(Fit *fit, uint64_t bits, uint64_t wide, bool narrow)
+{
+    if (*fit == kFitWide && bits % wide)
+        *fit = narrow ? kFitNarrow : kFitColumns;
+    if (*fit == kFitNarrow && bits % (wide / 2))
+        *fit = kFitColumns;
+}
+
+// Validates one matrix for (dt, N, M, mf).  *fit is lowered (never raised) when the matrix misses what the strip
+// kernels read and write with: w 16-byte aligned with ld and cols multiples of 16 bytes, a U8 mask and its pitch
+// multiples of the strip width; half of all that for narrow strips.
+static int check_mat(const HostMat &h, int idx, int dt, int M, int mf, bool need_mask, Fit *fit)
 {
     const size_t es = elem_size(dt);
     const int64_t C = 16 / (int64_t)es;
+    const bool narrow = dt == TMASK_BF16 && M == 4;
     if (!h.w || (need_mask && !h.mask))
         return fail(TMASK_ERR_NULL, "matrix %d: w or mask is NULL", idx);
     if (h.rows <= 0 || h.cols <= 0 || h.rows % M || h.cols % M || h.ld < h.cols)
@@ -922,14 +944,12 @@ static int check_mat(const HostMat &h, int idx, int dt, int M, int mf, bool need
         return fail(TMASK_ERR_SHAPE, "matrix %d: too large (ld, mask_ld and strip count must stay below 2^31)", idx);
     if ((uintptr_t)h.w % es)
         return fail(TMASK_ERR_ALIGN, "matrix %d: w must be aligned to its element size", idx);
-    if (((uintptr_t)h.w & 15) || (h.ld * es) % 16 || (h.cols * es) % 16)
-        *aligned = false;
+    lower_fit(fit, (uint64_t)(uintptr_t)h.w | (uint64_t)(h.ld * es) | (uint64_t)(h.cols * es), 16, narrow);
     if (h.mask) {
         if (mf == TMASK_MASK_U8) {
             if (h.mask_ld < h.cols)
                 return fail(TMASK_ERR_SHAPE, "matrix %d: mask_ld=%lld < cols", idx, (long long)h.mask_ld);
-            if (((uintptr_t)h.mask % C) || (h.mask_ld % C))
-                *aligned = false;
+            lower_fit(fit, (uint64_t)(uintptr_t)h.mask | (uint64_t)h.mask_ld, (uint64_t)C, narrow);
         } else {
             if (h.cols % 8)
                 return fail(TMASK_ERR_SHAPE, "matrix %d: BITS masks need cols to be a multiple of 8", idx);
@@ -940,21 +960,26 @@ static int check_mat(const HostMat &h, int idx, int dt, int M, int mf, bool need
     return TMASK_OK;
 }
 
-static uint32_t strips_of(const HostMat &h, int dt, int M)
+// sdt: the strip kernels' type (kF32, kBF16, or kBF16N for narrow strips)
+static int strip_type(int dt, Fit fit) { return fit == kFitNarrow ? (int)kBF16N : dt; }
+
+static int64_t strip_cols(int sdt) { return sdt == kBF16 ? 8 : 4; }
+
+static uint32_t strips_of(const HostMat &h, int sdt, int M)
 {
-    const int64_t C = 16 / (int64_t)elem_size(dt);
+    const int64_t C = strip_cols(sdt);
     return (uint32_t)((h.rows / M) * (h.cols / C));
 }
 
 static uint32_t tiles_of(uint32_t n_strips) { return (n_strips + kThreads - 1) / kThreads; }
 
-static void fill_desc(MatDev &d, const HostMat &h, int dt, int M, uint32_t tile0)
+static void fill_desc(MatDev &d, const HostMat &h, int sdt, int M, uint32_t tile0)
 {
-    const int64_t C = 16 / (int64_t)elem_size(dt);
+    const int64_t C = strip_cols(sdt);
     d.w = h.w; d.mask = h.mask; d.aux = nullptr;
     d.ld = (uint32_t)h.ld; d.mask_ld = (uint32_t)h.mask_ld;
     d.spr = (uint32_t)(h.cols / C);
-    d.n_strips = strips_of(h, dt, M);
+    d.n_strips = strips_of(h, sdt, M);
     magic_div(d.spr, &d.div_mul, &d.div_shift);
     d.tile0 = tile0; d.pad = 0;
 }
@@ -970,6 +995,7 @@ static batch_kernel_t pick_mask_kernel(int dt, int M, int mf)
     TMASK_PICK(kBF16, 4, kMaskU8) TMASK_PICK(kBF16, 8, kMaskU8) TMASK_PICK(kBF16, 16, kMaskU8)
     TMASK_PICK(kF32, 4, kMaskBits) TMASK_PICK(kF32, 8, kMaskBits) TMASK_PICK(kF32, 16, kMaskBits)
     TMASK_PICK(kBF16, 4, kMaskBits) TMASK_PICK(kBF16, 8, kMaskBits) TMASK_PICK(kBF16, 16, kMaskBits)
+    TMASK_PICK(kBF16N, 4, kMaskU8) TMASK_PICK(kBF16N, 4, kMaskBits)
 #undef TMASK_PICK
     return nullptr;
 }
@@ -982,6 +1008,7 @@ static batch_kernel_t pick_score_kernel(int dt, int M, int mf)
     TMASK_PICK(kBF16, 4, kMaskU8) TMASK_PICK(kBF16, 8, kMaskU8) TMASK_PICK(kBF16, 16, kMaskU8)
     TMASK_PICK(kF32, 4, kMaskBits) TMASK_PICK(kF32, 8, kMaskBits) TMASK_PICK(kF32, 16, kMaskBits)
     TMASK_PICK(kBF16, 4, kMaskBits) TMASK_PICK(kBF16, 8, kMaskBits) TMASK_PICK(kBF16, 16, kMaskBits)
+    TMASK_PICK(kBF16N, 4, kMaskU8) TMASK_PICK(kBF16N, 4, kMaskBits)
 #undef TMASK_PICK
     return nullptr;
 }
@@ -1076,19 +1103,21 @@ static int run_mask(const tmask_mat *mats, int n_mats, int dt, int N, int M, int
     int rc = check_common(mats, n_mats, dt, N, M, mf);
     if (rc)
         return rc;
-    bool want_obj = false, aligned = (M != 32);
+    bool want_obj = false;
+    Fit fit = fit_at_best(M);
     for (int i = 0; i < n_mats; i++) {
         const HostMat h{mats[i].w, mats[i].rows, mats[i].cols, mats[i].ld, mats[i].mask, mats[i].mask_ld,
                         mats[i].objective};
-        if ((rc = check_mat(h, i, dt, M, mf, true, &aligned)))
+        if ((rc = check_mat(h, i, dt, M, mf, true, &fit)))
             return rc;
         want_obj = want_obj || mats[i].objective;
     }
+    const int sdt = strip_type(dt, fit);
     if (own_scratch) {
         size_t tiles = 0;
         for (int i = 0; i < n_mats; i++) {
             const HostMat h{mats[i].w, mats[i].rows, mats[i].cols, mats[i].ld, nullptr, 0, nullptr};
-            tiles += aligned ? tiles_of(strips_of(h, dt, M)) : cw_workgroups(h.rows, h.cols, M);
+            tiles += fit != kFitColumns ? tiles_of(strips_of(h, sdt, M)) : cw_workgroups(h.rows, h.cols, M);
         }
         if (want_obj && tiles > kScratchPartials)
             return fail(TMASK_ERR_WORKSPACE,
@@ -1104,33 +1133,41 @@ static int run_mask(const tmask_mat *mats, int n_mats, int dt, int N, int M, int
     // Algorithm 1 at bf16, where keys are unique and a row lies in two lanes); the column-per-lane kernels take a
     // threshold from a sorting network
     const bool general_n = 2 * N != M && M == 16 && SOLVER != kSolveExact && !(SOLVER == kSolveApprox && dt == kBF16);
-    if (!aligned || general_n)     // also M = 32, or a matrix that the 16-byte strips cannot read
+    if (fit == kFitColumns || general_n)     // also M = 32, or a matrix that the strips cannot read
         return cw_run_mask(SOLVER == kSolveApprox ? 0 : SOLVER == kSolveExact ? 1 : 2, mats, n_mats, dt, N, M, mf, ws,
                            (hipStream_t)stream_);
     batch_kernel_t kern = nullptr;
     if constexpr (SOLVER != kSolveExact)      // exact: enumeration at M = 4, the balanced kernel at M = 8, 16 (below)
-        kern = pick_mask_kernel<SOLVER>(dt, M, mf);
+        kern = pick_mask_kernel<SOLVER>(sdt, M, mf);
     if (SOLVER == kSolveApprox && M == 4 && N == 2) {
-        if (dt == kF32)
+        if (sdt == kF32)
             kern = mf == kMaskU8 ? approx24_kernel<kF32, kMaskU8> : approx24_kernel<kF32, kMaskBits>;
+        else if (sdt == kBF16N)
+            kern = mf == kMaskU8 ? approx24_kernel<kBF16N, kMaskU8> : approx24_kernel<kBF16N, kMaskBits>;
         else
             kern = mf == kMaskU8 ? approx24_kernel<kBF16, kMaskU8> : approx24_kernel<kBF16, kMaskBits>;
     }
     if (SOLVER == kSolveExact && M == 4 && N == 2) {
-        if (dt == kF32)
+        if (sdt == kF32)
             kern = mf == kMaskU8 ? exact24_kernel<kF32, kMaskU8> : exact24_kernel<kF32, kMaskBits>;
+        else if (sdt == kBF16N)
+            kern = mf == kMaskU8 ? exact24_kernel<kBF16N, kMaskU8> : exact24_kernel<kBF16N, kMaskBits>;
         else
             kern = mf == kMaskU8 ? exact24_kernel<kBF16, kMaskU8> : exact24_kernel<kBF16, kMaskBits>;
     }
     if (SOLVER == kSolveExact && M == 4 && N == 1) {
-        if (dt == kF32)
+        if (sdt == kF32)
             kern = mf == kMaskU8 ? exact24_kernel<kF32, kMaskU8, 1> : exact24_kernel<kF32, kMaskBits, 1>;
+        else if (sdt == kBF16N)
+            kern = mf == kMaskU8 ? exact24_kernel<kBF16N, kMaskU8, 1> : exact24_kernel<kBF16N, kMaskBits, 1>;
         else
             kern = mf == kMaskU8 ? exact24_kernel<kBF16, kMaskU8, 1> : exact24_kernel<kBF16, kMaskBits, 1>;
     }
     if (SOLVER == kSolveExact && M == 4 && N == 3) {
-        if (dt == kF32)
+        if (sdt == kF32)
             kern = mf == kMaskU8 ? exact24_kernel<kF32, kMaskU8, 3> : exact24_kernel<kF32, kMaskBits, 3>;
+        else if (sdt == kBF16N)
+            kern = mf == kMaskU8 ? exact24_kernel<kBF16N, kMaskU8, 3> : exact24_kernel<kBF16N, kMaskBits, 3>;
         else
             kern = mf == kMaskU8 ? exact24_kernel<kBF16, kMaskU8, 3> : exact24_kernel<kBF16, kMaskBits, 3>;
     }
@@ -1171,7 +1208,7 @@ static int run_mask(const tmask_mat *mats, int n_mats, int dt, int N, int M, int
         for (int k = 0; k < nb; k++) {
             const tmask_mat &t = mats[first + k];
             const HostMat h{t.w, t.rows, t.cols, t.ld, t.mask, t.mask_ld, t.objective};
-            fill_desc(args.m[k], h, dt, M, tiles);
+            fill_desc(args.m[k], h, sdt, M, tiles);
             rargs.objective[k] = t.objective;
             rargs.tile0[k] = tiles;
             tiles += tiles_of(args.m[k].n_strips * unit_split);
@@ -1280,19 +1317,20 @@ int tmask_score(const tmask_mat *mats, int n_mats, tmask_dtype dt, int N, int M,
         return rc;
     if (!out)
         return fail(TMASK_ERR_NULL, "out is NULL");
-    bool aligned = (M != 32);
+    Fit fit = fit_at_best(M);
     for (int i = 0; i < n_mats; i++) {
         const HostMat h{mats[i].w, mats[i].rows, mats[i].cols, mats[i].ld, mats[i].mask, mats[i].mask_ld, nullptr};
-        if ((rc = check_mat(h, i, (int)dt, M, (int)mf, true, &aligned)))
+        if ((rc = check_mat(h, i, (int)dt, M, (int)mf, true, &fit)))
             return rc;
     }
     if ((rc = check_workspace(mats, n_mats, M, workspace, workspace_bytes)))
         return rc;
     if (per_block_obj && ((uintptr_t)per_block_obj & 3))
         return fail(TMASK_ERR_ALIGN, "per_block_obj must be 4-byte aligned");
-    if (!aligned)
+    if (fit == kFitColumns)
         return cw_run_score(mats, n_mats, (int)dt, N, M, (int)mf, out, per_block_obj, workspace, (hipStream_t)hip_stream);
-    const batch_kernel_t kern = pick_score_kernel((int)dt, M, (int)mf);
+    const int sdt = strip_type((int)dt, fit);
+    const batch_kernel_t kern = pick_score_kernel(sdt, M, (int)mf);
     hipStream_t stream = (hipStream_t)hip_stream;
     uint32_t partial0 = 0;
     size_t block0 = 0;
@@ -1306,7 +1344,7 @@ int tmask_score(const tmask_mat *mats, int n_mats, tmask_dtype dt, int N, int M,
         for (int k = 0; k < nb; k++) {
             const tmask_mat &t = mats[first + k];
             const HostMat h{t.w, t.rows, t.cols, t.ld, t.mask, t.mask_ld, nullptr};
-            fill_desc(args.m[k], h, (int)dt, M, tiles);
+            fill_desc(args.m[k], h, sdt, M, tiles);
             args.m[k].aux = per_block_obj ? (void *)(per_block_obj + block0) : nullptr;
             block0 += (size_t)(t.rows / M) * (size_t)(t.cols / M);
             rargs.tile0[k] = tiles;
@@ -1363,26 +1401,27 @@ int tmask_apply_pack(const tmask_pack_desc *descs, int n, tmask_dtype dt, int N,
     if (rc)
         return rc;
     // M = 32: the tiled kernel at 16:32 (a tile row's position bits are then whole bytes), the column-per-lane one else
-    bool aligned = (M != 32) || (N == 16);
+    Fit fit = (M != 32) || (N == 16) ? kFitWide : kFitColumns;
     for (int i = 0; i < n; i++) {
         const tmask_pack_desc &p = descs[i];
         const HostMat h{p.w, p.rows, p.cols, p.ld, const_cast<void *>(p.mask), p.mask_ld, nullptr};
-        if ((rc = check_mat(h, i, (int)dt, M, (int)mf, true, &aligned)))
+        if ((rc = check_mat(h, i, (int)dt, M, (int)mf, true, &fit)))
             return rc;
         if (!p.vals || !p.idx || !p.valsT || !p.idxT)
             return fail(TMASK_ERR_NULL, "matrix %d: a packed output pointer is NULL", i);
         if (((uintptr_t)p.vals | (uintptr_t)p.valsT) % elem_size((int)dt))
             return fail(TMASK_ERR_ALIGN, "matrix %d: vals and valsT must be aligned to the element size", i);
         if (((uintptr_t)p.vals & 3) || ((uintptr_t)p.valsT & 3))
-            aligned = false;
+            fit = kFitColumns;
         if (M == 32 && ((uintptr_t)p.vals & 15))     // its row groups leave as 16-byte stores only
-            aligned = false;
+            fit = kFitColumns;
     }
-    if (!aligned)
+    const bool narrow24 = fit == kFitNarrow && N == 2;           // the only kernel with narrow strips
+    if (fit != kFitWide && !narrow24)
         return cw_run_pack(descs, n, (int)dt, N, M, (int)mf, (hipStream_t)hip_stream);
     pack_kernel_t kern = pick_pack_kernel((int)dt, M, (int)mf, N);
     uint32_t TC = 256 / (uint32_t)elem_size((int)dt);
-    bool fast24 = (M == 4 && N == 2);
+    bool fast24 = (M == 4 && N == 2) && !narrow24;
     for (int i = 0; i < n && fast24; i++)
         fast24 = (((uintptr_t)descs[i].vals | (uintptr_t)descs[i].valsT) & 7) == 0;
     uint32_t TR = kPackTR, lds_reserve = 0, threads = kThreads;
@@ -1402,6 +1441,15 @@ int tmask_apply_pack(const tmask_pack_desc *descs, int n, tmask_dtype dt, int N,
         TR = 4 * QN * (64 / strips) * NW;
         threads = 64 * NW;
         lds_reserve = dt == TMASK_F32 ? kPack4LdsReservePackF32 : 0;
+    }
+    if (narrow24) {
+        // 8-byte strips, which write 4 bytes per row: tiles of 64 rows x 128 columns, a quarter of the others' bytes, since
+        // such matrices are mostly small (1000 x 2052: 272 workgroups)
+        kern = mf == TMASK_MASK_U8 ? pack24_kernel<kBF16N, kMaskU8, 32, 4, 2> : pack24_kernel<kBF16N, kMaskBits, 32, 4, 2>;
+        using PG = Pack4Geo<kBF16N, 32, 4, 2>;
+        TC = PG::TC;
+        TR = PG::TR;
+        threads = PG::NT;
     }
     bool fast48 = (M == 8 && N == 4 && dt == TMASK_BF16);
     for (int i = 0; i < n && fast48; i++)
@@ -1464,13 +1512,14 @@ int tmask_approx_pack(const tmask_fused_desc *descs, int n, tmask_dtype dt, int 
     bool fused24 = (M == 4 && N == 2);                         // both need aligned inputs and 8-byte aligned outputs,
     bool fused48 = (M == 8 && N == 4);                         // else the call runs as two steps
     int with_mask = 0;
-    bool want_obj = false, aligned = (M != 32);
+    bool want_obj = false;
+    Fit fit = fit_at_best(M);
     for (int i = 0; i < n; i++) {
         const tmask_fused_desc &p = descs[i];
         with_mask += p.mask ? 1 : 0;
         want_obj = want_obj || p.objective;
         const HostMat h{p.w, p.rows, p.cols, p.ld, p.mask, p.mask_ld, p.objective};
-        if ((rc = check_mat(h, i, (int)dt, M, (int)mf, p.mask != nullptr, &aligned)))
+        if ((rc = check_mat(h, i, (int)dt, M, (int)mf, p.mask != nullptr, &fit)))
             return rc;
         if (!p.vals || !p.idx || !p.valsT || !p.idxT)
             return fail(TMASK_ERR_NULL, "matrix %d: a packed output pointer is NULL", i);
@@ -1480,7 +1529,7 @@ int tmask_approx_pack(const tmask_fused_desc *descs, int n, tmask_dtype dt, int 
         fused24 = fused24 && out8;
         fused48 = fused48 && out8;
     }
-    const bool fused = aligned && (fused24 || fused48);
+    const bool fused = fit == kFitWide && (fused24 || fused48);
     if (with_mask != 0 && with_mask != n)
         return fail(TMASK_ERR_NULL, "mask must be given for all matrices or for none (%d of %d have one)", with_mask, n);
     if (!fused && with_mask == 0)
@@ -1588,12 +1637,12 @@ static int run_mask_dense(const tmask_mask_dense_desc *descs, int n, tmask_dtype
         return rc;
     const int64_t es = elem_size((int)dt);
     int with_mask = 0;
-    bool aligned = (M != 32);
+    Fit fit = fit_at_best(M);
     for (int i = 0; i < n; i++) {
         const tmask_mask_dense_desc &p = descs[i];
         with_mask += p.mask ? 1 : 0;
         const HostMat h{p.w, p.rows, p.cols, p.ld, p.mask, p.mask_ld, nullptr};
-        if ((rc = check_mat(h, i, (int)dt, M, (int)mf, p.mask != nullptr, &aligned)))
+        if ((rc = check_mat(h, i, (int)dt, M, (int)mf, p.mask != nullptr, &fit)))
             return rc;
         if (!p.out)
             return fail(TMASK_ERR_NULL, "matrix %d: out is NULL", i);
@@ -1602,21 +1651,21 @@ static int run_mask_dense(const tmask_mask_dense_desc *descs, int n, tmask_dtype
                         (long long)p.cols);
         if ((uintptr_t)p.out % (uintptr_t)es)
             return fail(TMASK_ERR_ALIGN, "matrix %d: out must be aligned to its element size", i);
-        if (((uintptr_t)p.out | (uint64_t)(p.ld_out * es)) & 15)
-            aligned = false;
+        lower_fit(&fit, (uint64_t)(uintptr_t)p.out | (uint64_t)(p.ld_out * es), 16, dt == TMASK_BF16 && M == 4);
     }
     if (with_mask != 0 && with_mask != n)
         return fail(TMASK_ERR_NULL, "mask must be given for all matrices or for none (%d of %d have one)", with_mask, n);
     // Algorithm 1 with N != M/2 at M = 16: the strip kernels have only their rank form there (see run_mask); the
     // row modes are faster on the strips (8192^2 fp32 5:16 with absorption: 101 against 121 us)
-    if (!aligned || (2 * N != M && M == 16 && mode == kDenseApprox && dt != kBF16)) {
+    if (fit == kFitColumns || (2 * N != M && M == 16 && mode == kDenseApprox && dt != kBF16)) {
         const bool absorb = mode == kDenseRow1DAbsorb || mode == kDenseRow1DHalfAbsorb;
         const bool rows_only = absorb || mode == kDenseRow1D || mode == kDenseRow1DHalf;
         return cw_run_dense(descs, n, (int)dt, N, M, (int)mf, absorb ? 2 : rows_only ? 1 : 0, (hipStream_t)hip_stream);
     }
+    const int sdt = strip_type((int)dt, fit);
     batch_kernel_t kern = nullptr;
 #define TMASK_PICK(DT, MM, FM) \
-    if ((int)dt == DT && M == MM && (int)mf == FM) \
+    if (sdt == DT && M == MM && (int)mf == FM) \
         kern = mode == kDenseApprox ? approx_dense_kernel<DT, MM, FM, kDenseApprox> \
              : mode == kDenseApproxHalf ? approx_dense_kernel<DT, MM, FM, kDenseApproxHalf> \
              : mode == kDenseRow1D ? approx_dense_kernel<DT, MM, FM, kDenseRow1D> \
@@ -1625,6 +1674,7 @@ static int run_mask_dense(const tmask_mask_dense_desc *descs, int n, tmask_dtype
     TMASK_PICK(kBF16, 4, kMaskU8) TMASK_PICK(kBF16, 8, kMaskU8) TMASK_PICK(kBF16, 16, kMaskU8)
     TMASK_PICK(kF32, 4, kMaskBits) TMASK_PICK(kF32, 8, kMaskBits) TMASK_PICK(kF32, 16, kMaskBits)
     TMASK_PICK(kBF16, 4, kMaskBits) TMASK_PICK(kBF16, 8, kMaskBits) TMASK_PICK(kBF16, 16, kMaskBits)
+    TMASK_PICK(kBF16N, 4, kMaskU8) TMASK_PICK(kBF16N, 4, kMaskBits)
 #undef TMASK_PICK
 #define TMASK_PICK(MM, FM) \
     if ((int)dt == kBF16 && M == MM && (int)mf == FM && mode >= kDenseRow1DHalf) \
@@ -1641,7 +1691,7 @@ static int run_mask_dense(const tmask_mask_dense_desc *descs, int n, tmask_dtype
         for (int k = 0; k < nb; k++) {
             const tmask_mask_dense_desc &p = descs[first + k];
             const HostMat h{p.w, p.rows, p.cols, p.ld, p.mask, p.mask_ld, nullptr};
-            fill_desc(args.m[k], h, (int)dt, M, tiles);
+            fill_desc(args.m[k], h, sdt, M, tiles);
             args.m[k].aux = p.out;
             args.m[k].pad = (uint32_t)p.ld_out;
             tiles += tiles_of(args.m[k].n_strips);

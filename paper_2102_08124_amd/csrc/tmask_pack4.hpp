@@ -1,5 +1,6 @@
 // tmask_apply_pack specialised to M = 4, N = 2 (the 2:4 transposable case); same output format as
 // the general kernel in tmask_pack.hpp (described in include/tmask.h).
+// kBF16N: matrices that are 8-byte aligned only, in strips of 8 bytes (one group of four per lane and row).
 //
 // One workgroup packs a tile of 64 KiB of W: S strips of 16 bytes wide, 4096 / S rows high (Pack4Geo).  A
 // wavefront owns 64 / S runs of four block-rows, a lane one strip of one run, so every load is a contiguous
@@ -76,7 +77,7 @@ __device__ __forceinline__ lanemask_t keep_flag(uint32_t m0, uint32_t m1, int c)
 template <int DT, int S = kPack4Strips, int NW = 4, int QN = 4>
 struct Pack4Geo {
     static constexpr int ES = (DT == kF32) ? 4 : 2;
-    static constexpr int C = 16 / ES;                  // columns per strip
+    static constexpr int C = DT == kBF16 ? 8 : 4;      // columns per strip
     static constexpr int NG = C / 4;                   // groups per strip row
     static constexpr int LPR = 64 / S;                 // block-rows a wavefront touches per step
     static constexpr int NT = 64 * NW;                 // threads per workgroup
@@ -205,9 +206,9 @@ __global__ __launch_bounds__(64 * NW) void pack24_kernel(const PackArgs args)
     const size_t pitchW = (size_t)(d.cols / 4) * 2;    // elements per row of vals
     // byte offsets of the lane against row 16 * LPR * w of the tile, column col0
     constexpr uint32_t RUN = 4u * QN;                   // rows of a lane's run of block-rows
-    const size_t lane_w = (size_t)sub * RUN * d.ld * ES + strip * 16u;
+    const size_t lane_w = (size_t)sub * RUN * d.ld * ES + strip * (uint32_t)(C * ES);
     const size_t lane_m = (size_t)sub * RUN * d.mask_ld;
-    const size_t lane_v = (size_t)sub * RUN * pitchW * ES + strip * 8u;
+    const size_t lane_v = (size_t)sub * RUN * pitchW * ES + strip * (uint32_t)(C * ES / 2);
 
     // Tiles that lie wholly inside the matrix take a copy of the code without any bounds test: no branch
     // splits the loop, so the waits on the prefetched rows are exact.
@@ -234,8 +235,14 @@ __global__ __launch_bounds__(64 * NW) void pack24_kernel(const PackArgs args)
             if (!EDGE || (strip_ok && row < d.rows)) {
 #pragma unroll
                 for (int i = 0; i < 4; i++) {
-                    raw[i] = __builtin_nontemporal_load(
-                        (const u32x4 *)((const char *)d.w + ((size_t)(wrow + i) * d.ld + col0) * ES + lane_w));
+                    const char *wp = (const char *)d.w + ((size_t)(wrow + i) * d.ld + col0) * ES + lane_w;
+                    if constexpr (DT == kBF16N) {
+                        const u32x2 v = __builtin_nontemporal_load((const u32x2 *)wp);
+                        raw[i].x = v.x;
+                        raw[i].y = v.y;
+                    } else {
+                        raw[i] = __builtin_nontemporal_load((const u32x4 *)wp);
+                    }
                     if constexpr (FMT == kMaskU8) {
                         const char *mp = (const char *)d.mask + ((size_t)(wrow + i) * d.mask_ld + col0) + lane_m + tcol;
                         if constexpr (C == 4) {
@@ -302,7 +309,7 @@ __global__ __launch_bounds__(64 * NW) void pack24_kernel(const PackArgs args)
                     }
                     rownib[i] |= nib << (4 * g);
                     // bf16: without the pins the compiler keeps every select result alive and merges at the end
-                    if constexpr (DT == kBF16) {
+                    if constexpr (DT != kF32) {
                         asm volatile("" : "+v"(rownib[i]));
                         asm volatile("" : "+v"(rowout[i][g]));
                     }
@@ -317,7 +324,7 @@ __global__ __launch_bounds__(64 * NW) void pack24_kernel(const PackArgs args)
                                  keep_flag<FMT>(m0[2], m1[2], 4 * g + c), keep_flag<FMT>(m0[3], m1[3], 4 * g + c), e[0][c],
                                  e[1][c], e[2][c], e[3][c], t0[c], t1[c], nib);
                     tnib[4 * g + c] |= nib << (4 * q);
-                    if constexpr (DT == kBF16) {
+                    if constexpr (DT != kF32) {
                         t0[c] |= t1[c] << 16;
                         asm volatile("" : "+v"(tnib[4 * g + c]));
                         asm volatile("" : "+v"(t0[c]));
@@ -339,10 +346,11 @@ __global__ __launch_bounds__(64 * NW) void pack24_kernel(const PackArgs args)
             if (ok) {
 #pragma unroll
                 for (int i = 0; i < 4; i++) {
-                    u32x2 v;
-                    v.x = rowout[i][0];
-                    v.y = rowout[i][1];
-                    stream_store(v, (u32x2 *)((char *)d.vals + ((size_t)(wrow + i) * pitchW + (size_t)(col0 / 4) * 2) * ES + lane_v));
+                    char *vp = (char *)d.vals + ((size_t)(wrow + i) * pitchW + (size_t)(col0 / 4) * 2) * ES + lane_v;
+                    if constexpr (DT == kBF16N)
+                        stream_store(rowout[i][0], (uint32_t *)vp);
+                    else
+                        stream_store(u32x2{rowout[i][0], rowout[i][1]}, (u32x2 *)vp);
                 }
             }
 #pragma unroll

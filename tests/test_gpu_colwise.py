@@ -312,6 +312,74 @@ def test_unaligned_packed_outputs_only():
         assert np.array_equal(gh.view(np.uint8), t.view(np.uint8))
 
 
+# ---------------------------------------------------------------- bf16, M = 4, 8-byte aligned: narrow strips ------
+
+@pytest.mark.parametrize("N", [1, 2, 3])
+@pytest.mark.parametrize("kind,fmt,rows,cols,ld", [
+    ("bf16", tm.TMASK_MASK_U8, 4, 4, 4), ("bf16", tm.TMASK_MASK_U8, 68, 132, 132), ("ties", tm.TMASK_MASK_U8, 64, 124, 124),
+    ("bf16", tm.TMASK_MASK_U8, 132, 2052, 2060), ("bf16", tm.TMASK_MASK_BITS, 20, 8, 12), ("ties", tm.TMASK_MASK_BITS, 72, 264, 268)])
+def test_narrow_strips(kind, fmt, rows, cols, ld, N):
+    """Widths or pitches that are a multiple of four bf16 entries, not of eight: every call against the oracle, alone and
+    with a matrix of the wide layout in the same batch."""
+    M = 4
+    w = _inputs(kind, rows, cols, seed=3960 + cols + N)
+    w = w if w.dtype == np.uint16 else wl.f32_to_bf16_bits(w)
+    w2 = _inputs("bf16", 16, 64, seed=3961)
+    wd, wd2 = _unaligned_dev(w, ld, 0), to_dev(w2)
+    ws, host = [wd, wd2], [w, w2]
+    obj = torch.full((6,), -1.0, dtype=torch.float64, device="cuda")
+    wsp = tm.alloc_workspace(ws, N, M)
+    masks = []
+    for k, fn in enumerate((tm.tmask_approx, tm.tmask_exact, tm.tmask_prune_1d)):
+        masks.append([m.fill_(0xCD) for m in tm.alloc_masks(ws, fmt)])
+        fn(ws, masks[-1], N, M, objective=obj[2 * k:2 * k + 2], mask_fmt=fmt, workspace=wsp)
+    torch.cuda.synchronize()
+    o = obj.cpu().numpy().reshape(3, 2)
+    got = [[mask_to_host(m, h.shape[1], fmt) for m, h in zip(ms, host)] for ms in masks]
+    for i, h in enumerate(host):
+        amask, aobj = oracle.approx(h, N, M)
+        _, eobj, epb = oracle.exact(h, N, M, per_block=True)
+        pmask, pobj = oracle.prune_1d(h, N, M)
+        assert np.array_equal(got[0][i], amask) and np.array_equal(got[2][i], pmask)
+        _check_exact(h, got[1][i], N, M, epb)
+        np.testing.assert_allclose(o[:, i], [aobj, eobj, pobj], rtol=1e-5)
+    scores, pbs = None, [oracle.score(h, g, N, M) for h, g in zip(host, got[0])]
+    sout = torch.zeros(2 * tm.SCORE_OUT_BYTES, dtype=torch.uint8, device="cuda")
+    pb = torch.full((sum(h.size // 16 for h in host),), -1.0, dtype=torch.float32, device="cuda")
+    tm.tmask_score(ws, masks[0], N, M, sout, per_block_obj=pb, mask_fmt=fmt, workspace=wsp)
+    packed = [tm.alloc_packed(x, N, M) for x in ws]
+    for pk in packed:
+        for t in pk:
+            t.view(torch.uint8).fill_(0xEE)
+    tm.tmask_apply_pack(ws, masks[1], packed, N, M, mask_fmt=fmt)
+    torch.cuda.synchronize()
+    scores = tm.read_scores(sout, 2)
+    np.testing.assert_allclose(pb.cpu().numpy(), np.concatenate([s.per_block.ravel() for s in pbs]), rtol=1e-5, atol=1e-30)
+    for sc, so in zip(scores, pbs):
+        assert (sc["kept"], sc["row_violations"], sc["col_violations"], sc["row_not_n"], sc["col_not_n"]) == \
+               (so.kept, so.row_violations, so.col_violations, so.row_not_n, so.col_not_n)
+        assert sc["retained_l1"] == pytest.approx(so.retained_l1, rel=1e-5)
+        assert sc["total_l1"] == pytest.approx(so.total_l1, rel=1e-5)
+    for pk, h, g in zip(packed, host, got[1]):
+        for have, t in zip(pk, oracle.apply_pack(h, g, N, M)):
+            hv = have.view(torch.int16).cpu().numpy().view(np.uint16) if have.dtype == torch.bfloat16 else have.cpu().numpy()
+            assert np.array_equal(hv.view(np.uint8), t.view(np.uint8))
+    # the masked copies: Algorithm 1 in place on a copy, row pruning with absorption into a padded buffer, masks written
+    out = _unaligned_dev(w, ld, 0)
+    dm = tm.alloc_masks([wd], fmt)
+    tm.tmask_approx_dense([out], dm, [out], N, M, mask_fmt=fmt)
+    out2 = torch.zeros((rows, ld), dtype=torch.bfloat16, device="cuda")[:, :cols]
+    tm.tmask_prune_1d_dense([wd], None, [out2], N, M, absorb_mean=True)
+    torch.cuda.synchronize()
+    amask, _ = oracle.approx(w, N, M)
+    assert np.array_equal(mask_to_host(dm[0], cols, fmt), amask)
+    assert np.array_equal(out.contiguous().view(torch.int16).cpu().numpy().view(np.uint16), np.where(amask != 0, w, 0))
+    wf = wl.bf16_bits_to_f32(w)
+    want = oracle.apply_dense(wf, oracle.prune_1d(w, N, M)[0], M, absorb_mean=True)
+    tol = 2.0 ** -20 * np.abs(wf.astype(np.float64)).reshape(rows, -1, M).sum(2).repeat(M, axis=1) + 2.0 ** -8 * np.abs(want)
+    assert np.all(np.abs(out2.float().cpu().numpy().astype(np.float64) - want) <= tol + 1e-30)
+
+
 # ---------------------------------------------------------------- batches beyond one launch ------
 
 def test_batches_of_300_matrices_cross_the_launch_limit_and_share_index_buckets():
