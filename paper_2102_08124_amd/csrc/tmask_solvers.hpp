@@ -2,10 +2,12 @@
 //   approx_keep   : Algorithm 1 of arXiv 2102.08124 (Sec. 4) in rank form
 //   exact24_block : Eq. 3 optimum for 2:4 over all 90 feasible patterns (factored enumeration)
 //   best_permutation4 : Eq. 3 optimum for 1:4 and 3:4 over the 24 permutations
-//   exact_costs / exact_priced_start / exact_phases : the pieces of the Eq. 3 optimum for M = 8, 16 by successive
+//   exact_costs / exact_priced_start / exact_search : the pieces of the Eq. 3 optimum for M = 8, 16 by successive
 //                   shortest augmenting paths on the bipartite row/column network of Fig. 3 (put together in
 //                   tmask_exact_balance.hpp)
 #pragma once
+#include <type_traits>
+
 #include "tmask_device.hpp"
 #include "tmask_networks.hpp"
 
@@ -358,21 +360,13 @@ __device__ __forceinline__ uint32_t best_permutation4(const float (&v)[4][4], fl
 // (row r -> column j through a pruned entry (r,j), column j -> row r' through an unpruned entry
 // (r',j)) with a label-correcting search over row labels, and flip the entries along it.
 //
-// One block is held by G lanes, CL columns each; row labels are replicated in the G lanes and
-// min-combined after each sweep, so all G lanes take the same decisions.
+// The start works on the strip layout (a block in G lanes, CL columns each, every lane busy); the few blocks that it
+// leaves unbalanced are handed to the searches through LDS, one column and row per lane.
 // =================================================================================================
 
 constexpr int kInfDist = 0x70000000;   // unreachable label; kInfDist - 2^S is still above kReachable
 constexpr int kReachable = 0x40000000; // every real label is below this: |label| <= (M-1) * 2^S < 2^30
 constexpr uint32_t kNoPred = 0xFFFFFFFFu;
-
-// r = lane-mask bit set ? a : b as exactly one v_cndmask (mask in a scalar register pair).
-__device__ __forceinline__ uint32_t lm_pick(lanemask_t m, uint32_t a, uint32_t b)
-{
-    uint32_t r;
-    asm("v_cndmask_b32_e64 %0, %1, %2, %3" : "=v"(r) : "v"(b), "v"(a), "s"(m));
-    return r;
-}
 
 constexpr int exact_cost_bits(int M) { return (M == 16) ? 26 : 27; }
 
@@ -410,47 +404,67 @@ __device__ __forceinline__ void exact_costs(const uint32_t (&key)[M][CL], int (&
 
 }
 
-// Pruned entries per row, identical in the G lanes of the block.
-template <int M, int CL, int G>
-__device__ __forceinline__ void exact_counts(const uint32_t (&xcol)[CL], uint32_t (&cnt)[M])
-{
-#pragma unroll
-    for (int i = 0; i < M; i++) {
-        uint32_t n = 0;
-#pragma unroll
-        for (int c = 0; c < CL; c++)
-            n += (xcol[c] >> i) & 1u;
-        if constexpr (G >= 2)
-            n += quad_xor<1>(n);
-        if constexpr (G == 4)
-            n += quad_xor<2>(n);
-        cnt[i] = n;
-    }
-}
-
-// Start for N = M/2 with row prices: column c prunes the K rows with the smallest cost + price (ties: lower
-// row first).  Whatever the prices, the result is the cheapest pruning for the row counts it has: the price
+// Start with row prices: column c prunes the K rows with the smallest cost + price (ties: by position, see below).
+// Whatever the prices, the result is the cheapest pruning for the row counts it has: the price
 // term of any pruning with those counts is the same sum over rows of price x count, so being cheapest under
 // cost + price means being cheapest under cost alone.  That is all the augmenting searches ask of their
-// start, so prices can even out the row counts before the first search: a row with too many pruned entries
-// becomes dearer to prune, one with too few cheaper, every column chooses again, in rounds with a shrinking
-// step: at M = 8 twelve rounds, first step 3/64 .. 3/32 of the largest cost, times 11/16 per round; at M = 16
-// twenty rounds, first step 1/32 .. 1/16 of the largest cost, times 3/4 per round (both settled by timing on
-// the device).  The prices of the round with the smallest total excess are kept; xcol is that round's choice
-// and the return value its excess.  On random blocks the searches that follow drop from 3.1 per block (no
-// prices) to 0.2 at M = 8 and from 6.3 to well under 0.5 at M = 16; a round costs about a third of one sweep of
-// a search and runs with every lane busy, where the searches keep 40-50 % of the lanes busy.
+// start, so prices can even out the row counts before the first search.
 //
-// Keys are (cost + price + 2^(S-1)) << 4 | tie-break with |price| < 2^(S-1): below 2^(S+5) <= 2^32 for costs < 2^S.
-// The tie-break of entry (i, j) is (i - j) mod M, not the row alone: columns with equal costs (blocks of an
+// The prices come from a few rounds of ascent on the dual of the row constraints, smoothed: instead of counting the
+// entries of a row below their column's threshold, each entry adds 0 ... 1 by where its key lies in a window of
+// width w around the middle between the column's K-th and (K+1)-th smallest key (one fused multiply-add with the
+// hardware's clamp and one addition, what a compare and a count cost), and a row's price moves by step x (that sum),
+// with some momentum; w and step shrink from round to round.  A count says by how many entries a row is out of
+// balance, the smoothed sum also how far away the balance is: blocks of N(0,1) entries left unbalanced, by emulation,
+// 2.5 % after 8 rounds at M = 8 and 6 % after 13 at M = 16, where 12 and 20 rounds on counts left 12 % and 14 %.
+// Schedules were settled by a search in emulation, the numbers of rounds by timing on the device (6 ... 10 and
+// 10 ... 18 are within 5 % of each other: more rounds, fewer searches).  Windows and
+// steps are multiples of the block's mean cost, and the prices start at 3/4 of what would make the row means equal,
+// which keeps heavy-tailed and row-scaled blocks as good.  All of it is fp32: the prices need no more, and every cost is a
+// float exactly (24 significant bits, as the weights have).  The prices are then rounded to integers and the choice
+// itself is taken on integer keys.
+//
+// Keys of that choice are (cost + price + 2^(S-1)) << 4 | tie-break with |price| < 2^(S-1): below 2^(S+5) <= 2^32 for
+// costs < 2^S.  The tie-break of entry (i, j) is (i - j) mod M, not the row alone: columns with equal costs (blocks of an
 // unstructured-sparse matrix are full of zeros) then prune different rows, a band, instead of all the same ones,
-// which no row price could tell apart (4096^2 fp32 with 90 % zeros: 4:8 270 -> 146 us, 8:16 931 -> 370 us; all zeros:
-// 181 -> 57 us, 544 -> 120 us).
-// Prices are held unshifted (the shift rides on the add that forms a key); the step times the count is a 24-bit
-// multiply-add (step < 2^23, counts <= M), the full 32-bit multiply runs at a quarter of the rate; the excess is
-// taken as half the sum of |count - K| (the counts of a block always add up to M*K), one instruction per row.
-// GENERAL: any 0 < K < M, the same in every lane (the threshold then comes from a full sort of the column's keys and a
-// register read at that index; 24 instead of 12 instructions at M = 8, 91 instead of 60 at M = 16); otherwise K = M/2.
+// which no row price could tell apart.  In such blocks prices that differ by little undo the band, so a wavefront in
+// which a block has an excess of more than two left tries its blocks without prices as well and keeps the better
+// choice (hardly ever on blocks of random values; 90 % zeros at 4:8: excess 10 -> 2.2).
+// xcol: the pruned rows of every column; the return value: the excess they leave.
+// GENERAL: any 0 < K < M, the same in every lane (the thresholds then come from a full sort of the column's keys and
+// register reads at those indexes; 24 instead of 16 instructions at M = 8, 91 instead of 72 at M = 16); otherwise
+// K = M/2.
+
+// clamp(a * b + c, 0, 1)
+__device__ __forceinline__ float fma_clamp01(float a, float b, float c)
+{
+    float r;
+    asm("v_fma_f32 %0, %1, %2, %3 clamp" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+
+// v + the value of lane (lane ^ X) within the quad, the move folded into the addition
+template <int X>
+__device__ __forceinline__ float quad_xor_sum(float v)
+{
+    constexpr int ctrl = (X == 1) ? 0xB1 : (X == 2) ? 0x4E : 0x1B;
+    return v + __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), ctrl, 0xF, 0xF, true));
+}
+
+// Schedule of the smoothed rounds: window and step in units of the block's mean cost, factors per round.
+template <int M>
+struct PriceSchedule;
+template <>
+struct PriceSchedule<8> {
+    static constexpr int rounds = 8;
+    static constexpr float window = 0.527f, window_next = 0.62f, step = 0.2325f, step_next = 0.66f, momentum = 0.22f;
+};
+template <>
+struct PriceSchedule<16> {
+    static constexpr int rounds = 13;
+    static constexpr float window = 0.445f, window_next = 0.703f, step = 0.192f, step_next = 0.736f, momentum = 0.2f;
+};
+
 template <int M, int CL, int G, bool GENERAL = false>
 __device__ __forceinline__ uint32_t exact_priced_start(const int (&cost)[M][CL], uint32_t gpos, uint32_t (&xcol)[CL],
                                                        uint32_t k_general = 0)
@@ -458,57 +472,138 @@ __device__ __forceinline__ uint32_t exact_priced_start(const int (&cost)[M][CL],
     constexpr int H = M / 2;
     const int K = GENERAL ? (int)__builtin_amdgcn_readfirstlane(k_general) : M / 2;
     constexpr int S = exact_cost_bits(M);
-    constexpr int ROUNDS = (M == 16) ? 20 : 12;
-    constexpr int PMIN = 1, PMAX = (1 << S) - 1;                // price + 2^(S-1)
-    uint32_t ck[M][CL];
-    int pr[M], best_pr[M];                                      // price + 2^(S-1)
+    constexpr float kOffset = (float)(1 << S);                  // added to the prices of the rounds: keys stay positive
+    using Sched = PriceSchedule<M>;
+    float cf[M][CL], pr[M], vel[M];
+    float mean = 0.f;
 #pragma unroll
     for (int i = 0; i < M; i++) {
-        pr[i] = 1 << (S - 1);
+        float sum = 0.f;
 #pragma unroll
-        for (int c = 0; c < CL; c++)
-            ck[i][c] = ((uint32_t)cost[i][c] << 4) | (((uint32_t)i - (gpos * (uint32_t)CL + (uint32_t)c)) & (uint32_t)(M - 1));
-    }
-    // the column's threshold key under the prices p: the K pruned rows are the keys below it
-    auto threshold = [&](int c, const int (&p)[M], uint32_t (&k)[M]) {
-        uint32_t lo[H], hi[H];
-#pragma unroll
-        for (int i = 0; i < M; i++)
-            k[i] = ((uint32_t)p[i] << 4) + ck[i][c];
-#pragma unroll
-        for (int i = 0; i < H; i++) {
-            lo[i] = k[i];
-            hi[i] = k[H + i];
+        for (int c = 0; c < CL; c++) {
+            cf[i][c] = (float)cost[i][c];
+            asm volatile("" : "+v"(cf[i][c]));                  // the integers end here
+            sum += cf[i][c];
         }
-        if constexpr (GENERAL) {
-            uint32_t srt[M];
+        if constexpr (G >= 2)
+            sum = quad_xor_sum<1>(sum);
+        if constexpr (G == 4)
+            sum = quad_xor_sum<2>(sum);
+        pr[i] = sum;
+        mean += sum;
+    }
+    mean = mean * (1.f / (M * M));
+#pragma unroll
+    for (int i = 0; i < M; i++) {
+        pr[i] = kOffset + 0.75f * (mean - pr[i] * (1.f / M));
+        vel[i] = 0.f;
+    }
+    const float unit = mean > 1.f ? mean : 1.f;                 // blocks of zeros
+    float slope = -(1.f / Sched::window) / unit, step = Sched::step * unit;
+    float drift = 0.f;                                          // what K per row and round adds to every price
+    float dvel = 0.f;
+#pragma unroll 1
+    for (int round = 0; round < Sched::rounds; round++) {
+        float f[M];
+#pragma unroll
+        for (int c = 0; c < CL; c++) {
+            uint32_t k[M];                                      // positive floats compare as integers
 #pragma unroll
             for (int i = 0; i < M; i++)
-                srt[i] = k[i];
-            sort_asc<M>(srt);
-            return srt[(uint32_t)K & (uint32_t)(M - 1)];      // the (K+1)-th smallest; the index is the same in every lane
-        } else {
-            return upper_half_min<H>(lo, hi);
+                k[i] = __float_as_uint(pr[i] + cf[i][c]);
+            float both;                                         // the K-th and the (K+1)-th smallest key, added
+            if constexpr (GENERAL) {
+                uint32_t srt[M];
+#pragma unroll
+                for (int i = 0; i < M; i++)
+                    srt[i] = k[i];
+                sort_asc<M>(srt);
+                both = __uint_as_float(srt[(uint32_t)(K - 1) & (uint32_t)(M - 1)]) + __uint_as_float(srt[(uint32_t)K & (uint32_t)(M - 1)]);
+            } else if constexpr (M == 8) {
+                const Eight e = columns_of_8(k);
+                both = __uint_as_float(fourth_of_8(e)) + __uint_as_float(fifth_of_8(e));
+            } else {
+                uint32_t lo[H], hi[H], below = 0u, above = 0xFFFFFFFFu;
+#pragma unroll
+                for (int i = 0; i < H; i++) {
+                    lo[i] = k[i];
+                    hi[i] = k[H + i];
+                }
+                sort_asc<H>(lo);
+                sort_asc<H>(hi);
+#pragma unroll
+                for (int i = 0; i < H; i += 2) {
+                    const uint32_t b0 = lo[i] < hi[H - 1 - i] ? lo[i] : hi[H - 1 - i], b1 = lo[i + 1] < hi[H - 2 - i] ? lo[i + 1] : hi[H - 2 - i];
+                    const uint32_t a0 = lo[i] < hi[H - 1 - i] ? hi[H - 1 - i] : lo[i], a1 = lo[i + 1] < hi[H - 2 - i] ? hi[H - 2 - i] : lo[i + 1];
+                    below = max3u(below, b0, b1);
+                    above = min3u(above, a0, a1);
+                }
+                both = __uint_as_float(below) + __uint_as_float(above);
+            }
+            const float at = 0.5f - (0.5f * slope) * both;      // clamp((middle - key) / w + 1/2)
+#pragma unroll
+            for (int i = 0; i < M; i++) {
+                const float x = fma_clamp01(__uint_as_float(k[i]), slope, at);
+                f[i] = c == 0 ? x : f[i] + x;
+            }
+            if constexpr (CL > 4 || M == 16)
+                __builtin_amdgcn_sched_barrier(0);   // one column at a time: interleaving them costs M registers each
         }
-    };
-    int step = (M == 16) ? (4 << (S - 7)) : (3 << (S - 6));
-    static_assert(((M == 16) ? (4 << (S - 7)) : (3 << (S - 6))) < (1 << 23), "the step is an operand of a 24-bit multiply");
-    uint32_t best = 0xFFFFFFFFu;                                 // twice the excess
-#pragma unroll 1
-    for (int round = 0; round <= ROUNDS; round++) {
+#pragma unroll
+        for (int i = 0; i < M; i++) {
+            if constexpr (G >= 2)
+                f[i] = quad_xor_sum<1>(f[i]);
+            if constexpr (G == 4)
+                f[i] = quad_xor_sum<2>(f[i]);
+            vel[i] = Sched::momentum * vel[i] + step * f[i];
+            pr[i] += vel[i];
+        }
+        dvel = Sched::momentum * dvel + step * (float)K;
+        drift += dvel;
+        slope *= 1.f / Sched::window_next;
+        step *= Sched::step_next;
+    }
+
+    // ---- the choice under the prices reached, on integer keys ----
+    constexpr int PMIN = 1, PMAX = (1 << S) - 1;                // price + 2^(S-1)
+    int pi[M];
+    auto choose = [&](auto priced, uint32_t (&x)[CL]) -> uint32_t {     // returns twice the excess
         uint32_t n[M];
 #pragma unroll
         for (int i = 0; i < M; i++)
             n[i] = 0;
 #pragma unroll
         for (int c = 0; c < CL; c++) {
-            uint32_t k[M];
-            const uint32_t t = threshold(c, pr, k);
+            uint32_t k[M], lo[H], hi[H];
 #pragma unroll
-            for (int i = 0; i < M; i++)
-                lm_inc(n[i], lm(k[i] < t));
-            if constexpr (CL > 4)
-                __builtin_amdgcn_sched_barrier(0);   // one column at a time: interleaving them costs M registers each
+            for (int i = 0; i < M; i++) {
+                const uint32_t v = (uint32_t)(int)cf[i][c] + (decltype(priced)::value ? (uint32_t)pi[i] : 1u << (S - 1));
+                k[i] = (v << 4) | (((uint32_t)i - (gpos * (uint32_t)CL + (uint32_t)c)) & (uint32_t)(M - 1));
+            }
+            uint32_t t;
+            if constexpr (GENERAL) {
+                uint32_t srt[M];
+#pragma unroll
+                for (int i = 0; i < M; i++)
+                    srt[i] = k[i];
+                sort_asc<M>(srt);
+                t = srt[(uint32_t)K & (uint32_t)(M - 1)];       // the (K+1)-th smallest; the index is the same in every lane
+            } else {
+#pragma unroll
+                for (int i = 0; i < H; i++) {
+                    lo[i] = k[i];
+                    hi[i] = k[H + i];
+                }
+                t = upper_half_min<H>(lo, hi);
+            }
+            x[c] = 0u;
+#pragma unroll
+            for (int i = M - 1; i >= 0; i--) {
+                const lanemask_t m = lm(k[i] < t);
+                lm_inc(n[i], m);
+                lm_shift_in(x[c], m);
+            }
+            __builtin_amdgcn_sched_barrier(0);       // the columns' keys one after the other
         }
         uint32_t e2 = 0;
 #pragma unroll
@@ -519,189 +614,129 @@ __device__ __forceinline__ uint32_t exact_priced_start(const int (&cost)[M][CL],
                 n[i] = quad_xor_sum<2>(n[i]);
             e2 = __builtin_amdgcn_sad_u8(n[i], (uint32_t)K, e2);      // counts are below 256: |n - K| of the low byte
         }
-        const bool better = e2 < best;
-        best = better ? e2 : best;
-        const int back = step * K;
+        return e2;
+    };
+    // opaque: else the integer costs and tie-breaks of the choice are computed ahead of the rounds and held through them
 #pragma unroll
-        for (int i = 0; i < M; i++) {
-            best_pr[i] = better ? pr[i] : best_pr[i];
-            const int p = __mul24(step, (int)n[i]) + pr[i] - back;
-            pr[i] = p > PMAX ? PMAX : p < PMIN ? PMIN : p;
-        }
-        step = (step * (M == 16 ? 12 : 11)) >> 4;
+    for (int i = 0; i < M; i++)
+#pragma unroll
+        for (int c = 0; c < CL; c++)
+            asm volatile("" : "+v"(cf[i][c]));
+    asm volatile("" : "+v"(gpos));
+#pragma unroll
+    for (int i = 0; i < M; i++) {
+        const float p = pr[i] - drift - (kOffset - (float)(1 << (S - 1)));
+        pi[i] = (int)__builtin_amdgcn_fmed3f(p, (float)PMIN, (float)(PMAX - 64));     // (float)PMAX would be 2^S
     }
+    uint32_t e2 = choose(std::true_type{}, xcol);
+    if (__any(e2 > 4u)) {
+        uint32_t x[CL];
+        const uint32_t e = choose(std::false_type{}, x);
+        const bool better = e < e2;
+        e2 = better ? e : e2;
 #pragma unroll
-    for (int c = 0; c < CL; c++) {
-        uint32_t k[M];
-        const uint32_t t = threshold(c, best_pr, k);
-        uint32_t x = 0;
-#pragma unroll
-        for (int i = 0; i < M; i++)
-            x |= (k[i] < t ? 1u : 0u) << i;
-        xcol[c] = x;
+        for (int c = 0; c < CL; c++)
+            xcol[c] = better ? x[c] : xcol[c];
     }
-    return best >> 1;
+    return e2 >> 1;
 }
 
-// Up to max_phases searches, each followed by its augmentations; cnt is kept up to date.  Returns true when
-// every row has exactly K pruned entries (always after at most M*M searches).
-template <int M, int CL, int G>
-__device__ __forceinline__ bool exact_phases(const int (&cost)[M][CL], uint32_t K, uint32_t gpos, uint32_t (&xcol)[CL],
-                                             uint32_t (&cnt)[M], int max_phases)
+// LDS of one wavefront's searches: labels and predecessors of the rows and columns of its 64 / M blocks.
+struct SearchLds {
+    int drow[64], dcol[64];
+    uint32_t prow[64], pcol[64];
+};
+
+// Augments until every row of the block has exactly K pruned entries (after at most M*M searches).  M lanes hold a
+// block, a wavefront 64 / M of them: lane j of the block holds column j (ccol, xcol: bit i = entry (i, j) pruned) and row
+// j (crow, xrow: bit c = entry (j, c) pruned).  All lanes of the wavefront take part; lanes with `active` false hold no block.
+//
+// A search labels the rows from those with excess, alternating a column step (lane j: the cheapest way into column j
+// through a pruned entry of a reached row) and a row step (lane j: the cheapest way into row j out of a column through an
+// unpruned entry); labels travel through LDS, which within a wavefront needs no barrier.  Labels only ever fall, and a
+// predecessor changes only when its label falls strictly: with exact integer sums and no negative cycle the
+// predecessor graph is then a forest, also among entries of equal cost.  The first reachable row that lacks pruned
+// entries takes its chain.
+template <int M>
+__device__ __forceinline__ void exact_search(const int (&ccol)[M], const int (&crow)[M], uint32_t &xcol, uint32_t xrow,
+                                             bool active, uint32_t K, SearchLds &lds)
 {
-    uint32_t rowid[M];   // row numbers in registers, operands of the selects below
+    const uint32_t lane = threadIdx.x & 63u, j = lane % M, base = lane - j;     // base: first lane of the block
+    constexpr uint32_t kSeg = (uint32_t)((1ull << M) - 1ull);
+    auto mine = [&](lanemask_t m) { return (uint32_t)(m >> base) & kSeg; };     // the block's bits of a ballot
+    auto fence = []() {                                          // LDS accesses of a wavefront happen in program order
+        __builtin_amdgcn_wave_barrier();
+        asm volatile("" ::: "memory");
+    };
+    uint32_t cnt = active ? (uint32_t)__builtin_popcount(xrow) : K;
+#pragma unroll 1
+    for (int search = 0; search < M * M; search++) {
+        const lanemask_t excess = lm(cnt > K);
+        if (excess == 0)
+            break;
+        int drow = cnt > K ? 0 : kInfDist;
+        uint32_t prow = kNoPred;
+        fence();
+        lds.drow[lane] = drow;
+        lds.prow[lane] = prow;
+        fence();
+        int dcol = kInfDist;
+        uint32_t pcol = 0;
+#pragma unroll 1
+        for (int it = 0; it <= M; it++) {
 #pragma unroll
-    for (int i = 0; i < M; i++)
-        rowid[i] = (uint32_t)i;
-
-    // ---- augment until every row has exactly K pruned ----
-    for (int phase = 0; phase < max_phases; phase++) {
-        int drow[M];
-        uint32_t prow[M];
-        lanemask_t any_excess = 0;
-        uint32_t deficit = 0;
+            for (int i = 0; i < M; i++) {
+                const int d = lds.drow[base + i];
+                const int v = d - ccol[i];
+                const bool better = ((xcol >> i) & 1u) && d < kReachable && v < dcol;
+                dcol = better ? v : dcol;
+                pcol = better ? (uint32_t)i : pcol;
+            }
+            lds.dcol[lane] = dcol;
+            lds.pcol[lane] = pcol;
+            fence();
+            bool changed = false;
 #pragma unroll
-        for (int i = 0; i < M; i++) {
-            const lanemask_t ex = lm(cnt[i] > K);
-            any_excess |= ex;
-            deficit |= (cnt[i] < K ? 1u : 0u) << i;
-            drow[i] = (int)lm_pick(ex, 0u, (uint32_t)kInfDist);
-            prow[i] = kNoPred;
+            for (int c = 0; c < M; c++) {
+                const int v = lds.dcol[base + c] + crow[c];      // from an unreached column: above every label
+                const bool better = !((xrow >> c) & 1u) && v < drow;
+                drow = better ? v : drow;
+                prow = better ? (uint32_t)c : prow;
+                changed = changed || better;
+            }
+            fence();
+            lds.drow[lane] = drow;
+            lds.prow[lane] = prow;
+            fence();
+            if (lm(changed) == 0)
+                break;
         }
-        if (!lm_test(any_excess))
-            return true;
-
-        // label-correcting sweeps over the columns
-        lanemask_t changed;
-        int sweeps = 0;
-        do {
-            changed = 0;
-#pragma unroll
-            for (int c = 0; c < CL; c++) {
-                lanemask_t pm[M];            // row i is pruned in this column
-#pragma unroll
-                for (int i = 0; i < M; i++)
-                    pm[i] = lm((xcol[c] & (1u << i)) != 0u);
-                // cheapest way to reach the column: through a pruned entry of a reached row
-                uint32_t dcol = (uint32_t)kInfDist, from = 0;
-#pragma unroll
-                for (int i = 0; i < M; i++) {
-                    const int t = drow[i] - cost[i][c];
-                    const lanemask_t better = pm[i] & lm(t < (int)dcol);
-                    dcol = lm_pick(better, (uint32_t)t, dcol);
-                    from = lm_pick(better, rowid[i], from);
-                }
-                // an unreachable column must not improve anything: kInfDist + cost >= every label
-                dcol = lm_pick(lm((int)dcol < kReachable), dcol, (uint32_t)kInfDist);
-                const uint32_t code = ((gpos * CL + c) << 4) | from;
-                // leave the column through its unpruned entries
-#pragma unroll
-                for (int i = 0; i < M; i++) {
-                    const int t = (int)dcol + cost[i][c];
-                    const lanemask_t better = ~pm[i] & lm(t < drow[i]);
-                    drow[i] = (int)lm_pick(better, (uint32_t)t, (uint32_t)drow[i]);
-                    prow[i] = lm_pick(better, code, prow[i]);
-                    changed |= better;
+        const uint32_t cand = mine(lm(cnt < K && drow < kReachable));
+        bool walking = mine(excess) != 0u && cand != 0u;
+        if (lm(walking) == 0)
+            break;                      // cannot happen for 0 < K < M; guards against looping on corrupt state
+        const uint32_t target = walking ? (uint32_t)__builtin_ctz(cand) : 0u;
+        uint32_t r = target, src = kNoPred;
+#pragma unroll 1
+        for (int step = 0; step <= M && lm(walking) != 0; step++) {
+            if (walking) {
+                const uint32_t c = lds.prow[base + r];
+                if (c == kNoPred) {
+                    src = r;                                     // the row with excess that the chain starts from
+                    walking = false;
+                } else {
+                    const uint32_t f = lds.pcol[base + c];       // (r, c) becomes pruned, (f, c) becomes unpruned
+                    if (j == c)
+                        xcol ^= (1u << r) | (1u << f);
+                    if (j == r || j == f)
+                        xrow ^= 1u << c;
+                    r = f;
                 }
             }
-            uint32_t chg = lm_test(changed) ? 1u : 0u;
-            if constexpr (G >= 2) {
-                const bool before = (gpos ^ 1u) < gpos;
-#pragma unroll
-                for (int i = 0; i < M; i++) {
-                    const int od = (int)quad_xor<1>((uint32_t)drow[i]);
-                    const uint32_t op = quad_xor<1>(prow[i]);
-                    const bool take = (od < drow[i]) || (od == drow[i] && before);
-                    drow[i] = take ? od : drow[i];
-                    prow[i] = take ? op : prow[i];
-                }
-                chg |= quad_xor<1>(chg);
-            }
-            if constexpr (G == 4) {
-                const bool before = (gpos ^ 2u) < gpos;
-#pragma unroll
-                for (int i = 0; i < M; i++) {
-                    const int od = (int)quad_xor<2>((uint32_t)drow[i]);
-                    const uint32_t op = quad_xor<2>(prow[i]);
-                    const bool take = (od < drow[i]) || (od == drow[i] && before);
-                    drow[i] = take ? od : drow[i];
-                    prow[i] = take ? op : prow[i];
-                }
-                chg |= quad_xor<2>(chg);
-            }
-            changed = lm(chg != 0u);
-            sweeps++;
-        } while (lm_test(changed) && sweeps <= M);
-
-        // At convergence every predecessor edge is tight (label of the head = label of the tail + edge cost), so
-        // flipping along ANY predecessor chain keeps the reduced costs of the residual network non-negative:
-        // the pruning stays cheapest for its row imbalances.  One search therefore serves several augmentations:
-        // every reachable row that lacks pruned entries takes its chain, as long as the chains use different
-        // columns and different rows (a row with excess may end several chains while its excess lasts).
-        uint32_t cand = 0;
-#pragma unroll
-        for (int i = 0; i < M; i++)
-            cand |= (((deficit >> i) & 1u) && drow[i] < kReachable ? 1u : 0u) << i;
-        if (cand == 0u)
-            break;   // cannot happen for 0 < K < M; guards against looping on corrupt state
-        uint32_t used_rows = 0, used_cols = 0;
-        while (cand) {
-            const uint32_t target = (uint32_t)__builtin_ctz(cand);
-            cand &= cand - 1u;
-            // first walk: which rows and columns does the chain use, and where does it end
-            uint32_t r = target, rows = 0, cols = 0;
-            bool ended = false;
-            for (int step = 0; step < M; step++) {
-                uint32_t pp = kNoPred;
-#pragma unroll
-                for (int i = 0; i < M; i++)
-                    pp = (r == (uint32_t)i) ? prow[i] : pp;
-                if (pp == kNoPred) {
-                    ended = true;
-                    break;
-                }
-                rows |= 1u << r;
-                cols |= 1u << (pp >> 4);
-                r = pp & 15u;
-            }
-            uint32_t src_cnt = 0;
-#pragma unroll
-            for (int i = 0; i < M; i++)
-                src_cnt = (r == (uint32_t)i) ? cnt[i] : src_cnt;
-            const bool ok = ended && (rows & used_rows) == 0u && (cols & used_cols) == 0u &&
-                            ((used_rows >> r) & 1u) == 0u && src_cnt > K;
-            if (!ok)
-                continue;   // left for the next search
-            used_rows |= rows;
-            used_cols |= cols;
-            // second walk: flip the entries along the chain back to the row with excess
-            const uint32_t src = r;
-            r = target;
-            for (int step = 0; step < M; step++) {
-                uint32_t pp = kNoPred;
-#pragma unroll
-                for (int i = 0; i < M; i++)
-                    pp = (r == (uint32_t)i) ? prow[i] : pp;
-                if (pp == kNoPred)
-                    break;
-                const uint32_t j = pp >> 4, f = pp & 15u;
-#pragma unroll
-                for (int c = 0; c < CL; c++)
-                    if (j == gpos * CL + c)
-                        xcol[c] ^= (1u << r) | (1u << f);
-                r = f;
-            }
-            // the chain's end loses one pruned entry, the target gains one
-#pragma unroll
-            for (int i = 0; i < M; i++)
-                cnt[i] += (target == (uint32_t)i ? 1u : 0u) - (src == (uint32_t)i ? 1u : 0u);
         }
+        if (src != kNoPred)
+            cnt += (j == target ? 1u : 0u) - (j == src ? 1u : 0u);
     }
-    bool excess = false;
-#pragma unroll
-    for (int i = 0; i < M; i++)
-        excess |= cnt[i] > K;
-    return !excess;
 }
 
 }  // namespace tmask

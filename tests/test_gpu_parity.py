@@ -181,6 +181,24 @@ def test_exact_on_unstructured_sparse_matrices(N, M, zeros, kind):
     assert obj[0] == pytest.approx(oobj, rel=1e-5, abs=1e-30)
 
 
+@pytest.mark.parametrize("fmt", FMTS)
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("N,M", [(4, 8), (1, 8), (7, 8), (8, 16), (1, 16), (15, 16)])
+def test_exact_more_unbalanced_blocks_than_search_slots(N, M, dt, fmt):
+    # 195 blocks (M = 8: 128 to a workgroup, M = 16: 64; 32 and 16 are searched at a time), most of them left unbalanced by
+    # the start, with a part-filled last workgroup: half zeros, few distinct values, rows scaled by up to 2^40
+    rng = np.random.default_rng(1700 + N + M)
+    rows, cols = 3 * M, 65 * M
+    base = wl.gaussian_f32(rows, cols, seed=1701 + M)
+    for w in (np.where(rng.random(base.shape) < 0.5, np.float32(0), base), wl.tie_heavy_f32(rows, cols, 1702, levels=3),
+              base * np.exp2(rng.integers(-20, 21, size=(rows, 1))).astype(np.float32)):
+        w = w if dt == "f32" else wl.f32_to_bf16_bits(w)
+        (mask,), obj = run_masks(tm.tmask_exact, [w], N, M, fmt)
+        _, oobj, opb = oracle.exact(w, N, M, per_block=True, threads=8)
+        _check_exact(w, mask, N, M, opb)
+        assert obj[0] == pytest.approx(oobj, rel=1e-5)
+
+
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
 @pytest.mark.parametrize("N,M", NM)
 def test_exact_structured_blocks(N, M, dt):
