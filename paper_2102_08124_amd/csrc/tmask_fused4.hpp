@@ -15,10 +15,11 @@
 
 namespace tmask {
 
-template <int DT, int FMT, bool WMASK, int S>
+template <int DT, int FMT, bool WMASK, int S, int QN = 4>
 __global__ __launch_bounds__(kThreads) void approx_pack24_kernel(const FusedArgs args)
 {
-    using PG = Pack4Geo<DT, S>;
+    using PG = Pack4Geo<DT, S, 4, QN>;
+    constexpr uint32_t RUN = 4u * QN;                   // rows of a lane's run of block-rows
     constexpr int ES = PG::ES, C = PG::C, NG = PG::NG, TR = PG::TR, TC = PG::TC, OTD = PG::OTD, TCP = PG::TCP,
                   IDXB = PG::IDXB, IDXTB = PG::IDXTB, LPR = PG::LPR;
 
@@ -38,14 +39,14 @@ __global__ __launch_bounds__(kThreads) void approx_pack24_kernel(const FusedArgs
     // its fixed offsets (its strip inside the run, the distance of its sub-row)
     const uint32_t w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t strip = l % (uint32_t)S, sub = l / (uint32_t)S;
-    const uint32_t q4 = w * LPR + sub;                 // this lane's run of four block-rows inside the tile
+    const uint32_t q4 = w * LPR + sub;                 // this lane's run of QN block-rows inside the tile
     const uint32_t tcol = strip * C;                   // first column of the lane inside the tile
     const uint32_t col = col0 + tcol;
     const bool strip_ok = col < d.cols;
     const size_t pitchW = (size_t)(d.cols / 4) * 2;    // elements per row of vals
-    const size_t lane_w = (size_t)sub * 16u * d.ld * ES + strip * 16u;
-    const size_t lane_v = (size_t)sub * 16u * pitchW * ES + strip * 8u;
-    const size_t lane_m = (size_t)sub * 16u * d.mask_ld;
+    const size_t lane_w = (size_t)sub * RUN * d.ld * ES + strip * 16u;
+    const size_t lane_v = (size_t)sub * RUN * pitchW * ES + strip * 8u;
+    const size_t lane_m = (size_t)sub * RUN * d.mask_ld;
     float acc = 0.f;
 
     // Tiles wholly inside the matrix run a copy of the loop without bounds tests (no branch splits it).
@@ -59,8 +60,8 @@ __global__ __launch_bounds__(kThreads) void approx_pack24_kernel(const FusedArgs
         // loads run one block-row ahead of the work on them
         u32x4 rawb[2][4];
         auto issue = [&](int q, u32x4 (&raw)[4]) {
-            const uint32_t wrow = row0 + 16u * LPR * w + 4u * (uint32_t)q;    // scalar: the row of sub-row 0
-            const uint32_t row = wrow + 16u * sub;
+            const uint32_t wrow = row0 + RUN * LPR * w + 4u * (uint32_t)q;    // scalar: the row of sub-row 0
+            const uint32_t row = wrow + RUN * sub;
 #pragma unroll
             for (int i = 0; i < 4; i++)
                 raw[i] = u32x4{0u, 0u, 0u, 0u};
@@ -74,12 +75,12 @@ __global__ __launch_bounds__(kThreads) void approx_pack24_kernel(const FusedArgs
         issue(0, rawb[0]);
 
 #pragma unroll
-        for (int q = 0; q < 4; q++) {
-            const uint32_t brl = 4 * q4 + q;                       // block-row inside the tile
-            const uint32_t wrow = row0 + 16u * LPR * w + 4u * (uint32_t)q;
-            const uint32_t row = wrow + 16u * sub;
+        for (int q = 0; q < QN; q++) {
+            const uint32_t brl = QN * q4 + q;                       // block-row inside the tile
+            const uint32_t wrow = row0 + RUN * LPR * w + 4u * (uint32_t)q;
+            const uint32_t row = wrow + RUN * sub;
             const bool ok = !EDGE || (strip_ok && row < d.rows);
-            if (q + 1 < 4)
+            if (q + 1 < QN)
                 issue(q + 1, rawb[(q + 1) & 1]);
             __builtin_amdgcn_sched_barrier(0);
             u32x4(&raw)[4] = rawb[q & 1];
@@ -229,27 +230,27 @@ __global__ __launch_bounds__(kThreads) void approx_pack24_kernel(const FusedArgs
         // block-rows of this wavefront that lie outside the matrix must not leave position bits either
         if (EDGE) {
             const uint32_t brs_in = (d.rows - row0) / 4;           // block-rows of the tile inside the matrix
-            const uint32_t mine = brs_in > 4 * q4 ? brs_in - 4 * q4 : 0;
-            const uint32_t keepmask = mine >= 4 ? 0xFFFFu : ((1u << (4 * mine)) - 1u);
+            const uint32_t mine = brs_in > QN * q4 ? brs_in - QN * q4 : 0;
+            const uint32_t keepmask = mine >= (uint32_t)QN ? 0xFFFFu : ((1u << (4 * mine)) - 1u);
 #pragma unroll
             for (int c = 0; c < C; c++)
                 tnib[c] &= keepmask;
         }
-        // a lane's four nibbles per column are two bytes: two rows of C bytes each
+        // a lane's QN nibbles per column are QN / 2 bytes: as many rows of C bytes each
 #pragma unroll
-        for (int t = 0; t < 2; t++) {
+        for (int t = 0; t < QN / 2; t++) {
             uint32_t b[C / 4];
 #pragma unroll
             for (int h = 0; h < C / 4; h++)
                 b[h] = ((tnib[4 * h] >> (8 * t)) & 0xFFu) | (((tnib[4 * h + 1] >> (8 * t)) & 0xFFu) << 8) |
                        (((tnib[4 * h + 2] >> (8 * t)) & 0xFFu) << 16) | (((tnib[4 * h + 3] >> (8 * t)) & 0xFFu) << 24);
             if constexpr (C == 4) {
-                *(uint32_t *)&IDXT[2 * q4 + t][tcol] = b[0];
+                *(uint32_t *)&IDXT[(QN / 2) * q4 + t][tcol] = b[0];
             } else {
                 u32x2 v;
                 v.x = b[0];
                 v.y = b[1];
-                *(u32x2 *)&IDXT[2 * q4 + t][tcol] = v;
+                *(u32x2 *)&IDXT[(QN / 2) * q4 + t][tcol] = v;
             }
         }
     };
@@ -258,7 +259,7 @@ __global__ __launch_bounds__(kThreads) void approx_pack24_kernel(const FusedArgs
     else
         compute(std::true_type{});
     __syncthreads();
-    pack24_copy_out<DT, S>(d, row0, col0, OT, IDXT, IDX);
+    pack24_copy_out<DT, S, 4, QN>(d, row0, col0, OT, IDXT, IDX);
     if (args.partials) {
         __syncthreads();                                   // every wavefront is done reading IDX
         double *red = (double *)&IDX[0][0];

@@ -1013,6 +1013,24 @@ static batch_kernel_t pick_score_kernel(int dt, int M, int mf)
     return nullptr;
 }
 
+// Whether a launch over these matrices has at most `per_cu` tiles of TR x TC for a compute unit, so that tiles of half the
+// height (one or two block-rows per lane instead of two or four) pay.  A launch of a tile or two per compute unit takes
+// as long as a tile does, and half the work per lane nearly halves that; with more tiles the shorter runs per column of W^T
+// cost more.  Whole tile / half tile in us, graph replays: bf16 4:8 compression 1024^2 10.8 / 7.8, 4096 x 3072 (384 tiles)
+// 18.9 / 18.4, 4096^2 (512) 20.3 / 26.0; in one pass 14.4 / 9.8, 4096^2 21.9 / 20.8, 20 x 1024^2 (640) 28.9 / 26.8, 4096 x
+// 6144 (768) 31.0 / 35.1.  bf16 2:4 the same lines; fp32 2:4 1024^2 8.3 / 6.3, 6 x 1024^2 (384) 15.1 / 13.4, 4096 x 2048
+// (512) 16.7 / 19.0; in one pass 10.0 / 7.0, 512 tiles 14.6 / 13.7, 768 tiles 22.7 / 26.8.
+constexpr double kHalfTilesPack = 1.5, kHalfTilesFusedF32 = 2.0, kHalfTilesFusedBf16 = 2.5;
+
+template <typename DESC>
+static bool few_tiles(const DESC *descs, int n, int64_t TR, int64_t TC, double per_cu)
+{
+    uint64_t tiles = 0;
+    for (int i = 0; i < n; i++)
+        tiles += (uint64_t)((descs[i].rows + TR - 1) / TR) * (uint64_t)((descs[i].cols + TC - 1) / TC);
+    return (double)tiles <= per_cu * cu_count();
+}
+
 static int check_common(const void *mats, int n_mats, int dt, int N, int M, int mf)
 {
     if (!mats)
@@ -1431,16 +1449,19 @@ int tmask_apply_pack(const tmask_pack_desc *descs, int n, tmask_dtype dt, int N,
         constexpr int SF = 64, SB = 32;
         // four wavefronts working through four block-rows each (eight with two each halves the time a tile stays
         // resident, and measured the same within 1 % at fp32, 8 % slower at bf16)
-        constexpr int NW = 4, QN = 4;
-        if (dt == TMASK_F32)
-            kern = mf == TMASK_MASK_U8 ? pack24_kernel<kF32, kMaskU8, SF, NW, QN> : pack24_kernel<kF32, kMaskBits, SF, NW, QN>;
-        else
-            kern = mf == TMASK_MASK_U8 ? pack24_kernel<kBF16, kMaskU8, SB, NW, QN> : pack24_kernel<kBF16, kMaskBits, SB, NW, QN>;
+        constexpr int NW = 4;
         const uint32_t strips = dt == TMASK_F32 ? SF : SB;
         TC = strips * 16 / (uint32_t)elem_size((int)dt);
-        TR = 4 * QN * (64 / strips) * NW;
+        TR = 4 * 4 * (64 / strips) * NW;
+        const bool small = few_tiles(descs, n, TR, TC, kHalfTilesPack);
+#define TMASK_PICK(DT, SS, FM, QN) \
+        if ((int)dt == DT && (int)mf == FM && small == (QN == 2)) kern = pack24_kernel<DT, FM, SS, NW, QN>;
+        TMASK_PICK(kF32, SF, kMaskU8, 4) TMASK_PICK(kF32, SF, kMaskBits, 4) TMASK_PICK(kBF16, SB, kMaskU8, 4) TMASK_PICK(kBF16, SB, kMaskBits, 4)
+        TMASK_PICK(kF32, SF, kMaskU8, 2) TMASK_PICK(kF32, SF, kMaskBits, 2) TMASK_PICK(kBF16, SB, kMaskU8, 2) TMASK_PICK(kBF16, SB, kMaskBits, 2)
+#undef TMASK_PICK
+        TR = small ? TR / 2 : TR;
         threads = 64 * NW;
-        lds_reserve = dt == TMASK_F32 ? kPack4LdsReservePackF32 : 0;
+        lds_reserve = dt == TMASK_F32 && !small ? kPack4LdsReservePackF32 : 0;
     }
     if (narrow24) {
         // 8-byte strips, which write 4 bytes per row: tiles of 64 rows x 128 columns, a quarter of the others' bytes, since
@@ -1455,10 +1476,13 @@ int tmask_apply_pack(const tmask_pack_desc *descs, int n, tmask_dtype dt, int N,
     for (int i = 0; i < n && fast48; i++)
         fast48 = (((uintptr_t)descs[i].vals | (uintptr_t)descs[i].valsT) & 7) == 0;
     if (fast48) {
-        kern = mf == TMASK_MASK_U8 ? pack48_bf16_kernel<kMaskU8, false, false, PackArgs>
-                                   : pack48_bf16_kernel<kMaskBits, false, false, PackArgs>;
-        TC = Pack8Geo::TC;
-        TR = Pack8Geo::TR;
+        const bool small = few_tiles(descs, n, Pack8Geo<2>::TR, Pack8Geo<2>::TC, kHalfTilesPack);
+        if (mf == TMASK_MASK_U8)
+            kern = small ? pack48_bf16_kernel<kMaskU8, false, false, PackArgs, 1> : pack48_bf16_kernel<kMaskU8, false, false, PackArgs>;
+        else
+            kern = small ? pack48_bf16_kernel<kMaskBits, false, false, PackArgs, 1> : pack48_bf16_kernel<kMaskBits, false, false, PackArgs>;
+        TC = Pack8Geo<2>::TC;
+        TR = small ? Pack8Geo<1>::TR : Pack8Geo<2>::TR;
     }
     bool fast48f = (M == 8 && N == 4 && dt == TMASK_F32);
     for (int i = 0; i < n && fast48f; i++)
@@ -1553,24 +1577,34 @@ int tmask_approx_pack(const tmask_fused_desc *descs, int n, tmask_dtype dt, int 
     constexpr int SF = 64, SB = 32;
     const uint32_t strips = dt == TMASK_F32 ? SF : SB;
     using G8F = Pack8F32Geo<kPack8F32Strips>;
-    const uint32_t TC = fused48 ? (dt == TMASK_F32 ? (uint32_t)G8F::TC : (uint32_t)Pack8Geo::TC)
+    const uint32_t TC = fused48 ? (dt == TMASK_F32 ? (uint32_t)G8F::TC : (uint32_t)Pack8Geo<2>::TC)
                                 : strips * 16 / (uint32_t)elem_size((int)dt);
-    const uint32_t kPack4Rows = fused48 ? (dt == TMASK_F32 ? (uint32_t)G8F::TR : (uint32_t)Pack8Geo::TR) : 4096 / strips;
-    if (want_obj) {
+    uint32_t kPack4Rows = !fused48 ? 4096 / strips : dt == TMASK_F32 ? (uint32_t)G8F::TR : (uint32_t)Pack8Geo<2>::TR;
+    auto partials_bytes = [&](uint32_t tile_rows) {
         size_t tiles = 0;
         for (int i = 0; i < n; i++)
-            tiles += (size_t)((descs[i].cols + TC - 1) / TC) * (size_t)((descs[i].rows + kPack4Rows - 1) / kPack4Rows);
+            tiles += (size_t)((descs[i].cols + TC - 1) / TC) * (size_t)((descs[i].rows + tile_rows - 1) / tile_rows);
+        return tiles * sizeof(double);
+    };
+    // half tiles leave more partial sums than the workspace was asked to hold: only where it happens to
+    const bool small = !(fused48 && dt == TMASK_F32) && few_tiles(descs, n, kPack4Rows, TC, dt == TMASK_F32 ? kHalfTilesFusedF32 : kHalfTilesFusedBf16) &&
+                       (!want_obj || workspace_bytes >= partials_bytes(kPack4Rows / 2));
+    if (small)
+        kPack4Rows /= 2;
+    if (want_obj) {
         if (!workspace || ((uintptr_t)workspace & 255))
             return fail(TMASK_ERR_WORKSPACE, "workspace is NULL or not 256-byte aligned");
-        if (workspace_bytes < tiles * sizeof(double))
-            return fail(TMASK_ERR_WORKSPACE, "workspace has %zu bytes, %zu needed", workspace_bytes, tiles * sizeof(double));
+        const size_t need = partials_bytes(kPack4Rows);
+        if (workspace_bytes < need)
+            return fail(TMASK_ERR_WORKSPACE, "workspace has %zu bytes, %zu needed", workspace_bytes, need);
     }
     typedef void (*fused_kernel_t)(const FusedArgs);
     fused_kernel_t kern = nullptr;
-#define TMASK_PICK(DT, FM, SS) \
-    if ((int)dt == DT && (int)mf == FM) \
-        kern = with_mask ? approx_pack24_kernel<DT, FM, true, SS> : approx_pack24_kernel<DT, FM, false, SS>;
-    TMASK_PICK(kF32, kMaskU8, SF) TMASK_PICK(kF32, kMaskBits, SF) TMASK_PICK(kBF16, kMaskU8, SB) TMASK_PICK(kBF16, kMaskBits, SB)
+#define TMASK_PICK(DT, FM, SS, QN) \
+    if ((int)dt == DT && (int)mf == FM && small == (QN == 2)) \
+        kern = with_mask ? approx_pack24_kernel<DT, FM, true, SS, QN> : approx_pack24_kernel<DT, FM, false, SS, QN>;
+    TMASK_PICK(kF32, kMaskU8, SF, 4) TMASK_PICK(kF32, kMaskBits, SF, 4) TMASK_PICK(kBF16, kMaskU8, SB, 4) TMASK_PICK(kBF16, kMaskBits, SB, 4)
+    TMASK_PICK(kF32, kMaskU8, SF, 2) TMASK_PICK(kF32, kMaskBits, SF, 2) TMASK_PICK(kBF16, kMaskU8, SB, 2) TMASK_PICK(kBF16, kMaskBits, SB, 2)
 #undef TMASK_PICK
     if (fused48 && dt == TMASK_F32) {
         constexpr int S8 = kPack8F32Strips;
@@ -1580,11 +1614,11 @@ int tmask_approx_pack(const tmask_fused_desc *descs, int n, tmask_dtype dt, int 
             kern = with_mask ? pack48_f32_kernel<kMaskBits, S8, true, true, FusedArgs>
                              : pack48_f32_kernel<kMaskBits, S8, true, false, FusedArgs>;
     } else if (fused48) {
-        if (mf == TMASK_MASK_U8)
-            kern = with_mask ? pack48_bf16_kernel<kMaskU8, true, true, FusedArgs> : pack48_bf16_kernel<kMaskU8, true, false, FusedArgs>;
-        else
-            kern = with_mask ? pack48_bf16_kernel<kMaskBits, true, true, FusedArgs>
-                             : pack48_bf16_kernel<kMaskBits, true, false, FusedArgs>;
+#define TMASK_PICK(FM, ST) \
+        if ((int)mf == FM && small == (ST == 1)) \
+            kern = with_mask ? pack48_bf16_kernel<FM, true, true, FusedArgs, ST> : pack48_bf16_kernel<FM, true, false, FusedArgs, ST>;
+        TMASK_PICK(kMaskU8, 1) TMASK_PICK(kMaskU8, 2) TMASK_PICK(kMaskBits, 1) TMASK_PICK(kMaskBits, 2)
+#undef TMASK_PICK
     }
     hipStream_t stream = (hipStream_t)hip_stream;
     uint32_t partial0 = 0;
@@ -1611,7 +1645,7 @@ int tmask_approx_pack(const tmask_fused_desc *descs, int n, tmask_dtype dt, int 
         args.n = (uint32_t)nb; args.partial0 = partial0; args.partials = want_obj ? workspace : nullptr;
         {
             ProfileScope prof(stream, first + kMaxPackBatch >= n);
-            hipLaunchKernelGGL(kern, dim3(tiles), dim3(kThreads), (fused24 && dt == TMASK_F32) ? kPack4LdsReserveFusedF32 : 0, stream,
+            hipLaunchKernelGGL(kern, dim3(tiles), dim3(kThreads), (fused24 && dt == TMASK_F32 && !small) ? kPack4LdsReserveFusedF32 : 0, stream,
                                args);
         }
         hipError_t e = hipGetLastError();

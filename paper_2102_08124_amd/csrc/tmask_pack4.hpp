@@ -154,16 +154,20 @@ __device__ __forceinline__ void pack24_copy_out(const PackDev &d, uint32_t row0,
         const size_t pitch = ((size_t)d.rows + 7) / 8;
         const uint32_t nb = (brs_valid + 1) / 2;
         unsigned char *dst = (unsigned char *)d.idxT + (size_t)col0 * pitch + row0 / 8;
-        if (nb == TR / 8 && (pitch & 7) == 0 && (((uintptr_t)dst) & 7) == 0) {
-            constexpr uint32_t P = TR / 64;   // 8-byte pieces per column
+        constexpr uint32_t PB = TR % 64 == 0 ? 8 : 4;     // bytes per store
+        if (nb == TR / 8 && (pitch & (PB - 1)) == 0 && (((uintptr_t)dst) & (PB - 1)) == 0) {
+            constexpr uint32_t P = TR / 8 / PB;           // pieces per column
             for (uint32_t j = tid; j < cols_valid * P; j += kNT) {
                 const uint32_t cc = j / P, x = j % P;
-                u32x2 v;
-                v.x = (uint32_t)IDXT[8 * x][cc] | ((uint32_t)IDXT[8 * x + 1][cc] << 8) |
-                      ((uint32_t)IDXT[8 * x + 2][cc] << 16) | ((uint32_t)IDXT[8 * x + 3][cc] << 24);
-                v.y = (uint32_t)IDXT[8 * x + 4][cc] | ((uint32_t)IDXT[8 * x + 5][cc] << 8) |
-                      ((uint32_t)IDXT[8 * x + 6][cc] << 16) | ((uint32_t)IDXT[8 * x + 7][cc] << 24);
-                *(u32x2 *)(dst + (size_t)cc * pitch + 8 * x) = v;
+                uint32_t v[PB / 4];
+#pragma unroll
+                for (uint32_t h = 0; h < PB / 4; h++)
+                    v[h] = (uint32_t)IDXT[PB * x + 4 * h][cc] | ((uint32_t)IDXT[PB * x + 4 * h + 1][cc] << 8) |
+                           ((uint32_t)IDXT[PB * x + 4 * h + 2][cc] << 16) | ((uint32_t)IDXT[PB * x + 4 * h + 3][cc] << 24);
+                if constexpr (PB == 8)
+                    *(u32x2 *)(dst + (size_t)cc * pitch + 8 * x) = u32x2{v[0], v[1]};
+                else
+                    *(uint32_t *)(dst + (size_t)cc * pitch + 4 * x) = v[0];
             }
         } else {
             for (uint32_t j = tid; j < cols_valid * nb; j += kNT) {

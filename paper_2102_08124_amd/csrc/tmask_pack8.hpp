@@ -17,10 +17,11 @@
 
 namespace tmask {
 
+template <int STEPS = 2>
 struct Pack8Geo {
     static constexpr int S = 32;                 // strips per tile row
     static constexpr int LPR = 64 / S;           // runs of block-rows a wavefront covers at a time
-    static constexpr int NSTEP = 2;              // block-rows per run
+    static constexpr int NSTEP = STEPS;          // block-rows per run
     static constexpr int TR = 4 * LPR * NSTEP * 8, TC = S * 8;
     static constexpr int NBR = TR / 8;           // block-rows per tile
     static constexpr int OTD = NBR * 2;          // dwords per column of W^T in the tile
@@ -142,10 +143,11 @@ __device__ __forceinline__ void pack48_copy_out(const PackDev &d, uint32_t row0,
 // APPROX = false: tmask_apply_pack (ARGS = PackArgs, the mask is read).  APPROX = true: tmask_approx_pack
 // (ARGS = FusedArgs): the keep flags come from Algorithm 1 in its threshold form (approx_half_bf16) on the
 // lane's block; the mask is written if WMASK, the kept magnitudes' sum goes to the workgroup's partial.
-template <int FMT, bool APPROX, bool WMASK, typename ARGS>
+// STEPS: blocks per lane, one after the other; 1 halves the tile (64 rows).
+template <int FMT, bool APPROX, bool WMASK, typename ARGS, int STEPS = 2>
 __global__ __launch_bounds__(kThreads) void pack48_bf16_kernel(const ARGS args)
 {
-    using PG = Pack8Geo;
+    using PG = Pack8Geo<STEPS>;
     constexpr int ES = 2, S = PG::S, LPR = PG::LPR, NSTEP = PG::NSTEP, TR = PG::TR, TC = PG::TC, OTD = PG::OTD,
                   TCP = PG::TCP, IDXB = PG::IDXB, IDXTB = PG::IDXTB;
 
@@ -234,9 +236,9 @@ __global__ __launch_bounds__(kThreads) void pack48_bf16_kernel(const ARGS args)
         }
     };
     issue(0);
-    if constexpr (!APPROX)
+    if constexpr (!APPROX && NSTEP == 2)
         issue(1);
-    static_assert(NSTEP == 2, "the load schedule above is written for two blocks per lane");
+    static_assert(NSTEP <= 2, "the load schedule above is written for at most two blocks per lane");
 
     float acc = 0.f;
     uint32_t tcode[8];                                    // position bits of the lane's columns, 12 per block-row
@@ -276,8 +278,10 @@ __global__ __launch_bounds__(kThreads) void pack48_bf16_kernel(const ARGS args)
             // moves all its additions there and keeps every keep flag and magnitude alive until then
             asm volatile("" : "+v"(acc));
             __builtin_amdgcn_sched_barrier(0);
-            if (q == 0)
-                issue(1);
+            if constexpr (NSTEP == 2) {
+                if (q == 0)
+                    issue(1);
+            }
             __builtin_amdgcn_sched_barrier(0);
         }
         // keep bits per row, and the block with its pruned values zeroed
@@ -351,15 +355,24 @@ __global__ __launch_bounds__(kThreads) void pack48_bf16_kernel(const ARGS args)
         *(u32x4 *)&OT[2 * brl + 1][tcol] = u32x4{oc1[0], oc1[1], oc1[2], oc1[3]};
         *(u32x4 *)&OT[2 * brl + 1][tcol + 4] = u32x4{oc1[4], oc1[5], oc1[6], oc1[7]};
     }
-    // the lane's two block-rows are neighbours: 24 position bits = three whole bytes per column
+    // two block-rows that are neighbours have 24 position bits = three whole bytes per column: the lane's own two, or its
+    // one and that of the lane half a wavefront further (which holds the next block-row)
+    static_assert(LPR == 2, "lanes l and l + 32 hold neighbouring runs");
+    if constexpr (NSTEP == 1) {
+#pragma unroll
+        for (int c = 0; c < 8; c++)
+            tcode[c] |= (uint32_t)__shfl_xor((int)tcode[c], 32, 64) << 12;
+    }
 #pragma unroll
     for (int t = 0; t < 3; t++) {
+        if (NSTEP == 1 && sub != 0)
+            break;
         u32x2 v;
         v.x = ((tcode[0] >> (8 * t)) & 0xFFu) | (((tcode[1] >> (8 * t)) & 0xFFu) << 8) |
               (((tcode[2] >> (8 * t)) & 0xFFu) << 16) | (((tcode[3] >> (8 * t)) & 0xFFu) << 24);
         v.y = ((tcode[4] >> (8 * t)) & 0xFFu) | (((tcode[5] >> (8 * t)) & 0xFFu) << 8) |
               (((tcode[6] >> (8 * t)) & 0xFFu) << 16) | (((tcode[7] >> (8 * t)) & 0xFFu) << 24);
-        *(u32x2 *)&IDXT[3 * q2 + t][tcol] = v;
+        *(u32x2 *)&IDXT[3 * (NSTEP == 1 ? w : q2) + t][tcol] = v;
     }
     __syncthreads();
 

@@ -12,7 +12,7 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 from paper_2102_08124_amd import binding as tm        # noqa: E402
-from tests.gpu_util import run_fused, to_dev          # noqa: E402
+from tests.gpu_util import run_fused, run_pack, to_dev     # noqa: E402
 
 
 def _w(dt, rows, cols, seed):
@@ -151,3 +151,45 @@ def test_fused_argument_errors():
     torch.cuda.synchronize()
     # nothing was written by the rejected calls
     assert ctypes.sizeof(tm.tmask_fused_desc) == 88
+
+
+@pytest.mark.parametrize("fmt", [tm.TMASK_MASK_U8, tm.TMASK_MASK_BITS])
+@pytest.mark.parametrize("dt,N,M", [("f32", 2, 4), ("bf16", 2, 4), ("bf16", 4, 8)])
+def test_whole_tiles_of_a_large_launch(dt, N, M, fmt):
+    """Launches of few tiles take tiles of half the height; a large matrix in the batch puts the ragged ones through the
+    whole tiles, in one pass and as compression of a given mask."""
+    ws = [_w(dt, 68 if M == 4 else 136, 1032, seed=2710), _w(dt, 260 if M == 4 else 264, 520, seed=2711), _w(dt, 128, 1024, seed=2712),
+          _w(dt, 6144, 4096 if dt == "f32" else 8192, seed=2713)]
+    got, masks, objs = run_fused(ws, N, M, fmt=fmt)
+    _check(ws[:3], N, M, got, masks, objs)
+    for have, packed in ((got[:3], None), (run_pack(ws, masks, N, M, fmt=fmt), got)):
+        if packed is not None:
+            for a, b in zip(have, packed):
+                for x, y in zip(a, b):
+                    assert np.array_equal(x.view(np.uint8), y.view(np.uint8))
+    # the first rows of the large one
+    rows = 16 * M
+    omask, _ = oracle.approx(ws[3][:rows], N, M)
+    vals, idx, _, _ = oracle.apply_pack(ws[3][:rows], omask, N, M)
+    assert np.array_equal(masks[3][:rows] != 0, omask != 0)
+    assert np.array_equal(got[3][0][:rows].view(np.uint8), vals.view(np.uint8)) and np.array_equal(got[3][1][:rows], idx)
+
+
+@pytest.mark.parametrize("dt,N,M", [("f32", 2, 4), ("bf16", 2, 4), ("bf16", 4, 8)])
+def test_workspace_for_whole_tiles_is_enough(dt, N, M):
+    w = _w(dt, 256, 1024, seed=2720)
+    tiles = (256 // (64 if dt == "f32" else 128)) * (1024 // 256)
+    wd = to_dev(w)
+    pk = tm.alloc_packed(wd, N, M)
+    obj = torch.zeros(1, dtype=torch.float64, device="cuda")
+    wsp = torch.empty(8 * tiles, dtype=torch.uint8, device="cuda")
+    tm.tmask_approx_pack([wd], None, [pk], N, M, objective=obj, workspace=wsp)
+    torch.cuda.synchronize()
+    omask, oobj = oracle.approx(w, N, M)
+    for g, t in zip(pk, oracle.apply_pack(w, omask, N, M)):
+        gh = g.view(torch.int16).cpu().numpy().view(np.uint16) if g.dtype == torch.bfloat16 else g.cpu().numpy()
+        assert np.array_equal(gh.view(np.uint8), t.view(np.uint8))
+    assert float(obj[0]) == pytest.approx(oobj, rel=1e-5)
+    with pytest.raises(tm.TmaskError) as e:
+        tm.tmask_approx_pack([wd], None, [pk], N, M, objective=obj, workspace=wsp[:8 * tiles - 8])
+    assert e.value.code == tm.TMASK_ERR_WORKSPACE
