@@ -172,6 +172,29 @@ def test_m32_approx_pack_and_dense_calls():
         assert np.all(np.abs(got_f - want) <= tol + 1e-30)
 
 
+@pytest.mark.parametrize("fmt", FMTS)
+@pytest.mark.parametrize("kind", ["bf16", "ties_bf16", "zeros", "special"])
+def test_m32_bf16_by_rows_and_by_columns(kind, fmt):
+    """16:32 of aligned bf16 matrices is read by rows, two keys to a register; one pitch that is odd sends the whole batch
+    the column-per-lane way.  Both against the oracle: half tiles, one block, more block-rows than one XCD takes."""
+    hs = []
+    for k, (rows, cols) in enumerate([(32, 32), (32, 96), (96, 416), (320, 1056)]):
+        w = _inputs({"zeros": "bf16", "special": "special"}.get(kind, kind), rows, cols, seed=3230 + k)
+        w = w if w.dtype == np.uint16 else wl.f32_to_bf16_bits(w)
+        hs.append(np.where(wl.f32_to_bf16_bits(wl.gaussian_f32(rows, cols, 3240 + k)) & 0x4000, w, 0x8000) if kind == "zeros" else w)
+    hs = [h.astype(np.uint16) for h in hs]
+    want = [oracle.approx(h, 16, 32) for h in hs]
+    for pad in (0, 8, 1):
+        got, obj = run_masks(tm.tmask_approx, hs, 16, 32, fmt, ld_pad=pad)
+        for g, o, (om, oo) in zip(got, obj, want):
+            assert np.array_equal(g, om)
+            if kind != "special":
+                assert o == pytest.approx(oo, rel=1e-5)
+        got, _ = run_masks(tm.tmask_approx, hs, 16, 32, fmt, ld_pad=pad, with_objective=False)
+        for g, (om, _) in zip(got, want):
+            assert np.array_equal(g, om)
+
+
 def test_m32_argument_errors():
     w = torch.zeros((64, 64), dtype=torch.float32, device="cuda")
     m = tm.alloc_masks([w])[0]
