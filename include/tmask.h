@@ -37,8 +37,8 @@
  *   one-pass tmask_approx_pack kernels), dense outputs 16-byte aligned with a 16-byte pitch.  bf16 at M = 4 needs half
  *   of all that (8-byte strips: a width or pitch that is a multiple of four; the one-pass tmask_approx_pack kernels and
  *   tmask_apply_pack at N != 2 excepted).  A call in which some
- *   matrix misses any of this, and every call with M = 32 (tmask_apply_pack at 16:32 with `vals` 16-byte aligned
- *   excepted), runs on element-wise kernels instead (one lane per column of a block): correct for every layout above, bound by the vector ALU or by LDS traffic instead of by
+ *   matrix misses any of this, and every call with M = 32 (tmask_apply_pack at 16:32 with `vals` 16-byte aligned, and
+ *   tmask_approx at 16:32 of bf16 with 16-byte aligned rows and masks, excepted), runs on element-wise kernels instead (one lane per column of a block): correct for every layout above, bound by the vector ALU or by LDS traffic instead of by
  *   memory.
  *
  * Errors
