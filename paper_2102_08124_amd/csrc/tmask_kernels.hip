@@ -85,23 +85,28 @@ __global__ __launch_bounds__(kThreads) void mask_kernel(const BatchArgs args)
     }
 }
 
-// tmask_approx for 2:4: same tiling as mask_kernel, decisions taken as lane-mask logic.
+// A strip of tmask_approx for 2:4, decisions taken as lane-mask logic; returns what the lane keeps.
+template <int DT, int FMT>
+__device__ __forceinline__ float approx24_strip(const MatDev &md, uint32_t s)
+{
+    const StripPos pos = strip_pos(md, s);
+    uint32_t a[4][Geo<DT, 4>::C];
+    u32x4 raw[4];
+    load_strip<DT, 4>(md, pos, a, raw);
+    return approx_2of4_strip<DT, FMT>(md, pos, a);
+}
+
+// tmask_approx for 2:4: same tiling as mask_kernel.
 template <int DT, int FMT>
 __global__ __launch_bounds__(kThreads) void approx24_kernel(const BatchArgs args)
 {
-    using Ge = Geo<DT, 4>;
     __shared__ double red[kThreads / 64];
     const uint32_t tile = blockIdx.x;
     const MatDev md = args.m[find_matrix(args, tile)];
     const uint32_t s = (tile - md.tile0) * kThreads + threadIdx.x;
     float acc = 0.f;
-    if (s < md.n_strips) {
-        const StripPos pos = strip_pos(md, s);
-        uint32_t a[4][Ge::C];
-        u32x4 raw[4];
-        load_strip<DT, 4>(md, pos, a, raw);
-        acc = approx_2of4_strip<DT, FMT>(md, pos, a);
-    }
+    if (s < md.n_strips)
+        acc = approx24_strip<DT, FMT>(md, s);
     if (args.partials) {
         const double t = block_sum_f32(acc, red);
         if (threadIdx.x == 0)
@@ -171,58 +176,96 @@ __global__ __launch_bounds__(kThreads, (M == 16 && FMT == kMaskBits) ? 4 : 1) vo
     }
 }
 
-// tmask_exact at M = 4: every block by enumeration (NK = 2: all 90 patterns; NK = 1, 3: the 24 permutations, kept
-// resp. pruned), the kept sum comes with the optimum.
+// A strip of tmask_exact at M = 4: every block by enumeration (NK = 2: all 90 patterns; NK = 1, 3: the 24 permutations,
+// kept resp. pruned), the kept sum comes with the optimum.
+template <int DT, int FMT, int NK>
+__device__ __forceinline__ float exact24_strip(const MatDev &md, uint32_t s)
+{
+    using Ge = Geo<DT, 4>;
+    const StripPos pos = strip_pos(md, s);
+    uint32_t a[4][Ge::C];
+    u32x4 raw[4];
+    uint32_t bits[4] = {0u, 0u, 0u, 0u};
+    load_strip<DT, 4>(md, pos, a, raw);
+    float sum = 0.f;
+#pragma unroll
+    for (int b = 0; b < Ge::B; b++) {
+        float v[4][4];
+#pragma unroll
+        for (int i = 0; i < 4; i++)
+#pragma unroll
+            for (int c = 0; c < 4; c++)
+                v[i][c] = __uint_as_float(a[i][b * 4 + c]);
+        float best;
+        uint32_t m16;
+        if constexpr (NK == 2) {
+            m16 = exact24_block(v, best);
+        } else if constexpr (NK == 1) {
+            m16 = best_permutation4<true>(v, best);
+        } else {
+            m16 = ~best_permutation4<false>(v, best) & 0xFFFFu;
+            float all = 0.f;
+#pragma unroll
+            for (int i = 0; i < 4; i++)
+                all += (v[i][0] + v[i][1]) + (v[i][2] + v[i][3]);
+            best = all - best;
+        }
+        sum += best;
+#pragma unroll
+        for (int i = 0; i < 4; i++)
+            bits[i] |= ((m16 >> (4 * i)) & 0xFu) << (4 * b);
+    }
+    store_mask<DT, 4, FMT>(md, pos, bits);
+    return sum;
+}
+
 template <int DT, int FMT, int NK = 2>
 __global__ __launch_bounds__(kThreads) void exact24_kernel(const BatchArgs args)
 {
-    using Ge = Geo<DT, 4>;
     __shared__ double red[kThreads / 64];
     const uint32_t tile = blockIdx.x;
     const MatDev md = args.m[find_matrix(args, tile)];
     const uint32_t s = (tile - md.tile0) * kThreads + threadIdx.x;
     float acc = 0.f;
-    if (s < md.n_strips) {
-        const StripPos pos = strip_pos(md, s);
-        uint32_t a[4][Ge::C];
-        u32x4 raw[4];
-        uint32_t bits[4] = {0u, 0u, 0u, 0u};
-        load_strip<DT, 4>(md, pos, a, raw);
-        float sum = 0.f;
-#pragma unroll
-        for (int b = 0; b < Ge::B; b++) {
-            float v[4][4];
-#pragma unroll
-            for (int i = 0; i < 4; i++)
-#pragma unroll
-                for (int c = 0; c < 4; c++)
-                    v[i][c] = __uint_as_float(a[i][b * 4 + c]);
-            float best;
-            uint32_t m16;
-            if constexpr (NK == 2) {
-                m16 = exact24_block(v, best);
-            } else if constexpr (NK == 1) {
-                m16 = best_permutation4<true>(v, best);
-            } else {
-                m16 = ~best_permutation4<false>(v, best) & 0xFFFFu;
-                float all = 0.f;
-#pragma unroll
-                for (int i = 0; i < 4; i++)
-                    all += (v[i][0] + v[i][1]) + (v[i][2] + v[i][3]);
-                best = all - best;
-            }
-            sum += best;
-#pragma unroll
-            for (int i = 0; i < 4; i++)
-                bits[i] |= ((m16 >> (4 * i)) & 0xFu) << (4 * b);
-        }
-        store_mask<DT, 4, FMT>(md, pos, bits);
-        acc = sum;
-    }
+    if (s < md.n_strips)
+        acc = exact24_strip<DT, FMT, NK>(md, s);
     if (args.partials) {
         const double t = block_sum_f32(acc, red);
         if (threadIdx.x == 0)
             ((double *)args.partials)[args.partial0 + tile] = t;
+    }
+}
+
+// A few small matrices with their objectives, 2:4: a workgroup of 1024 threads takes a whole matrix, a strip per thread, and
+// writes its objective itself, so that the call is one launch instead of two, and one with 1.8 KB of arguments instead of
+// 16.  Such a call is bound by its launches (each 2.3 us of host time, 1.2 more for the large arguments) and by the few
+// microseconds that a kernel lasts at least.  Back to back / in a graph, 1 ... 32 matrices of 1024 strips: fp32 8.2 - 9.3 / 4.5 -
+// 5.4 -> 4.9 - 5.3 / 3.3 - 3.9 us, bf16 8.2 - 9.2 / 5.2 - 6.2 -> 4.8 - 5.4 / 4.6 - 5.3.  Two strips per thread are as slow as two
+// launches in a graph (fp32 5.3 against 4.8 us, bf16 8.4 against 5.3): a compute unit alone moves 50 GB/s.
+constexpr int kWholeThreads = 1024, kWholeMats = 32;
+
+struct WholeArgs {
+    MatDev m[kWholeMats];     // aux: the objective (or null)
+};
+
+template <int SOLVER, int DT, int FMT>
+__global__ __launch_bounds__(kWholeThreads) void whole24_kernel(const WholeArgs args)
+{
+    __shared__ double red[kWholeThreads / 64];
+    const MatDev md = args.m[blockIdx.x];
+    float acc = 0.f;
+    if (threadIdx.x < md.n_strips)
+        acc = SOLVER == kSolveApprox ? approx24_strip<DT, FMT>(md, threadIdx.x) : exact24_strip<DT, FMT, 2>(md, threadIdx.x);
+    const float sum = wave_sum(acc);
+    if ((threadIdx.x & 63u) == 0)
+        red[threadIdx.x >> 6] = (double)sum;
+    __syncthreads();
+    if (threadIdx.x == 0 && md.aux) {
+        double total = red[0];
+#pragma unroll
+        for (int k = 1; k < kWholeThreads / 64; k++)
+            total += red[k];
+        *(double *)md.aux = total;
     }
 }
 
@@ -1113,6 +1156,31 @@ static int scratch_of_current_device(void **out)
     return TMASK_OK;
 }
 
+// One launch for at most kWholeMats matrices of at most kWholeThreads strips at 2:4 (checked by the caller, like the rest).
+template <int SOLVER>
+static int run_whole(const tmask_mat *mats, int n_mats, int sdt, int mf, hipStream_t stream)
+{
+    WholeArgs args;
+    for (int k = 0; k < n_mats; k++) {
+        const tmask_mat &t = mats[k];
+        fill_desc(args.m[k], HostMat{t.w, t.rows, t.cols, t.ld, t.mask, t.mask_ld, t.objective}, sdt, 4, (uint32_t)k);
+        args.m[k].aux = t.objective;
+    }
+    memset(args.m + n_mats, 0, sizeof(MatDev) * (size_t)(kWholeMats - n_mats));
+    void (*kern)(const WholeArgs) = nullptr;
+#define TMASK_PICK(DT) \
+    if (sdt == DT) \
+        kern = mf == kMaskU8 ? whole24_kernel<SOLVER, DT, kMaskU8> : whole24_kernel<SOLVER, DT, kMaskBits>;
+    TMASK_PICK(kF32) TMASK_PICK(kBF16) TMASK_PICK(kBF16N)
+#undef TMASK_PICK
+    {
+        ProfileScope prof(stream, true);
+        hipLaunchKernelGGL(kern, dim3(n_mats), dim3(kWholeThreads), 0, stream, args);
+    }
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess ? TMASK_OK : hip_fail(e, "mask kernel launch");
+}
+
 // own_scratch: the partial sums go to the library's static array instead of a caller workspace (ws, ws_bytes unused).
 template <int SOLVER>
 static int run_mask(const tmask_mat *mats, int n_mats, int dt, int N, int M, int mf, void *ws, size_t ws_bytes,
@@ -1154,6 +1222,15 @@ static int run_mask(const tmask_mat *mats, int n_mats, int dt, int N, int M, int
     if (fit == kFitColumns || general_n)     // also M = 32, or a matrix that the strips cannot read
         return cw_run_mask(SOLVER == kSolveApprox ? 0 : SOLVER == kSolveExact ? 1 : 2, mats, n_mats, dt, N, M, mf, ws,
                            (hipStream_t)stream_);
+    if constexpr (SOLVER != kSolveRow1D) {       // without objectives the call is one launch anyway
+        bool whole = M == 4 && N == 2 && want_obj && n_mats <= kWholeMats;
+        for (int i = 0; i < n_mats && whole; i++) {
+            const HostMat h{mats[i].w, mats[i].rows, mats[i].cols, mats[i].ld, nullptr, 0, nullptr};
+            whole = strips_of(h, sdt, M) <= (uint32_t)kWholeThreads;
+        }
+        if (whole)
+            return run_whole<SOLVER>(mats, n_mats, sdt, mf, (hipStream_t)stream_);
+    }
     batch_kernel_t kern = nullptr;
     if constexpr (SOLVER != kSolveExact)      // exact: enumeration at M = 4, the balanced kernel at M = 8, 16 (below)
         kern = pick_mask_kernel<SOLVER>(sdt, M, mf);

@@ -15,7 +15,7 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 from paper_2102_08124_amd import binding as tm   # noqa: E402
-from tests.gpu_util import run_masks, run_score  # noqa: E402
+from tests.gpu_util import run_masks, run_score, to_dev, mask_to_host  # noqa: E402
 
 NM = [(2, 4), (4, 8), (8, 16)]
 FMTS = [tm.TMASK_MASK_U8, tm.TMASK_MASK_BITS]
@@ -378,3 +378,42 @@ def test_prune_1d_batched_with_strides():
             omask, oobj = oracle.prune_1d(w, 4, 8)
             assert np.array_equal(m, omask)
             assert o == pytest.approx(oobj, rel=1e-5)
+
+
+@pytest.mark.parametrize("fmt", [tm.TMASK_MASK_U8, tm.TMASK_MASK_BITS])
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+def test_small_matrices_in_one_launch(dt, fmt):
+    """2:4 with objectives: up to 32 matrices of up to 1024 strips go a matrix to a workgroup; more strips or one matrix more
+    takes the call the usual way."""
+    wide = 4 if dt == "f32" else 8
+    one = [(4, 8), (4, 64 * wide), (8, 66 * wide), (64, 64 * wide), (4, 1024 * wide), (16, 254 * wide)]
+
+    def gen(shapes, seed):
+        ws = [wl.gaussian_f32(r, c, seed + k) for k, (r, c) in enumerate(shapes)]
+        return ws if dt == "f32" else [wl.f32_to_bf16_bits(w) for w in ws]
+
+    for shapes in (one[:1], one, (one * 6)[:32], (one * 6)[:33], one + [(4, 1026 * wide)]):
+        ws = gen(shapes, 2800)
+        want = [oracle.approx(w, 2, 4) for w in ws[:8]]
+        masks, obj = run_masks(tm.tmask_approx, ws, 2, 4, fmt)
+        for (om, oo), m, o in zip(want, masks, obj):
+            assert np.array_equal(m, om)
+            assert o == pytest.approx(oo, rel=1e-5)
+        masks, obj = run_masks(tm.tmask_exact, ws, 2, 4, fmt)
+        for w, m, o in zip(ws[:8], masks, obj):
+            _, oo = oracle.exact(w, 2, 4)[:2]
+            b = refs.to_blocks(m, 4)
+            assert np.all(b.sum(axis=3) == 2) and np.all(b.sum(axis=2) == 2)
+            assert o == pytest.approx(oo, rel=1e-5)
+            assert float((refs.magnitudes(w).astype(np.float64) * m).sum()) == pytest.approx(oo, rel=1e-5)
+    # the call that takes no workspace
+    ws = gen(one, 2850)
+    wd = [to_dev(w) for w in ws]
+    masks = tm.alloc_masks(wd, fmt)
+    obj = torch.full((len(ws),), -1.0, dtype=torch.float64, device="cuda")
+    tm.tmask_approx_noalloc(wd, masks, 2, 4, objective=obj, mask_fmt=fmt)
+    torch.cuda.synchronize()
+    for w, m, o in zip(ws, masks, obj.cpu().numpy()):
+        om, oo = oracle.approx(w, 2, 4)
+        assert np.array_equal(mask_to_host(m, w.shape[1], fmt), om)
+        assert o == pytest.approx(oo, rel=1e-5)
