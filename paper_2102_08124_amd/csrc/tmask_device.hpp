@@ -220,13 +220,26 @@ __device__ __forceinline__ T block_sum(T v, T *lds /* kThreads/64 entries */)
     return r;
 }
 
-// Workgroup sum of per-thread fp32 values: fp32 inside a wavefront, fp64 across wavefronts.
+// Sum over a wavefront of what its lanes keep: fp32, in fp64 for narrow strips, whose 1024 values of eight bits no longer
+// add up exactly in fp32 (the column-per-lane kernels, which read such matrices otherwise, add 256 at a time: objective
+// against 64 bits 2e-11, 6e-10 in fp32).
+template <int DT>
+__device__ __forceinline__ double wave_kept(float v)
+{
+    if constexpr (DT == kBF16N)
+        return wave_sum((double)v);
+    else
+        return (double)wave_sum(v);
+}
+
+// Workgroup sum of per-thread fp32 values: inside a wavefront as above, fp64 across wavefronts.
+template <int DT = kF32>
 __device__ __forceinline__ double block_sum_f32(float v, double *lds /* kThreads/64 entries */)
 {
-    const float w = wave_sum(v);
+    const double w = wave_kept<DT>(v);
     const int wave = threadIdx.x >> 6;
     if ((threadIdx.x & 63) == 0)
-        lds[wave] = (double)w;
+        lds[wave] = w;
     __syncthreads();
     double r = lds[0];
 #pragma unroll

@@ -79,7 +79,7 @@ __global__ __launch_bounds__(kThreads) void mask_kernel(const BatchArgs args)
         acc = kept_sum<M, Ge::C>(a, bits);
     }
     if (args.partials) {
-        const double t = block_sum_f32(acc, red);
+        const double t = block_sum_f32<DT>(acc, red);
         if (threadIdx.x == 0)
             ((double *)args.partials)[args.partial0 + tile] = t;
     }
@@ -108,7 +108,7 @@ __global__ __launch_bounds__(kThreads) void approx24_kernel(const BatchArgs args
     if (s < md.n_strips)
         acc = approx24_strip<DT, FMT>(md, s);
     if (args.partials) {
-        const double t = block_sum_f32(acc, red);
+        const double t = block_sum_f32<DT>(acc, red);
         if (threadIdx.x == 0)
             ((double *)args.partials)[args.partial0 + tile] = t;
     }
@@ -230,7 +230,7 @@ __global__ __launch_bounds__(kThreads) void exact24_kernel(const BatchArgs args)
     if (s < md.n_strips)
         acc = exact24_strip<DT, FMT, NK>(md, s);
     if (args.partials) {
-        const double t = block_sum_f32(acc, red);
+        const double t = block_sum_f32<DT>(acc, red);
         if (threadIdx.x == 0)
             ((double *)args.partials)[args.partial0 + tile] = t;
     }
@@ -256,9 +256,9 @@ __global__ __launch_bounds__(kWholeThreads) void whole24_kernel(const WholeArgs 
     float acc = 0.f;
     if (threadIdx.x < md.n_strips)
         acc = SOLVER == kSolveApprox ? approx24_strip<DT, FMT>(md, threadIdx.x) : exact24_strip<DT, FMT, 2>(md, threadIdx.x);
-    const float sum = wave_sum(acc);
+    const double sum = wave_kept<DT>(acc);
     if ((threadIdx.x & 63u) == 0)
-        red[threadIdx.x >> 6] = (double)sum;
+        red[threadIdx.x >> 6] = sum;
     __syncthreads();
     if (threadIdx.x == 0 && md.aux) {
         double total = red[0];
@@ -789,14 +789,14 @@ __global__ __launch_bounds__(kThreads) void score_kernel(const BatchArgs args)
     // One reduction pass: fp32 / packed 32-bit counts inside a wavefront (a lane contributes at most
     // 128 kept, 16 row events and 8 column events, so 16-bit fields cannot overflow over 64 lanes),
     // then the four wavefronts in fp64 / 64-bit through LDS.
-    const float w_ret = wave_sum(retained), w_tot = wave_sum(total);
+    const double w_ret = wave_kept<DT>(retained), w_tot = wave_kept<DT>(total);
     const uint32_t w_a = wave_sum(kept | (rowv << 16));
     const uint32_t w_b = wave_sum(colv | (colne << 16));
     const uint32_t w_c = wave_sum(rowne);
     const int wave = threadIdx.x >> 6;
     if ((threadIdx.x & 63) == 0) {
-        redd[wave][0] = (double)w_ret;
-        redd[wave][1] = (double)w_tot;
+        redd[wave][0] = w_ret;
+        redd[wave][1] = w_tot;
         redu[wave][0] = w_a & 0xFFFFu;
         redu[wave][1] = w_a >> 16;
         redu[wave][2] = w_b & 0xFFFFu;
