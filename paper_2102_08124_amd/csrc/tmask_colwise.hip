@@ -430,7 +430,8 @@ __global__ __launch_bounds__(kCwThreads, M == 32 ? 4 : 1) void cw_mask_kernel(co
 // Magnitudes have 15 bits, so a packed minimum or maximum works on two at once, and the sign of a packed difference
 // compares two; the columns come through LDS, 64 bytes and 16 of padding to a row.  Bound by the vector ALU: about 850
 // instructions per tile of 32 x 64 against 1200 with a key to a register, in 47 registers (eight wavefronts per SIMD, four
-// with cw_mask_kernel's 117).  4096 x 3072, the whole call with its objective: 21.0 -> 16.9 us.
+// with cw_mask_kernel's 117).  4096 x 3072, the whole call with its objective: 21.0 -> 16.7 us;
+// 8192^2 kernel 69 -> 54 us.
 
 // bit c of the result: entry c (c < 16 in the low half of v[c], else in the high half of v[c - 16]) is less than t (both
 // halves the same); DOWN: t is less than entry c.  Four sign bits at a time into the top bits of the result's bytes.
@@ -477,18 +478,25 @@ __device__ __forceinline__ uint32_t pk_pruned16(const pk16 (&v)[16])
     return w;
 }
 
+// A workgroup is four wavefronts with a tile each: a quarter of the partial sums to add up (whole calls with a wavefront / with
+// four to a workgroup: 8192^2 61.7 / 57.6 us, 16384^2 221 / 201 us, 4096 x 3072 16.9 / 16.7).
+constexpr uint32_t kRowsTiles = 4;
+
 template <int FMT>
-__global__ __launch_bounds__(kCwThreads, 8) void cw_mask32_bf16_kernel(const CwArgs args)
+__global__ __launch_bounds__(64 * kRowsTiles, 8) void cw_mask32_bf16_kernel(const CwArgs args)
 {
     constexpr uint32_t kPitch = 20;                       // dwords: four of padding keep the 16-byte accesses conflict-free
-    __shared__ __align__(16) uint32_t T[64 * kPitch];
+    __shared__ __align__(16) uint32_t lds[kRowsTiles][64 * kPitch];
     const CwMat md = args.m[cw_find(args, blockIdx.x)];
-    const uint32_t lane = threadIdx.x, blk = lane >> 5, j = lane & 31u;
+    const uint32_t lane = threadIdx.x & 63u, blk = lane >> 5, j = lane & 31u;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    uint32_t *const T = lds[wave];                        // the wavefront's own: no barriers among its lanes
     double total = 0.0;
-    for (uint32_t t = blockIdx.x - md.wg0; t < md.n_tiles; t += md.n_wg) {
-        const CwTile p = cw_tile<4>(md, t);
-        const size_t row = (size_t)p.br * 32 + j;
-        const uint32_t col = p.col0 + blk * 32u;
+    const uint32_t t = (blockIdx.x - md.wg0) * kRowsTiles + wave;
+    if (t < md.n_tiles) {
+        const uint32_t br = (uint32_t)(((uint64_t)t * md.div_mul) >> md.div_shift);
+        const size_t row = (size_t)br * 32 + j;
+        const uint32_t col = (t - br * md.tpr) * 64u + blk * 32u;
         const bool active = col < md.cols;
         uint4 in[4] = {};
         if (active) {
@@ -507,13 +515,12 @@ __global__ __launch_bounds__(kCwThreads, 8) void cw_mask32_bf16_kernel(const CwA
             }
         }
         uint4 *mine = (uint4 *)&T[lane * kPitch];
-        __syncthreads();                                  // the previous tile's readers are done
 #pragma unroll
         for (int i = 0; i < 4; i++)
             mine[i] = make_uint4(__builtin_bit_cast(uint32_t, v[4 * i]), __builtin_bit_cast(uint32_t, v[4 * i + 1]),
                                  __builtin_bit_cast(uint32_t, v[4 * i + 2]), __builtin_bit_cast(uint32_t, v[4 * i + 3]));
         uint32_t keep = ~pk_pruned16(v);
-        __syncthreads();
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         {
             const unsigned short *c = (const unsigned short *)&T[blk * 32u * kPitch + (j & 15u)] + (j >> 4);
 #pragma unroll
@@ -551,11 +558,20 @@ __global__ __launch_bounds__(kCwThreads, 8) void cw_mask32_bf16_kernel(const CwA
                     acc += __uint_as_float(k & 0x7FFF0000u);
                 }
             }
-            total += (double)wave_sum(acc);
+            total = (double)wave_sum(acc);
         }
     }
-    if (args.partials && threadIdx.x == 0)
-        ((double *)args.partials)[args.partial0 + blockIdx.x] = total;
+    if (args.partials) {
+        double *const sum = (double *)&T[16];             // padding of the first row
+        if (lane == 0)
+            *sum = total;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            for (uint32_t k = 1; k < kRowsTiles; k++)
+                total += *(const double *)&lds[k][16];
+            ((double *)args.partials)[args.partial0 + blockIdx.x] = total;
+        }
+    }
 }
 
 // =====================================================================================================================
@@ -1159,7 +1175,7 @@ int cw_run_mask(int solver, const tmask_mat *mats, int n_mats, int dt, int N, in
     else
         kern = cw_pick_mask(solver == 0 ? kCwApprox : kCwRow1D, dt, M, mf);
     // 16:32 of bf16 by rows where every row of every matrix, and of every mask, starts where a wide access may (every
-    // size: 16.9 against 21.0 us at 4096 x 3072, and a tile does less work by itself too); any other pitch by columns
+    // size: 16.7 against 21.0 us at 4096 x 3072, and a tile does less work by itself too); any other pitch by columns
     bool by_rows = solver == 0 && dt == kBF16 && M == 32 && N == 16;
     const uintptr_t mask_align = mf == kMaskU8 ? 15 : 3;
     for (int i = 0; i < n_mats && by_rows; i++)
@@ -1177,6 +1193,8 @@ int cw_run_mask(int solver, const tmask_mat *mats, int n_mats, int dt, int N, in
         for (int k = 0; k < nb; k++) {
             const tmask_mat &t = mats[first + k];
             cw_fill(args.m[k], t.w, t.rows, t.cols, t.ld, t.mask, t.mask_ld, M, wgs);
+            if (by_rows)
+                args.m[k].n_wg = (args.m[k].n_tiles + kRowsTiles - 1) / kRowsTiles;
             objective[k] = t.objective;
             wg0[k] = wgs;
             wgs += args.m[k].n_wg;
@@ -1186,7 +1204,7 @@ int cw_run_mask(int solver, const tmask_mat *mats, int n_mats, int dt, int N, in
         args.partial0 = partial0; args.partials = want_obj ? ws : nullptr;
         {
             ProfileScope prof(stream, first + kMaxCwBatch >= n_mats);
-            hipLaunchKernelGGL(kern, dim3(wgs), dim3(kCwThreads), 0, stream, args);
+            hipLaunchKernelGGL(kern, dim3(wgs), dim3(by_rows ? 64 * kRowsTiles : kCwThreads), 0, stream, args);
         }
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess)
