@@ -72,12 +72,14 @@ __device__ __forceinline__ void store_quad(const SpmmArgs &p, uint32_t tok, uint
 // ---------------------------------------------------------------------------------------------------------------------
 __device__ __forceinline__ void copy16(const unsigned char *base, uint32_t lane_off, uint32_t lds)
 {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(lane_off), "s"(base));
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(lane_off), "s"(base)
+                 : "m0");
 }
 
 __device__ __forceinline__ void copy4(const unsigned char *base, uint32_t lane_off, uint32_t lds)
 {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds), "v"(lane_off), "s"(base));
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds), "v"(lane_off), "s"(base)
+                 : "m0");
 }
 
 // at most N of the wavefront's global memory operations are still in flight (they finish in order)
@@ -343,7 +345,9 @@ constexpr int kTileRing = 3;
 
 // acc += A B with the sums in accumulation registers.  As the builtin, with 256 of them, the compiler moves sums between
 // the two register files in every step.  What it would do for the builtin is done here by hand: two wait states in case
-// an operand was just written by a vector instruction; and whoever reads the sums afterwards waits (sums_ready).
+// an operand was just written by a vector instruction; and whoever reads the sums afterwards waits (sums_ready) and takes
+// them through take_sums.  The compiler does not know that sums are in flight between the two: a test reads the assembly
+// for anything that touches an accumulation register there.
 __device__ __forceinline__ void multiply32(f32x16 &acc, bf16x8 a, bf16x16 b, int sel)
 {
     asm volatile("s_nop 1\n\tv_smfmac_f32_32x32x32_bf16 %0, %1, %2, %3" : "+a"(acc) : "v"(a), "v"(b), "v"(sel));
@@ -356,6 +360,10 @@ __device__ __forceinline__ void sums_ready()
     asm volatile("s_nop 15\n\ts_nop 15");
     __builtin_amdgcn_sched_barrier(0);
 }
+
+// What reads these sums hangs on this point, which stays behind sums_ready() (no volatile asm passes another) and behind
+// the stores before it, so that no more than one tile's results wait in vector registers.
+__device__ __forceinline__ void take_sums(f32x16 &acc) { asm volatile("" : "+a"(acc)::"memory"); }
 
 template <int RT, int CT, bool OUT_BF16>
 __global__ __launch_bounds__(256, RT * CT <= 4 ? 2 : 1) void spmm24_tile_kernel(const SpmmArgs p)
@@ -511,6 +519,7 @@ __global__ __launch_bounds__(256, RT * CT <= 4 ? 2 : 1) void spmm24_tile_kernel(
             const uint32_t tok = tok0 + (uint32_t)ct * 32u;
 #pragma unroll
             for (int rt = 0; rt < RT; rt++) {
+                take_sums(acc[rt][ct]);
                 if constexpr (OUT_BF16) {
                     // pairs of lanes l, l + 32 exchange quads so that each holds eight consecutive rows
                     typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -581,13 +590,14 @@ __global__ __launch_bounds__(256, RT * CT <= 4 ? 2 : 1) void spmm24_tile_kernel(
 #pragma unroll
             for (int j = 0; j < CT; j++)
                 acc[i][j] = (f32x16)(0.f);
-        for (uint32_t k = 0; k < steps; k++) {
+        uint32_t k = 0;
+        do {                                                    // steps is not zero: no path on which the sums stay as they are
             const uint32_t next = image == (kTileRing - 1) * kImage ? 0 : image + kImage;
             half(f[0], f[1], image, 1, std::false_type{});
             arrive();
             half(f[1], f[0], next, 0, std::true_type{});
             image = next;
-        }
+        } while (++k < steps);
         sums_ready();
         stored = store_tile(mj) ? kTileRing - 1u : 0u;
     }
