@@ -20,12 +20,12 @@
 // one whose wavefronts share a large tile.  tmask_spmm24 (at the end) chooses between their tile sizes.
 #include <hip/hip_runtime.h>
 
-#include <cmath>
 #include <cstdint>
 #include <type_traits>
 
 #include "../../include/tmask.h"
 #include "tmask_host.hpp"
+#include "tmask_spmm_choice.hpp"
 
 namespace tmask {
 
@@ -36,7 +36,7 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t su32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t su32x2 __attribute__((ext_vector_type(2)));
 
-constexpr int kSpKS = 64;            // k per step
+constexpr int kSpKS = (int)kSpmmStep;
 
 struct SpmmArgs {
     const void *vals;     // rows x cols/2 bf16
@@ -604,40 +604,16 @@ __global__ __launch_bounds__(256, RT * CT <= 4 ? 2 : 1) void spmm24_tile_kernel(
     wait_copies<0>();                                           // the last copies land while the workgroup still owns its LDS
 }
 
-// The tile sizes, and what a product takes with each, in microseconds: fixed + rounds (per_round + per_step cols / 64).
-// A round is what the compute units do side by side.  `resident` workgroups share a compute unit: of the smallest tiles so
-// many that rounds count in fractions; two of 128 x 128, which together take 1.6 times as long as one.  The coefficients
-// are a fit to 100 products (rows and cols 256 .. 4096, 1 .. 8192 tokens, bf16 results) timed with every tile size; the
-// choice they lead to is on average 0.3 % and at most 10 % slower than the fastest tile, and 3.3 times as fast (geometric
-// mean) as one kernel with 256 x 128 tiles for all: small tiles win while they fill no more than a few rounds, because a
-// compute unit alone moves 50 GB/s whatever its tile (W 4096 x 1024, 16 tokens: 15.8 -> 3.6 us on 16 x 16 tiles, 19 on
-// 256 x 256; 1024 x 4096, 1003 tokens: 55 -> 16 us on 64 x 64 tiles, 60 on 256 x 256), large ones when there are many,
-// because they move less (4096 x 1024, 8192 tokens: 55 us on 256 x 256, 70 on 128 x 128, 163 on 64 x 64).
-struct SpmmVariant {
-    void (*kernel[2])(const SpmmArgs);   // fp32, bf16 results
-    int64_t rows, tokens;                // of a tile
-    uint32_t resident, persistent;       // workgroups per compute unit; at most that many are launched (0: one per tile)
-    double fixed, per_round, per_step;
-    double estimate(uint64_t tiles, double steps, uint64_t cus) const
-    {
-        const double full = (double)tiles / (double)cus;
-        double rounds = ceil(full);
-        if (resident == 3)
-            rounds = full > 1.0 ? full : 1.0;
-        else if (resident == 2 && full > 1.0)
-            rounds = 1.6 * (full > 2.0 ? ceil(2.0 * full) / 4.0 : 1.0);
-        return fixed + rounds * (per_round + per_step * steps);
-    }
-};
-
-static const SpmmVariant kSpmmVariants[] = {
-    {{spmm24_ksplit_kernel<1, 1, 4, 4, false>, spmm24_ksplit_kernel<1, 1, 4, 4, true>}, 16, 16, 3, 0, 2.78, 0.295, 0.033},
-    {{spmm24_ksplit_kernel<2, 2, 4, 4, false>, spmm24_ksplit_kernel<2, 2, 4, 4, true>}, 32, 32, 1, 0, 1.47, 1.55, 0.071},
-    {{spmm24_ksplit_kernel<4, 4, 4, 3, false>, spmm24_ksplit_kernel<4, 4, 4, 3, true>}, 64, 64, 1, 0, 0.83, 3.16, 0.138},
-    {{spmm24_ksplit_kernel<8, 4, 4, 2, false>, spmm24_ksplit_kernel<8, 4, 4, 2, true>}, 128, 64, 1, 0, 0.17, 5.14, 0.197},
-    {{spmm24_tile_kernel<2, 2, false>, spmm24_tile_kernel<2, 2, true>}, 128, 128, 2, 2, 0.0, 4.2, 0.38},
-    {{spmm24_tile_kernel<2, 4, false>, spmm24_tile_kernel<2, 4, true>}, 128, 256, 1, 1, 0.0, 5.74, 0.524},
-    {{spmm24_tile_kernel<4, 4, false>, spmm24_tile_kernel<4, 4, true>}, 256, 256, 1, 1, 0.0, 8.08, 0.782},
+// The kernels of the tile sizes of kSpmmTile: fp32, bf16 results.
+typedef void (*spmm_kernel_t)(const SpmmArgs);
+static const spmm_kernel_t kSpmmKernels[kSpmmTiles][2] = {
+    {spmm24_ksplit_kernel<1, 1, 4, 4, false>, spmm24_ksplit_kernel<1, 1, 4, 4, true>},
+    {spmm24_ksplit_kernel<2, 2, 4, 4, false>, spmm24_ksplit_kernel<2, 2, 4, 4, true>},
+    {spmm24_ksplit_kernel<4, 4, 4, 3, false>, spmm24_ksplit_kernel<4, 4, 4, 3, true>},
+    {spmm24_ksplit_kernel<8, 4, 4, 2, false>, spmm24_ksplit_kernel<8, 4, 4, 2, true>},
+    {spmm24_tile_kernel<2, 2, false>, spmm24_tile_kernel<2, 2, true>},
+    {spmm24_tile_kernel<2, 4, false>, spmm24_tile_kernel<2, 4, true>},
+    {spmm24_tile_kernel<4, 4, false>, spmm24_tile_kernel<4, 4, true>},
 };
 
 }  // namespace tmask
@@ -666,28 +642,22 @@ extern "C" int tmask_spmm24(const void *vals, const void *idx, int64_t rows, int
     p.vals = vals; p.idx = idx; p.x = x; p.y = y;
     p.rows = (uint32_t)rows; p.cols = (uint32_t)cols; p.tokens = (uint32_t)tokens;
     p.ld_x = (uint32_t)ld_x; p.ld_y = (uint32_t)ld_y;
-    if ((uint64_t)((rows + 255) / 256) * (uint64_t)((tokens + 127) / 128) > 0x7FFFFFFFull)
+    if ((uint64_t)((rows + 255) / 256) * (uint64_t)((tokens + 127) / 128) > 0x7FFFFFFFull)    // 256 x 256 tiles always fit below that
         return fail(TMASK_ERR_SHAPE, "too many tiles");
     const uint64_t cus = (uint64_t)cu_count();
-    const SpmmVariant *best = nullptr;
-    double best_us = 0.0;
-    for (const SpmmVariant &v : kSpmmVariants) {
-        const uint64_t tiles = (uint64_t)((rows + v.rows - 1) / v.rows) * (uint64_t)((tokens + v.tokens - 1) / v.tokens);
-        const double us = v.estimate(tiles, (double)(cols / kSpKS), cus);
-        if (tiles <= 0x7FFFFFFFull && (!best || us < best_us)) {
-            best = &v;
-            best_us = us;
-        }
-    }
-    p.tiles_r = (uint32_t)((rows + best->rows - 1) / best->rows);
-    p.tiles_t = (uint32_t)((tokens + best->tokens - 1) / best->tokens);
+    const int choice = spmm_choose(rows, cols, tokens, cus);
+    if (choice < 0)
+        return fail(TMASK_ERR_SHAPE, "too many tiles");
+    const SpmmTile &tile = kSpmmTile[choice];
+    p.tiles_r = (uint32_t)((rows + tile.rows - 1) / tile.rows);
+    p.tiles_t = (uint32_t)((tokens + tile.tokens - 1) / tile.tokens);
     uint32_t grid = p.tiles_r * p.tiles_t;
-    if (best->persistent && grid > best->persistent * cus)
-        grid = (uint32_t)(best->persistent * cus) & ~7u;        // a multiple of the XCD count, which the tile numbering assumes
+    if (tile.persistent && grid > tile.persistent * cus)
+        grid = (uint32_t)(tile.persistent * cus) & ~7u;         // a multiple of the XCD count, which the tile numbering assumes
     hipStream_t stream = (hipStream_t)hip_stream;
     {
         ProfileScope prof(stream, true);
-        hipLaunchKernelGGL(best->kernel[out_dt == TMASK_BF16 ? 1 : 0], dim3(grid), dim3(256), 0, stream, p);
+        hipLaunchKernelGGL(kSpmmKernels[choice][out_dt == TMASK_BF16 ? 1 : 0], dim3(grid), dim3(kSpmmThreads), 0, stream, p);
     }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess)
