@@ -507,24 +507,33 @@ __global__ __launch_bounds__(256, RT * CT <= 4 ? 2 : 1) void spmm24_tile_kernel(
         wait_lds_reads();
     };
 
-    // Writes the tile; returns whether all of kStores store instructions were issued.
+    // Writes the tile; returns whether all of kStores store instructions were issued.  A store covers 64 contiguous bytes of
+    // each of sixteen tokens (32 of 32 tokens as the sums lie in the lanes: twice the requests for the same lines, and products
+    // with a short reduction are bound by what they write: fp32 8192 x 64, 8192 tokens 55 -> 50 us on 128 x 128 tiles, 62 ->
+    // 53 on 256 x 256; bf16 4096 x 1024, 8192 tokens 52 -> 50).  Instruction tiles that lie outside the matrix are skipped
+    // whole (1048576 x 64, 4 tokens: 38 -> 31 us).
     auto store_tile = [&](uint32_t j) -> bool {
         uint32_t row0, tok0;
         locate(j, row0, tok0);
         const bool whole = row0 + TR <= p.rows && tok0 + TT <= p.tokens;
         row0 += wr * RT * 32u;
-        tok0 += wc * CT * 32u + m;
+        tok0 += wc * CT * 32u;
+        // lane 16 g + n writes rows r .. of tokens n and n + 16 of each instruction tile, the four g side by side
+        const uint32_t lane_r = (OUT_BF16 ? 16u : 8u) * ((lane >> 4) & 1u) + (OUT_BF16 ? 8u : 4u) * a, lane_t = lane & 15u;
 #pragma unroll
         for (int ct = 0; ct < CT; ct++) {
-            const uint32_t tok = tok0 + (uint32_t)ct * 32u;
 #pragma unroll
             for (int rt = 0; rt < RT; rt++) {
+                if (row0 + (uint32_t)rt * 32u >= p.rows || tok0 + (uint32_t)ct * 32u >= p.tokens)
+                    continue;
                 take_sums(acc[rt][ct]);
+                const uint32_t r = row0 + (uint32_t)rt * 32u + lane_r, tok = tok0 + (uint32_t)ct * 32u + lane_t;
                 if constexpr (OUT_BF16) {
-                    // pairs of lanes l, l + 32 exchange quads so that each holds eight consecutive rows
+                    // lanes l, l + 32 exchange quads so that each holds eight consecutive rows of its token, then l, l + 16
+                    // so that the four lanes of a token hold its 32 rows
                     typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
                     typedef float f32x2 __attribute__((ext_vector_type(2)));
-                    uint32_t d[8];
+                    uint32_t d[8], e[2][4];
 #pragma unroll
                     for (int q = 0; q < 8; q++) {
                         union { bf16x2 h; uint32_t u; } cv;
@@ -532,23 +541,47 @@ __global__ __launch_bounds__(256, RT * CT <= 4 ? 2 : 1) void spmm24_tile_kernel(
                         d[q] = cv.u;
                     }
 #pragma unroll
-                    for (int q = 0; q < 2; q++) {
-                        const auto lo = __builtin_amdgcn_permlane32_swap(d[4 * q], d[4 * q + 2], false, false);
-                        const auto hi = __builtin_amdgcn_permlane32_swap(d[4 * q + 1], d[4 * q + 3], false, false);
-                        const uint32_t r = row0 + (uint32_t)rt * 32u + (uint32_t)q * 16u + a * 8u;
-                        unsigned char *dst = (unsigned char *)p.y + ((size_t)tok * p.ld_y + r) * 2u;
-                        if (whole || (tok < p.tokens && r + 8u <= p.rows))
-                            *(su32x4 *)dst = su32x4{lo[0], hi[0], lo[1], hi[1]};
-                        else if (tok < p.tokens && r + 4u <= p.rows)
-                            *(su32x2 *)dst = su32x2{lo[0], hi[0]};
+                    for (int q = 0; q < 2; q++)
+#pragma unroll
+                        for (int k = 0; k < 2; k++) {
+                            const auto x = __builtin_amdgcn_permlane32_swap(d[4 * q + k], d[4 * q + 2 + k], false, false);
+                            e[q][k] = x[0];
+                            e[q][2 + k] = x[1];
+                        }
+                    su32x4 v[2];
+#pragma unroll
+                    for (int k = 0; k < 4; k++) {
+                        const auto x = __builtin_amdgcn_permlane16_swap(e[0][k], e[1][k], false, false);
+                        v[0][k] = x[0];
+                        v[1][k] = x[1];
+                    }
+#pragma unroll
+                    for (uint32_t h = 0; h < 2; h++) {
+                        const uint32_t t = tok + 16u * h;
+                        unsigned char *dst = (unsigned char *)p.y + ((size_t)t * p.ld_y + r) * 2u;
+                        if (whole || (t < p.tokens && r + 8u <= p.rows))
+                            *(su32x4 *)dst = v[h];
+                        else if (t < p.tokens && r + 4u <= p.rows)
+                            *(su32x2 *)dst = su32x2{v[h].x, v[h].y};
                     }
                 } else {
+                    // lanes l, l + 16 exchange quads so that the four lanes of a token hold sixteen of its rows
 #pragma unroll
-                    for (int q = 0; q < 4; q++) {
-                        const uint32_t r = row0 + (uint32_t)rt * 32u + (uint32_t)q * 8u + a * 4u;
-                        if (whole || (tok < p.tokens && r + 4u <= p.rows))
-                            *(f32x4 *)((unsigned char *)p.y + ((size_t)tok * p.ld_y + r) * 4u) =
-                                f32x4{acc[rt][ct][4 * q], acc[rt][ct][4 * q + 1], acc[rt][ct][4 * q + 2], acc[rt][ct][4 * q + 3]};
+                    for (uint32_t q = 0; q < 2; q++) {
+                        su32x4 v[2];
+#pragma unroll
+                        for (int k = 0; k < 4; k++) {
+                            const auto x = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[rt][ct][8 * q + k]),
+                                                                            __float_as_uint(acc[rt][ct][8 * q + 4 + k]), false, false);
+                            v[0][k] = x[0];
+                            v[1][k] = x[1];
+                        }
+#pragma unroll
+                        for (uint32_t h = 0; h < 2; h++) {
+                            const uint32_t t = tok + 16u * h, rq = r + 16u * q;
+                            if (whole || (t < p.tokens && rq + 4u <= p.rows))
+                                *(su32x4 *)((unsigned char *)p.y + ((size_t)t * p.ld_y + rq) * 4u) = v[h];
+                        }
                     }
                 }
             }
