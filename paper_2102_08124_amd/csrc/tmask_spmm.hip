@@ -678,7 +678,7 @@ extern "C" int tmask_spmm24(const void *vals, const void *idx, int64_t rows, int
     if ((uint64_t)((rows + 255) / 256) * (uint64_t)((tokens + 127) / 128) > 0x7FFFFFFFull)    // 256 x 256 tiles always fit below that
         return fail(TMASK_ERR_SHAPE, "too many tiles");
     const uint64_t cus = (uint64_t)cu_count();
-    const int choice = spmm_choose(rows, cols, tokens, cus);
+    const int choice = spmm_choose(rows, cols, tokens, out_dt == TMASK_F32, cus);
     if (choice < 0)
         return fail(TMASK_ERR_SHAPE, "too many tiles");
     const SpmmTile &tile = kSpmmTile[choice];
