@@ -418,9 +418,12 @@ __device__ __forceinline__ void exact_costs(const uint32_t (&key)[M][CL], int (&
 // balance, the smoothed sum also how far away the balance is: blocks of N(0,1) entries left unbalanced, by emulation,
 // 2.5 % after 8 rounds at M = 8 and 6 % after 13 at M = 16, where 12 and 20 rounds on counts left 12 % and 14 %.
 // Schedules were settled by a search in emulation, the numbers of rounds by timing on the device (6 ... 10 and
-// 10 ... 18 are within 5 % of each other: more rounds, fewer searches).  Windows and
-// steps are multiples of the block's mean cost, and the prices start at 3/4 of what would make the row means equal,
-// which keeps heavy-tailed and row-scaled blocks as good.  All of it is fp32: the prices need no more, and every cost is a
+// 10 ... 18 are within 5 % of each other: more rounds, fewer searches).  Windows and steps are multiples of the block's
+// mean cost or, if that is less, of sqrt(2) times the mean difference of two entries of a column half a block apart, row
+// means taken off: blocks whose rows, or columns, resemble one another differ by a small part of their mean, which windows
+// of that size cannot tell apart (columns equal up to 1 %: excess left at 8:16 47 -> 2.4; 2048^2 fp32 1760 -> 300 us).  The
+// prices start at what makes the row means equal, or a quarter less where these differ no more than three times what
+// chance gives, which keeps heavy-tailed blocks as good.  All of it is fp32: the prices need no more, and every cost is a
 // float exactly (24 significant bits, as the weights have).  The prices are then rounded to integers and the choice
 // itself is taken on integer keys.
 //
@@ -493,12 +496,37 @@ __device__ __forceinline__ uint32_t exact_priced_start(const int (&cost)[M][CL],
         mean += sum;
     }
     mean = mean * (1.f / (M * M));
+    // how far the row means lie apart (their deviations go to pr), and, row means taken off, two entries of a column half a
+    // block apart
+    float row_dev = 0.f, spread = 0.f;
 #pragma unroll
     for (int i = 0; i < M; i++) {
-        pr[i] = kOffset + 0.75f * (mean - pr[i] * (1.f / M));
+        pr[i] = mean - pr[i] * (1.f / M);
+        row_dev += __builtin_fabsf(pr[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < H; i++) {
+        const float rows = pr[i] - pr[H + i];
+#pragma unroll
+        for (int c = 0; c < CL; c++)
+            spread += __builtin_fabsf((cf[i][c] - cf[H + i][c]) + rows);
+    }
+    if constexpr (G >= 2)
+        spread = quad_xor_sum<1>(spread);
+    if constexpr (G == 4)
+        spread = quad_xor_sum<2>(spread);
+    spread *= 2.f / (M * M);
+    // three times what chance makes of the row means of independent entries, against what they are
+    const float chance = 3.f * spread * (M == 16 ? 2.828427f : 2.f) * __builtin_amdgcn_rcpf(row_dev);      // sqrt(M / 2) M / M
+    const float part = 1.f - 0.25f * (chance < 1.f ? chance : 1.f);
+#pragma unroll
+    for (int i = 0; i < M; i++) {
+        pr[i] = kOffset + part * pr[i];
         vel[i] = 0.f;
     }
-    const float unit = mean > 1.f ? mean : 1.f;                 // blocks of zeros
+    float unit = 1.414214f * spread;
+    unit = unit < mean ? unit : mean;
+    unit = unit > 1.f ? unit : 1.f;                             // blocks of zeros, and of costs that rows and columns explain
     float slope = -(1.f / Sched::window) / unit, step = Sched::step * unit;
     float drift = 0.f;                                          // what K per row and round adds to every price
     float dvel = 0.f;

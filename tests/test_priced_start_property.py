@@ -37,8 +37,9 @@ def test_column_greedy_under_row_prices_is_cheapest_for_its_row_counts(M, K):
 
 
 def test_prices_that_follow_the_imbalance_reduce_it():
-    # the rounds the kernel runs: price += step * (count - K), step shrinking; the excess left never grows when the
-    # best round is kept, and on random blocks it falls well below the unpriced start's
+    # price += step * (count - K), step shrinking, as the column-per-lane kernel moves its prices (the smoothed
+    # rounds of the strip kernel are in test_price_rounds.py): the excess left never grows when the best round is kept, and on
+    # random blocks it falls well below the unpriced start's
     rng = np.random.default_rng(77)
     M, K = 8, 4
     before = after = 0
