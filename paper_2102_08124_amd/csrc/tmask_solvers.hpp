@@ -669,10 +669,12 @@ __device__ __forceinline__ uint32_t exact_priced_start(const int (&cost)[M][CL],
     return e2 >> 1;
 }
 
-// LDS of one wavefront's searches: labels and predecessors of the rows and columns of its 64 / M blocks.
+// LDS of one wavefront's searches: labels and predecessors of the rows and columns of its 64 / M blocks, the chain that each
+// row would take and the row it starts from, and the entries that the chains flip.
 struct SearchLds {
     int drow[64], dcol[64];
     uint32_t prow[64], pcol[64];
+    uint32_t chain[64], start[64], flip_row[64], flip_col[64];
 };
 
 // Augments until every row of the block has exactly K pruned entries (after at most M*M searches).  M lanes hold a
@@ -683,12 +685,20 @@ struct SearchLds {
 // through a pruned entry of a reached row) and a row step (lane j: the cheapest way into row j out of a column through an
 // unpruned entry); labels travel through LDS, which within a wavefront needs no barrier.  Labels only ever fall, and a
 // predecessor changes only when its label falls strictly: with exact integer sums and no negative cycle the
-// predecessor graph is then a forest, also among entries of equal cost.  The first reachable row that lacks pruned
-// entries takes its chain.
+// predecessor graph is then a forest, also among entries of equal cost.
+//
+// At convergence every predecessor edge is tight (label of the head = label of the tail + edge cost), so flipping along any
+// set of chains with no column in common keeps the pruning cheapest for its row counts.  The first reachable row that
+// lacks pruned entries takes its chain; at M = 16, when four or more rows have excess, as in blocks of tied values, every
+// such row does whose chain is still free, as long as that finds more than one.  (2048^2 8:16 with 50 % zeros 242 ->
+// 200 us, three levels 207 -> 172; at M = 8 the second walk costs more than it saves, 70 -> 75 us with 70 % zeros.)
 template <int M>
 __device__ __forceinline__ void exact_search(const int (&ccol)[M], const int (&crow)[M], uint32_t &xcol, uint32_t xrow,
                                              bool active, uint32_t K, SearchLds &lds)
 {
+    static_assert(M <= 16, "a chain's rows and columns share a word");
+    constexpr bool SEVERAL = M == 16;
+    bool several = true;
     const uint32_t lane = threadIdx.x & 63u, j = lane % M, base = lane - j;     // base: first lane of the block
     constexpr uint32_t kSeg = (uint32_t)((1ull << M) - 1ull);
     auto mine = [&](lanemask_t m) { return (uint32_t)(m >> base) & kSeg; };     // the block's bits of a ballot
@@ -702,6 +712,7 @@ __device__ __forceinline__ void exact_search(const int (&ccol)[M], const int (&c
         const lanemask_t excess = lm(cnt > K);
         if (excess == 0)
             break;
+        uint32_t over = mine(excess);
         int drow = cnt > K ? 0 : kInfDist;
         uint32_t prow = kNoPred;
         fence();
@@ -739,31 +750,94 @@ __device__ __forceinline__ void exact_search(const int (&ccol)[M], const int (&c
             if (lm(changed) == 0)
                 break;
         }
-        const uint32_t cand = mine(lm(cnt < K && drow < kReachable));
-        bool walking = mine(excess) != 0u && cand != 0u;
-        if (lm(walking) == 0)
+        const bool lacks = cnt < K && drow < kReachable;
+        uint32_t cand = mine(lm(lacks));
+        if (lm(cand != 0u) == 0)
             break;                      // cannot happen for 0 < K < M; guards against looping on corrupt state
-        const uint32_t target = walking ? (uint32_t)__builtin_ctz(cand) : 0u;
-        uint32_t r = target, src = kNoPred;
+        if (!SEVERAL || !several || lm(__builtin_popcount(over) >= 4) == 0) {
+            // the first reachable row takes its chain
+            const uint32_t target = cand != 0u ? (uint32_t)__builtin_ctz(cand) : 0u;
+            uint32_t r = target, src = kNoPred;
+            bool walking = cand != 0u;
 #pragma unroll 1
-        for (int step = 0; step <= M && lm(walking) != 0; step++) {
-            if (walking) {
-                const uint32_t c = lds.prow[base + r];
-                if (c == kNoPred) {
-                    src = r;                                     // the row with excess that the chain starts from
-                    walking = false;
-                } else {
-                    const uint32_t f = lds.pcol[base + c];       // (r, c) becomes pruned, (f, c) becomes unpruned
-                    if (j == c)
-                        xcol ^= (1u << r) | (1u << f);
-                    if (j == r || j == f)
-                        xrow ^= 1u << c;
-                    r = f;
+            for (int step = 0; step <= M && lm(walking) != 0; step++) {
+                if (walking) {
+                    const uint32_t c = lds.prow[base + r];
+                    if (c == kNoPred) {
+                        src = r;                                 // the row with excess that the chain starts from
+                        walking = false;
+                    } else {
+                        const uint32_t f = lds.pcol[base + c];   // (r, c) becomes pruned, (f, c) becomes unpruned
+                        if (j == c)
+                            xcol ^= (1u << r) | (1u << f);
+                        if (j == r || j == f)
+                            xrow ^= 1u << c;
+                        r = f;
+                    }
                 }
             }
+            if (src != kNoPred)
+                cnt += (j == target ? 1u : 0u) - (j == src ? 1u : 0u);
+        } else if constexpr (SEVERAL) {
+            // every reachable row walks its chain, a lane each ...
+            uint32_t r = j, chain = 0u, start = kNoPred;
+            bool walking = lacks;
+            lds.flip_row[lane] = 0u;
+            lds.flip_col[lane] = 0u;
+#pragma unroll 1
+            for (int step = 0; step <= M && lm(walking) != 0; step++) {
+                if (walking) {
+                    const uint32_t c = lds.prow[base + r];
+                    if (c == kNoPred) {
+                        start = r;
+                        walking = false;
+                    } else {
+                        chain |= 1u << r | 0x10000u << c;
+                        r = lds.pcol[base + c];
+                    }
+                }
+            }
+            lds.chain[lane] = chain;
+            lds.start[lane] = start;
+            fence();
+            // ... the lowest takes it, and so does each after it that shares no row or column with those taken and whose
+            // first row has excess left
+            uint32_t used = 0u, n = 0u;
+            bool taken = false;
+#pragma unroll 1
+            while (lm(cand != 0u) != 0) {
+                over = mine(lm(cnt > K));
+                const uint32_t t = cand != 0u ? (uint32_t)__builtin_ctz(cand) : 0u;
+                const uint32_t ch = lds.chain[base + t], s = lds.start[base + t];
+                if (cand != 0u && s < (uint32_t)M && (ch & used) == 0u && (over >> (s & 31u) & 1u)) {
+                    used |= ch;
+                    n++;
+                    taken = taken || j == t;
+                    cnt += (j == t ? 1u : 0u) - (j == s ? 1u : 0u);
+                }
+                cand &= cand - 1u;
+            }
+            several = lm(n > 1u) != 0;                           // else one at a time from now on
+            r = j;
+#pragma unroll 1
+            for (int step = 0; step <= M && lm(taken) != 0; step++) {
+                if (taken) {
+                    const uint32_t c = lds.prow[base + r];
+                    if (c == kNoPred) {
+                        taken = false;
+                    } else {
+                        const uint32_t f = lds.pcol[base + c];
+                        lds.flip_col[base + c] = 1u << r | 1u << f;      // no other chain has this column
+                        atomicXor(&lds.flip_row[base + r], 1u << c);
+                        atomicXor(&lds.flip_row[base + f], 1u << c);     // several chains may start from one row
+                        r = f;
+                    }
+                }
+            }
+            fence();
+            xcol ^= lds.flip_col[lane];
+            xrow ^= lds.flip_row[lane];
         }
-        if (src != kNoPred)
-            cnt += (j == target ? 1u : 0u) - (j == src ? 1u : 0u);
     }
 }
 

@@ -200,6 +200,27 @@ def test_exact_more_unbalanced_blocks_than_search_slots(N, M, dt, fmt):
 
 
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("N", [8, 4, 12])
+def test_exact_with_many_rows_out_of_balance(N, dt):
+    # blocks whose start leaves four or more rows with excess: a search then takes several chains at once; among them blocks
+    # of other kinds, which take one at a time in the same wavefront
+    M, rows, cols = 16, 3 * 16, 21 * 16
+    rng = np.random.default_rng(1710 + N)
+    base = np.abs(wl.gaussian_f32(rows, cols, seed=1711))
+    few = np.where(rng.random(base.shape) < 0.02, base * np.float32(1e4), base)
+    alike = np.repeat(np.abs(wl.gaussian_f32(rows, cols // M, seed=1712)), M, axis=1) + np.float32(0.001) * base
+    tied = wl.tie_heavy_f32(rows, cols, 1713, levels=2)
+    sparse = np.where(rng.random(base.shape) < 0.6, np.float32(0), base)
+    mixed = np.where((np.arange(cols) // M % 3 == 0)[None, :], tied, np.where((np.arange(cols) // M % 3 == 1)[None, :], base, few))
+    for w in (few, alike, tied, sparse, mixed):
+        w = w if dt == "f32" else wl.f32_to_bf16_bits(w)
+        (mask,), obj = run_masks(tm.tmask_exact, [w], N, M, tm.TMASK_MASK_U8)
+        _, oobj, opb = oracle.exact(w, N, M, per_block=True, threads=8)
+        _check_exact(w, mask, N, M, opb)
+        assert obj[0] == pytest.approx(oobj, rel=1e-5, abs=1e-30)
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
 @pytest.mark.parametrize("N,M", NM)
 def test_exact_structured_blocks(N, M, dt):
     """Blocks on which "every column prunes its lightest rows" is as lopsided as it gets (whole rows lighter than
