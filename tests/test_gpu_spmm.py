@@ -165,3 +165,21 @@ def test_every_tile_size_at_its_edges(rows, cols, tokens, out):
     want = oracle.spmm(vals, idx, rows, cols, 2, 4, x_bits[sample])
     bound = _bound(vals, idx, rows, cols, x_bits[sample]) + (2.0 ** -8 * np.abs(want) if out == "bf16" else 0.0)
     assert (np.abs(got - want) <= bound).all()
+
+
+# Long, ragged reductions for each tile that splits them (33 and more steps: every wavefront goes around its ring and both
+# index buffers several times, and the last unit is cut short), the combinations of tile and result type that the shapes
+# above leave out, and thin products on the large tiles.  test_spmm_choice.py checks on the CPU that they still do.
+LONG_AND_THIN = [
+    (20, 2112, 16, "f32"), (36, 8256, 9, "bf16"), (1020, 4160, 16, "bf16"),                       # 16 x 16
+    (260, 4160, 499, "f32"), (516, 4096, 300, "bf16"),                                            # 32 x 32
+    (772, 2112, 700, "f32"), (1028, 4160, 300, "bf16"),                                           # 64 x 64
+    (1028, 4096, 1003, "f32"), (1028, 4160, 1100, "f32"), (1284, 2112, 1003, "bf16"),             # 128 x 64
+    (2052, 2112, 2003, "f32"), (2052, 1088, 3003, "bf16"),                                        # 128 x 256
+    (1028, 4160, 8200, "f32"), (4100, 1088, 8195, "f32"),                                         # 256 x 256
+    (4100, 640, 8195, "f32"), (20, 64, 200003, "bf16"), (100, 64, 70001, "f32"), (200004, 64, 5, "f32")]   # 128 x 128
+
+
+@pytest.mark.parametrize("rows,cols,tokens,out", LONG_AND_THIN)
+def test_long_reductions_and_thin_products(rows, cols, tokens, out):
+    test_every_tile_size_at_its_edges(rows, cols, tokens, out)

@@ -74,3 +74,28 @@ def test_the_choice_is_near_the_fastest_tile(choice, rows, cols, tokens, out, us
     tiles = [(16, 16), (32, 32), (64, 64), (128, 64), (128, 128), (128, 256), (256, 256)]
     picked = us[tiles.index(choice(rows, cols, tokens, out == "f32")[:2])]
     assert picked <= 1.15 * min(us)        # the fit's largest miss is 13 %
+
+
+def test_the_products_of_the_gpu_tests_cover_every_tile(choice):
+    """Which tile the shapes in test_gpu_spmm.py take: each one with both result types, each that splits the reduction with
+    one that takes a wavefront through both of its index buffers and around its ring again and ends within a unit, each
+    shared one with whole and partial tiles in one launch, the persistent ones with several tiles to a workgroup."""
+    pytest.importorskip("torch")
+    from tests import test_gpu_spmm as gpu
+    edges = gpu.test_every_tile_size_at_its_edges.pytestmark[0].args[1]
+    seen = {}
+    for rows, cols, tokens, out in list(edges) + gpu.LONG_AND_THIN:
+        tile = choice(rows, cols, tokens, out == "f32")
+        seen.setdefault((tile[:2], out), []).append((rows, cols, tokens, tile[2]))
+    for size in ((16, 16), (32, 32), (64, 64), (128, 64), (128, 128), (128, 256), (256, 256)):
+        for out in ("f32", "bf16"):
+            shapes = seen[size, out]
+            assert any(r % size[0] and t % size[1] for r, c, t, p in shapes), (size, out)
+            tiles = [-(-r // size[0]) * -(-t // size[1]) for r, c, t, p in shapes]
+            if shapes[0][3] == 0:
+                # a unit is four steps of 64; four wavefronts deal them out, so nine give the first one three
+                assert any(c > 8 * 256 for r, c, t, p in shapes), (size, out)
+            elif size != (128, 256):                                  # never chosen for more tiles than compute units
+                assert max(tiles) > shapes[0][3] * CUS, (size, out)
+        if shapes[0][3] == 0:
+            assert any(c > 8 * 256 and c % 256 for o in ("f32", "bf16") for r, c, t, p in seen[size, o]), size
