@@ -5,8 +5,9 @@
 // collected (by rank, deterministic), their costs and starts go to LDS, and every wavefront takes 64 / M of them at a
 // time, M lanes to a block: a step of a search is then a few dozen instructions instead of the hundreds it takes where a
 // lane holds four columns (with those, after a sort of the blocks by their excess, half of the kernel's time was one
-// wavefront of each workgroup searching).  4096 x 4096 fp32, whole calls: 4:8 100 -> 54 us, 8:16 196 -> 95 us, of which the
-// searches are 8 and 15, the load, the last choice, mask and objective 30.
+// wavefront of each workgroup searching).  4096 x 4096 fp32, whole calls: 4:8 100 -> 53 us, 8:16 196 -> 90 us.  By copies
+// that leave them out, the searches take 13 and 25 of that, the price rounds 14 and 35, and the load, the last choice, mask,
+// objective and its second stage 26 and 30.
 #pragma once
 #include <type_traits>
 
@@ -39,7 +40,9 @@ __device__ __forceinline__ void unpack_row(const u32x4 &r, uint32_t (&a)[C])
 // A bf16 lane takes half a strip, four columns, as an fp32 lane does (the host launches twice the workgroups): eight
 // columns of a block and the prices' state do not fit a lane's registers.
 constexpr bool exact_half_strips(int dt, int M) { return dt == kBF16 && M >= 8; }
-constexpr int exact_workgroups_per_cu(int dt, int M) { return M == 16 ? 3 : 5; }     // by registers: 168 and 102
+// Workgroups per compute unit, which the registers are held to: 96 at M = 8 (the bf16 and any-N forms keep up to five values
+// of a lane in scratch memory), 168 at M = 16 (nine to sixteen values in all forms, 40 - 68 bytes).
+constexpr int exact_workgroups_per_cu(int dt, int M) { return M == 16 ? 3 : 5; }
 
 // GENERAL: any N (K = args.K pruned per line); otherwise N = M/2.
 template <int DT, int M, int FMT, bool GENERAL = false>

@@ -241,7 +241,7 @@ __global__ __launch_bounds__(kThreads) void exact24_kernel(const BatchArgs args)
 // 16.  Such a call is bound by its launches (each 2.3 us of host time, 1.2 more for the large arguments) and by the few
 // microseconds that a kernel lasts at least.  Back to back / in a graph, 1 ... 32 matrices of 1024 strips: fp32 8.2 - 9.3 / 4.5 -
 // 5.4 -> 4.9 - 5.3 / 3.3 - 3.9 us, bf16 8.2 - 9.2 / 5.2 - 6.2 -> 4.8 - 5.4 / 4.6 - 5.3.  Two strips per thread are as slow as two
-// launches in a graph (fp32 5.3 against 4.8 us, bf16 8.4 against 5.3): a compute unit alone moves 50 GB/s.
+// launches in a graph (fp32 5.3 against 4.8 us, bf16 8.4 against 5.3): one compute unit then moves all of it in two goes.
 constexpr int kWholeThreads = 1024, kWholeMats = 32;
 
 struct WholeArgs {

@@ -327,12 +327,13 @@ __global__ __launch_bounds__(64 * W, 1) void spmm24_ksplit_kernel(const SpmmArgs
 // instruction.  Positions are assigned to k as in the split kernel: lane a's values of a half step (32 k) are the 16 bytes
 // at 16 a of the row's 32, its x values the 16 bytes at 16 a and 32 + 16 a of the token's 64.
 //
-// What bounds it is what a compute unit can pull from the caches (about 10 TB/s over the chip, whatever the tile), so the
-// tile is as large as the registers allow: 256 x 256, with 256 accumulator registers per lane, moves 50 KB per 2^22
-// products, a third of what the 256 x 128 tiles of a kernel with eight wavefronts moved that staged them through
-// registers (W 4096 x 1024, 8192 tokens: 77 -> 55 us, 1.25 PFLOP/s dense equivalent; matrix instructions and LDS reads
-// alone, without the copies, take two thirds of that).  Steps of 64 k arrive in a ring of three LDS images by direct
-// copies, two steps ahead.  The fragments of a half step are read while the half before it is multiplied.  One barrier per
+// What bounds a step is the arrival of its tiles: a 256 x 256 one needs 50 KB, which one compute unit by itself has in 0.63 us
+// (81 GB/s) and each of 256 at work in 1.08 us (47 GB/s, 12 TB/s over the chip; 128 x 128: 0.31 and 0.43 us, 15 TB/s), while
+// its matrix instructions take 0.43.  So the tile is as large as the registers allow: 256 x 256, with 256 accumulator
+// registers per lane, moves 50 KB per 2^22 products, a third of what the 256 x 128 tiles of a kernel with eight wavefronts
+// moved that staged them through registers.  A tile costs 7 to 8 us besides its steps, with bf16 results: the first copies,
+// and the results, which leave while nothing is multiplied (W 4096 x 1024, 8192 tokens: 77 -> 50 us, two rounds of sixteen
+// steps).  Steps of 64 k arrive in a ring of three LDS images by direct copies, two steps ahead.  The fragments of a half step are read while the half before it is multiplied.  One barrier per
 // step, between its halves: when all wavefronts have read the second half of step g its image is overwritten by step
 // g + 3, and step g + 1, whose copies every wavefront has waited for, may be read.  Workgroups are persistent and treat
 // the steps of all their tiles as one stream, so the copies of a tile's first steps are in flight while the one before
