@@ -392,16 +392,15 @@ __device__ __forceinline__ void exact_costs(const uint32_t (&key)[M][CL], int (&
         kmax = o > kmax ? o : kmax;
     }
     const uint32_t emax = (kmax >> 23) ? (kmax >> 23) : 1u;
+    // |w| 2^k for the k that brings the block's maximum to [2^(S-1), 2^S): exact, then truncated.  Infinities and NaN count as
+    // the magnitudes whose bits follow the largest finite one's; a block that has any takes its exponents one lower.
+    const uint32_t lower = emax == 255u ? 0x800000u : 0u;
+    const int shift = S + 126 - (int)emax + (emax == 255u ? 1 : 0);
 #pragma unroll
     for (int i = 0; i < M; i++)
 #pragma unroll
-        for (int c = 0; c < CL; c++) {
-            const uint32_t e = key[i][c] >> 23;
-            const uint32_t mant = (key[i][c] & 0x7FFFFFu) | (e ? 0x800000u : 0u);
-            const uint32_t sh = emax - (e ? e : 1u);
-            cost[i][c] = sh < 32u ? (int)((mant << (S - 24)) >> sh) : 0;
-        }
-
+        for (int c = 0; c < CL; c++)
+            cost[i][c] = (int)__builtin_ldexpf(__uint_as_float(__builtin_elementwise_sub_sat(key[i][c], lower)), shift);
 }
 
 // Start with row prices: column c prunes the K rows with the smallest cost + price (ties: by position, see below).

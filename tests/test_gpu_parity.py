@@ -199,6 +199,28 @@ def test_exact_more_unbalanced_blocks_than_search_slots(N, M, dt, fmt):
         assert obj[0] == pytest.approx(oobj, rel=1e-5)
 
 
+@pytest.mark.parametrize("N,M", [(4, 8), (3, 8), (8, 16)])
+def test_exact_at_the_ends_of_the_exponent_range(N, M):
+    # costs are the magnitudes scaled by a power of two per block: blocks of denormals, of denormals and the smallest normal
+    # numbers, up to the largest finite number, and with both ends in one block; relative to each block's own optimum
+    base = np.abs(wl.gaussian_f32(M, 5 * M, seed=1720 + M))
+    base /= base.max()
+    scale = np.repeat(np.array([2.0 ** -127, 2.0 ** -125, 1.0, 2.0 ** 127, 2.0 ** 120]), M)
+    w = (base.astype(np.float64) * scale).astype(np.float32)
+    w[:, 2 * M:3 * M:3] = np.float32(2.0 ** -149)
+    w[0, 3 * M] = np.finfo(np.float32).max
+    (mask,), _ = run_masks(tm.tmask_exact, [w], N, M, tm.TMASK_MASK_U8)
+    b = refs.to_blocks(mask, M)
+    assert np.all(b.sum(axis=3) == N) and np.all(b.sum(axis=2) == N)
+    _, _, opb = oracle.exact(w, N, M, per_block=True)
+    np.testing.assert_allclose(refs.per_block_sums(refs.magnitudes(w).astype(np.float64) * mask, M), opb, rtol=1e-5, atol=0)
+    # infinities and NaN: the mask is still valid
+    w[1, ::7], w[2, ::11] = np.inf, np.nan
+    (mask,), _ = run_masks(tm.tmask_exact, [w], N, M, tm.TMASK_MASK_U8)
+    b = refs.to_blocks(mask, M)
+    assert np.all(b.sum(axis=3) == N) and np.all(b.sum(axis=2) == N)
+
+
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
 @pytest.mark.parametrize("N", [8, 4, 12])
 def test_exact_with_many_rows_out_of_balance(N, dt):
