@@ -5,9 +5,9 @@
 // collected (by rank, deterministic), their costs and starts go to LDS, and every wavefront takes 64 / M of them at a
 // time, M lanes to a block: a step of a search is then a few dozen instructions instead of the hundreds it takes where a
 // lane holds four columns (with those, after a sort of the blocks by their excess, half of the kernel's time was one
-// wavefront of each workgroup searching).  4096 x 4096 fp32, whole calls: 4:8 100 -> 53 us, 8:16 196 -> 90 us.  By copies
-// that leave them out, the searches take 13 and 25 of that, the price rounds 14 and 35, and the load, the last choice, mask,
-// objective and its second stage 26 and 30.
+// wavefront of each workgroup searching).  4096 x 4096 fp32, whole calls: 4:8 100 -> 49 us, 8:16 196 -> 89 us.  By copies
+// that leave them out, the searches take 11 and 25 of that, the price rounds 14 and 37, and the load, the last choice, mask,
+// objective and its second stage 24 and 27.
 #pragma once
 #include <type_traits>
 
