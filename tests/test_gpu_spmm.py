@@ -139,12 +139,12 @@ def test_spmm_argument_errors():
 
 
 @pytest.mark.parametrize("rows,cols,tokens,out", [
-    (20, 64, 1, "f32"), (20, 1088, 17, "bf16"), (132, 320, 33, "f32"),                # one unit, one step in the last unit
-    (1020, 576, 129, "bf16"), (4092, 1088, 41, "f32"), (2044, 192, 127, "bf16"),
+    (20, 64, 1, "f32"), (20, 1088, 17, "bf16"), (132, 320, 33, "f32"),                # 16 x 16: one unit, one step in the last unit
+    (1020, 576, 129, "bf16"), (4092, 1088, 41, "f32"), (2044, 192, 127, "bf16"),      # 32 x 32
     (1028, 1088, 499, "f32"), (1100, 64, 640, "bf16"), (4092, 1088, 509, "bf16"),     # 64 x 64 and 128 x 64 tiles
     (3076, 128, 1001, "f32"), (4092, 64, 4100, "bf16"), (4100, 192, 4090, "f32"), (4100, 960, 4097, "bf16"),   # 128 x 128
-    (4092, 1024, 2003, "bf16"), (2052, 192, 4099, "f32"), (4100, 64, 2040, "bf16"),   # 128 x 256, 256 x 256
-    (4100, 256, 5000, "f32"), (4092, 320, 8190, "bf16"), (4100, 640, 8195, "bf16")])  # several tiles per workgroup
+    (4092, 1024, 2003, "bf16"), (2052, 192, 4099, "f32"), (4100, 64, 2040, "bf16"),   # 128 x 256, and 128 x 128 again
+    (4100, 256, 5000, "f32"), (4092, 320, 8190, "bf16"), (4100, 640, 8195, "bf16")])  # 128 x 128 and 256 x 256, several per workgroup
 def test_every_tile_size_at_its_edges(rows, cols, tokens, out):
     """Shapes that take each of the tile sizes, with rows, tokens and the reduction off their multiples: sampled tokens
     against the oracle's float64 product, nothing written outside y."""
