@@ -46,6 +46,7 @@ struct SpmmArgs {
     uint32_t rows, cols, tokens;
     uint32_t ld_x, ld_y;
     uint32_t tiles_r, tiles_t;
+    uint32_t lines;       // the shared tiles write whole lines of y, with streaming stores
 };
 
 // y[tok][r .. r+3] (fp32 -> bf16 rounds to nearest even, by the hardware's packed conversion)
@@ -513,78 +514,105 @@ __global__ __launch_bounds__(256, RT * CT <= 4 ? 2 : 1) void spmm24_tile_kernel(
     // with a short reduction are bound by what they write: fp32 8192 x 64, 8192 tokens 55 -> 50 us on 128 x 128 tiles, 62 ->
     // 53 on 256 x 256; bf16 4096 x 1024, 8192 tokens 52 -> 50).  Instruction tiles that lie outside the matrix are skipped
     // whole (1048576 x 64, 4 tokens: 38 -> 31 us).
+    // With p.lines it covers whole lines of 128 bytes of eight tokens, and the stores are streaming ones: as plain stores the
+    // results push out of L2 the panels that the next tiles read (8192 tokens, three / four rotating sets of buffers, us: 4096 x
+    // 1024 bf16 52 -> 48 / 57.5 -> 50, fp32 64 -> 55 / 68 -> 59; 1024 x 4096 fp32 63 -> 49; 1024 x 256 bf16 10.0 -> 8.1; one set of
+    // buffers, which stays in the memory-side cache: 4096 x 1024 bf16 50.3 -> 50.5).  Streaming stores of parts of lines lose
+    // (fp32 8192 x 64 54 -> 78), which is where the line lies on the host.
     auto store_tile = [&](uint32_t j) -> bool {
         uint32_t row0, tok0;
         locate(j, row0, tok0);
         const bool whole = row0 + TR <= p.rows && tok0 + TT <= p.tokens;
         row0 += wr * RT * 32u;
         tok0 += wc * CT * 32u;
-        // lane 16 g + n writes rows r .. of tokens n and n + 16 of each instruction tile, the four g side by side
-        const uint32_t lane_r = (OUT_BF16 ? 16u : 8u) * ((lane >> 4) & 1u) + (OUT_BF16 ? 8u : 4u) * a, lane_t = lane & 15u;
+        constexpr uint32_t kPiece = OUT_BF16 ? 8u : 4u;         // results of a lane's 16 bytes
+        auto put = [&](uint32_t tok, uint32_t r, su32x4 v, auto streamed) {
+            unsigned char *dst = (unsigned char *)p.y + ((size_t)tok * p.ld_y + r) * (16u / kPiece);
+            if (whole || (tok < p.tokens && r + kPiece <= p.rows)) {
+                if constexpr (decltype(streamed)::value)
+                    __builtin_nontemporal_store(v, (su32x4 *)dst);
+                else
+                    *(su32x4 *)dst = v;
+            } else if (OUT_BF16 && tok < p.tokens && r + 4u <= p.rows) {
+                *(su32x2 *)dst = su32x2{v.x, v.y};
+            }
+        };
+        // Lane 16 g + n holds 16 bytes of token tok + n, the four g side by side: v0 of the 64 bytes at r, v1 of the 64 after.
+        // Lines: lanes n < 8 keep v0 and take the v0 of token n + 8 for the second store, lanes n >= 8 the same with v1.
+        const uint32_t n = lane & 15u, lane_r = kPiece * (2u * ((lane >> 4) & 1u) + a);
+        auto put_pair = [&](uint32_t tok, uint32_t r, su32x4 v0, su32x4 v1) {
+            constexpr uint32_t kNext = 4u * kPiece;
+            if (p.lines) {
+                const bool upper = n >= 8u;
+                su32x4 s0, s1;
+#pragma unroll
+                for (int k = 0; k < 4; k++) {
+                    const uint32_t got = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(upper ? v0[k] : v1[k]), 0x128, 0xF, 0xF, false);   // row_ror:8
+                    s0[k] = upper ? got : v0[k];
+                    s1[k] = upper ? v1[k] : got;
+                }
+                const uint32_t t = tok + (n & 7u), rr = r + (upper ? kNext : 0u);
+                put(t, rr, s0, std::true_type{});
+                put(t + 8u, rr, s1, std::true_type{});
+            } else {
+                put(tok + n, r, v0, std::false_type{});
+                put(tok + n, r + kNext, v1, std::false_type{});
+            }
+        };
+        constexpr int kPair = OUT_BF16 ? 2 : 1;                 // instruction tiles to a line
 #pragma unroll
         for (int ct = 0; ct < CT; ct++) {
 #pragma unroll
-            for (int rt = 0; rt < RT; rt++) {
+            for (int rt = 0; rt < RT; rt += kPair) {
                 if (row0 + (uint32_t)rt * 32u >= p.rows || tok0 + (uint32_t)ct * 32u >= p.tokens)
                     continue;
-                take_sums(acc[rt][ct]);
-                const uint32_t r = row0 + (uint32_t)rt * 32u + lane_r, tok = tok0 + (uint32_t)ct * 32u + lane_t;
+                const uint32_t r = row0 + (uint32_t)rt * 32u + lane_r, tok = tok0 + (uint32_t)ct * 32u;
+                su32x4 v[2][2];                                 // of the line's first and second 64 bytes, tokens n and n + 16
                 if constexpr (OUT_BF16) {
-                    // lanes l, l + 32 exchange quads so that each holds eight consecutive rows of its token, then l, l + 16
-                    // so that the four lanes of a token hold its 32 rows
-                    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-                    typedef float f32x2 __attribute__((ext_vector_type(2)));
-                    uint32_t d[8], e[2][4];
 #pragma unroll
-                    for (int q = 0; q < 8; q++) {
-                        union { bf16x2 h; uint32_t u; } cv;
-                        cv.h = __builtin_convertvector(f32x2{acc[rt][ct][2 * q], acc[rt][ct][2 * q + 1]}, bf16x2);
-                        d[q] = cv.u;
-                    }
+                    for (int z = 0; z < 2; z++) {
+                        take_sums(acc[rt + z][ct]);
+                        // lanes l, l + 32 exchange quads so that each holds eight consecutive rows of its token, then l, l + 16
+                        // so that the four lanes of a token hold its 32 rows
+                        typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+                        typedef float f32x2 __attribute__((ext_vector_type(2)));
+                        uint32_t d[8], e[2][4];
 #pragma unroll
-                    for (int q = 0; q < 2; q++)
-#pragma unroll
-                        for (int k = 0; k < 2; k++) {
-                            const auto x = __builtin_amdgcn_permlane32_swap(d[4 * q + k], d[4 * q + 2 + k], false, false);
-                            e[q][k] = x[0];
-                            e[q][2 + k] = x[1];
+                        for (int q = 0; q < 8; q++) {
+                            union { bf16x2 h; uint32_t u; } cv;
+                            cv.h = __builtin_convertvector(f32x2{acc[rt + z][ct][2 * q], acc[rt + z][ct][2 * q + 1]}, bf16x2);
+                            d[q] = cv.u;
                         }
-                    su32x4 v[2];
 #pragma unroll
-                    for (int k = 0; k < 4; k++) {
-                        const auto x = __builtin_amdgcn_permlane16_swap(e[0][k], e[1][k], false, false);
-                        v[0][k] = x[0];
-                        v[1][k] = x[1];
-                    }
+                        for (int q = 0; q < 2; q++)
 #pragma unroll
-                    for (uint32_t h = 0; h < 2; h++) {
-                        const uint32_t t = tok + 16u * h;
-                        unsigned char *dst = (unsigned char *)p.y + ((size_t)t * p.ld_y + r) * 2u;
-                        if (whole || (t < p.tokens && r + 8u <= p.rows))
-                            *(su32x4 *)dst = v[h];
-                        else if (t < p.tokens && r + 4u <= p.rows)
-                            *(su32x2 *)dst = su32x2{v[h].x, v[h].y};
+                            for (int k = 0; k < 2; k++) {
+                                const auto x = __builtin_amdgcn_permlane32_swap(d[4 * q + k], d[4 * q + 2 + k], false, false);
+                                e[q][k] = x[0];
+                                e[q][2 + k] = x[1];
+                            }
+#pragma unroll
+                        for (int k = 0; k < 4; k++) {
+                            const auto x = __builtin_amdgcn_permlane16_swap(e[0][k], e[1][k], false, false);
+                            v[z][0][k] = x[0];
+                            v[z][1][k] = x[1];
+                        }
                     }
                 } else {
+                    take_sums(acc[rt][ct]);
                     // lanes l, l + 16 exchange quads so that the four lanes of a token hold sixteen of its rows
 #pragma unroll
-                    for (uint32_t q = 0; q < 2; q++) {
-                        su32x4 v[2];
+                    for (uint32_t q = 0; q < 2; q++)
 #pragma unroll
                         for (int k = 0; k < 4; k++) {
                             const auto x = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[rt][ct][8 * q + k]),
                                                                             __float_as_uint(acc[rt][ct][8 * q + 4 + k]), false, false);
-                            v[0][k] = x[0];
-                            v[1][k] = x[1];
+                            v[q][0][k] = x[0];
+                            v[q][1][k] = x[1];
                         }
-#pragma unroll
-                        for (uint32_t h = 0; h < 2; h++) {
-                            const uint32_t t = tok + 16u * h, rq = r + 16u * q;
-                            if (whole || (t < p.tokens && rq + 4u <= p.rows))
-                                *(su32x4 *)((unsigned char *)p.y + ((size_t)t * p.ld_y + rq) * 4u) = v[h];
-                        }
-                    }
                 }
+                put_pair(tok, r, v[0][0], v[1][0]);
+                put_pair(tok + 16u, r, v[0][1], v[1][1]);
             }
         }
         return whole;
@@ -688,6 +716,11 @@ extern "C" int tmask_spmm24(const void *vals, const void *idx, int64_t rows, int
     uint32_t grid = p.tiles_r * p.tiles_t;
     if (tile.persistent && grid > tile.persistent * cus)
         grid = (uint32_t)(tile.persistent * cus) & ~7u;         // a multiple of the XCD count, which the tile numbering assumes
+    // Whole lines by streaming stores where y and its pitch are multiples of 64 bytes and a token's results fill a line: at other
+    // pitches lines are cut, and the streaming stores lose (512 columns, 8192 tokens, plain / streaming us: fp32 1000 rows 15 /
+    // 21, 1004 15.0 / 16.5, 1032 18.4 / 23.0, 1040 (64 bytes) 19.0 / 18.0, 1120 (128) 19.8 / 18.0; bf16 1032 16.1 / 16.6,
+    // 1040 (32) 16.2 / 16.1, 1056 (64) 16.5 / 15.7, 1088 (128) 17.0 / 15.8; 2052 22.4 / 23.8).
+    p.lines = (((uintptr_t)y | (uintptr_t)(ld_y * ysz)) & 63) == 0 && rows * ysz >= 128;
     hipStream_t stream = (hipStream_t)hip_stream;
     {
         ProfileScope prof(stream, true);

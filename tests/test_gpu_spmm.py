@@ -183,3 +183,35 @@ LONG_AND_THIN = [
 @pytest.mark.parametrize("rows,cols,tokens,out", LONG_AND_THIN)
 def test_long_reductions_and_thin_products(rows, cols, tokens, out):
     test_every_tile_size_at_its_edges(rows, cols, tokens, out)
+
+
+@pytest.mark.parametrize("out,step", [("f32", 16), ("bf16", 32)])
+@pytest.mark.parametrize("rows,cols,tokens", [
+    (2052, 192, 4099), (4100, 64, 2040), (36, 64, 70001),      # 128 x 128 (thin: one instruction tile and a part of one)
+    (2052, 1088, 3003), (4100, 640, 8195)])                    # 128 x 256, 256 x 256
+def test_results_as_whole_lines(rows, cols, tokens, out, step):
+    """Where y and its pitch are multiples of 64 bytes the shared tiles write whole lines of 128, elsewhere (a base 16 bytes off,
+    a pitch of 64 n + 16 bytes) runs of 64: the same bits either way, and nothing outside y.  step: results in 64 bytes."""
+    w_bits = wl.f32_to_bf16_bits(wl.gaussian_f32(rows, cols, seed=6500 + rows, std=0.05))
+    vals, idx, _, _ = oracle.apply_pack(w_bits, oracle.approx(w_bits, 2, 4, threads=8)[0], 2, 4)
+    vd, id_ = _bf16_dev(vals), torch.from_numpy(idx).cuda()
+    x_bits = wl.f32_to_bf16_bits(wl.gaussian_f32(tokens, cols, seed=6501 + tokens))
+    x = to_dev(x_bits)
+    dtype = torch.float32 if out == "f32" else torch.bfloat16
+    unit = 4 if out == "f32" else 8                            # results in 16 bytes
+    got = []
+    for off, ld in ((0, -(-rows // step) * step + step), (unit, -(-rows // step) * step + step), (0, -(-rows // step) * step + unit)):
+        flat = torch.full(((tokens + 2) * ld + 256,), -7.0, dtype=dtype, device="cuda")
+        y = flat[off:off + tokens * ld].view(tokens, ld)[:, :rows]
+        assert (y.data_ptr() % 64 == 0) == (off == 0)
+        tm.tmask_spmm24(vd, id_, rows, cols, x, y)
+        torch.cuda.synchronize()
+        got.append(y.clone())
+        y.fill_(-7.0)
+        assert bool((flat == -7.0).all())
+    assert torch.equal(got[0], got[1]) and torch.equal(got[0], got[2])
+    sample = np.unique(np.concatenate([np.arange(33), np.arange(tokens - 33, tokens), np.arange(0, tokens, 61)]))
+    want = oracle.spmm(vals, idx, rows, cols, 2, 4, x_bits[sample])
+    bound = _bound(vals, idx, rows, cols, x_bits[sample]) + (2.0 ** -8 * np.abs(want) if out == "bf16" else 0.0)
+    have = got[0][torch.from_numpy(sample).cuda()].float().cpu().numpy().astype(np.float64)
+    assert (np.abs(have - want) <= bound).all()
