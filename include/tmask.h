@@ -19,11 +19,13 @@
  *   is DEVICE memory owned by the caller; descriptor arrays (`tmask_mat*`, `tmask_pack_desc*`, `tmask_fused_desc*`
  *   and the other `*_desc` types) are HOST memory read before the call returns.  Work is enqueued on `hip_stream` (a hipStream_t,
  *   NULL = default stream); the library never synchronises, allocates or frees device memory, and
- *   holds no state between calls (two documented exceptions: the one-shot events of tmask_profile_next, which are
- *   thread-local, and the static scratch array of tmask_approx_noalloc).  Outputs are valid once the stream has
+ *   holds no state between calls (documented exceptions: the one-shot events of tmask_profile_next, which are
+ *   thread-local, the static scratch array of tmask_approx_noalloc, and a counter that numbers launches).  Outputs are valid once the stream has
  *   been synchronised.
  *   The workspace (at least tmask_workspace_bytes(), 256-byte aligned) is scratch for the duration
- *   of the enqueued work; calls that overlap on different streams need different workspaces.
+ *   of the enqueued work; calls that overlap on different streams need different workspaces
+ *   (calls that share one all the same leave objectives and scores undefined: NaN if a workgroup waits for a partial
+ *   result that another call has overwritten, for some seconds at the most).  Its contents before a call do not matter.
  *
  * Layout requirements (checked; violations return TMASK_ERR_SHAPE / TMASK_ERR_ALIGN)
  *   rows and cols multiples of M (the paper's only requirement: Sec. 4 speaks of the M x M blocks of a weight

@@ -45,8 +45,11 @@ struct CwArgs {
     CwMat m[kMaxCwBatch];
     uint32_t n, K, N, partial0;
     void *partials;
+    Tags tags;
+    double *objective[kMaxCwBatch];
+    ScorePartial *score;
 };
-static_assert(sizeof(CwArgs) <= 16384, "descriptor table is sized to stay a small kernel argument");
+static_assert(sizeof(CwArgs) <= 16384 + 2048, "descriptor table is sized to stay a small kernel argument");
 
 __device__ __forceinline__ int cw_find(const CwArgs &a, uint32_t wg)
 {
@@ -59,6 +62,13 @@ __device__ __forceinline__ int cw_find(const CwArgs &a, uint32_t wg)
             hi = mid - 1;
     }
     return lo;
+}
+
+// The objective of a mask kernel's workgroup; md: matrix number k of the launch.
+template <bool EARLY>
+__device__ __forceinline__ Handover cw_objective(const CwArgs &args, const CwMat &md, int k)
+{
+    return handover<8, 2, EARLY>(args.partials, args.tags, args.partial0 + blockIdx.x, blockIdx.x - md.wg0, md.n_wg, args.objective[k]);
 }
 
 template <int DT>
@@ -346,7 +356,9 @@ __global__ __launch_bounds__(kCwThreads, M == 32 ? 4 : 1) void cw_mask_kernel(co
 {
     constexpr int NB = 64 / M;
     __shared__ uint32_t T[NB][M][M + 1];
-    const CwMat md = args.m[cw_find(args, blockIdx.x)];
+    const int which = cw_find(args, blockIdx.x);
+    const CwMat md = args.m[which];
+    const Handover out = cw_objective<false>(args, md, which);     // registers are short
     const uint32_t lane = threadIdx.x, blk = lane / M, j = lane % M;
     const uint32_t K = args.K;
     double total = 0.0;
@@ -421,8 +433,8 @@ __global__ __launch_bounds__(kCwThreads, M == 32 ? 4 : 1) void cw_mask_kernel(co
             }
         }
     }
-    if (args.partials && threadIdx.x == 0)
-        ((double *)args.partials)[args.partial0 + blockIdx.x] = total;
+    if (out.dst)
+        hand_over<kCwThreads>(out, total, nullptr);
 }
 
 // ---- 16:32 of bf16 matrices whose rows can be read 16 bytes at a time -------------------------------------------------
@@ -487,7 +499,10 @@ __global__ __launch_bounds__(64 * kRowsTiles, 8) void cw_mask32_bf16_kernel(cons
 {
     constexpr uint32_t kPitch = 20;                       // dwords: four of padding keep the 16-byte accesses conflict-free
     __shared__ __align__(16) uint32_t lds[kRowsTiles][64 * kPitch];
-    const CwMat md = args.m[cw_find(args, blockIdx.x)];
+    __shared__ double red[kRowsTiles];
+    const int which = cw_find(args, blockIdx.x);
+    const CwMat md = args.m[which];
+    const Handover out = cw_objective<true>(args, md, which);
     const uint32_t lane = threadIdx.x & 63u, blk = lane >> 5, j = lane & 31u;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     uint32_t *const T = lds[wave];                        // the wavefront's own: no barriers among its lanes
@@ -543,7 +558,7 @@ __global__ __launch_bounds__(64 * kRowsTiles, 8) void cw_mask32_bf16_kernel(cons
                 *(uint32_t *)((unsigned char *)md.mask + row * md.mask_ld + (col >> 3)) = keep;
             }
         }
-        if (args.partials) {
+        if (out.dst) {
             float acc = 0.f;
 #pragma unroll
             for (int i = 0; i < 4; i++) {                 // the lane's own magnitudes, back from LDS
@@ -561,16 +576,15 @@ __global__ __launch_bounds__(64 * kRowsTiles, 8) void cw_mask32_bf16_kernel(cons
             total = (double)wave_sum(acc);
         }
     }
-    if (args.partials) {
+    if (out.dst) {
         double *const sum = (double *)&T[16];             // padding of the first row
         if (lane == 0)
             *sum = total;
         __syncthreads();
-        if (threadIdx.x == 0) {
-            for (uint32_t k = 1; k < kRowsTiles; k++)
-                total += *(const double *)&lds[k][16];
-            ((double *)args.partials)[args.partial0 + blockIdx.x] = total;
-        }
+        total = *(const double *)&lds[0][16];
+        for (uint32_t k = 1; k < kRowsTiles; k++)
+            total += *(const double *)&lds[k][16];
+        hand_over<64 * kRowsTiles>(out, total, red);
     }
 }
 
@@ -603,7 +617,9 @@ __global__ __launch_bounds__(kCwThreads, M == 32 ? 3 : 1) void cw_exact_kernel(c
     __shared__ int DROW[NB][M], DCOL[NB][M];
     __shared__ uint32_t PROW[NB][M], PCOL[NB][M];
     __shared__ uint32_t PK[NB][M];
-    const CwMat md = args.m[cw_find(args, blockIdx.x)];
+    const int which = cw_find(args, blockIdx.x);
+    const CwMat md = args.m[which];
+    const Handover out = cw_objective<false>(args, md, which);     // registers are short
     const uint32_t lane = threadIdx.x, blk = lane / M, j = lane % M;
     const uint32_t K = args.K;
     double total = 0.0;
@@ -788,8 +804,8 @@ __global__ __launch_bounds__(kCwThreads, M == 32 ? 3 : 1) void cw_exact_kernel(c
             acc += (p.active && ((keep >> i) & 1u)) ? __uint_as_float(key[i]) : 0.f;
         total += (double)wave_sum(acc);
     }
-    if (args.partials && threadIdx.x == 0)
-        ((double *)args.partials)[args.partial0 + blockIdx.x] = total;
+    if (out.dst)
+        hand_over<kCwThreads>(out, total, nullptr);
 }
 
 // =====================================================================================================================
@@ -799,11 +815,14 @@ __global__ __launch_bounds__(kCwThreads, M == 32 ? 3 : 1) void cw_exact_kernel(c
 template <int DT, int M, int FMT>
 __global__ __launch_bounds__(kCwThreads) void cw_score_kernel(const CwArgs args)
 {
-    const CwMat md = args.m[cw_find(args, blockIdx.x)];
+    const int which = cw_find(args, blockIdx.x);
+    const CwMat md = args.m[which];
+    const Handover out = handover<sizeof(ScorePartial), 7>(args.partials, args.tags, args.partial0 + blockIdx.x, blockIdx.x - md.wg0, md.n_wg,
+                                                           args.score + which);
     const uint32_t lane = threadIdx.x, blk = lane / M, j = lane % M;
     const uint32_t N = args.N;
     double retained = 0.0, total = 0.0;
-    unsigned long long kept = 0, rowv = 0, colv = 0, rowne = 0, colne = 0;
+    uint32_t kept = 0, rowv = 0, colv = 0, rowne = 0, colne = 0;
     for (uint32_t t = blockIdx.x - md.wg0; t < md.n_tiles; t += md.n_wg) {
         const CwTile p = cw_tile<M == 32 ? 4 : 1>(md, t);
         const uint32_t bits = cw_load_mask<M, FMT>(md, p);
@@ -835,11 +854,8 @@ __global__ __launch_bounds__(kCwThreads) void cw_score_kernel(const CwArgs args)
         retained += (double)wave_sum(ret);
         total += (double)wave_sum(tot);
     }
-    if (threadIdx.x == 0) {
-        ScorePartial *out = (ScorePartial *)args.partials + args.partial0 + blockIdx.x;
-        out->retained = retained; out->total = total;
-        out->kept = kept; out->rowv = rowv; out->colv = colv; out->rowne = rowne; out->colne = colne;
-    }
+    const ScoreSums own = {retained, total, kept, rowv, colv, rowne, colne};
+    hand_over_score<kCwThreads>(out, own);
 }
 
 // =====================================================================================================================
@@ -1163,7 +1179,7 @@ static cw_kernel_t cw_pick_mask(int solver, int dt, int M, int mf)
 
 // solver: 0 = Algorithm 1, 1 = exact, 2 = row pruning.  Arguments are validated by the caller; `ws` (if any objective
 // is wanted) holds at least one double per workgroup.
-int cw_run_mask(int solver, const tmask_mat *mats, int n_mats, int dt, int N, int M, int mf, void *ws, hipStream_t stream)
+int cw_run_mask(int solver, const tmask_mat *mats, int n_mats, int dt, int N, int M, int mf, void *ws, bool tagged, hipStream_t stream)
 {
     bool want_obj = false;
     for (int i = 0; i < n_mats; i++)
@@ -1187,21 +1203,24 @@ int cw_run_mask(int solver, const tmask_mat *mats, int n_mats, int dt, int N, in
         const int nb = n_mats - first < kMaxCwBatch ? n_mats - first : kMaxCwBatch;
         CwArgs args;
         memset(&args, 0, sizeof args);
-        double *objective[kMaxCwBatch];
         uint32_t wg0[kMaxCwBatch + 1];
-        uint32_t wgs = 0;
+        uint32_t wgs = 0, most = 0;
         for (int k = 0; k < nb; k++) {
             const tmask_mat &t = mats[first + k];
             cw_fill(args.m[k], t.w, t.rows, t.cols, t.ld, t.mask, t.mask_ld, M, wgs);
             if (by_rows)
                 args.m[k].n_wg = (args.m[k].n_tiles + kRowsTiles - 1) / kRowsTiles;
-            objective[k] = t.objective;
+            args.objective[k] = t.objective;
+            most = most > args.m[k].n_wg ? most : args.m[k].n_wg;
             wg0[k] = wgs;
             wgs += args.m[k].n_wg;
         }
         wg0[nb] = wgs;
         args.n = (uint32_t)nb; args.K = (uint32_t)(M - N); args.N = (uint32_t)N;
         args.partial0 = partial0; args.partials = want_obj ? ws : nullptr;
+        const bool one_launch = want_obj && tagged && adds_up_itself(wgs, most, by_rows ? 64 * kRowsTiles : kCwThreads, false);
+        if (one_launch)
+            args.tags = draw_tags();
         {
             ProfileScope prof(stream, first + kMaxCwBatch >= n_mats);
             hipLaunchKernelGGL(kern, dim3(wgs), dim3(by_rows ? 64 * kRowsTiles : kCwThreads), 0, stream, args);
@@ -1209,8 +1228,8 @@ int cw_run_mask(int solver, const tmask_mat *mats, int n_mats, int dt, int N, in
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess)
             return hip_fail(e, "column-wise mask kernel launch");
-        if (want_obj) {
-            const int rc = launch_objective_reduce(objective, wg0, nb, partial0, ws, stream);
+        if (want_obj && !one_launch) {
+            const int rc = launch_objective_reduce(args.objective, wg0, nb, partial0, ws, stream);
             if (rc)
                 return rc;
         }
@@ -1232,18 +1251,23 @@ int cw_run_score(const tmask_mat *mats, int n_mats, int dt, int N, int M, int mf
         CwArgs args;
         memset(&args, 0, sizeof args);
         uint32_t wg0[kMaxCwBatch + 1];
-        uint32_t wgs = 0;
+        uint32_t wgs = 0, most = 0;
         for (int k = 0; k < nb; k++) {
             const tmask_mat &t = mats[first + k];
             cw_fill(args.m[k], t.w, t.rows, t.cols, t.ld, t.mask, t.mask_ld, M, wgs);
             args.m[k].aux = per_block_obj ? (void *)(per_block_obj + block0) : nullptr;
             block0 += (size_t)(t.rows / M) * (size_t)(t.cols / M);
+            most = most > args.m[k].n_wg ? most : args.m[k].n_wg;
             wg0[k] = wgs;
             wgs += args.m[k].n_wg;
         }
         wg0[nb] = wgs;
         args.n = (uint32_t)nb; args.K = (uint32_t)(M - N); args.N = (uint32_t)N;
         args.partial0 = partial0; args.partials = ws;
+        args.score = (ScorePartial *)(out + first);
+        const bool one_launch = adds_up_itself(wgs, most, kCwThreads, true);
+        if (one_launch)
+            args.tags = draw_tags();
         {
             ProfileScope prof(stream, first + kMaxCwBatch >= n_mats);
             hipLaunchKernelGGL(kern, dim3(wgs), dim3(kCwThreads), 0, stream, args);
@@ -1251,9 +1275,11 @@ int cw_run_score(const tmask_mat *mats, int n_mats, int dt, int N, int M, int mf
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess)
             return hip_fail(e, "column-wise score kernel launch");
-        const int rc = launch_score_reduce(wg0, nb, partial0, ws, out + first, stream);
-        if (rc)
-            return rc;
+        if (!one_launch) {
+            const int rc = launch_score_reduce(wg0, nb, partial0, ws, out + first, stream);
+            if (rc)
+                return rc;
+        }
         partial0 += wgs;
     }
     return TMASK_OK;

@@ -44,7 +44,7 @@ constexpr int kMaxBatch = 256;       // matrices per launch (descriptor table tr
 struct MatDev {
     const void *w;
     void *mask;
-    void *aux;           // score: per-block objective base for this matrix (float*), else unused
+    void *aux;           // masks: the objective; score: per-block objective base for this matrix (float*); dense: the output
     uint32_t ld;         // elements
     uint32_t mask_ld;    // bytes
     uint32_t spr;        // strips per block-row = cols / C
@@ -52,7 +52,7 @@ struct MatDev {
     uint32_t div_mul;    // s / spr == (uint64(s) * div_mul) >> div_shift for s < 2^31
     uint32_t div_shift;
     uint32_t tile0;      // first workgroup of this matrix inside the launch
-    uint32_t pad;
+    uint32_t pad;        // masks, score: workgroups of this matrix; dense: leading dimension of the output
 };
 
 // Which matrix does workgroup `tile` belong to?  A binary search over the table costs a chain of dependent scalar
@@ -67,6 +67,12 @@ struct CoarseIndex {
     uint32_t e[kCoarse];
 };
 
+// How the workgroups of a launch hand their partial results to the one that adds up those of a matrix: see take_words.
+// a = 0: they leave them for a second launch.
+struct Tags {
+    uint32_t a, b;
+};
+
 struct BatchArgs {
     MatDev m[kMaxBatch];
     CoarseIndex ci;
@@ -75,9 +81,11 @@ struct BatchArgs {
     uint32_t N;
     uint32_t partial0;   // index of this launch's first partial in the workspace
     void *partials;      // workspace
+    Tags tags;
+    struct ScorePartial *score;   // score: the results, one per matrix of the launch
 };
 
-// What a workgroup of the score kernels leaves for the second-stage reduction.
+// What a workgroup of the score kernels leaves to be added up; the results of the call have the same layout.
 struct ScorePartial {
     double retained, total;
     unsigned long long kept, rowv, colv, rowne, colne;
@@ -246,6 +254,208 @@ __device__ __forceinline__ double block_sum_f32(float v, double *lds /* kThreads
     for (int k = 1; k < kThreads / 64; k++)
         r += lds[k];
     return r;
+}
+
+// ---- partial results, added up in the launch that leaves them ----------------------------------------------------------
+//
+// A second launch that adds a workgroup's partial results costs 3-4 us on the device and 2 on the host, as much as a small
+// matrix takes; counting the workgroups that are done needs a counter that is zero when the launch begins, and the
+// workspace holds anything.  So a partial result travels as words of 32 bits of it beside 32 bits of tag, which the host
+// draws for each launch, and the last workgroup of a matrix reads the words of the others until their tags are right: every
+// word proves by itself that it was written by this launch.  It then clears them, so that a captured launch, whose tags are
+// the same each time it is replayed, finds none of its own.  (Contents of a workspace pass for a result only if they hold both
+// 32-bit tags of a call in the right places, two tags that differ and are drawn anew for each call.)
+// The wait ends: workgroups start in the order of their numbers on each XCD, so of those that are not done the lowest one
+// has started or finds its place held by none that waits, and it waits for nobody itself.  Should a result never come, the
+// wait gives up after some seconds and the sum is NaN.
+
+constexpr uint32_t kMostReads = 1u << 21;     // of one record, a microsecond or more each
+
+__device__ __forceinline__ void put_word(unsigned long long *at, uint32_t value, uint32_t tag)
+{
+    __hip_atomic_store(at, ((unsigned long long)tag << 32) | value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ __forceinline__ unsigned long long get_word(const unsigned long long *at)
+{
+    return __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The words of a record (even ones tagged a, odd ones b), cleared when all of them are there; false if they never came.  A read
+// goes to memory and takes 2-3 us behind what the chip has in flight; four records at a time took
+// registers, and with them a wavefront of occupancy, for no gain.
+template <int W>
+__device__ __forceinline__ bool take_words(unsigned long long *at, const Tags &tags, uint32_t (&v)[W])
+{
+    bool all;
+    uint32_t reads = 0;
+    do {
+        if (reads)
+            __builtin_amdgcn_s_sleep(1);
+        unsigned long long w[W];
+#pragma unroll
+        for (int k = 0; k < W; k++)
+            w[k] = get_word(at + k);
+        all = true;
+#pragma unroll
+        for (int k = 0; k < W; k++) {
+            v[k] = (uint32_t)w[k];
+            all = all && (uint32_t)(w[k] >> 32) == ((k & 1) ? tags.b : tags.a);
+        }
+    } while (!all && ++reads < kMostReads);
+#pragma unroll
+    for (int k = 0; k < W; k++)
+        __hip_atomic_store(at + k, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return all;
+}
+
+__device__ __forceinline__ double words_as_double(uint32_t lo, uint32_t hi, bool came)
+{
+    return came ? __hiloint2double((int)hi, (int)lo) : __hiloint2double(0x7FF80000, 0);
+}
+
+// Where a workgroup's part of a sum goes: the workgroup is number `which` of `others` + 1.
+struct Handover {
+    void *dst;                       // of the whole sum; null: nobody asked for it
+    unsigned long long *records;     // of the matrix' workgroups
+    uint32_t a, b, which, others;
+};
+
+// partials: the workspace or null; index: the workgroup's number among all of the call; which of count: among its matrix'; SIZE
+// of a result for a second launch, which is then the whole of the sum; WORDS of a record.
+template <int SIZE, int WORDS, bool EARLY = true>
+__device__ __forceinline__ Handover handover(void *partials, const Tags &tags, uint32_t index, uint32_t which, uint32_t count, void *dst)
+{
+    const bool tagged = tags.a != 0u;
+    Handover h;
+    h.dst = !partials ? nullptr : tagged ? dst : (void *)((char *)partials + (size_t)index * SIZE);
+    h.records = (unsigned long long *)partials + (size_t)(index - which) * WORDS;
+    h.a = tags.a;
+    h.b = tags.b;
+    h.which = tagged ? which : 0u;
+    h.others = tagged ? count - 1u : 0u;
+    // Read now, with the descriptor: at the workgroup's end these would be a chain of scalar loads that nothing overlaps
+    // (4096 x 3072 bf16, 16:32: 15.2 / 14.95 us).
+    if constexpr (EARLY)
+        asm volatile("" : "+s"(h.dst), "+s"(h.records), "+s"(h.a), "+s"(h.b), "+s"(h.which), "+s"(h.others));
+    return h;
+}
+
+// Leaves t (the same in every thread) in the workgroup's record, or, as the last workgroup of its matrix, adds all of them to
+// *dst (not null), in the order of objective_reduce_kernel<256>: result i by thread i mod 256, one after the other, then each
+// wavefront, then the four.  red: four doubles of LDS (THREADS = 64: unused, a lane does the work of four).
+template <int THREADS>
+__device__ __forceinline__ void hand_over(const Handover &h, double t, double *red)
+{
+    const Tags tags{h.a, h.b};
+    if (h.which != h.others) {
+        if (threadIdx.x == 0) {
+            const unsigned long long bits = (unsigned long long)__double_as_longlong(t);
+            put_word(h.records + 2u * h.which, (uint32_t)bits, tags.a);
+            put_word(h.records + 2u * h.which + 1u, (uint32_t)(bits >> 32), tags.b);
+        }
+        return;
+    }
+    if (h.others == 0u) {
+        if (threadIdx.x == 0)
+            *(double *)h.dst = t;
+        return;
+    }
+    static_assert(THREADS == 64 || THREADS == kThreads, "the order above");
+    double total = 0.0;
+#pragma nounroll
+    for (uint32_t q = 0; q < (uint32_t)kThreads; q += THREADS) {
+        const uint32_t first = threadIdx.x + q;
+        double sum = 0.0;
+#pragma nounroll
+        for (uint32_t i = first; i < h.others; i += kThreads) {
+            uint32_t v[2];
+            const bool came = take_words<2>(h.records + 2u * i, tags, v);
+            sum += words_as_double(v[0], v[1], came);
+        }
+        if (h.others % kThreads == first)
+            sum += t;
+        sum = wave_sum(sum);
+        total = q == 0 ? sum : total + sum;
+    }
+    if constexpr (THREADS > 64) {
+        __syncthreads();                          // what red held has been read
+        if ((threadIdx.x & 63u) == 0)
+            red[threadIdx.x >> 6] = total;
+        __syncthreads();
+        total = ((red[0] + red[1]) + red[2]) + red[3];
+    }
+    if (threadIdx.x == 0)
+        *(double *)h.dst = total;
+}
+
+// The objective of the strip kernels.
+__device__ __forceinline__ Handover objective_of(const BatchArgs &args, const MatDev &md, uint32_t tile)
+{
+    return handover<8, 2>(args.partials, args.tags, args.partial0 + tile, tile - md.tile0, md.pad, md.aux);
+}
+
+// What a workgroup of the score kernels counts: at most 2^15 entries each (256 lanes x 128), so two counts share a word, and
+// those of a matrix' workgroups that hand theirs over add up in 32 bits.
+struct ScoreSums {
+    double retained, total;
+    uint32_t kept, rowv, colv, rowne, colne;
+};
+
+// The same for the seven sums of a score.
+template <int THREADS>
+__device__ __forceinline__ void hand_over_score(const Handover &h, ScoreSums own)
+{
+    constexpr int W = 7;
+    const Tags tags{h.a, h.b};
+    if (h.which != h.others) {
+        if (threadIdx.x == 0) {
+            const unsigned long long r = (unsigned long long)__double_as_longlong(own.retained);
+            const unsigned long long t = (unsigned long long)__double_as_longlong(own.total);
+            const uint32_t v[W] = {(uint32_t)r, (uint32_t)(r >> 32), (uint32_t)t, (uint32_t)(t >> 32), own.kept | (own.rowv << 16),
+                                   own.colv | (own.rowne << 16), own.colne};
+#pragma unroll
+            for (int k = 0; k < W; k++)
+                put_word(h.records + (size_t)W * h.which + k, v[k], (k & 1) ? tags.b : tags.a);
+        }
+        return;
+    }
+    ScorePartial *const dst = (ScorePartial *)h.dst;
+    if (h.others == 0u) {
+        if (threadIdx.x == 0)
+            *dst = ScorePartial{own.retained, own.total, own.kept, own.rowv, own.colv, own.rowne, own.colne};
+        return;
+    }
+    if (threadIdx.x != 0)
+        own = ScoreSums{};
+#pragma nounroll
+    for (uint32_t i = threadIdx.x; i < h.others; i += THREADS) {
+        uint32_t v[W];
+        const bool came = take_words<W>(h.records + (size_t)W * i, tags, v);
+        own.retained += words_as_double(v[0], v[1], came);
+        own.total += words_as_double(v[2], v[3], came);
+        own.kept += v[4] & 0xFFFFu; own.rowv += v[4] >> 16;
+        own.colv += v[5] & 0xFFFFu; own.rowne += v[5] >> 16;
+        own.colne += v[6];
+    }
+    own = ScoreSums{wave_sum(own.retained), wave_sum(own.total), wave_sum(own.kept), wave_sum(own.rowv), wave_sum(own.colv),
+                    wave_sum(own.rowne), wave_sum(own.colne)};
+    if constexpr (THREADS > 64) {
+        __shared__ ScoreSums sums[THREADS / 64];
+        if ((threadIdx.x & 63u) == 0)
+            sums[threadIdx.x >> 6] = own;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+#pragma unroll
+            for (int k = 1; k < THREADS / 64; k++) {
+                const ScoreSums o = sums[k];
+                own.retained += o.retained; own.total += o.total;
+                own.kept += o.kept; own.rowv += o.rowv; own.colv += o.colv; own.rowne += o.rowne; own.colne += o.colne;
+            }
+        }
+    }
+    if (threadIdx.x == 0)
+        *dst = ScorePartial{own.retained, own.total, own.kept, own.rowv, own.colv, own.rowne, own.colne};
 }
 
 // ---- tile addressing ----------------------------------------------------------------------------

@@ -65,6 +65,7 @@ __global__ __launch_bounds__(kThreads, exact_workgroups_per_cu(DT, M)) void exac
 
     const uint32_t tile = blockIdx.x;
     const MatDev md = args.m[find_matrix(args, tile)];
+    const Handover out = objective_of(args, md, tile);
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
     const uint32_t s = (tile - md.tile0) * kThreads + tid;
     const uint32_t gpos = tid & (G - 1);
@@ -214,11 +215,8 @@ __global__ __launch_bounds__(kThreads, exact_workgroups_per_cu(DT, M)) void exac
                 acc += ((bits[i] >> c) & 1u) ? __uint_as_float(a[c]) : 0.f;
         }
     }
-    if (args.partials) {
-        const double t = block_sum_f32(acc, red);
-        if (threadIdx.x == 0)
-            ((double *)args.partials)[args.partial0 + tile] = t;
-    }
+    if (out.dst)
+        hand_over<kThreads>(out, block_sum_f32(acc, red), red);
 }
 
 }  // namespace tmask

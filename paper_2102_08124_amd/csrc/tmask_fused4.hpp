@@ -29,7 +29,9 @@ __global__ __launch_bounds__(kThreads) void approx_pack24_kernel(const FusedArgs
     // the four doubles of the objective's workgroup sum reuse the first bytes of IDX once the tile is written out
 
     const uint32_t tile = blockIdx.x;
-    const PackDev d = args.d[find_pack_desc(args, tile)];
+    const int which = find_pack_desc(args, tile);
+    const PackDev d = args.d[which];
+    const Handover out = objective_of<TR>(args, d, which, tile);
     const uint32_t tl = tile - d.tile0;
     uint32_t ty, tx;
     tile_coords(tl, d.tiles_x, (d.rows + TR - 1) / TR, kPackRunRows / TR, ty, tx);
@@ -260,12 +262,10 @@ __global__ __launch_bounds__(kThreads) void approx_pack24_kernel(const FusedArgs
         compute(std::true_type{});
     __syncthreads();
     pack24_copy_out<DT, S, 4, QN>(d, row0, col0, OT, IDXT, IDX);
-    if (args.partials) {
+    if (out.dst) {
         __syncthreads();                                   // every wavefront is done reading IDX
         double *red = (double *)&IDX[0][0];
-        const double t = block_sum_f32(acc, red);
-        if (threadIdx.x == 0)
-            ((double *)args.partials)[args.partial0 + tile] = t;
+        hand_over<kThreads>(out, block_sum_f32(acc, red), red);
     }
 }
 

@@ -31,6 +31,18 @@ struct ProfileScope {
     }
 };
 
+// Whether a launch adds up its own partial results (hand_over, hand_over_score): `total` workgroups of `threads`, no matrix with
+// more than `most`.  Back to back, two launches / one, us: 512^2 .. 1536^2 masks at 2:4 and 4:8 9.3-10.2 / 6.9-7.3, 4096^2 bf16 14.6 /
+// 13.0, six matrices fp32 2:4 (3072 workgroups) 15.2 / 13.7, 52 (5724) 23.5 / 22.8, optimal 4:8 of them 59.1 / 57.2; 144 (36864) 147 /
+// 153: by then hundreds of last workgroups read while others stream.  A score's record is seven words: 512^2 and 1024^2 mask,
+// compression and score (256 workgroups) 25.3 / 20.3, 2048^2 (1024) 30.6 / 30.2, six matrices (3072) 60 / 67.
+inline bool adds_up_itself(uint32_t total, uint32_t most, uint32_t threads, bool score)
+{
+    return score ? total <= 512u : total <= 8192u && most <= 8u * threads;
+}
+
+Tags draw_tags();
+
 // Second-stage reductions (tmask_kernels.hip) for kernels of other translation units: first0[k] = index, inside the
 // launch, of the first partial result of matrix k; first0[nb] = their number.
 int launch_objective_reduce(double *const *objective, const uint32_t *first0, int nb, uint32_t partial0, const void *partials,
@@ -39,9 +51,10 @@ int launch_score_reduce(const uint32_t *first0, int nb, uint32_t partial0, const
                         hipStream_t stream);
 
 // The column-per-lane kernels (tmask_colwise.hip): M = 32, and matrices that miss the strip kernels' alignment.
-// Arguments are validated by the callers.  solver: 0 = Algorithm 1, 1 = exact, 2 = row pruning; dense mode: 0 =
+// Arguments are validated by the callers.  solver: 0 = Algorithm 1, 1 = exact, 2 = row pruning; tagged: ws
+// has room for 16 bytes per workgroup and is this call's alone; dense mode: 0 =
 // Algorithm 1, 1 = row pruning, 2 = row pruning with mean absorption.
-int cw_run_mask(int solver, const tmask_mat *mats, int n_mats, int dt, int N, int M, int mf, void *ws, hipStream_t stream);
+int cw_run_mask(int solver, const tmask_mat *mats, int n_mats, int dt, int N, int M, int mf, void *ws, bool tagged, hipStream_t stream);
 int cw_run_score(const tmask_mat *mats, int n_mats, int dt, int N, int M, int mf, tmask_score_out *out, float *per_block_obj,
                  void *ws, hipStream_t stream);
 int cw_run_pack(const tmask_pack_desc *descs, int n, int dt, int N, int M, int mf, hipStream_t stream);

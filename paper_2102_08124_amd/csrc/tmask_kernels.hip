@@ -1,6 +1,8 @@
 // tmask: streaming kernels (approx / exact / score) and the C ABI.  gfx950 only.
 #include <hip/hip_runtime.h>
 
+#include <atomic>
+#include <chrono>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
@@ -37,6 +39,7 @@ __global__ __launch_bounds__(kThreads) void mask_kernel(const BatchArgs args)
     __shared__ double red[kThreads / 64];
     const uint32_t tile = blockIdx.x;
     const MatDev md = args.m[find_matrix(args, tile)];
+    const Handover out = objective_of(args, md, tile);
     const uint32_t s = (tile - md.tile0) * kThreads + threadIdx.x;
     const uint32_t gpos = threadIdx.x & (Ge::G - 1);
     float acc = 0.f;
@@ -78,11 +81,8 @@ __global__ __launch_bounds__(kThreads) void mask_kernel(const BatchArgs args)
         store_mask<DT, M, FMT>(md, pos, bits);
         acc = kept_sum<M, Ge::C>(a, bits);
     }
-    if (args.partials) {
-        const double t = block_sum_f32<DT>(acc, red);
-        if (threadIdx.x == 0)
-            ((double *)args.partials)[args.partial0 + tile] = t;
-    }
+    if (out.dst)
+        hand_over<kThreads>(out, block_sum_f32<DT>(acc, red), red);
 }
 
 // A strip of tmask_approx for 2:4, decisions taken as lane-mask logic; returns what the lane keeps.
@@ -103,15 +103,13 @@ __global__ __launch_bounds__(kThreads) void approx24_kernel(const BatchArgs args
     __shared__ double red[kThreads / 64];
     const uint32_t tile = blockIdx.x;
     const MatDev md = args.m[find_matrix(args, tile)];
+    const Handover out = objective_of(args, md, tile);
     const uint32_t s = (tile - md.tile0) * kThreads + threadIdx.x;
     float acc = 0.f;
     if (s < md.n_strips)
         acc = approx24_strip<DT, FMT>(md, s);
-    if (args.partials) {
-        const double t = block_sum_f32<DT>(acc, red);
-        if (threadIdx.x == 0)
-            ((double *)args.partials)[args.partial0 + tile] = t;
-    }
+    if (out.dst)
+        hand_over<kThreads>(out, block_sum_f32<DT>(acc, red), red);
 }
 
 // tmask_approx for fp32 with N = M/2, M = 8 or 16: thresholds on magnitudes; a wavefront in which some
@@ -124,6 +122,7 @@ __global__ __launch_bounds__(kThreads, (M == 16 && FMT == kMaskBits) ? 4 : 1) vo
     __shared__ double red[kThreads / 64];
     const uint32_t tile = blockIdx.x;
     const MatDev md = args.m[find_matrix(args, tile)];
+    const Handover out = objective_of(args, md, tile);
     const uint32_t s = (tile - md.tile0) * kThreads + threadIdx.x;
     const uint32_t gpos = threadIdx.x & (Ge::G - 1);
     float acc = 0.f;
@@ -169,11 +168,8 @@ __global__ __launch_bounds__(kThreads, (M == 16 && FMT == kMaskBits) ? 4 : 1) vo
             store_mask<kF32, M, kMaskBits>(md, pos, bits);
         }
     }
-    if (args.partials) {
-        const double t = block_sum_f32(acc, red);
-        if (threadIdx.x == 0)
-            ((double *)args.partials)[args.partial0 + tile] = t;
-    }
+    if (out.dst)
+        hand_over<kThreads>(out, block_sum_f32(acc, red), red);
 }
 
 // A strip of tmask_exact at M = 4: every block by enumeration (NK = 2: all 90 patterns; NK = 1, 3: the 24 permutations,
@@ -225,15 +221,13 @@ __global__ __launch_bounds__(kThreads) void exact24_kernel(const BatchArgs args)
     __shared__ double red[kThreads / 64];
     const uint32_t tile = blockIdx.x;
     const MatDev md = args.m[find_matrix(args, tile)];
+    const Handover out = objective_of(args, md, tile);
     const uint32_t s = (tile - md.tile0) * kThreads + threadIdx.x;
     float acc = 0.f;
     if (s < md.n_strips)
         acc = exact24_strip<DT, FMT, NK>(md, s);
-    if (args.partials) {
-        const double t = block_sum_f32<DT>(acc, red);
-        if (threadIdx.x == 0)
-            ((double *)args.partials)[args.partial0 + tile] = t;
-    }
+    if (out.dst)
+        hand_over<kThreads>(out, block_sum_f32<DT>(acc, red), red);
 }
 
 // A few small matrices with their objectives, 2:4: a workgroup of 1024 threads takes a whole matrix, a strip per thread, and
@@ -278,6 +272,7 @@ __global__ __launch_bounds__(kThreads) void approx_sel_bf16_kernel(const BatchAr
     __shared__ double red[kThreads / 64];
     const uint32_t tile = blockIdx.x;
     const MatDev md = args.m[find_matrix(args, tile)];
+    const Handover out = objective_of(args, md, tile);
     const uint32_t s = (tile - md.tile0) * kThreads + threadIdx.x;
     const uint32_t gpos = threadIdx.x & (Ge::G - 1);
     float acc = 0.f;
@@ -306,11 +301,8 @@ __global__ __launch_bounds__(kThreads) void approx_sel_bf16_kernel(const BatchAr
             store_mask<kBF16, M, kMaskBits>(md, pos, bits);
         }
     }
-    if (args.partials) {
-        const double t = block_sum_f32(acc, red);
-        if (threadIdx.x == 0)
-            ((double *)args.partials)[args.partial0 + tile] = t;
-    }
+    if (out.dst)
+        hand_over<kThreads>(out, block_sum_f32(acc, red), red);
 }
 
 // tmask_approx_dense / tmask_prune_1d_dense: a mask and the masked copy W (.) S in one pass.  Same tiling as the
@@ -492,7 +484,7 @@ struct ReduceArgs {
 // Second stage of the objective: workgroup m adds the partials of matrix m in a fixed order.  1024 threads: one
 // matrix can have hundreds of thousands of partials, and the loop is a chain of load latencies.
 constexpr int kReduceThreads = 1024;
-constexpr int kReduceThreadsSmall = 256;    // when no matrix of the launch has more than 512 partial results
+constexpr int kReduceThreadsSmall = 256;    // objectives: when no matrix of the launch has more than 2048 partial results; scores: 512
 
 template <int THREADS>
 __global__ __launch_bounds__(THREADS) void objective_reduce_kernel(const ReduceArgs args)
@@ -503,23 +495,33 @@ __global__ __launch_bounds__(THREADS) void objective_reduce_kernel(const ReduceA
     double *dst = args.objective[m];
     if (!dst)
         return;
-    // four independent partial sums per thread keep several loads in flight; the order of additions is fixed
+    // several loads of a thread are in flight; the order of additions is fixed: with 256 threads that of hand_over, with 1024
+    // four sums side by side
     const uint32_t t0 = args.tile0[m], t1 = args.tile0[m + 1];
     const double *src = args.partials + args.partial0;
     double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
     uint32_t t = t0 + threadIdx.x;
     for (; t + 7 * kReduceThreads < t1; t += 8 * kReduceThreads) {
-        const double v0 = src[t], v1 = src[t + kReduceThreads], v2 = src[t + 2 * kReduceThreads], v3 = src[t + 3 * kReduceThreads];
-        const double v4 = src[t + 4 * kReduceThreads], v5 = src[t + 5 * kReduceThreads], v6 = src[t + 6 * kReduceThreads],
-                     v7 = src[t + 7 * kReduceThreads];
-        a0 += v0; a1 += v1; a2 += v2; a3 += v3;
-        a0 += v4; a1 += v5; a2 += v6; a3 += v7;
+        double v[8];
+#pragma unroll
+        for (int k = 0; k < 8; k++)
+            v[k] = src[t + k * kReduceThreads];
+        if constexpr (kReduceThreads == kReduceThreadsSmall) {
+#pragma unroll
+            for (int k = 0; k < 8; k++)
+                a0 += v[k];
+        } else {
+            a0 += v[0]; a1 += v[1]; a2 += v[2]; a3 += v[3];
+            a0 += v[4]; a1 += v[5]; a2 += v[6]; a3 += v[7];
+        }
     }
-    for (; t + 3 * kReduceThreads < t1; t += 4 * kReduceThreads) {
-        a0 += src[t];
-        a1 += src[t + kReduceThreads];
-        a2 += src[t + 2 * kReduceThreads];
-        a3 += src[t + 3 * kReduceThreads];
+    if constexpr (kReduceThreads != kReduceThreadsSmall) {
+        for (; t + 3 * kReduceThreads < t1; t += 4 * kReduceThreads) {
+            a0 += src[t];
+            a1 += src[t + kReduceThreads];
+            a2 += src[t + 2 * kReduceThreads];
+            a3 += src[t + 3 * kReduceThreads];
+        }
     }
     for (; t < t1; t += kReduceThreads)
         a0 += src[t];
@@ -536,13 +538,14 @@ __global__ __launch_bounds__(THREADS) void objective_reduce_kernel(const ReduceA
     }
 }
 
-// One workgroup per matrix; 256 threads instead of 1024 when every matrix has at most 512 partial results.
+// One workgroup per matrix; 256 threads instead of 1024 when every matrix has at most 2048 partial results, as in hand_over, whose
+// sums have to be the same bits (tmask_approx_noalloc takes two launches where tmask_approx takes one).
 static void enqueue_objective_reduce(const ReduceArgs &rargs, int nb, hipStream_t stream)
 {
     uint32_t most = 0;
     for (int k = 0; k < nb; k++)
         most = rargs.tile0[k + 1] - rargs.tile0[k] > most ? rargs.tile0[k + 1] - rargs.tile0[k] : most;
-    if (most <= 2 * kReduceThreadsSmall)
+    if (most <= 8 * kReduceThreadsSmall)
         hipLaunchKernelGGL(objective_reduce_kernel<kReduceThreadsSmall>, dim3(nb), dim3(kReduceThreadsSmall), 0, stream, rargs);
     else
         hipLaunchKernelGGL(objective_reduce_kernel<kReduceThreads>, dim3(nb), dim3(kReduceThreads), 0, stream, rargs);
@@ -633,14 +636,16 @@ __device__ __forceinline__ void score_strip_bf16_m4(const MatDev &md, StripPos p
 }
 
 template <int DT, int M, int FMT>
-__global__ __launch_bounds__(kThreads) void score_kernel(const BatchArgs args)
+__global__ __launch_bounds__(kThreads, M == 4 && DT != kBF16N ? 8 : 1) void score_kernel(const BatchArgs args)
 {
     using Ge = Geo<DT, M>;
     constexpr int C = Ge::C, CL = Ge::CL;
     __shared__ double redd[kThreads / 64][2];
     __shared__ uint32_t redu[kThreads / 64][5];
     const uint32_t tile = blockIdx.x;
-    const MatDev md = args.m[find_matrix(args, tile)];
+    const int which = find_matrix(args, tile);
+    const MatDev md = args.m[which];
+    const Handover out = handover<sizeof(ScorePartial), 7>(args.partials, args.tags, args.partial0 + tile, tile - md.tile0, md.pad, args.score + which);
     const uint32_t s = (tile - md.tile0) * kThreads + threadIdx.x;
     const uint32_t gpos = threadIdx.x & (Ge::G - 1);
     const uint32_t N = args.N;
@@ -804,21 +809,15 @@ __global__ __launch_bounds__(kThreads) void score_kernel(const BatchArgs args)
         redu[wave][4] = w_b >> 16;
     }
     __syncthreads();
+    ScoreSums own = {};
     if (threadIdx.x == 0) {
-        ScorePartial *out = (ScorePartial *)args.partials + args.partial0 + tile;
-        double r0 = 0.0, r1 = 0.0;
-        unsigned long long u[5] = {0, 0, 0, 0, 0};
 #pragma unroll
         for (int k = 0; k < kThreads / 64; k++) {
-            r0 += redd[k][0];
-            r1 += redd[k][1];
-#pragma unroll
-            for (int q = 0; q < 5; q++)
-                u[q] += redu[k][q];
+            own.retained += redd[k][0]; own.total += redd[k][1];
+            own.kept += redu[k][0]; own.rowv += redu[k][1]; own.colv += redu[k][2]; own.rowne += redu[k][3]; own.colne += redu[k][4];
         }
-        out->retained = r0; out->total = r1;
-        out->kept = u[0]; out->rowv = u[1]; out->colv = u[2]; out->rowne = u[3]; out->colne = u[4];
     }
+    hand_over_score<kThreads>(out, own);
 }
 
 struct ScoreReduceArgs {
@@ -1124,6 +1123,22 @@ int hip_fail(hipError_t e, const char *what)
 // One-shot profiling events (tmask_profile_next): recorded around the main kernel of the next call.
 thread_local hipEvent_t g_prof_start = nullptr, g_prof_stop = nullptr;
 
+// The tags of a launch that adds up its own partial results: two numbers that no other launch of this process has beside
+// each other, scattered (splitmix64 of a counter that starts anywhere), neither zero, not equal.
+Tags draw_tags()
+{
+    static std::atomic<uint64_t> next{(uint64_t)std::chrono::steady_clock::now().time_since_epoch().count() ^ (uint64_t)(uintptr_t)&g_prof_start};
+    for (;;) {
+        uint64_t z = next.fetch_add(0x9E3779B97F4A7C15ull, std::memory_order_relaxed);
+        z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+        z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+        z ^= z >> 31;
+        const Tags t{(uint32_t)z, (uint32_t)(z >> 32)};
+        if (t.a && t.b && t.a != t.b)
+            return t;
+    }
+}
+
 // Scratch memory of tmask_approx_noalloc: the per-workgroup partial sums of the objective, which the other entry
 // points keep in the caller's workspace.  One copy per GPU, held until the process ends; every call on a GPU shares
 // it, so calls that overlap on one GPU race.  Nothing in it has to start at zero: every partial a call reads was
@@ -1220,7 +1235,7 @@ static int run_mask(const tmask_mat *mats, int n_mats, int dt, int N, int M, int
     // threshold from a sorting network
     const bool general_n = 2 * N != M && M == 16 && SOLVER != kSolveExact && !(SOLVER == kSolveApprox && dt == kBF16);
     if (fit == kFitColumns || general_n)     // also M = 32, or a matrix that the strips cannot read
-        return cw_run_mask(SOLVER == kSolveApprox ? 0 : SOLVER == kSolveExact ? 1 : 2, mats, n_mats, dt, N, M, mf, ws,
+        return cw_run_mask(SOLVER == kSolveApprox ? 0 : SOLVER == kSolveExact ? 1 : 2, mats, n_mats, dt, N, M, mf, ws, !own_scratch,
                            (hipStream_t)stream_);
     if constexpr (SOLVER != kSolveRow1D) {       // without objectives the call is one launch anyway
         bool whole = M == 4 && N == 2 && want_obj && n_mats <= kWholeMats;
@@ -1299,19 +1314,26 @@ static int run_mask(const tmask_mat *mats, int n_mats, int dt, int N, int M, int
         ReduceArgs rargs;
         memset(&args, 0, sizeof args);
         memset(&rargs, 0, sizeof rargs);
-        uint32_t tiles = 0;
+        uint32_t tiles = 0, most = 0;
         for (int k = 0; k < nb; k++) {
             const tmask_mat &t = mats[first + k];
             const HostMat h{t.w, t.rows, t.cols, t.ld, t.mask, t.mask_ld, t.objective};
             fill_desc(args.m[k], h, sdt, M, tiles);
             rargs.objective[k] = t.objective;
             rargs.tile0[k] = tiles;
-            tiles += tiles_of(args.m[k].n_strips * unit_split);
+            args.m[k].aux = t.objective;
+            args.m[k].pad = tiles_of(args.m[k].n_strips * unit_split);
+            most = most > args.m[k].pad ? most : args.m[k].pad;
+            tiles += args.m[k].pad;
         }
         rargs.tile0[nb] = tiles;
         fill_coarse(args.ci, rargs.tile0, nb, tiles);
         args.n_mats = (uint32_t)nb; args.K = (uint32_t)(M - N); args.N = (uint32_t)N;
         args.partial0 = partial0; args.partials = want_obj ? ws : nullptr;
+        // the array of tmask_approx_noalloc has room for the sums alone, and calls that overlap share it
+        const bool one_launch = want_obj && !own_scratch && adds_up_itself(tiles, most, kThreads, false);
+        if (one_launch)
+            args.tags = draw_tags();
         {
             ProfileScope prof(stream, first + kMaxBatch >= n_mats);
             hipLaunchKernelGGL(kern, dim3(tiles), dim3(kThreads), 0, stream, args);
@@ -1319,7 +1341,7 @@ static int run_mask(const tmask_mat *mats, int n_mats, int dt, int N, int M, int
         hipError_t e = hipGetLastError();
         if (e != hipSuccess)
             return hip_fail(e, "mask kernel launch");
-        if (want_obj) {
+        if (want_obj && !one_launch) {
             rargs.n_mats = (uint32_t)nb; rargs.partial0 = partial0; rargs.partials = (const double *)ws;
             enqueue_objective_reduce(rargs, nb, stream);
             e = hipGetLastError();
@@ -1435,7 +1457,7 @@ int tmask_score(const tmask_mat *mats, int n_mats, tmask_dtype dt, int N, int M,
         ScoreReduceArgs rargs;
         memset(&args, 0, sizeof args);
         memset(&rargs, 0, sizeof rargs);
-        uint32_t tiles = 0;
+        uint32_t tiles = 0, most = 0;
         for (int k = 0; k < nb; k++) {
             const tmask_mat &t = mats[first + k];
             const HostMat h{t.w, t.rows, t.cols, t.ld, t.mask, t.mask_ld, nullptr};
@@ -1443,12 +1465,19 @@ int tmask_score(const tmask_mat *mats, int n_mats, tmask_dtype dt, int N, int M,
             args.m[k].aux = per_block_obj ? (void *)(per_block_obj + block0) : nullptr;
             block0 += (size_t)(t.rows / M) * (size_t)(t.cols / M);
             rargs.tile0[k] = tiles;
-            tiles += tiles_of(args.m[k].n_strips);
+            args.m[k].pad = tiles_of(args.m[k].n_strips);
+            most = most > args.m[k].pad ? most : args.m[k].pad;
+            tiles += args.m[k].pad;
         }
         rargs.tile0[nb] = tiles;
         fill_coarse(args.ci, rargs.tile0, nb, tiles);
         args.n_mats = (uint32_t)nb; args.K = (uint32_t)(M - N); args.N = (uint32_t)N;
         args.partial0 = partial0; args.partials = workspace;
+        static_assert(sizeof(ScorePartial) == sizeof(tmask_score_out), "the last workgroup of a matrix writes its result");
+        args.score = (ScorePartial *)(out + first);
+        const bool one_launch = adds_up_itself(tiles, most, kThreads, true);
+        if (one_launch)
+            args.tags = draw_tags();
         {
             ProfileScope prof(stream, first + kMaxBatch >= n_mats);
             hipLaunchKernelGGL(kern, dim3(tiles), dim3(kThreads), 0, stream, args);
@@ -1456,8 +1485,7 @@ int tmask_score(const tmask_mat *mats, int n_mats, tmask_dtype dt, int N, int M,
         hipError_t e = hipGetLastError();
         if (e != hipSuccess)
             return hip_fail(e, "score kernel launch");
-        const int rc = launch_score_reduce(rargs.tile0, nb, partial0, workspace, out + first, stream);
-        if (rc)
+        if (!one_launch && (rc = launch_score_reduce(rargs.tile0, nb, partial0, workspace, out + first, stream)))
             return rc;
         partial0 += tiles;
     }
@@ -1705,7 +1733,7 @@ int tmask_approx_pack(const tmask_fused_desc *descs, int n, tmask_dtype dt, int 
         ReduceArgs rargs;
         memset(&args, 0, sizeof args);
         memset(&rargs, 0, sizeof rargs);
-        uint32_t tiles = 0;
+        uint32_t tiles = 0, most = 0;
         for (int k = 0; k < nb; k++) {
             const tmask_fused_desc &p = descs[first + k];
             PackDev &d = args.d[k];
@@ -1715,11 +1743,17 @@ int tmask_approx_pack(const tmask_fused_desc *descs, int n, tmask_dtype dt, int 
             d.tile0 = tiles;
             rargs.objective[k] = p.objective;
             rargs.tile0[k] = tiles;
-            tiles += d.tiles_x * ((d.rows + kPack4Rows - 1) / kPack4Rows);
+            args.objective[k] = p.objective;
+            const uint32_t own = d.tiles_x * ((d.rows + kPack4Rows - 1) / kPack4Rows);
+            most = most > own ? most : own;
+            tiles += own;
         }
         rargs.tile0[nb] = tiles;
         fill_coarse(args.ci, rargs.tile0, nb, tiles);
         args.n = (uint32_t)nb; args.partial0 = partial0; args.partials = want_obj ? workspace : nullptr;
+        const bool one_launch = want_obj && adds_up_itself(tiles, most, kThreads, false) && workspace_bytes >= 2 * partials_bytes(kPack4Rows);
+        if (one_launch)
+            args.tags = draw_tags();
         {
             ProfileScope prof(stream, first + kMaxPackBatch >= n);
             hipLaunchKernelGGL(kern, dim3(tiles), dim3(kThreads), (fused24 && dt == TMASK_F32 && !small) ? kPack4LdsReserveFusedF32 : 0, stream,
@@ -1728,7 +1762,7 @@ int tmask_approx_pack(const tmask_fused_desc *descs, int n, tmask_dtype dt, int 
         hipError_t e = hipGetLastError();
         if (e != hipSuccess)
             return hip_fail(e, "fused approx+pack kernel launch");
-        if (want_obj) {
+        if (want_obj && !one_launch) {
             rargs.n_mats = (uint32_t)nb; rargs.partial0 = partial0; rargs.partials = (const double *)workspace;
             enqueue_objective_reduce(rargs, nb, stream);
             e = hipGetLastError();

@@ -45,8 +45,10 @@ struct FusedArgs {
     uint32_t n;
     uint32_t partial0;          // index of this launch's first partial in the workspace
     void *partials;             // one double per workgroup, or null
+    Tags tags;
+    double *objective[kMaxPackBatch];
 };
-static_assert(sizeof(FusedArgs) <= 16384 + 2048, "descriptor table is sized to stay a small kernel argument");
+static_assert(sizeof(FusedArgs) <= 16384 + 4096, "descriptor table is sized to stay a small kernel argument");
 
 
 // Tile number inside a matrix -> tile coordinates, for the kernels that write W^T in short runs per column.
@@ -79,6 +81,13 @@ __device__ __forceinline__ int find_pack_desc(const Args &args, uint32_t tile)
             hi = mid - 1;
     }
     return lo;
+}
+
+// The objective of the one-pass kernels; d: the matrix, number k of the launch, in tiles TR rows high.
+template <int TR>
+__device__ __forceinline__ Handover objective_of(const FusedArgs &args, const PackDev &d, int k, uint32_t tile)
+{
+    return handover<8, 2>(args.partials, args.tags, args.partial0 + tile, tile - d.tile0, d.tiles_x * ((d.rows + TR - 1u) / TR), args.objective[k]);
 }
 
 template <uint32_t ADJ = 1>

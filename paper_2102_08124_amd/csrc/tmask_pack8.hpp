@@ -185,7 +185,11 @@ __global__ __launch_bounds__(kThreads) void pack48_bf16_kernel(const ARGS args)
     }
 
     const uint32_t tile = blockIdx.x;
-    const PackDev d = args.d[find_pack_desc(args, tile)];
+    const int which = find_pack_desc(args, tile);
+    const PackDev d = args.d[which];
+    Handover out;
+    if constexpr (APPROX)
+        out = objective_of<TR>(args, d, which, tile);
     const uint32_t tl = tile - d.tile0;
     uint32_t ty, tx;
     tile_coords<APPROX ? 1 : 2>(tl, d.tiles_x, (d.rows + TR - 1) / TR, kPackRunRows / TR, ty, tx);
@@ -378,10 +382,8 @@ __global__ __launch_bounds__(kThreads) void pack48_bf16_kernel(const ARGS args)
 
     pack48_copy_out<ES, TR, TC, TCP, IDXB, IDXTB, kThreads>(d, row0, col0, OT, IDXT, IDX);
     if constexpr (APPROX) {
-        if (args.partials) {
-            const double t = block_sum_f32(acc, red);
-            if (threadIdx.x == 0)
-                ((double *)args.partials)[args.partial0 + tile] = t;
+        if (out.dst) {
+            hand_over<kThreads>(out, block_sum_f32(acc, red), red);
         }
     }
 }
@@ -478,7 +480,11 @@ __global__ __launch_bounds__(256) void pack48_f32_kernel(const ARGS args)
     }
 
     const uint32_t tile = blockIdx.x;
-    const PackDev d = args.d[find_pack_desc(args, tile)];
+    const int which = find_pack_desc(args, tile);
+    const PackDev d = args.d[which];
+    Handover out;
+    if constexpr (APPROX)
+        out = objective_of<TR>(args, d, which, tile);
     const uint32_t tl = tile - d.tile0;
     uint32_t ty, tx;
     tile_coords(tl, d.tiles_x, (d.rows + TR - 1) / TR, kPackRunRows / TR, ty, tx);
@@ -662,10 +668,8 @@ __global__ __launch_bounds__(256) void pack48_f32_kernel(const ARGS args)
     __syncthreads();
     pack48_copy_out<ES, TR, TC, TCP, IDXB, IDXTB, NT>(d, row0, col0, OT, IDXT, IDX);
     if constexpr (APPROX) {
-        if (args.partials) {
-            const double t = block_sum_f32(acc, red);
-            if (threadIdx.x == 0)
-                ((double *)args.partials)[args.partial0 + tile] = t;
+        if (out.dst) {
+            hand_over<kThreads>(out, block_sum_f32(acc, red), red);
         }
     }
 }
