@@ -1,4 +1,5 @@
-"""Thin ctypes binding over libtmask.so (include/tmask.h).
+"""Thin binding over libtmask.so (include/tmask.h): ctypes, and for the calls of a training or decoding loop the native
+module _calls (csrc/tmask_calls.cpp), which takes the usual arguments and leaves the others to the code here.
 
 Argument marshalling only: every step of the path runs in the HIP kernels.  PyTorch provides the
 device memory (tensors) and the stream; nothing here computes on tensors.  There is no CPU
@@ -7,6 +8,7 @@ fallback: if the library is missing or a call fails, an exception is raised.
 from __future__ import annotations
 
 import ctypes as C
+import importlib
 import os
 from typing import Optional, Sequence
 
@@ -14,6 +16,7 @@ import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libtmask.so")
+CALLS_PATH = os.path.join(_HERE, "_calls.so")
 
 TMASK_F32, TMASK_BF16 = 0, 1
 TMASK_MASK_U8, TMASK_MASK_BITS = 0, 1
@@ -75,15 +78,16 @@ class tmask_score_out(C.Structure):
 
 SCORE_OUT_BYTES = C.sizeof(tmask_score_out)
 _lib = None
+_calls = None
 
 
 def load_library():
     """Loads libtmask.so; raises if it has not been built (python -m paper_2102_08124_amd.build)."""
-    global _lib
+    global _lib, _calls
     if _lib is not None:
         return _lib
-    if not os.path.exists(LIB_PATH):
-        raise RuntimeError("libtmask.so is missing: build it with `python -m paper_2102_08124_amd.build` "
+    if not os.path.exists(LIB_PATH) or not os.path.exists(CALLS_PATH):
+        raise RuntimeError("libtmask.so or _calls.so is missing: build it with `python -m paper_2102_08124_amd.build` "
                            "(there is no fallback path)")
     L = C.CDLL(LIB_PATH)
     vp, ci, sz = C.c_void_p, C.c_int, C.c_size_t
@@ -123,6 +127,11 @@ def load_library():
     L.tmask_last_error.argtypes = []
     L.tmask_version.restype = ci
     L.tmask_version.argtypes = []
+    # addresses for the native calls
+    L.at = {name: C.cast(getattr(L, name), vp).value for name in
+            ("tmask_approx", "tmask_exact", "tmask_prune_1d", "tmask_apply_pack", "tmask_approx_pack", "tmask_approx_dense",
+             "tmask_score", "tmask_spmm24")}
+    _calls = importlib.import_module(__package__ + "._calls")
     _lib = L
     return L
 
@@ -264,16 +273,25 @@ def _ws_args(workspace):
     return C.c_void_p(workspace.data_ptr()), workspace.numel() * workspace.element_size()
 
 
-def _run_mask(fn, ws, masks, N, M, objective, mask_fmt, workspace, stream):
+def _call_batch(name, b, N, M, mask_fmt, workspace, stream):
+    L = _lib or load_library()
+    rc = _calls.batch(L.at[name], C.addressof(b.arr), b.n, b.dt, N, M, mask_fmt, workspace, stream)
+    if rc is None:
+        wp, wb = _ws_args(workspace)
+        rc = getattr(L, name)(b.arr, b.n, b.dt, N, M, mask_fmt, wp, wb, _stream_ptr(stream))
+    if rc != TMASK_OK:
+        _check(rc)
+
+
+def _run_mask(name, ws, masks, N, M, objective, mask_fmt, workspace, stream):
     b = ws if isinstance(ws, MatBatch) else MatBatch(ws, masks, objective)
-    wp, wb = _ws_args(workspace)
-    _check(fn(b.arr, b.n, b.dt, N, M, mask_fmt, wp, wb, _stream_ptr(stream)))
+    _call_batch(name, b, N, M, mask_fmt, workspace, stream)
 
 
 def tmask_approx(ws, masks, N: int, M: int, objective: Optional[torch.Tensor] = None,
                  mask_fmt: int = TMASK_MASK_U8, workspace: Optional[torch.Tensor] = None, stream=None) -> None:
     """Algorithm 1 on every M x M block of every matrix; masks (and objective[k]) are written in place."""
-    _run_mask(load_library().tmask_approx, ws, masks, N, M, objective, mask_fmt, workspace, stream)
+    _run_mask("tmask_approx", ws, masks, N, M, objective, mask_fmt, workspace, stream)
 
 
 def tmask_approx_noalloc(ws, masks, N: int, M: int, objective: Optional[torch.Tensor] = None,
@@ -286,27 +304,32 @@ def tmask_approx_noalloc(ws, masks, N: int, M: int, objective: Optional[torch.Te
 def tmask_exact(ws, masks, N: int, M: int, objective: Optional[torch.Tensor] = None,
                 mask_fmt: int = TMASK_MASK_U8, workspace: Optional[torch.Tensor] = None, stream=None) -> None:
     """Optimum of Eq. 3 on every block; masks (and objective[k]) are written in place."""
-    _run_mask(load_library().tmask_exact, ws, masks, N, M, objective, mask_fmt, workspace, stream)
+    _run_mask("tmask_exact", ws, masks, N, M, objective, mask_fmt, workspace, stream)
 
 
 def tmask_prune_1d(ws, masks, N: int, M: int, objective: Optional[torch.Tensor] = None,
                    mask_fmt: int = TMASK_MASK_U8, workspace: Optional[torch.Tensor] = None, stream=None) -> None:
     """Structured N:M magnitude pruning along rows (non-transposable baseline); same arguments as tmask_approx."""
-    _run_mask(load_library().tmask_prune_1d, ws, masks, N, M, objective, mask_fmt, workspace, stream)
+    _run_mask("tmask_prune_1d", ws, masks, N, M, objective, mask_fmt, workspace, stream)
 
 
 def tmask_score(ws, masks, N: int, M: int, out: torch.Tensor, per_block_obj: Optional[torch.Tensor] = None,
                 mask_fmt: int = TMASK_MASK_U8, workspace: Optional[torch.Tensor] = None, stream=None) -> None:
     """out: CUDA uint8 tensor of len(ws) * SCORE_OUT_BYTES bytes (array of tmask_score_out)."""
     b = ws if isinstance(ws, MatBatch) else MatBatch(ws, masks, None)
+    L = _lib or load_library()
+    rc = _calls.score(L.at["tmask_score"], C.addressof(b.arr), b.n, b.dt, N, M, mask_fmt, out, b.n * SCORE_OUT_BYTES, per_block_obj,
+                      workspace, stream)
+    if rc is not None:
+        return None if rc == TMASK_OK else _check(rc)
     if out.numel() * out.element_size() < b.n * SCORE_OUT_BYTES or not out.is_cuda or not out.is_contiguous():
         raise ValueError("out is too small")
     if per_block_obj is not None and (per_block_obj.dtype != torch.float32 or not per_block_obj.is_contiguous()):
         raise ValueError("per_block_obj must be contiguous float32")
     wp, wb = _ws_args(workspace)
-    _check(load_library().tmask_score(b.arr, b.n, b.dt, N, M, mask_fmt, C.c_void_p(out.data_ptr()),
-                                      C.c_void_p(per_block_obj.data_ptr()) if per_block_obj is not None else None,
-                                      wp, wb, _stream_ptr(stream)))
+    _check(L.tmask_score(b.arr, b.n, b.dt, N, M, mask_fmt, C.c_void_p(out.data_ptr()),
+                         C.c_void_p(per_block_obj.data_ptr()) if per_block_obj is not None else None,
+                         wp, wb, _stream_ptr(stream)))
 
 
 def read_scores(out: torch.Tensor, n: int):
@@ -339,22 +362,24 @@ def tmask_apply_pack(ws, masks, packed, N: int, M: int, mask_fmt: int = TMASK_MA
                      workspace: Optional[torch.Tensor] = None, stream=None) -> None:
     """packed[k] = (vals, idx, valsT, idxT) tensors for matrix k (see alloc_packed), written in place."""
     b = ws if isinstance(ws, PackBatch) else PackBatch(ws, masks, packed, N, M)
-    wp, wb = _ws_args(workspace)
-    _check(load_library().tmask_apply_pack(b.arr, b.n, b.dt, N, M, mask_fmt, wp, wb, _stream_ptr(stream)))
+    _call_batch("tmask_apply_pack", b, N, M, mask_fmt, workspace, stream)
 
 
 def tmask_approx_pack(ws, masks, packed, N: int, M: int, objective: Optional[torch.Tensor] = None,
                       mask_fmt: int = TMASK_MASK_U8, workspace: Optional[torch.Tensor] = None, stream=None) -> None:
     """Algorithm 1 and the compression of W and W^T in one call; masks may be None for 2:4 and for 4:8."""
     b = ws if isinstance(ws, FusedBatch) else FusedBatch(ws, masks, packed, N, M, objective)
-    wp, wb = _ws_args(workspace)
-    _check(load_library().tmask_approx_pack(b.arr, b.n, b.dt, N, M, mask_fmt, wp, wb, _stream_ptr(stream)))
+    _call_batch("tmask_approx_pack", b, N, M, mask_fmt, workspace, stream)
 
 
 def tmask_spmm24(vals: torch.Tensor, idx: torch.Tensor, rows: int, cols: int, x: torch.Tensor, y: torch.Tensor,
                  stream=None) -> None:
     """y[t][r] = sum_c x[t][c] * Wd[r][c] with Wd (rows x cols) given by its compressed 2:4 form (vals, idx).
     x: tokens x cols bfloat16 (row stride = leading dimension), y: tokens x rows float32 or bfloat16."""
+    L = _lib or load_library()
+    rc = _calls.spmm24(L.at["tmask_spmm24"], vals, idx, rows, cols, x, y, stream)
+    if rc is not None:
+        return None if rc == TMASK_OK else _check(rc)
     if x.dtype != torch.bfloat16 or vals.dtype != torch.bfloat16 or idx.dtype != torch.uint8:
         raise TypeError("vals and x must be bfloat16, idx uint8")
     if x.dim() != 2 or y.dim() != 2 or x.stride(1) != 1 or y.stride(1) != 1 or not (x.is_cuda and y.is_cuda):
@@ -364,8 +389,8 @@ def tmask_spmm24(vals: torch.Tensor, idx: torch.Tensor, rows: int, cols: int, x:
     if tuple(vals.shape) != (rows, cols // 2) or tuple(idx.shape) != (rows, cols // 8) or not vals.is_contiguous() \
             or not idx.is_contiguous():
         raise ValueError("vals must be rows x cols/2 and idx rows x cols/8, contiguous")
-    _check(load_library().tmask_spmm24(vals.data_ptr(), idx.data_ptr(), rows, cols, x.data_ptr(), x.stride(0),
-                                       y.data_ptr(), y.stride(0), x.shape[0], dtype_code(y), _stream_ptr(stream)))
+    _check(L.tmask_spmm24(vals.data_ptr(), idx.data_ptr(), rows, cols, x.data_ptr(), x.stride(0),
+                          y.data_ptr(), y.stride(0), x.shape[0], dtype_code(y), _stream_ptr(stream)))
 
 
 MD_KINDS = {"unstructured": 0, "structured": 1, "transposable": 2, "sequential": 3}
@@ -460,7 +485,12 @@ def tmask_approx_dense(ws, masks, outs, N: int, M: int, mask_fmt: int = TMASK_MA
     (outs[k] may be ws[k]); masks[k] receives the mask, or masks is None and no mask is written.  `ws` may be a
     DenseBatch (then masks and outs are ignored)."""
     arr, n, dt = (ws.arr, ws.n, ws.dt) if isinstance(ws, DenseBatch) else _dense_descs(ws, masks, outs)
-    _check(load_library().tmask_approx_dense(arr, n, dt, N, M, mask_fmt, _stream_ptr(stream)))
+    L = _lib or load_library()
+    rc = _calls.dense(L.at["tmask_approx_dense"], C.addressof(arr), n, dt, N, M, mask_fmt, stream)
+    if rc is None:
+        rc = L.tmask_approx_dense(arr, n, dt, N, M, mask_fmt, _stream_ptr(stream))
+    if rc != TMASK_OK:
+        _check(rc)
 
 
 def tmask_prune_1d_dense(ws, masks, outs, N: int, M: int, absorb_mean: bool = False,

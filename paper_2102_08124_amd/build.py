@@ -1,4 +1,4 @@
-"""Builds libtmask.so (the HIP kernels + C ABI) in-tree for gfx950 with hipcc.
+"""Builds libtmask.so (the HIP kernels + C ABI) in-tree for gfx950 with hipcc, and _calls.so (the native half of binding.py).
 
 Usage: python -m paper_2102_08124_amd.build [--force]
 """
@@ -7,10 +7,13 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libtmask.so")
+CALLS = os.path.join(HERE, "_calls.so")
+CALLS_SOURCE = os.path.join(CSRC, "tmask_calls.cpp")
 SOURCES = ["tmask_kernels.hip", "tmask_colwise.hip", "tmask_spmm.hip", "tmask_extras.hip"]
 HEADERS = ["tmask_device.hpp", "tmask_solvers.hpp", "tmask_pack.hpp", "tmask_approx4.hpp", "tmask_networks.hpp", "tmask_approx_sel.hpp", "tmask_pack4.hpp", "tmask_pack8.hpp", "tmask_exact_balance.hpp", "tmask_fused4.hpp", "tmask_spmm_choice.hpp", "tmask_host.hpp", os.path.join("..", "..", "include", "tmask.h")]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -27,9 +30,32 @@ def _stale() -> bool:
     return any(os.path.getmtime(os.path.join(CSRC, f)) > t for f in SOURCES + HEADERS)
 
 
+def build_calls(force: bool = False, verbose: bool = False) -> str:
+    """The extension module that turns tensors into arguments; links against the torch that will load it."""
+    if not force and os.path.exists(CALLS) and os.path.getmtime(CALLS) >= os.path.getmtime(CALLS_SOURCE):
+        return CALLS
+    import torch
+    root = os.path.dirname(torch.__file__)
+    tmp = CALLS + ".tmp%d" % os.getpid()
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+           "-I" + os.path.join(root, "include"), "-I" + os.path.join(root, "include", "torch", "csrc", "api", "include"),
+           "-I" + sysconfig.get_paths()["include"], "-I/opt/rocm/include", "-L" + os.path.join(root, "lib"), "-o", tmp, CALLS_SOURCE,
+           "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        sys.stderr.write(res.stdout + res.stderr)
+        raise RuntimeError("g++ failed compiling tmask_calls.cpp")
+    os.replace(tmp, CALLS)
+    return CALLS
+
+
 def build(force: bool = False, verbose: bool = False) -> str:
-    """Compile if sources are newer than the library (or always with force=True).  The translation units are
-    compiled side by side into _build/ (not tracked), then linked."""
+    """Compile what is older than its sources (or everything with force=True).  The translation units are compiled side by
+    side into _build/ (not tracked), then linked."""
+    build_calls(force, verbose)
     if not (force or _stale()):
         return LIB
     from concurrent.futures import ThreadPoolExecutor
