@@ -62,9 +62,10 @@ struct MatDev {
 // first workgroup (high half).  One load narrows the search to that range, usually a single matrix.
 constexpr int kCoarse = 256;
 
+template <int N>
 struct CoarseIndex {
     uint32_t shift;
-    uint32_t e[kCoarse];
+    uint32_t e[N];
 };
 
 // How the workgroups of a launch hand their partial results to the one that adds up those of a matrix: see take_words.
@@ -73,9 +74,14 @@ struct Tags {
     uint32_t a, b;
 };
 
-struct BatchArgs {
-    MatDev m[kMaxBatch];
-    CoarseIndex ci;
+// CAP matrices.  The arguments of a launch are copied to where the device reads them, 16 KB in about a microsecond, and a small
+// call has little else to do; so the kernels whose calls can be that short exist with a table of eight too.  Back to back, us: masked
+// copy 256^2 .. 1024^2 5.4 -> 4.2, optimal 2:4 of 512^2 5.4 -> 4.6, masks at 4:8 5.3 -> 5.0, mask, compression and score of
+// 1000 x 2052 22.7 -> 21.1; the slower ones (other N, the optimal masks at M = 8, 16) would gain 0.2 us of 14 or more.
+template <int CAP>
+struct BatchArgsOf {
+    MatDev m[CAP];
+    CoarseIndex<CAP == kMaxBatch ? kCoarse : 16> ci;
     uint32_t n_mats;
     uint32_t K;          // pruned per row/column = M - N
     uint32_t N;
@@ -84,6 +90,10 @@ struct BatchArgs {
     Tags tags;
     struct ScorePartial *score;   // score: the results, one per matrix of the launch
 };
+using BatchArgs = BatchArgsOf<kMaxBatch>;
+
+constexpr int kFewMats = 8;
+using FewArgs = BatchArgsOf<kFewMats>;
 
 // What a workgroup of the score kernels leaves to be added up; the results of the call have the same layout.
 struct ScorePartial {
@@ -390,7 +400,8 @@ __device__ __forceinline__ void hand_over(const Handover &h, double t, double *r
 }
 
 // The objective of the strip kernels.
-__device__ __forceinline__ Handover objective_of(const BatchArgs &args, const MatDev &md, uint32_t tile)
+template <int CAP>
+__device__ __forceinline__ Handover objective_of(const BatchArgsOf<CAP> &args, const MatDev &md, uint32_t tile)
 {
     return handover<8, 2>(args.partials, args.tags, args.partial0 + tile, tile - md.tile0, md.pad, md.aux);
 }
@@ -461,7 +472,8 @@ __device__ __forceinline__ void hand_over_score(const Handover &h, ScoreSums own
 // ---- tile addressing ----------------------------------------------------------------------------
 
 // Which matrix of the batch does workgroup `tile` belong to (largest m with tile0[m] <= tile).
-__device__ __forceinline__ int find_matrix(const BatchArgs &a, uint32_t tile)
+template <int CAP>
+__device__ __forceinline__ int find_matrix(const BatchArgsOf<CAP> &a, uint32_t tile)
 {
     const uint32_t e = a.ci.e[tile >> a.ci.shift];
     int lo = (int)(e & 0xFFFFu), hi = (int)(e >> 16);

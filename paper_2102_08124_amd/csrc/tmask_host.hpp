@@ -63,14 +63,15 @@ size_t cw_workgroups(int64_t rows, int64_t cols, int M);     // workgroups (= pa
 
 // Fills the coarse index of a launch (see CoarseIndex): first0[k] = first workgroup of matrix k, n matrices,
 // `total` workgroups.
-inline void fill_coarse(CoarseIndex &ci, const uint32_t *first0, int n, uint32_t total)
+template <int N>
+inline void fill_coarse(CoarseIndex<N> &ci, const uint32_t *first0, int n, uint32_t total)
 {
     uint32_t shift = 0;
-    while (total > 0 && ((total - 1u) >> shift) >= (uint32_t)kCoarse)
+    while (total > 0 && ((total - 1u) >> shift) >= (uint32_t)N)
         shift++;
     ci.shift = shift;
     const uint32_t buckets = total ? ((total - 1u) >> shift) + 1u : 1u;
-    uint32_t first[kCoarse + 1];
+    uint32_t first[N + 1];
     int m = 0;
     for (uint32_t b = 0; b < buckets; b++) {
         const uint32_t t = b << shift;
@@ -79,7 +80,7 @@ inline void fill_coarse(CoarseIndex &ci, const uint32_t *first0, int n, uint32_t
         first[b] = (uint32_t)m;
     }
     first[buckets] = (uint32_t)(n - 1);
-    for (uint32_t b = 0; b < (uint32_t)kCoarse; b++)
+    for (uint32_t b = 0; b < (uint32_t)N; b++)
         ci.e[b] = b < buckets ? (first[b] | (first[b + 1] << 16)) : 0u;
 }
 

@@ -97,8 +97,8 @@ __device__ __forceinline__ float approx24_strip(const MatDev &md, uint32_t s)
 }
 
 // tmask_approx for 2:4: same tiling as mask_kernel.
-template <int DT, int FMT>
-__global__ __launch_bounds__(kThreads) void approx24_kernel(const BatchArgs args)
+template <int DT, int FMT, typename Args>
+__global__ __launch_bounds__(kThreads) void approx24_kernel(const Args args)
 {
     __shared__ double red[kThreads / 64];
     const uint32_t tile = blockIdx.x;
@@ -115,8 +115,8 @@ __global__ __launch_bounds__(kThreads) void approx24_kernel(const BatchArgs args
 // tmask_approx for fp32 with N = M/2, M = 8 or 16: thresholds on magnitudes; a wavefront in which some
 // line has a tie across its cut redoes its strips with the form that resolves ties by position (uniform branch).
 // GENERAL (M = 8): any N, thresholds read from the sorted line; ties send the wavefront to the rank form.
-template <int M, int FMT, bool GENERAL = false>
-__global__ __launch_bounds__(kThreads, (M == 16 && FMT == kMaskBits) ? 4 : 1) void approx_sel_f32_kernel(const BatchArgs args)
+template <int M, int FMT, bool GENERAL, typename Args>
+__global__ __launch_bounds__(kThreads, (M == 16 && FMT == kMaskBits) ? 4 : 1) void approx_sel_f32_kernel(const Args args)
 {
     using Ge = Geo<kF32, M>;
     __shared__ double red[kThreads / 64];
@@ -215,8 +215,8 @@ __device__ __forceinline__ float exact24_strip(const MatDev &md, uint32_t s)
     return sum;
 }
 
-template <int DT, int FMT, int NK = 2>
-__global__ __launch_bounds__(kThreads) void exact24_kernel(const BatchArgs args)
+template <int DT, int FMT, int NK, typename Args>
+__global__ __launch_bounds__(kThreads) void exact24_kernel(const Args args)
 {
     __shared__ double red[kThreads / 64];
     const uint32_t tile = blockIdx.x;
@@ -265,8 +265,8 @@ __global__ __launch_bounds__(kWholeThreads) void whole24_kernel(const WholeArgs 
 
 // tmask_approx for bf16 with N = M/2, M = 8 or 16: thresholds from min/max networks on unique keys.  GENERAL: any N,
 // the threshold read from the sorted line at index K = M - N (8192^2 3:8: 40 us; 63 us in the rank form).
-template <int M, int FMT, bool GENERAL = false>
-__global__ __launch_bounds__(kThreads) void approx_sel_bf16_kernel(const BatchArgs args)
+template <int M, int FMT, bool GENERAL, typename Args>
+__global__ __launch_bounds__(kThreads) void approx_sel_bf16_kernel(const Args args)
 {
     using Ge = Geo<kBF16, M>;
     __shared__ double red[kThreads / 64];
@@ -316,8 +316,8 @@ __global__ __launch_bounds__(kThreads) void approx_sel_bf16_kernel(const BatchAr
 // threshold on unique keys (row_half_keep_bf16) and only the raw rows need registers.
 enum { kDenseApprox = 0, kDenseApproxHalf = 1, kDenseRow1D = 2, kDenseRow1DAbsorb = 3, kDenseRow1DHalf = 4, kDenseRow1DHalfAbsorb = 5 };
 
-template <int DT, int M, int FMT, int MODE>
-__global__ __launch_bounds__(kThreads) void approx_dense_kernel(const BatchArgs args)
+template <int DT, int M, int FMT, int MODE, typename Args>
+__global__ __launch_bounds__(kThreads) void approx_dense_kernel(const Args args)
 {
     constexpr bool HALFN = MODE == kDenseApproxHalf;
     constexpr bool ROWHALF = MODE == kDenseRow1DHalf || MODE == kDenseRow1DHalfAbsorb;
@@ -635,8 +635,8 @@ __device__ __forceinline__ void score_strip_bf16_m4(const MatDev &md, StripPos p
     total = tot;
 }
 
-template <int DT, int M, int FMT>
-__global__ __launch_bounds__(kThreads, M == 4 && DT != kBF16N ? 8 : 1) void score_kernel(const BatchArgs args)
+template <int DT, int M, int FMT, typename Args>
+__global__ __launch_bounds__(kThreads, M == 4 && DT != kBF16N ? 8 : 1) void score_kernel(const Args args)
 {
     using Ge = Geo<DT, M>;
     constexpr int C = Ge::C, CL = Ge::CL;
@@ -1026,33 +1026,53 @@ static void fill_desc(MatDev &d, const HostMat &h, int sdt, int M, uint32_t tile
     d.tile0 = tile0; d.pad = 0;
 }
 
-typedef void (*batch_kernel_t)(const BatchArgs);
+// A kernel with the two sizes of its table; few may be null.
+struct BatchKernel {
+    void (*many)(const BatchArgs);
+    void (*few)(const FewArgs);
+};
+#define TMASK_BOTH(KERN, ...) BatchKernel{KERN<__VA_ARGS__, BatchArgs>, KERN<__VA_ARGS__, FewArgs>}
+#define TMASK_MANY(KERN, ...) BatchKernel{KERN<__VA_ARGS__>, nullptr}
 
-template <int SOLVER>
-static batch_kernel_t pick_mask_kernel(int dt, int M, int mf)
+// Calls go(table, kernel) with the table that a launch over n matrices takes, cleared.
+template <typename Go>
+static int with_table(const BatchKernel &k, int n, Go go)
 {
-#define TMASK_PICK(DT, MM, FM) \
-    if (dt == DT && M == MM && mf == FM) return mask_kernel<SOLVER, DT, MM, FM>;
-    TMASK_PICK(kF32, 4, kMaskU8) TMASK_PICK(kF32, 8, kMaskU8) TMASK_PICK(kF32, 16, kMaskU8)
-    TMASK_PICK(kBF16, 4, kMaskU8) TMASK_PICK(kBF16, 8, kMaskU8) TMASK_PICK(kBF16, 16, kMaskU8)
-    TMASK_PICK(kF32, 4, kMaskBits) TMASK_PICK(kF32, 8, kMaskBits) TMASK_PICK(kF32, 16, kMaskBits)
-    TMASK_PICK(kBF16, 4, kMaskBits) TMASK_PICK(kBF16, 8, kMaskBits) TMASK_PICK(kBF16, 16, kMaskBits)
-    TMASK_PICK(kBF16N, 4, kMaskU8) TMASK_PICK(kBF16N, 4, kMaskBits)
-#undef TMASK_PICK
-    return nullptr;
+    if (k.few && n <= kFewMats) {
+        FewArgs args;
+        memset(&args, 0, sizeof args);
+        return go(args, k.few);
+    }
+    BatchArgs args;
+    memset(&args, 0, sizeof args);
+    return go(args, k.many);
 }
 
-static batch_kernel_t pick_score_kernel(int dt, int M, int mf)
+template <int SOLVER>
+static BatchKernel pick_mask_kernel(int dt, int M, int mf)
 {
 #define TMASK_PICK(DT, MM, FM) \
-    if (dt == DT && M == MM && mf == FM) return score_kernel<DT, MM, FM>;
+    if (dt == DT && M == MM && mf == FM) return TMASK_MANY(mask_kernel, SOLVER, DT, MM, FM);
     TMASK_PICK(kF32, 4, kMaskU8) TMASK_PICK(kF32, 8, kMaskU8) TMASK_PICK(kF32, 16, kMaskU8)
     TMASK_PICK(kBF16, 4, kMaskU8) TMASK_PICK(kBF16, 8, kMaskU8) TMASK_PICK(kBF16, 16, kMaskU8)
     TMASK_PICK(kF32, 4, kMaskBits) TMASK_PICK(kF32, 8, kMaskBits) TMASK_PICK(kF32, 16, kMaskBits)
     TMASK_PICK(kBF16, 4, kMaskBits) TMASK_PICK(kBF16, 8, kMaskBits) TMASK_PICK(kBF16, 16, kMaskBits)
     TMASK_PICK(kBF16N, 4, kMaskU8) TMASK_PICK(kBF16N, 4, kMaskBits)
 #undef TMASK_PICK
-    return nullptr;
+    return BatchKernel{nullptr, nullptr};
+}
+
+static BatchKernel pick_score_kernel(int dt, int M, int mf)
+{
+#define TMASK_PICK(DT, MM, FM) \
+    if (dt == DT && M == MM && mf == FM) return TMASK_BOTH(score_kernel, DT, MM, FM);
+    TMASK_PICK(kF32, 4, kMaskU8) TMASK_PICK(kF32, 8, kMaskU8) TMASK_PICK(kF32, 16, kMaskU8)
+    TMASK_PICK(kBF16, 4, kMaskU8) TMASK_PICK(kBF16, 8, kMaskU8) TMASK_PICK(kBF16, 16, kMaskU8)
+    TMASK_PICK(kF32, 4, kMaskBits) TMASK_PICK(kF32, 8, kMaskBits) TMASK_PICK(kF32, 16, kMaskBits)
+    TMASK_PICK(kBF16, 4, kMaskBits) TMASK_PICK(kBF16, 8, kMaskBits) TMASK_PICK(kBF16, 16, kMaskBits)
+    TMASK_PICK(kBF16N, 4, kMaskU8) TMASK_PICK(kBF16N, 4, kMaskBits)
+#undef TMASK_PICK
+    return BatchKernel{nullptr, nullptr};
 }
 
 // Whether a launch over these matrices has at most `per_cu` tiles of TR x TC for a compute unit, so that tiles of half the
@@ -1246,105 +1266,106 @@ static int run_mask(const tmask_mat *mats, int n_mats, int dt, int N, int M, int
         if (whole)
             return run_whole<SOLVER>(mats, n_mats, sdt, mf, (hipStream_t)stream_);
     }
-    batch_kernel_t kern = nullptr;
+    BatchKernel kern{nullptr, nullptr};
     if constexpr (SOLVER != kSolveExact)      // exact: enumeration at M = 4, the balanced kernel at M = 8, 16 (below)
         kern = pick_mask_kernel<SOLVER>(sdt, M, mf);
     if (SOLVER == kSolveApprox && M == 4 && N == 2) {
         if (sdt == kF32)
-            kern = mf == kMaskU8 ? approx24_kernel<kF32, kMaskU8> : approx24_kernel<kF32, kMaskBits>;
+            kern = mf == kMaskU8 ? TMASK_BOTH(approx24_kernel, kF32, kMaskU8) : TMASK_BOTH(approx24_kernel, kF32, kMaskBits);
         else if (sdt == kBF16N)
-            kern = mf == kMaskU8 ? approx24_kernel<kBF16N, kMaskU8> : approx24_kernel<kBF16N, kMaskBits>;
+            kern = mf == kMaskU8 ? TMASK_BOTH(approx24_kernel, kBF16N, kMaskU8) : TMASK_BOTH(approx24_kernel, kBF16N, kMaskBits);
         else
-            kern = mf == kMaskU8 ? approx24_kernel<kBF16, kMaskU8> : approx24_kernel<kBF16, kMaskBits>;
+            kern = mf == kMaskU8 ? TMASK_BOTH(approx24_kernel, kBF16, kMaskU8) : TMASK_BOTH(approx24_kernel, kBF16, kMaskBits);
     }
     if (SOLVER == kSolveExact && M == 4 && N == 2) {
         if (sdt == kF32)
-            kern = mf == kMaskU8 ? exact24_kernel<kF32, kMaskU8> : exact24_kernel<kF32, kMaskBits>;
+            kern = mf == kMaskU8 ? TMASK_BOTH(exact24_kernel, kF32, kMaskU8, 2) : TMASK_BOTH(exact24_kernel, kF32, kMaskBits, 2);
         else if (sdt == kBF16N)
-            kern = mf == kMaskU8 ? exact24_kernel<kBF16N, kMaskU8> : exact24_kernel<kBF16N, kMaskBits>;
+            kern = mf == kMaskU8 ? TMASK_BOTH(exact24_kernel, kBF16N, kMaskU8, 2) : TMASK_BOTH(exact24_kernel, kBF16N, kMaskBits, 2);
         else
-            kern = mf == kMaskU8 ? exact24_kernel<kBF16, kMaskU8> : exact24_kernel<kBF16, kMaskBits>;
+            kern = mf == kMaskU8 ? TMASK_BOTH(exact24_kernel, kBF16, kMaskU8, 2) : TMASK_BOTH(exact24_kernel, kBF16, kMaskBits, 2);
     }
     if (SOLVER == kSolveExact && M == 4 && N == 1) {
         if (sdt == kF32)
-            kern = mf == kMaskU8 ? exact24_kernel<kF32, kMaskU8, 1> : exact24_kernel<kF32, kMaskBits, 1>;
+            kern = mf == kMaskU8 ? TMASK_MANY(exact24_kernel, kF32, kMaskU8, 1, BatchArgs) : TMASK_MANY(exact24_kernel, kF32, kMaskBits, 1, BatchArgs);
         else if (sdt == kBF16N)
-            kern = mf == kMaskU8 ? exact24_kernel<kBF16N, kMaskU8, 1> : exact24_kernel<kBF16N, kMaskBits, 1>;
+            kern = mf == kMaskU8 ? TMASK_MANY(exact24_kernel, kBF16N, kMaskU8, 1, BatchArgs) : TMASK_MANY(exact24_kernel, kBF16N, kMaskBits, 1, BatchArgs);
         else
-            kern = mf == kMaskU8 ? exact24_kernel<kBF16, kMaskU8, 1> : exact24_kernel<kBF16, kMaskBits, 1>;
+            kern = mf == kMaskU8 ? TMASK_MANY(exact24_kernel, kBF16, kMaskU8, 1, BatchArgs) : TMASK_MANY(exact24_kernel, kBF16, kMaskBits, 1, BatchArgs);
     }
     if (SOLVER == kSolveExact && M == 4 && N == 3) {
         if (sdt == kF32)
-            kern = mf == kMaskU8 ? exact24_kernel<kF32, kMaskU8, 3> : exact24_kernel<kF32, kMaskBits, 3>;
+            kern = mf == kMaskU8 ? TMASK_MANY(exact24_kernel, kF32, kMaskU8, 3, BatchArgs) : TMASK_MANY(exact24_kernel, kF32, kMaskBits, 3, BatchArgs);
         else if (sdt == kBF16N)
-            kern = mf == kMaskU8 ? exact24_kernel<kBF16N, kMaskU8, 3> : exact24_kernel<kBF16N, kMaskBits, 3>;
+            kern = mf == kMaskU8 ? TMASK_MANY(exact24_kernel, kBF16N, kMaskU8, 3, BatchArgs) : TMASK_MANY(exact24_kernel, kBF16N, kMaskBits, 3, BatchArgs);
         else
-            kern = mf == kMaskU8 ? exact24_kernel<kBF16, kMaskU8, 3> : exact24_kernel<kBF16, kMaskBits, 3>;
+            kern = mf == kMaskU8 ? TMASK_MANY(exact24_kernel, kBF16, kMaskU8, 3, BatchArgs) : TMASK_MANY(exact24_kernel, kBF16, kMaskBits, 3, BatchArgs);
     }
     if (SOLVER == kSolveExact && (M == 8 || M == 16)) {
 #define TMASK_PICK(DT, MM, FM) \
     if (dt == DT && M == MM && mf == FM) \
-        kern = 2 * N == M ? exact_balanced_kernel<DT, MM, FM, false> : exact_balanced_kernel<DT, MM, FM, true>;
+        kern = 2 * N == M ? TMASK_MANY(exact_balanced_kernel, DT, MM, FM, false) : TMASK_MANY(exact_balanced_kernel, DT, MM, FM, true);
         TMASK_PICK(kF32, 8, kMaskU8) TMASK_PICK(kF32, 16, kMaskU8) TMASK_PICK(kBF16, 8, kMaskU8)
         TMASK_PICK(kBF16, 16, kMaskU8) TMASK_PICK(kF32, 8, kMaskBits) TMASK_PICK(kF32, 16, kMaskBits)
         TMASK_PICK(kBF16, 8, kMaskBits) TMASK_PICK(kBF16, 16, kMaskBits)
 #undef TMASK_PICK
     }
     if (SOLVER == kSolveApprox && dt == kF32 && M == 8 && N == 4)
-        kern = mf == kMaskU8 ? approx_sel_f32_kernel<8, kMaskU8> : approx_sel_f32_kernel<8, kMaskBits>;
+        kern = mf == kMaskU8 ? TMASK_BOTH(approx_sel_f32_kernel, 8, kMaskU8, false) : TMASK_BOTH(approx_sel_f32_kernel, 8, kMaskBits, false);
     if (SOLVER == kSolveApprox && dt == kF32 && M == 16 && N == 8)
-        kern = mf == kMaskU8 ? approx_sel_f32_kernel<16, kMaskU8> : approx_sel_f32_kernel<16, kMaskBits>;
+        kern = mf == kMaskU8 ? TMASK_BOTH(approx_sel_f32_kernel, 16, kMaskU8, false) : TMASK_BOTH(approx_sel_f32_kernel, 16, kMaskBits, false);
     if (SOLVER == kSolveApprox && dt == kBF16 && M == 16 && N != 8)
-        kern = mf == kMaskU8 ? approx_sel_bf16_kernel<16, kMaskU8, true> : approx_sel_bf16_kernel<16, kMaskBits, true>;
+        kern = mf == kMaskU8 ? TMASK_MANY(approx_sel_bf16_kernel, 16, kMaskU8, true, BatchArgs) : TMASK_MANY(approx_sel_bf16_kernel, 16, kMaskBits, true, BatchArgs);
     if (SOLVER == kSolveApprox && dt == kF32 && M == 8 && N != 4)
-        kern = mf == kMaskU8 ? approx_sel_f32_kernel<8, kMaskU8, true> : approx_sel_f32_kernel<8, kMaskBits, true>;
+        kern = mf == kMaskU8 ? TMASK_MANY(approx_sel_f32_kernel, 8, kMaskU8, true, BatchArgs) : TMASK_MANY(approx_sel_f32_kernel, 8, kMaskBits, true, BatchArgs);
     if (SOLVER == kSolveApprox && dt == kBF16 && M == 8 && N == 4)
-        kern = mf == kMaskU8 ? approx_sel_bf16_kernel<8, kMaskU8> : approx_sel_bf16_kernel<8, kMaskBits>;
+        kern = mf == kMaskU8 ? TMASK_BOTH(approx_sel_bf16_kernel, 8, kMaskU8, false) : TMASK_BOTH(approx_sel_bf16_kernel, 8, kMaskBits, false);
     if (SOLVER == kSolveApprox && dt == kBF16 && M == 16 && N == 8)
-        kern = mf == kMaskU8 ? approx_sel_bf16_kernel<16, kMaskU8> : approx_sel_bf16_kernel<16, kMaskBits>;
+        kern = mf == kMaskU8 ? TMASK_BOTH(approx_sel_bf16_kernel, 16, kMaskU8, false) : TMASK_BOTH(approx_sel_bf16_kernel, 16, kMaskBits, false);
     if (SOLVER == kSolveApprox && dt == kBF16 && M == 8 && N != 4)
-        kern = mf == kMaskU8 ? approx_sel_bf16_kernel<8, kMaskU8, true> : approx_sel_bf16_kernel<8, kMaskBits, true>;
+        kern = mf == kMaskU8 ? TMASK_MANY(approx_sel_bf16_kernel, 8, kMaskU8, true, BatchArgs) : TMASK_MANY(approx_sel_bf16_kernel, 8, kMaskBits, true, BatchArgs);
     // the exact kernel for bf16 8:16 gives a lane half a strip: twice the workgroups
     const uint32_t unit_split = (SOLVER == kSolveExact && exact_half_strips(dt, M)) ? 2u : 1u;
     hipStream_t stream = (hipStream_t)stream_;
     uint32_t partial0 = 0;
     for (int first = 0; first < n_mats; first += kMaxBatch) {
         const int nb = n_mats - first < kMaxBatch ? n_mats - first : kMaxBatch;
-        BatchArgs args;
         ReduceArgs rargs;
-        memset(&args, 0, sizeof args);
-        memset(&rargs, 0, sizeof rargs);
         uint32_t tiles = 0, most = 0;
-        for (int k = 0; k < nb; k++) {
-            const tmask_mat &t = mats[first + k];
-            const HostMat h{t.w, t.rows, t.cols, t.ld, t.mask, t.mask_ld, t.objective};
-            fill_desc(args.m[k], h, sdt, M, tiles);
-            rargs.objective[k] = t.objective;
-            rargs.tile0[k] = tiles;
-            args.m[k].aux = t.objective;
-            args.m[k].pad = tiles_of(args.m[k].n_strips * unit_split);
-            most = most > args.m[k].pad ? most : args.m[k].pad;
-            tiles += args.m[k].pad;
-        }
-        rargs.tile0[nb] = tiles;
-        fill_coarse(args.ci, rargs.tile0, nb, tiles);
-        args.n_mats = (uint32_t)nb; args.K = (uint32_t)(M - N); args.N = (uint32_t)N;
-        args.partial0 = partial0; args.partials = want_obj ? ws : nullptr;
-        // the array of tmask_approx_noalloc has room for the sums alone, and calls that overlap share it
-        const bool one_launch = want_obj && !own_scratch && adds_up_itself(tiles, most, kThreads, false);
-        if (one_launch)
-            args.tags = draw_tags();
-        {
-            ProfileScope prof(stream, first + kMaxBatch >= n_mats);
-            hipLaunchKernelGGL(kern, dim3(tiles), dim3(kThreads), 0, stream, args);
-        }
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess)
-            return hip_fail(e, "mask kernel launch");
+        bool one_launch = false;
+        rc = with_table(kern, nb, [&](auto &args, auto kernel) -> int {
+            for (int k = 0; k < nb; k++) {
+                const tmask_mat &t = mats[first + k];
+                const HostMat h{t.w, t.rows, t.cols, t.ld, t.mask, t.mask_ld, t.objective};
+                fill_desc(args.m[k], h, sdt, M, tiles);
+                rargs.objective[k] = t.objective;
+                rargs.tile0[k] = tiles;
+                args.m[k].aux = t.objective;
+                args.m[k].pad = tiles_of(args.m[k].n_strips * unit_split);
+                most = most > args.m[k].pad ? most : args.m[k].pad;
+                tiles += args.m[k].pad;
+            }
+            rargs.tile0[nb] = tiles;
+            fill_coarse(args.ci, rargs.tile0, nb, tiles);
+            args.n_mats = (uint32_t)nb; args.K = (uint32_t)(M - N); args.N = (uint32_t)N;
+            args.partial0 = partial0; args.partials = want_obj ? ws : nullptr;
+            // the array of tmask_approx_noalloc has room for the sums alone, and calls that overlap share it
+            one_launch = want_obj && !own_scratch && adds_up_itself(tiles, most, kThreads, false);
+            if (one_launch)
+                args.tags = draw_tags();
+            {
+                ProfileScope prof(stream, first + kMaxBatch >= n_mats);
+                hipLaunchKernelGGL(kernel, dim3(tiles), dim3(kThreads), 0, stream, args);
+            }
+            const hipError_t e = hipGetLastError();
+            return e == hipSuccess ? TMASK_OK : hip_fail(e, "mask kernel launch");
+        });
+        if (rc)
+            return rc;
         if (want_obj && !one_launch) {
             rargs.n_mats = (uint32_t)nb; rargs.partial0 = partial0; rargs.partials = (const double *)ws;
             enqueue_objective_reduce(rargs, nb, stream);
-            e = hipGetLastError();
+            const hipError_t e = hipGetLastError();
             if (e != hipSuccess)
                 return hip_fail(e, "objective reduce launch");
         }
@@ -1447,45 +1468,46 @@ int tmask_score(const tmask_mat *mats, int n_mats, tmask_dtype dt, int N, int M,
     if (fit == kFitColumns)
         return cw_run_score(mats, n_mats, (int)dt, N, M, (int)mf, out, per_block_obj, workspace, (hipStream_t)hip_stream);
     const int sdt = strip_type((int)dt, fit);
-    const batch_kernel_t kern = pick_score_kernel(sdt, M, (int)mf);
+    const BatchKernel kern = pick_score_kernel(sdt, M, (int)mf);
     hipStream_t stream = (hipStream_t)hip_stream;
     uint32_t partial0 = 0;
     size_t block0 = 0;
     for (int first = 0; first < n_mats; first += kMaxBatch) {
         const int nb = n_mats - first < kMaxBatch ? n_mats - first : kMaxBatch;
-        BatchArgs args;
-        ScoreReduceArgs rargs;
-        memset(&args, 0, sizeof args);
-        memset(&rargs, 0, sizeof rargs);
+        uint32_t tile0[kMaxBatch + 1];
         uint32_t tiles = 0, most = 0;
-        for (int k = 0; k < nb; k++) {
-            const tmask_mat &t = mats[first + k];
-            const HostMat h{t.w, t.rows, t.cols, t.ld, t.mask, t.mask_ld, nullptr};
-            fill_desc(args.m[k], h, sdt, M, tiles);
-            args.m[k].aux = per_block_obj ? (void *)(per_block_obj + block0) : nullptr;
-            block0 += (size_t)(t.rows / M) * (size_t)(t.cols / M);
-            rargs.tile0[k] = tiles;
-            args.m[k].pad = tiles_of(args.m[k].n_strips);
-            most = most > args.m[k].pad ? most : args.m[k].pad;
-            tiles += args.m[k].pad;
-        }
-        rargs.tile0[nb] = tiles;
-        fill_coarse(args.ci, rargs.tile0, nb, tiles);
-        args.n_mats = (uint32_t)nb; args.K = (uint32_t)(M - N); args.N = (uint32_t)N;
-        args.partial0 = partial0; args.partials = workspace;
-        static_assert(sizeof(ScorePartial) == sizeof(tmask_score_out), "the last workgroup of a matrix writes its result");
-        args.score = (ScorePartial *)(out + first);
-        const bool one_launch = adds_up_itself(tiles, most, kThreads, true);
-        if (one_launch)
-            args.tags = draw_tags();
-        {
-            ProfileScope prof(stream, first + kMaxBatch >= n_mats);
-            hipLaunchKernelGGL(kern, dim3(tiles), dim3(kThreads), 0, stream, args);
-        }
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess)
-            return hip_fail(e, "score kernel launch");
-        if (!one_launch && (rc = launch_score_reduce(rargs.tile0, nb, partial0, workspace, out + first, stream)))
+        bool one_launch = false;
+        rc = with_table(kern, nb, [&](auto &args, auto kernel) -> int {
+            for (int k = 0; k < nb; k++) {
+                const tmask_mat &t = mats[first + k];
+                const HostMat h{t.w, t.rows, t.cols, t.ld, t.mask, t.mask_ld, nullptr};
+                fill_desc(args.m[k], h, sdt, M, tiles);
+                args.m[k].aux = per_block_obj ? (void *)(per_block_obj + block0) : nullptr;
+                block0 += (size_t)(t.rows / M) * (size_t)(t.cols / M);
+                tile0[k] = tiles;
+                args.m[k].pad = tiles_of(args.m[k].n_strips);
+                most = most > args.m[k].pad ? most : args.m[k].pad;
+                tiles += args.m[k].pad;
+            }
+            tile0[nb] = tiles;
+            fill_coarse(args.ci, tile0, nb, tiles);
+            args.n_mats = (uint32_t)nb; args.K = (uint32_t)(M - N); args.N = (uint32_t)N;
+            args.partial0 = partial0; args.partials = workspace;
+            static_assert(sizeof(ScorePartial) == sizeof(tmask_score_out), "the last workgroup of a matrix writes its result");
+            args.score = (ScorePartial *)(out + first);
+            one_launch = adds_up_itself(tiles, most, kThreads, true);
+            if (one_launch)
+                args.tags = draw_tags();
+            {
+                ProfileScope prof(stream, first + kMaxBatch >= n_mats);
+                hipLaunchKernelGGL(kernel, dim3(tiles), dim3(kThreads), 0, stream, args);
+            }
+            const hipError_t e = hipGetLastError();
+            return e == hipSuccess ? TMASK_OK : hip_fail(e, "score kernel launch");
+        });
+        if (rc)
+            return rc;
+        if (!one_launch && (rc = launch_score_reduce(tile0, nb, partial0, workspace, out + first, stream)))
             return rc;
         partial0 += tiles;
     }
@@ -1493,6 +1515,7 @@ int tmask_score(const tmask_mat *mats, int n_mats, tmask_dtype dt, int N, int M,
 }
 
 typedef void (*pack_kernel_t)(const PackArgs);
+typedef void (*few_pack_kernel_t)(const FewPackArgs);
 
 static pack_kernel_t pick_pack_kernel(int dt, int M, int mf, int N)
 {
@@ -1543,6 +1566,7 @@ int tmask_apply_pack(const tmask_pack_desc *descs, int n, tmask_dtype dt, int N,
     if (fit != kFitWide && !narrow24)
         return cw_run_pack(descs, n, (int)dt, N, M, (int)mf, (hipStream_t)hip_stream);
     pack_kernel_t kern = pick_pack_kernel((int)dt, M, (int)mf, N);
+    few_pack_kernel_t few = nullptr;      // of kern, where it has one
     uint32_t TC = 256 / (uint32_t)elem_size((int)dt);
     bool fast24 = (M == 4 && N == 2) && !narrow24;
     for (int i = 0; i < n && fast24; i++)
@@ -1560,7 +1584,7 @@ int tmask_apply_pack(const tmask_pack_desc *descs, int n, tmask_dtype dt, int N,
         TR = 4 * 4 * (64 / strips) * NW;
         const bool small = few_tiles(descs, n, TR, TC, kHalfTilesPack);
 #define TMASK_PICK(DT, SS, FM, QN) \
-        if ((int)dt == DT && (int)mf == FM && small == (QN == 2)) kern = pack24_kernel<DT, FM, SS, NW, QN>;
+        if ((int)dt == DT && (int)mf == FM && small == (QN == 2)) { kern = pack24_kernel<DT, FM, SS, NW, QN>; few = pack24_kernel<DT, FM, SS, NW, QN, FewPackArgs>; }
         TMASK_PICK(kF32, SF, kMaskU8, 4) TMASK_PICK(kF32, SF, kMaskBits, 4) TMASK_PICK(kBF16, SB, kMaskU8, 4) TMASK_PICK(kBF16, SB, kMaskBits, 4)
         TMASK_PICK(kF32, SF, kMaskU8, 2) TMASK_PICK(kF32, SF, kMaskBits, 2) TMASK_PICK(kBF16, SB, kMaskU8, 2) TMASK_PICK(kBF16, SB, kMaskBits, 2)
 #undef TMASK_PICK
@@ -1572,6 +1596,7 @@ int tmask_apply_pack(const tmask_pack_desc *descs, int n, tmask_dtype dt, int N,
         // 8-byte strips, which write 4 bytes per row: tiles of 64 rows x 128 columns, a quarter of the others' bytes, since
         // such matrices are mostly small (1000 x 2052: 272 workgroups)
         kern = mf == TMASK_MASK_U8 ? pack24_kernel<kBF16N, kMaskU8, 32, 4, 2> : pack24_kernel<kBF16N, kMaskBits, 32, 4, 2>;
+        few = mf == TMASK_MASK_U8 ? pack24_kernel<kBF16N, kMaskU8, 32, 4, 2, FewPackArgs> : pack24_kernel<kBF16N, kMaskBits, 32, 4, 2, FewPackArgs>;
         using PG = Pack4Geo<kBF16N, 32, 4, 2>;
         TC = PG::TC;
         TR = PG::TR;
@@ -1582,10 +1607,13 @@ int tmask_apply_pack(const tmask_pack_desc *descs, int n, tmask_dtype dt, int N,
         fast48 = (((uintptr_t)descs[i].vals | (uintptr_t)descs[i].valsT) & 7) == 0;
     if (fast48) {
         const bool small = few_tiles(descs, n, Pack8Geo<2>::TR, Pack8Geo<2>::TC, kHalfTilesPack);
-        if (mf == TMASK_MASK_U8)
-            kern = small ? pack48_bf16_kernel<kMaskU8, false, false, PackArgs, 1> : pack48_bf16_kernel<kMaskU8, false, false, PackArgs>;
-        else
-            kern = small ? pack48_bf16_kernel<kMaskBits, false, false, PackArgs, 1> : pack48_bf16_kernel<kMaskBits, false, false, PackArgs>;
+#define TMASK_PICK(FM, ST) \
+        if ((int)mf == FM && small == (ST == 1)) { \
+            kern = pack48_bf16_kernel<FM, false, false, PackArgs, ST>; \
+            few = pack48_bf16_kernel<FM, false, false, FewPackArgs, ST>; \
+        }
+        TMASK_PICK(kMaskU8, 1) TMASK_PICK(kMaskU8, 2) TMASK_PICK(kMaskBits, 1) TMASK_PICK(kMaskBits, 2)
+#undef TMASK_PICK
         TC = Pack8Geo<2>::TC;
         TR = small ? Pack8Geo<1>::TR : Pack8Geo<2>::TR;
     }
@@ -1595,39 +1623,50 @@ int tmask_apply_pack(const tmask_pack_desc *descs, int n, tmask_dtype dt, int N,
     if (fast48f) {
         kern = mf == TMASK_MASK_U8 ? pack48_f32_kernel<kMaskU8, kPack8F32Strips, false, false, PackArgs>
                                    : pack48_f32_kernel<kMaskBits, kPack8F32Strips, false, false, PackArgs>;
+        few = mf == TMASK_MASK_U8 ? pack48_f32_kernel<kMaskU8, kPack8F32Strips, false, false, FewPackArgs>
+                                  : pack48_f32_kernel<kMaskBits, kPack8F32Strips, false, false, FewPackArgs>;
         TC = Pack8F32Geo<kPack8F32Strips>::TC;
         TR = Pack8F32Geo<kPack8F32Strips>::TR;
     }
     hipStream_t stream = (hipStream_t)hip_stream;
     for (int first = 0; first < n; first += kMaxPackBatch) {
         const int nb = n - first < kMaxPackBatch ? n - first : kMaxPackBatch;
-        PackArgs args;
-        memset(&args, 0, sizeof args);
-        uint32_t tiles = 0;
-        for (int k = 0; k < nb; k++) {
-            const tmask_pack_desc &p = descs[first + k];
-            PackDev &d = args.d[k];
-            d.w = p.w; d.mask = p.mask; d.vals = p.vals; d.idx = p.idx; d.valsT = p.valsT; d.idxT = p.idxT;
-            d.rows = (uint32_t)p.rows; d.cols = (uint32_t)p.cols; d.ld = (uint32_t)p.ld; d.mask_ld = (uint32_t)p.mask_ld;
-            d.tiles_x = (d.cols + TC - 1) / TC;
-            d.tile0 = tiles;
-            tiles += d.tiles_x * ((d.rows + TR - 1) / TR);
+        auto go = [&](auto &args, auto kernel) -> int {
+            memset(&args, 0, sizeof args);
+            uint32_t tiles = 0;
+            for (int k = 0; k < nb; k++) {
+                const tmask_pack_desc &p = descs[first + k];
+                PackDev &d = args.d[k];
+                d.w = p.w; d.mask = p.mask; d.vals = p.vals; d.idx = p.idx; d.valsT = p.valsT; d.idxT = p.idxT;
+                d.rows = (uint32_t)p.rows; d.cols = (uint32_t)p.cols; d.ld = (uint32_t)p.ld; d.mask_ld = (uint32_t)p.mask_ld;
+                d.tiles_x = (d.cols + TC - 1) / TC;
+                d.tile0 = tiles;
+                tiles += d.tiles_x * ((d.rows + TR - 1) / TR);
+            }
+            {
+                uint32_t first0[kMaxPackBatch + 1];
+                for (int k = 0; k < nb; k++)
+                    first0[k] = args.d[k].tile0;
+                first0[nb] = tiles;
+                fill_coarse(args.ci, first0, nb, tiles);
+            }
+            args.n = (uint32_t)nb; args.N = (uint32_t)N;
+            {
+                ProfileScope prof(stream, first + kMaxPackBatch >= n);
+                hipLaunchKernelGGL(kernel, dim3(tiles), dim3(threads), lds_reserve, stream, args);
+            }
+            const hipError_t e = hipGetLastError();
+            return e == hipSuccess ? TMASK_OK : hip_fail(e, "pack kernel launch");
+        };
+        if (few && nb <= kFewMats) {
+            FewPackArgs args;
+            rc = go(args, few);
+        } else {
+            PackArgs args;
+            rc = go(args, kern);
         }
-        {
-            uint32_t first0[kMaxPackBatch + 1];
-            for (int k = 0; k < nb; k++)
-                first0[k] = args.d[k].tile0;
-            first0[nb] = tiles;
-            fill_coarse(args.ci, first0, nb, tiles);
-        }
-        args.n = (uint32_t)nb; args.N = (uint32_t)N;
-        {
-            ProfileScope prof(stream, first + kMaxPackBatch >= n);
-            hipLaunchKernelGGL(kern, dim3(tiles), dim3(threads), lds_reserve, stream, args);
-        }
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess)
-            return hip_fail(e, "pack kernel launch");
+        if (rc)
+            return rc;
     }
     return TMASK_OK;
 }
@@ -1808,13 +1847,13 @@ static int run_mask_dense(const tmask_mask_dense_desc *descs, int n, tmask_dtype
         return cw_run_dense(descs, n, (int)dt, N, M, (int)mf, absorb ? 2 : rows_only ? 1 : 0, (hipStream_t)hip_stream);
     }
     const int sdt = strip_type((int)dt, fit);
-    batch_kernel_t kern = nullptr;
+    BatchKernel kern{nullptr, nullptr};
 #define TMASK_PICK(DT, MM, FM) \
     if (sdt == DT && M == MM && (int)mf == FM) \
-        kern = mode == kDenseApprox ? approx_dense_kernel<DT, MM, FM, kDenseApprox> \
-             : mode == kDenseApproxHalf ? approx_dense_kernel<DT, MM, FM, kDenseApproxHalf> \
-             : mode == kDenseRow1D ? approx_dense_kernel<DT, MM, FM, kDenseRow1D> \
-             : mode == kDenseRow1DAbsorb ? approx_dense_kernel<DT, MM, FM, kDenseRow1DAbsorb> : kern;
+        kern = mode == kDenseApprox ? TMASK_MANY(approx_dense_kernel, DT, MM, FM, kDenseApprox, BatchArgs) \
+             : mode == kDenseApproxHalf ? TMASK_BOTH(approx_dense_kernel, DT, MM, FM, kDenseApproxHalf) \
+             : mode == kDenseRow1D ? TMASK_MANY(approx_dense_kernel, DT, MM, FM, kDenseRow1D, BatchArgs) \
+             : mode == kDenseRow1DAbsorb ? TMASK_MANY(approx_dense_kernel, DT, MM, FM, kDenseRow1DAbsorb, BatchArgs) : kern;
     TMASK_PICK(kF32, 4, kMaskU8) TMASK_PICK(kF32, 8, kMaskU8) TMASK_PICK(kF32, 16, kMaskU8)
     TMASK_PICK(kBF16, 4, kMaskU8) TMASK_PICK(kBF16, 8, kMaskU8) TMASK_PICK(kBF16, 16, kMaskU8)
     TMASK_PICK(kF32, 4, kMaskBits) TMASK_PICK(kF32, 8, kMaskBits) TMASK_PICK(kF32, 16, kMaskBits)
@@ -1823,39 +1862,40 @@ static int run_mask_dense(const tmask_mask_dense_desc *descs, int n, tmask_dtype
 #undef TMASK_PICK
 #define TMASK_PICK(MM, FM) \
     if ((int)dt == kBF16 && M == MM && (int)mf == FM && mode >= kDenseRow1DHalf) \
-        kern = mode == kDenseRow1DHalf ? approx_dense_kernel<kBF16, MM, FM, kDenseRow1DHalf> \
-                                       : approx_dense_kernel<kBF16, MM, FM, kDenseRow1DHalfAbsorb>;
+        kern = mode == kDenseRow1DHalf ? TMASK_MANY(approx_dense_kernel, kBF16, MM, FM, kDenseRow1DHalf, BatchArgs) \
+                                       : TMASK_MANY(approx_dense_kernel, kBF16, MM, FM, kDenseRow1DHalfAbsorb, BatchArgs);
     TMASK_PICK(8, kMaskU8) TMASK_PICK(16, kMaskU8) TMASK_PICK(8, kMaskBits) TMASK_PICK(16, kMaskBits)
 #undef TMASK_PICK
     hipStream_t stream = (hipStream_t)hip_stream;
     for (int first = 0; first < n; first += kMaxBatch) {
         const int nb = n - first < kMaxBatch ? n - first : kMaxBatch;
-        BatchArgs args;
-        memset(&args, 0, sizeof args);
-        uint32_t tiles = 0;
-        for (int k = 0; k < nb; k++) {
-            const tmask_mask_dense_desc &p = descs[first + k];
-            const HostMat h{p.w, p.rows, p.cols, p.ld, p.mask, p.mask_ld, nullptr};
-            fill_desc(args.m[k], h, sdt, M, tiles);
-            args.m[k].aux = p.out;
-            args.m[k].pad = (uint32_t)p.ld_out;
-            tiles += tiles_of(args.m[k].n_strips);
-        }
-        {
-            uint32_t first0[kMaxBatch + 1];
-            for (int k = 0; k < nb; k++)
-                first0[k] = args.m[k].tile0;
-            first0[nb] = tiles;
-            fill_coarse(args.ci, first0, nb, tiles);
-        }
-        args.n_mats = (uint32_t)nb; args.K = (uint32_t)(M - N); args.N = (uint32_t)N;
-        {
-            ProfileScope prof(stream, first + kMaxBatch >= n);
-            hipLaunchKernelGGL(kern, dim3(tiles), dim3(kThreads), 0, stream, args);
-        }
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess)
-            return hip_fail(e, "mask + dense copy kernel launch");
+        rc = with_table(kern, nb, [&](auto &args, auto kernel) -> int {
+            uint32_t tiles = 0;
+            for (int k = 0; k < nb; k++) {
+                const tmask_mask_dense_desc &p = descs[first + k];
+                const HostMat h{p.w, p.rows, p.cols, p.ld, p.mask, p.mask_ld, nullptr};
+                fill_desc(args.m[k], h, sdt, M, tiles);
+                args.m[k].aux = p.out;
+                args.m[k].pad = (uint32_t)p.ld_out;
+                tiles += tiles_of(args.m[k].n_strips);
+            }
+            {
+                uint32_t first0[kMaxBatch + 1];
+                for (int k = 0; k < nb; k++)
+                    first0[k] = args.m[k].tile0;
+                first0[nb] = tiles;
+                fill_coarse(args.ci, first0, nb, tiles);
+            }
+            args.n_mats = (uint32_t)nb; args.K = (uint32_t)(M - N); args.N = (uint32_t)N;
+            {
+                ProfileScope prof(stream, first + kMaxBatch >= n);
+                hipLaunchKernelGGL(kernel, dim3(tiles), dim3(kThreads), 0, stream, args);
+            }
+            const hipError_t e = hipGetLastError();
+            return e == hipSuccess ? TMASK_OK : hip_fail(e, "mask + dense copy kernel launch");
+        });
+        if (rc)
+            return rc;
     }
     return TMASK_OK;
 }

@@ -30,18 +30,21 @@ struct PackDev {
     uint32_t tile0;     // first workgroup of this matrix inside the launch
 };
 
-struct PackArgs {
-    PackDev d[kMaxPackBatch];
-    CoarseIndex ci;
+template <int CAP>
+struct PackArgsOf {
+    PackDev d[CAP];
+    CoarseIndex<CAP == kMaxPackBatch ? kCoarse : 16> ci;
     uint32_t n;
     uint32_t N;
 };
+using PackArgs = PackArgsOf<kMaxPackBatch>;
+using FewPackArgs = PackArgsOf<kFewMats>;
 static_assert(sizeof(PackArgs) <= 16384 + 2048, "descriptor table is sized to stay a small kernel argument");
 
 // Arguments of the kernels that compute the mask themselves (tmask_approx_pack).
 struct FusedArgs {
     PackDev d[kMaxPackBatch];   // mask = output here (may be null when WMASK is false)
-    CoarseIndex ci;
+    CoarseIndex<kCoarse> ci;
     uint32_t n;
     uint32_t partial0;          // index of this launch's first partial in the workspace
     void *partials;             // one double per workgroup, or null

@@ -178,8 +178,8 @@ __device__ __forceinline__ void pack24_copy_out(const PackDev &d, uint32_t row0,
     }
 }
 
-template <int DT, int FMT, int S, int NW, int QN>
-__global__ __launch_bounds__(64 * NW) void pack24_kernel(const PackArgs args)
+template <int DT, int FMT, int S, int NW, int QN, typename Args = PackArgs>
+__global__ __launch_bounds__(64 * NW) void pack24_kernel(const Args args)
 {
     static_assert(QN == 2 || QN == 4, "a lane works through two or four block-rows");
     using PG = Pack4Geo<DT, S, NW, QN>;
