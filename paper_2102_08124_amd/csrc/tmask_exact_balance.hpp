@@ -94,11 +94,17 @@ __global__ __launch_bounds__(kThreads, exact_workgroups_per_cu(DT, M)) void exac
                 r = raw[i];
             unpack_row<DT, C>(r, a[i]);
 #pragma unroll
-            for (int c = 0; c < C; c++) {
-                const uint32_t band = (((uint32_t)i + gpos * 4u + (uint32_t)c) & (M - 1)) < NKEEP ? 0x3F800000u : 0u;
-                a[i][c] = valid ? a[i][c] : band;
+            for (int c = 0; c < C; c++)
                 asm volatile("" : "+v"(a[i][c]));                // the raw rows end here
-            }
+        }
+        if (!valid) {                                            // hardly any wavefront: as selects, two instructions a weight
+#pragma unroll
+            for (int i = 0; i < M; i++)
+#pragma unroll
+                for (int c = 0; c < C; c++) {
+                    a[i][c] = (((uint32_t)i + gpos * 4u + (uint32_t)c) & (M - 1)) < NKEEP ? 0x3F800000u : 0u;
+                    asm volatile("" : "+v"(a[i][c]));
+                }
         }
     };
 
@@ -107,7 +113,7 @@ __global__ __launch_bounds__(kThreads, exact_workgroups_per_cu(DT, M)) void exac
     uint32_t e;
     {
         uint32_t a[M][C];
-        int cost[M][C];
+        float cost[M][C];
         load_block(a);
         exact_costs<M, C, G>(a, cost);
         e = exact_priced_start<M, C, G, GENERAL>(cost, gpos, xcol, K);

@@ -370,9 +370,10 @@ constexpr uint32_t kNoPred = 0xFFFFFFFFu;
 
 constexpr int exact_cost_bits(int M) { return (M == 16) ? 26 : 27; }
 
-// |W| keys (fp32 bit patterns) of one block -> integer costs, see above.
-template <int M, int CL, int G>
-__device__ __forceinline__ void exact_costs(const uint32_t (&key)[M][CL], int (&cost)[M][CL])
+// |W| keys (fp32 bit patterns) of one block -> integer costs, see above; as floats (which hold every cost: 24 significant bits)
+// or integers.
+template <int M, int CL, int G, typename T>
+__device__ __forceinline__ void exact_costs(const uint32_t (&key)[M][CL], T (&cost)[M][CL])
 {
     constexpr int S = exact_cost_bits(M);
     static_assert((M - 1) * (1ll << S) < kReachable, "labels must stay below the reachability threshold");
@@ -394,13 +395,33 @@ __device__ __forceinline__ void exact_costs(const uint32_t (&key)[M][CL], int (&
     const uint32_t emax = (kmax >> 23) ? (kmax >> 23) : 1u;
     // |w| 2^k for the k that brings the block's maximum to [2^(S-1), 2^S): exact, then truncated.  Infinities and NaN count as
     // the magnitudes whose bits follow the largest finite one's; a block that has any takes its exponents one lower.
-    const uint32_t lower = emax == 255u ? 0x800000u : 0u;
     const int shift = S + 126 - (int)emax + (emax == 255u ? 1 : 0);
+    uint32_t k[M][CL];
 #pragma unroll
     for (int i = 0; i < M; i++)
 #pragma unroll
         for (int c = 0; c < CL; c++)
-            cost[i][c] = (int)__builtin_ldexpf(__uint_as_float(__builtin_elementwise_sub_sat(key[i][c], lower)), shift);
+            k[i][c] = key[i][c];
+    if (__any(emax == 255u)) {                                  // not an instruction for each weight of the others
+        const uint32_t lower = emax == 255u ? 0x800000u : 0u;
+#pragma unroll
+        for (int i = 0; i < M; i++)
+#pragma unroll
+            for (int c = 0; c < CL; c++) {
+                k[i][c] = __builtin_elementwise_sub_sat(k[i][c], lower);
+                asm volatile("" : "+v"(k[i][c]));
+            }
+    }
+#pragma unroll
+    for (int i = 0; i < M; i++)
+#pragma unroll
+        for (int c = 0; c < CL; c++) {
+            const float scaled = __builtin_ldexpf(__uint_as_float(k[i][c]), shift);
+            if constexpr (std::is_same_v<T, float>)
+                cost[i][c] = __builtin_truncf(scaled);
+            else
+                cost[i][c] = (int)scaled;
+        }
 }
 
 // Start with row prices: column c prunes the K rows with the smallest cost + price (ties: by position, see below).
@@ -413,7 +434,8 @@ __device__ __forceinline__ void exact_costs(const uint32_t (&key)[M][CL], int (&
 // entries of a row below their column's threshold, each entry adds 0 ... 1 by where its key lies in a window of
 // width w around the middle between the column's K-th and (K+1)-th smallest key (one fused multiply-add with the
 // hardware's clamp and one addition, what a compare and a count cost), and a row's price moves by step x (that sum),
-// with some momentum; w and step shrink from round to round.  A count says by how many entries a row is out of
+// with some momentum (kept in units of the round's step: a price moves by step x v, v <- sum + momentum / step_next x v, two
+// instructions); w and step shrink from round to round.  A count says by how many entries a row is out of
 // balance, the smoothed sum also how far away the balance is: blocks of N(0,1) entries left unbalanced, by emulation,
 // 2.5 % after 8 rounds at M = 8 and 6 % after 13 at M = 16, where 12 and 20 rounds on counts left 12 % and 14 %.
 // Schedules were settled by a search in emulation, the numbers of rounds by timing on the device (6 ... 10 and
@@ -468,7 +490,7 @@ struct PriceSchedule<16> {
 };
 
 template <int M, int CL, int G, bool GENERAL = false>
-__device__ __forceinline__ uint32_t exact_priced_start(const int (&cost)[M][CL], uint32_t gpos, uint32_t (&xcol)[CL],
+__device__ __forceinline__ uint32_t exact_priced_start(const float (&cost)[M][CL], uint32_t gpos, uint32_t (&xcol)[CL],
                                                        uint32_t k_general = 0)
 {
     constexpr int H = M / 2;
@@ -483,8 +505,8 @@ __device__ __forceinline__ uint32_t exact_priced_start(const int (&cost)[M][CL],
         float sum = 0.f;
 #pragma unroll
         for (int c = 0; c < CL; c++) {
-            cf[i][c] = (float)cost[i][c];
-            asm volatile("" : "+v"(cf[i][c]));                  // the integers end here
+            cf[i][c] = cost[i][c];
+            asm volatile("" : "+v"(cf[i][c]));                  // the weights end here
             sum += cf[i][c];
         }
         if constexpr (G >= 2)
@@ -526,9 +548,10 @@ __device__ __forceinline__ uint32_t exact_priced_start(const int (&cost)[M][CL],
     float unit = 1.414214f * spread;
     unit = unit < mean ? unit : mean;
     unit = unit > 1.f ? unit : 1.f;                             // blocks of zeros, and of costs that rows and columns explain
-    float slope = -(1.f / Sched::window) / unit, step = Sched::step * unit;
+    float slope = -(1.f / Sched::window) * __builtin_amdgcn_rcpf(unit), step = Sched::step * unit;
     float drift = 0.f;                                          // what K per row and round adds to every price
     float dvel = 0.f;
+    constexpr float kCarry = Sched::momentum / Sched::step_next;
 #pragma unroll 1
     for (int round = 0; round < Sched::rounds; round++) {
         float f[M];
@@ -582,11 +605,12 @@ __device__ __forceinline__ uint32_t exact_priced_start(const int (&cost)[M][CL],
                 f[i] = quad_xor_sum<1>(f[i]);
             if constexpr (G == 4)
                 f[i] = quad_xor_sum<2>(f[i]);
-            vel[i] = Sched::momentum * vel[i] + step * f[i];
-            pr[i] += vel[i];
+            // in place: as an expression it is an accumulation into f and a move
+            asm("v_fma_f32 %0, %1, %0, %2" : "+v"(vel[i]) : "s"(kCarry), "v"(f[i]));
+            pr[i] = __builtin_fmaf(step, vel[i], pr[i]);
         }
-        dvel = Sched::momentum * dvel + step * (float)K;
-        drift += dvel;
+        dvel = __builtin_fmaf(kCarry, dvel, (float)K);
+        drift = __builtin_fmaf(step, dvel, drift);
         slope *= 1.f / Sched::window_next;
         step *= Sched::step_next;
     }
