@@ -183,42 +183,39 @@ __global__ __launch_bounds__(kThreads, exact_workgroups_per_cu(DT, M)) void exac
     __builtin_amdgcn_sched_barrier(0);
     float acc = 0.f;
     if (valid) {
-        uint32_t bits[M];
+        // the kept entries of eight rows in a word, a column to a byte: row i's mask bytes are a shift and an AND (as bits put
+        // together one by one and spread again they were ten instructions a row)
+        uint32_t kept[M / 8];
+        if constexpr (M == 8) {
+            kept[0] = ~(xcol[0] | (xcol[1] << 8) | (xcol[2] << 16) | (xcol[3] << 24));
+        } else {
+            const uint32_t x01 = __builtin_amdgcn_perm(xcol[1], xcol[0], 0x05010400u), x23 = __builtin_amdgcn_perm(xcol[3], xcol[2], 0x05010400u);
+            kept[0] = ~__builtin_amdgcn_perm(x23, x01, 0x05040100u);
+            kept[1] = ~__builtin_amdgcn_perm(x23, x01, 0x07060302u);
+        }
+        char *mrow = (char *)md.mask + (size_t)pos.br * M * md.mask_ld + (FMT == kMaskU8 ? col : col >> 3);
 #pragma unroll
         for (int i = 0; i < M; i++) {
-            bits[i] = 0;
-#pragma unroll
-            for (int c = 0; c < C; c++)
-                bits[i] |= (((xcol[c] >> i) & 1u) ^ 1u) << c;
-        }
-        if constexpr (HALF) {
-            // four mask entries per row and lane: four bytes, or a nibble that the even lane of a pair completes
-            char *mrow = (char *)md.mask + (size_t)pos.br * M * md.mask_ld;
-#pragma unroll
-            for (int i = 0; i < M; i++) {
-                if constexpr (FMT == kMaskU8) {
-                    stream_store(bits_to_bytes4(bits[i]), (uint32_t *)(mrow + (size_t)i * md.mask_ld + col));
-                } else {
-                    const uint32_t other = quad_xor<1>(bits[i]);
-                    if ((s & 1u) == 0)
-                        mrow[(size_t)i * md.mask_ld + (col >> 3)] = (char)(bits[i] | (other << 4));
-                }
+            const uint32_t bytes = (kept[i / 8] >> (i % 8)) & 0x01010101u;
+            if constexpr (FMT == kMaskU8) {
+                stream_store(bytes, (uint32_t *)mrow);
+            } else {                                             // a nibble, which the even lane of a pair completes
+                const uint32_t bits = bytes4_to_bits(bytes), other = quad_xor<1>(bits);
+                if ((s & 1u) == 0)
+                    *mrow = (char)(bits | (other << 4));
             }
-        } else {
-            store_mask<DT, M, FMT>(md, pos, bits);
+            mrow += md.mask_ld;
         }
         // the magnitudes are read again: they need not occupy registers in between
 #pragma unroll
         for (int i = 0; i < M; i++) {
             const Row r = __builtin_nontemporal_load((const Row *)(base + i * row_bytes));
-            uint32_t a[C];
-            if constexpr (HALF)
-                unpack_row<DT, C>(u32x4{r.x, r.y, 0u, 0u}, a);
-            else
-                unpack_row<DT, C>(r, a);
 #pragma unroll
-            for (int c = 0; c < C; c++)
-                acc += ((bits[i] >> c) & 1u) ? __uint_as_float(a[c]) : 0.f;
+            for (int c = 0; c < C; c++) {
+                const uint32_t w = DT == kF32 ? r[c] : (c & 1) ? r[c / 2] & 0xFFFF0000u : r[c / 2] << 16;
+                const uint32_t pruned = (uint32_t)__builtin_amdgcn_sbfe((int)xcol[c], (uint32_t)i, 1u);     // all ones or none
+                acc += __builtin_fabsf(__uint_as_float(w & ~pruned));
+            }
         }
     }
     if (out.dst)

@@ -599,12 +599,21 @@ __device__ __forceinline__ uint32_t exact_priced_start(const float (&cost)[M][CL
             if constexpr (CL > 4 || M == 16)
                 __builtin_amdgcn_sched_barrier(0);   // one column at a time: interleaving them costs M registers each
         }
+        // all rows a step at a time: a value that was just written cannot be read across lanes for two wait states
+        if constexpr (G >= 2) {
+#pragma unroll
+            for (int i = 0; i < M; i++)
+                f[i] = quad_xor_sum<1>(f[i]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if constexpr (G == 4) {
+#pragma unroll
+            for (int i = 0; i < M; i++)
+                f[i] = quad_xor_sum<2>(f[i]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
 #pragma unroll
         for (int i = 0; i < M; i++) {
-            if constexpr (G >= 2)
-                f[i] = quad_xor_sum<1>(f[i]);
-            if constexpr (G == 4)
-                f[i] = quad_xor_sum<2>(f[i]);
             // in place: as an expression it is an accumulation into f and a move
             asm("v_fma_f32 %0, %1, %0, %2" : "+v"(vel[i]) : "s"(kCarry), "v"(f[i]));
             pr[i] = __builtin_fmaf(step, vel[i], pr[i]);
