@@ -1204,21 +1204,22 @@ int cw_run_mask(int solver, const tmask_mat *mats, int n_mats, int dt, int N, in
         CwArgs args;
         memset(&args, 0, sizeof args);
         uint32_t wg0[kMaxCwBatch + 1];
-        uint32_t wgs = 0, most = 0;
+        uint32_t wgs = 0;
+        LaunchSums sums;
         for (int k = 0; k < nb; k++) {
             const tmask_mat &t = mats[first + k];
             cw_fill(args.m[k], t.w, t.rows, t.cols, t.ld, t.mask, t.mask_ld, M, wgs);
             if (by_rows)
                 args.m[k].n_wg = (args.m[k].n_tiles + kRowsTiles - 1) / kRowsTiles;
             args.objective[k] = t.objective;
-            most = most > args.m[k].n_wg ? most : args.m[k].n_wg;
+            sums.add(args.m[k].n_wg, t.objective);
             wg0[k] = wgs;
             wgs += args.m[k].n_wg;
         }
         wg0[nb] = wgs;
         args.n = (uint32_t)nb; args.K = (uint32_t)(M - N); args.N = (uint32_t)N;
         args.partial0 = partial0; args.partials = want_obj ? ws : nullptr;
-        const bool one_launch = want_obj && tagged && adds_up_itself(wgs, most, by_rows ? 64 * kRowsTiles : kCwThreads, false);
+        const bool one_launch = want_obj && tagged && adds_up_itself(sums, by_rows ? 64 * kRowsTiles : kCwThreads, false);
         if (one_launch)
             args.tags = draw_tags();
         {
@@ -1251,13 +1252,14 @@ int cw_run_score(const tmask_mat *mats, int n_mats, int dt, int N, int M, int mf
         CwArgs args;
         memset(&args, 0, sizeof args);
         uint32_t wg0[kMaxCwBatch + 1];
-        uint32_t wgs = 0, most = 0;
+        uint32_t wgs = 0;
+        LaunchSums sums;
         for (int k = 0; k < nb; k++) {
             const tmask_mat &t = mats[first + k];
             cw_fill(args.m[k], t.w, t.rows, t.cols, t.ld, t.mask, t.mask_ld, M, wgs);
             args.m[k].aux = per_block_obj ? (void *)(per_block_obj + block0) : nullptr;
             block0 += (size_t)(t.rows / M) * (size_t)(t.cols / M);
-            most = most > args.m[k].n_wg ? most : args.m[k].n_wg;
+            sums.add(args.m[k].n_wg, true);
             wg0[k] = wgs;
             wgs += args.m[k].n_wg;
         }
@@ -1265,7 +1267,7 @@ int cw_run_score(const tmask_mat *mats, int n_mats, int dt, int N, int M, int mf
         args.n = (uint32_t)nb; args.K = (uint32_t)(M - N); args.N = (uint32_t)N;
         args.partial0 = partial0; args.partials = ws;
         args.score = (ScorePartial *)(out + first);
-        const bool one_launch = adds_up_itself(wgs, most, kCwThreads, true);
+        const bool one_launch = adds_up_itself(sums, kCwThreads, true);
         if (one_launch)
             args.tags = draw_tags();
         {

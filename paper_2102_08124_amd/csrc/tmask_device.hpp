@@ -275,9 +275,9 @@ __device__ __forceinline__ double block_sum_f32(float v, double *lds /* kThreads
 // word proves by itself that it was written by this launch.  It then clears them, so that a captured launch, whose tags are
 // the same each time it is replayed, finds none of its own.  (Contents of a workspace pass for a result only if they hold both
 // 32-bit tags of a call in the right places, two tags that differ and are drawn anew for each call.)
-// The wait ends: workgroups start in the order of their numbers on each XCD, so of those that are not done the lowest one
-// has started or finds its place held by none that waits, and it waits for nobody itself.  Should a result never come, the
-// wait gives up after some seconds and the sum is NaN.
+// The wait ends: so few workgroups wait at a time that every workgroup finds a place that none of them holds (see kMostWaiting),
+// and those that are waited for wait for nobody.  Should a result never come, the wait gives up after some seconds and the sum
+// is NaN.
 
 constexpr uint32_t kMostReads = 1u << 21;     // of one record, a microsecond or more each
 

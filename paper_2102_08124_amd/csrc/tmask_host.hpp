@@ -4,6 +4,7 @@
 
 #include "../../include/tmask.h"
 #include "tmask_device.hpp"
+#include "tmask_sum_choice.hpp"
 
 namespace tmask {
 
@@ -30,16 +31,6 @@ struct ProfileScope {
         }
     }
 };
-
-// Whether a launch adds up its own partial results (hand_over, hand_over_score): `total` workgroups of `threads`, no matrix with
-// more than `most`.  Back to back, two launches / one, us: 512^2 .. 1536^2 masks at 2:4 and 4:8 9.3-10.2 / 6.9-7.3, 4096^2 bf16 14.6 /
-// 13.0, six matrices fp32 2:4 (3072 workgroups) 15.2 / 13.7, 52 (5724) 23.5 / 22.8, optimal 4:8 of them 59.1 / 57.2; 144 (36864) 147 /
-// 153: by then hundreds of last workgroups read while others stream.  A score's record is seven words: 512^2 and 1024^2 mask,
-// compression and score (256 workgroups) 17.1 / 16.7, 1024 x 2048 (512) 18.6 / 19.3, six matrices (3072) 60 / 67.
-inline bool adds_up_itself(uint32_t total, uint32_t most, uint32_t threads, bool score)
-{
-    return score ? total <= 256u : total <= 8192u && most <= 8u * threads;
-}
 
 Tags draw_tags();
 

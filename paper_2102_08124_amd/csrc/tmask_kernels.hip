@@ -1332,7 +1332,8 @@ static int run_mask(const tmask_mat *mats, int n_mats, int dt, int N, int M, int
     for (int first = 0; first < n_mats; first += kMaxBatch) {
         const int nb = n_mats - first < kMaxBatch ? n_mats - first : kMaxBatch;
         ReduceArgs rargs;
-        uint32_t tiles = 0, most = 0;
+        uint32_t tiles = 0;
+        LaunchSums sums;
         bool one_launch = false;
         rc = with_table(kern, nb, [&](auto &args, auto kernel) -> int {
             for (int k = 0; k < nb; k++) {
@@ -1343,7 +1344,7 @@ static int run_mask(const tmask_mat *mats, int n_mats, int dt, int N, int M, int
                 rargs.tile0[k] = tiles;
                 args.m[k].aux = t.objective;
                 args.m[k].pad = tiles_of(args.m[k].n_strips * unit_split);
-                most = most > args.m[k].pad ? most : args.m[k].pad;
+                sums.add(args.m[k].pad, t.objective);
                 tiles += args.m[k].pad;
             }
             rargs.tile0[nb] = tiles;
@@ -1351,7 +1352,7 @@ static int run_mask(const tmask_mat *mats, int n_mats, int dt, int N, int M, int
             args.n_mats = (uint32_t)nb; args.K = (uint32_t)(M - N); args.N = (uint32_t)N;
             args.partial0 = partial0; args.partials = want_obj ? ws : nullptr;
             // the array of tmask_approx_noalloc has room for the sums alone, and calls that overlap share it
-            one_launch = want_obj && !own_scratch && adds_up_itself(tiles, most, kThreads, false);
+            one_launch = want_obj && !own_scratch && adds_up_itself(sums, kThreads, false);
             if (one_launch)
                 args.tags = draw_tags();
             {
@@ -1476,7 +1477,8 @@ int tmask_score(const tmask_mat *mats, int n_mats, tmask_dtype dt, int N, int M,
     for (int first = 0; first < n_mats; first += kMaxBatch) {
         const int nb = n_mats - first < kMaxBatch ? n_mats - first : kMaxBatch;
         uint32_t tile0[kMaxBatch + 1];
-        uint32_t tiles = 0, most = 0;
+        uint32_t tiles = 0;
+        LaunchSums sums;
         bool one_launch = false;
         rc = with_table(kern, nb, [&](auto &args, auto kernel) -> int {
             for (int k = 0; k < nb; k++) {
@@ -1487,7 +1489,7 @@ int tmask_score(const tmask_mat *mats, int n_mats, tmask_dtype dt, int N, int M,
                 block0 += (size_t)(t.rows / M) * (size_t)(t.cols / M);
                 tile0[k] = tiles;
                 args.m[k].pad = tiles_of(args.m[k].n_strips);
-                most = most > args.m[k].pad ? most : args.m[k].pad;
+                sums.add(args.m[k].pad, true);
                 tiles += args.m[k].pad;
             }
             tile0[nb] = tiles;
@@ -1496,7 +1498,7 @@ int tmask_score(const tmask_mat *mats, int n_mats, tmask_dtype dt, int N, int M,
             args.partial0 = partial0; args.partials = workspace;
             static_assert(sizeof(ScorePartial) == sizeof(tmask_score_out), "the last workgroup of a matrix writes its result");
             args.score = (ScorePartial *)(out + first);
-            one_launch = adds_up_itself(tiles, most, kThreads, true);
+            one_launch = adds_up_itself(sums, kThreads, true);
             if (one_launch)
                 args.tags = draw_tags();
             {
@@ -1773,7 +1775,8 @@ int tmask_approx_pack(const tmask_fused_desc *descs, int n, tmask_dtype dt, int 
         ReduceArgs rargs;
         memset(&args, 0, sizeof args);
         memset(&rargs, 0, sizeof rargs);
-        uint32_t tiles = 0, most = 0;
+        uint32_t tiles = 0;
+        LaunchSums sums;
         for (int k = 0; k < nb; k++) {
             const tmask_fused_desc &p = descs[first + k];
             PackDev &d = args.d[k];
@@ -1785,13 +1788,13 @@ int tmask_approx_pack(const tmask_fused_desc *descs, int n, tmask_dtype dt, int 
             rargs.tile0[k] = tiles;
             args.objective[k] = p.objective;
             const uint32_t own = d.tiles_x * ((d.rows + kPack4Rows - 1) / kPack4Rows);
-            most = most > own ? most : own;
+            sums.add(own, p.objective);
             tiles += own;
         }
         rargs.tile0[nb] = tiles;
         fill_coarse(args.ci, rargs.tile0, nb, tiles);
         args.n = (uint32_t)nb; args.partial0 = partial0; args.partials = want_obj ? workspace : nullptr;
-        const bool one_launch = want_obj && adds_up_itself(tiles, most, kThreads, false) && workspace_bytes >= 2 * partials_bytes(kPack4Rows);
+        const bool one_launch = want_obj && adds_up_itself(sums, kThreads, false) && workspace_bytes >= 2 * partials_bytes(kPack4Rows);
         if (one_launch)
             args.tags = draw_tags();
         {

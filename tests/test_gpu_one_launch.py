@@ -116,6 +116,35 @@ def test_one_pass_with_a_small_workspace(dtype, N, M):
         assert torch.allclose(g, ref, rtol=2e-6, atol=0.0)
 
 
+@pytest.mark.parametrize("shape,dtype,N,M", [((256, 256), F32, 2, 4), ((256, 256), F32, 1, 4), ((256, 256), F32, 4, 8), ((256, 256), BF16, 4, 8),
+                                             ((256, 256), BF16, 8, 16), ((256, 512), F32, 5, 16), ((64, 256), BF16, 16, 32),
+                                             ((64, 256), F32, 16, 32), ((256, 516), BF16, 1, 4)])
+@pytest.mark.parametrize("n,few", [(7, True), (8, False)])
+def test_how_many_matrices_a_launch_adds_up(shape, dtype, N, M, n, few):
+    """Seven waiting workgroups to a launch.  The workspace shows which way a call went: what a launch hands over to itself it
+    clears, what it leaves for a second launch stays."""
+    ws = _weights([shape] * n, dtype, 31)
+    masks, wsp = tm.alloc_masks(ws), tm.alloc_workspace(ws, N, M)
+    obj = torch.zeros(n, dtype=torch.float64, device="cuda")
+    out = torch.zeros(n * tm.SCORE_OUT_BYTES, dtype=torch.uint8, device="cuda")
+    calls = [(lambda f=f: f(ws, masks, N, M, objective=obj, workspace=wsp)) for f in (tm.tmask_approx, tm.tmask_exact, tm.tmask_prune_1d)]
+    if 2 * N == M <= 8:
+        packed = [tm.alloc_packed(w, N, M) for w in ws]
+        calls.append(lambda: tm.tmask_approx_pack(ws, masks, packed, N, M, objective=obj, workspace=wsp))
+    for k, call in enumerate(calls):
+        wsp.zero_()
+        obj.fill_(-1.0)
+        call()
+        torch.cuda.synchronize()
+        assert bool(wsp.any()) != few, k
+        assert torch.allclose(obj, _kept(ws, masks), rtol=2e-5, atol=0.0)
+    wsp.zero_()
+    tm.tmask_score(ws, masks, N, M, out, workspace=wsp)
+    torch.cuda.synchronize()
+    assert bool(wsp.any()) != few
+    assert [s["kept"] for s in tm.read_scores(out, n)] == [int((m != 0).sum()) for m in masks]
+
+
 def test_replays_with_anything_in_the_workspace_between():
     shapes = [(1024, 1024), (520, 136)]
     ws = _weights(shapes, F32, 19)
