@@ -267,8 +267,14 @@ def alloc_workspace(ws: Sequence[torch.Tensor], N: int, M: int) -> torch.Tensor:
     return torch.empty(max(tmask_workspace_bytes(ws, N, M), 256), dtype=torch.uint8, device=ws[0].device)
 
 
+def _device_reads(t: torch.Tensor) -> bool:
+    """Whether a kernel can follow the tensor's pointer: device memory, or host memory that is pinned."""
+    return t.is_cuda or (t.device.type == "cpu" and t.is_pinned())
+
+
 def _ws_args(workspace):
-    if workspace is None:
+    """Host memory counts as no workspace: calls that need none take it, the others say that there is none."""
+    if workspace is None or not _device_reads(workspace):
         return None, 0
     return C.c_void_p(workspace.data_ptr()), workspace.numel() * workspace.element_size()
 
@@ -324,8 +330,9 @@ def tmask_score(ws, masks, N: int, M: int, out: torch.Tensor, per_block_obj: Opt
         return None if rc == TMASK_OK else _check(rc)
     if out.numel() * out.element_size() < b.n * SCORE_OUT_BYTES or not out.is_cuda or not out.is_contiguous():
         raise ValueError("out is too small")
-    if per_block_obj is not None and (per_block_obj.dtype != torch.float32 or not per_block_obj.is_contiguous()):
-        raise ValueError("per_block_obj must be contiguous float32")
+    if per_block_obj is not None and (per_block_obj.dtype != torch.float32 or not per_block_obj.is_contiguous()
+                                      or not _device_reads(per_block_obj)):
+        raise ValueError("per_block_obj must be contiguous float32 in device memory")
     wp, wb = _ws_args(workspace)
     _check(L.tmask_score(b.arr, b.n, b.dt, N, M, mask_fmt, C.c_void_p(out.data_ptr()),
                          C.c_void_p(per_block_obj.data_ptr()) if per_block_obj is not None else None,
@@ -389,6 +396,8 @@ def tmask_spmm24(vals: torch.Tensor, idx: torch.Tensor, rows: int, cols: int, x:
     if tuple(vals.shape) != (rows, cols // 2) or tuple(idx.shape) != (rows, cols // 8) or not vals.is_contiguous() \
             or not idx.is_contiguous():
         raise ValueError("vals must be rows x cols/2 and idx rows x cols/8, contiguous")
+    if not _device_reads(vals) or not _device_reads(idx):
+        raise ValueError("vals and idx must be device tensors")
     _check(L.tmask_spmm24(vals.data_ptr(), idx.data_ptr(), rows, cols, x.data_ptr(), x.stride(0),
                           y.data_ptr(), y.stride(0), x.shape[0], dtype_code(y), _stream_ptr(stream)))
 

@@ -4,7 +4,7 @@
 // (one 256 x 64 layer 5.1 -> 4.5 us back to back, a product with 16 tokens 5.8 -> 3.5).
 //
 // Every function returns the C function's result, or None where something is not as it usually is (a type, a shape, a value
-// outside int, a tensor that has no memory of its own): binding.py then goes through the same arguments step by step and raises
+// outside int, a tensor that has no memory of its own or none on the device): binding.py then goes through the same arguments step by step and raises
 // what is to be raised.  No function raises by itself, and none keeps anything between calls.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
@@ -80,7 +80,7 @@ bool as_workspace(PyObject *o, void **out, size_t *bytes)
     if (o == Py_None)
         return true;
     const at::Tensor *t;
-    if (!as_tensor(o, &t))
+    if (!as_tensor(o, &t) || !t->is_cuda())
         return false;
     *out = t->data_ptr();
     *bytes = (size_t)t->numel() * (size_t)t->element_size();
@@ -168,7 +168,7 @@ PyObject *score(PyObject *, PyObject *const *a, Py_ssize_t n)
                 return false;
             out = o->data_ptr();
             if (a[9] != Py_None) {
-                if (!as_tensor(a[9], &p) || p->scalar_type() != at::kFloat || !p->is_contiguous())
+                if (!as_tensor(a[9], &p) || p->scalar_type() != at::kFloat || !p->is_cuda() || !p->is_contiguous())
                     return false;
                 per_block = p->data_ptr();
             }
@@ -200,7 +200,7 @@ PyObject *spmm24(PyObject *, PyObject *const *a, Py_ssize_t n)
             if (y->scalar_type() != at::kFloat && y->scalar_type() != at::kBFloat16)
                 return false;
             if (x->dim() != 2 || y->dim() != 2 || vals->dim() != 2 || idx->dim() != 2 || x->stride(1) != 1 || y->stride(1) != 1 ||
-                !x->is_cuda() || !y->is_cuda() || !vals->is_contiguous() || !idx->is_contiguous())
+                !x->is_cuda() || !y->is_cuda() || !vals->is_cuda() || !idx->is_cuda() || !vals->is_contiguous() || !idx->is_contiguous())
                 return false;
             if (cols < 0 || x->size(1) != cols || y->size(0) != x->size(0) || y->size(1) != rows || vals->size(0) != rows ||
                 vals->size(1) != cols / 2 || idx->size(0) != rows || idx->size(1) != cols / 8)

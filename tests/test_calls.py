@@ -1,5 +1,6 @@
 """The native half of binding.py takes the usual arguments and leaves every other one to the Python half: it never raises, and on
 the GPU both halves give the same outputs and the same errors."""
+import ctypes
 import types
 
 import pytest
@@ -31,6 +32,60 @@ def test_unusual_arguments_are_left_to_the_python_half():
     assert calls.spmm24(L.at["tmask_spmm24"], t, t, 4, 64, t, t, None) is None          # no device memory, wrong types
 
 
+class _Device:
+    """What the Python half asks of a device tensor."""
+    is_cuda, device = True, types.SimpleNamespace(type="cuda")
+
+    def __init__(self, *shape, dtype=torch.bfloat16):
+        self.shape, self.dtype = shape, dtype
+
+    dim = lambda self: len(self.shape)
+    stride = lambda self, k=0: (self.shape[1], 1)[k]
+    data_ptr = lambda self: 4096
+    is_contiguous = lambda self: True
+    numel = lambda self: self.shape[0] * (self.shape[1] if len(self.shape) > 1 else 1)
+    element_size = lambda self: 1
+
+
+def test_host_memory_reaches_no_kernel(monkeypatch):
+    """Neither half passes the address of a host tensor on: the library function, here one that only notes its arguments, is not
+    called, or is called without a workspace."""
+    seen = []
+
+    def note(*args):
+        seen.append(args)
+        return 0
+
+    L = tm.load_library()
+    fn = ctypes.CFUNCTYPE(ctypes.c_int, *[ctypes.c_void_p] * 12)(note)
+    at = ctypes.cast(fn, ctypes.c_void_p).value
+    host, stream = torch.zeros(4096, dtype=torch.uint8), types.SimpleNamespace(cuda_stream=0)
+    head = [at, 64, 1, 0, 2, 4, 0]
+    assert tm._calls.batch(*head, host, stream) is None
+    assert tm._calls.score(*head, host, 0, None, None, stream) is None and tm._calls.score(*head, host, 0, host, host, stream) is None
+    assert seen == [] and tm._calls.batch(*head, None, stream) == 0 and len(seen) == 1
+
+    seen.clear()
+    monkeypatch.setattr(tm, "_calls", NONE)
+    monkeypatch.setattr(tm, "_lib", types.SimpleNamespace(at=L.at, tmask_approx=note, tmask_score=note, tmask_spmm24=note))
+    batch = tm.MatBatch.__new__(tm.MatBatch)
+    batch.arr, batch.n, batch.dt = (tm.tmask_mat * 1)(), 1, 0
+    tm.tmask_approx(batch, None, 2, 4, workspace=host, stream=stream)
+    assert seen.pop()[6:8] == (None, 0)
+    out = _Device(tm.SCORE_OUT_BYTES, dtype=torch.uint8)
+    with pytest.raises(ValueError, match="device memory"):
+        tm.tmask_score(batch, None, 2, 4, out, per_block_obj=torch.zeros(64), stream=stream)
+    x, y = _Device(8, 128), _Device(8, 64, dtype=torch.float32)
+    vals, idx = torch.zeros((64, 64), dtype=torch.bfloat16), torch.zeros((64, 16), dtype=torch.uint8)
+    with pytest.raises(ValueError, match="device tensors"):
+        tm.tmask_spmm24(vals, _Device(64, 16, dtype=torch.uint8), 64, 128, x, y, stream=stream)
+    with pytest.raises(ValueError, match="device tensors"):
+        tm.tmask_spmm24(_Device(64, 64), idx, 64, 128, x, y, stream=stream)
+    assert seen == []
+    tm.tmask_spmm24(_Device(64, 64), _Device(64, 16, dtype=torch.uint8), 64, 128, x, y, stream=stream)
+    assert len(seen) == 1
+
+
 def _outcome(f):
     try:
         f()
@@ -58,6 +113,12 @@ def test_both_halves_do_the_same(monkeypatch):
     side = torch.cuda.Stream()
     spmm = lambda **k: tm.tmask_spmm24(*[{"vals": vals, "idx": idx, "rows": 64, "cols": 128, "x": x, "y": y, **k}[n]
                                          for n in ("vals", "idx", "rows", "cols", "x", "y")], stream=k.get("stream"))
+    plain = tm.MatBatch(w, masks)
+
+    def pinned(t):
+        host = torch.empty(t.shape, dtype=t.dtype, pin_memory=True)
+        return host.copy_(t)
+
     calls = [
         lambda: tm.tmask_approx(batch, None, 2, 4, workspace=wsp), lambda: tm.tmask_exact(batch, None, 4, 8, workspace=wsp, stream=side),
         lambda: tm.tmask_prune_1d(batch, None, 2, 4, workspace=wsp), lambda: tm.tmask_approx(batch, None, 3, 5, workspace=wsp),
@@ -70,6 +131,11 @@ def test_both_halves_do_the_same(monkeypatch):
         lambda: tm.tmask_score(batch, None, 2, 4, out, per_block_obj=per.double(), workspace=wsp),
         lambda: spmm(), lambda: spmm(stream=side), lambda: spmm(x=x.float()), lambda: spmm(y=y.half()), lambda: spmm(idx=idx[:, :8]),
         lambda: spmm(vals=vals.t()), lambda: spmm(x=x[:, ::2]), lambda: spmm(y=y.cpu()), lambda: spmm(rows=60), lambda: spmm(cols=64),
+        # host memory, which a kernel must not be given; pinned host memory, which it can read
+        lambda: spmm(vals=vals.cpu()), lambda: spmm(idx=idx.cpu()), lambda: spmm(vals=pinned(vals), idx=pinned(idx)),
+        lambda: tm.tmask_score(batch, None, 2, 4, out, per_block_obj=per.cpu(), workspace=wsp), lambda: tm.tmask_approx(batch, None, 2, 4, workspace=wsp.cpu()),
+        lambda: tm.tmask_score(batch, None, 2, 4, out, workspace=wsp.cpu()), lambda: tm.tmask_approx(plain, None, 2, 4, workspace=wsp.cpu()),
+        lambda: tm.tmask_approx_dense(w, None, [d.cpu() for d in dst], 2, 4),
         lambda: spmm(y=y[:, :32]), lambda: spmm(x=x[0]), lambda: spmm(x=torch.nn.Parameter(x)), lambda: spmm(y=torch.zeros((8, 66), device="cuda")[:, :64])]
     kept = [masks[0], obj, out, per, dst[0], y]
     seen = set()
