@@ -306,12 +306,13 @@ __device__ __forceinline__ bool take_words(unsigned long long *at, const Tags &t
 #pragma unroll
         for (int k = 0; k < W; k++)
             w[k] = get_word(at + k);
-        all = true;
+        uint32_t wrong = 0u;                      // not a chain of &&: its branches took 20 registers with a score's seven words
 #pragma unroll
         for (int k = 0; k < W; k++) {
             v[k] = (uint32_t)w[k];
-            all = all && (uint32_t)(w[k] >> 32) == ((k & 1) ? tags.b : tags.a);
+            wrong |= (uint32_t)(w[k] >> 32) ^ ((k & 1) ? tags.b : tags.a);
         }
+        all = wrong == 0u;
     } while (!all && ++reads < kMostReads);
 #pragma unroll
     for (int k = 0; k < W; k++)

@@ -636,7 +636,7 @@ __device__ __forceinline__ void score_strip_bf16_m4(const MatDev &md, StripPos p
 }
 
 template <int DT, int M, int FMT, typename Args>
-__global__ __launch_bounds__(kThreads, M == 4 && DT != kBF16N ? 8 : 1) void score_kernel(const Args args)
+__global__ __launch_bounds__(kThreads) void score_kernel(const Args args)
 {
     using Ge = Geo<DT, M>;
     constexpr int C = Ge::C, CL = Ge::CL;

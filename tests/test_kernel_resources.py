@@ -1,0 +1,71 @@
+"""Registers, scratch memory and LDS of the kernels in the built library, from the notes of its code objects: what decides how many
+wavefronts share a SIMD (512 registers, eight wavefronts) and how many workgroups a compute unit (160 KiB of LDS)."""
+import os
+import re
+import shutil
+import struct
+import subprocess
+
+import pytest
+
+from paper_2102_08124_amd import build
+
+LLVM = "/opt/rocm/llvm/bin"
+MAGIC = b"__CLANG_OFFLOAD_BUNDLE__"
+
+
+def _code_objects(blob):
+    """The gfx950 code objects of a library: each translation unit embeds a bundle."""
+    at = blob.find(MAGIC)
+    while at >= 0:
+        n, = struct.unpack_from("<Q", blob, at + len(MAGIC))
+        pos = at + len(MAGIC) + 8
+        for _ in range(n):
+            offset, size, length = struct.unpack_from("<QQQ", blob, pos)
+            name = blob[pos + 24:pos + 24 + length]
+            pos += 24 + length
+            if b"gfx950" in name and size:
+                yield blob[at + offset:at + offset + size]
+        at = blob.find(MAGIC, at + 1)
+
+
+@pytest.fixture(scope="module")
+def kernels(tmp_path_factory):
+    """kernel (template arguments, without those of its table) -> list of {vgpr, scratch, lds, threads}"""
+    readelf = os.path.join(LLVM, "llvm-readelf")
+    if not os.path.exists(readelf) or not shutil.which("c++filt"):
+        pytest.skip("no llvm-readelf or c++filt")
+    if not os.path.exists(build.LIB):
+        build.build()
+    folder, found = tmp_path_factory.mktemp("objects"), []
+    for k, code in enumerate(_code_objects(open(build.LIB, "rb").read())):
+        path = folder / ("%d.co" % k)
+        path.write_bytes(code)
+        notes = subprocess.run([readelf, "--notes", str(path)], check=True, capture_output=True, text=True).stdout
+        for entry in re.split(r"\n\s*- \.agpr_count:", notes)[1:]:
+            field = lambda name: int(re.search(r"\.%s:\s+(\d+)" % name, entry).group(1))
+            found.append((re.search(r"\.symbol:\s+(\S+)\.kd", entry).group(1),
+                          dict(vgpr=field("vgpr_count"), scratch=field("private_segment_fixed_size"), lds=field("group_segment_fixed_size"),
+                               threads=field("max_flat_workgroup_size"))))
+    names = subprocess.run(["c++filt"], input="\n".join(n for n, _ in found), check=True, capture_output=True, text=True).stdout.split("\n")
+    out = {}
+    for name, (_, use) in zip(names, found):
+        name = re.sub(r"\(.*|tmask::|^void ", "", name)
+        out.setdefault(re.sub(r"(, )?(Few)?(Batch|Pack)ArgsOf<\d+> ?|\s+(?=>)", "", name), []).append(use)
+    assert len(out) > 100
+    return out
+
+
+def _wavefronts(use):
+    """of a SIMD, by registers (allocated in eights)"""
+    return min(8, 512 // (-(-use["vgpr"] // 8) * 8))
+
+
+@pytest.mark.parametrize("dt", [0, 1, 2])
+@pytest.mark.parametrize("fmt", [0, 1])
+def test_scores_at_m4_leave_room_for_eight_wavefronts(kernels, dt, fmt):
+    """They are bound by what they read; records that are added up in the launch must not cost them a wavefront."""
+    uses = kernels["score_kernel<%d, 4, %d>" % (dt, fmt)]
+    assert len(uses) == 2                                      # the two sizes of the table
+    for use in uses:
+        assert _wavefronts(use) == 8 and use["scratch"] == 0, use
