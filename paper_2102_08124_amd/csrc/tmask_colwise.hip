@@ -499,7 +499,6 @@ __global__ __launch_bounds__(64 * kRowsTiles, 8) void cw_mask32_bf16_kernel(cons
 {
     constexpr uint32_t kPitch = 20;                       // dwords: four of padding keep the 16-byte accesses conflict-free
     __shared__ __align__(16) uint32_t lds[kRowsTiles][64 * kPitch];
-    __shared__ double red[kRowsTiles];
     const int which = cw_find(args, blockIdx.x);
     const CwMat md = args.m[which];
     const Handover out = cw_objective<true>(args, md, which);
@@ -584,7 +583,7 @@ __global__ __launch_bounds__(64 * kRowsTiles, 8) void cw_mask32_bf16_kernel(cons
         total = *(const double *)&lds[0][16];
         for (uint32_t k = 1; k < kRowsTiles; k++)
             total += *(const double *)&lds[k][16];
-        hand_over<64 * kRowsTiles>(out, total, red);
+        hand_over<64 * kRowsTiles>(out, total, (double *)lds);     // no LDS of its own: 20480 bytes, eight workgroups per compute unit
     }
 }
 

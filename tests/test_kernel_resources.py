@@ -61,6 +61,12 @@ def _wavefronts(use):
     return min(8, 512 // (-(-use["vgpr"] // 8) * 8))
 
 
+@pytest.mark.parametrize("fmt", [0, 1])
+def test_16_of_32_by_rows_has_eight_workgroups_on_a_compute_unit(kernels, fmt):
+    use, = kernels["cw_mask32_bf16_kernel<%d>" % fmt]
+    assert use["threads"] == 256 and _wavefronts(use) == 8 and 160 * 1024 // use["lds"] >= 8, use
+
+
 @pytest.mark.parametrize("dt", [0, 1, 2])
 @pytest.mark.parametrize("fmt", [0, 1])
 def test_scores_at_m4_leave_room_for_eight_wavefronts(kernels, dt, fmt):
