@@ -33,7 +33,7 @@ constexpr int kMaxCwBatch = 224;
 struct CwMat {
     const void *w;
     void *mask;          // output of the mask kernels (may be null for the dense one-pass calls), input of score / pack
-    void *aux;           // mask kernels: dense output (or null); score: per-block objective of this matrix (or null)
+    void *aux;           // masks: the objective; dense: the output; score: per-block objective of this matrix; or null
     uint32_t ld, mask_ld, ld_aux, cols;
     uint32_t tpr;        // tiles per block-row = ceil(cols / 64)
     uint32_t n_tiles;    // tpr * rows / M
@@ -46,10 +46,9 @@ struct CwArgs {
     uint32_t n, K, N, partial0;
     void *partials;
     Tags tags;
-    double *objective[kMaxCwBatch];
     ScorePartial *score;
 };
-static_assert(sizeof(CwArgs) <= 16384 + 2048, "descriptor table is sized to stay a small kernel argument");
+static_assert(sizeof(CwArgs) <= 16384, "descriptor table is sized to stay a small kernel argument");
 
 __device__ __forceinline__ int cw_find(const CwArgs &a, uint32_t wg)
 {
@@ -64,11 +63,19 @@ __device__ __forceinline__ int cw_find(const CwArgs &a, uint32_t wg)
     return lo;
 }
 
-// The objective of a mask kernel's workgroup; md: matrix number k of the launch.
+// The objective of a mask kernel's workgroup; md: its matrix.
 template <bool EARLY>
-__device__ __forceinline__ Handover cw_objective(const CwArgs &args, const CwMat &md, int k)
+__device__ __forceinline__ Handover cw_objective(const CwArgs &args, const CwMat &md)
 {
-    return handover<8, 2, EARLY>(args.partials, args.tags, args.partial0 + blockIdx.x, blockIdx.x - md.wg0, md.n_wg, args.objective[k]);
+    return handover<8, 2, EARLY>(args.partials, args.tags, args.partial0 + blockIdx.x, blockIdx.x - md.wg0, md.n_wg, md.aux);
+}
+
+// The same behind a loop over tiles, for matrix number k of the launch.  It is read there and not before: eight scalar registers
+// held through the loop are eight more that spill into vector registers (512^2 fp32 5:16, mask alone: 33.7 us without, 34.5 with them).
+__device__ __forceinline__ Handover cw_objective_at_end(const CwArgs &args, int k)
+{
+    asm volatile("" : "+s"(k));
+    return cw_objective<false>(args, args.m[k]);
 }
 
 template <int DT>
@@ -358,7 +365,7 @@ __global__ __launch_bounds__(kCwThreads, M == 32 ? 4 : 1) void cw_mask_kernel(co
     __shared__ uint32_t T[NB][M][M + 1];
     const int which = cw_find(args, blockIdx.x);
     const CwMat md = args.m[which];
-    const Handover out = cw_objective<false>(args, md, which);     // registers are short
+    void *const dense = args.partials ? nullptr : md.aux;          // else md.aux is the objective
     const uint32_t lane = threadIdx.x, blk = lane / M, j = lane % M;
     const uint32_t K = args.K;
     double total = 0.0;
@@ -405,12 +412,12 @@ __global__ __launch_bounds__(kCwThreads, M == 32 ? 4 : 1) void cw_mask_kernel(co
             acc += ((keep >> i) & 1u) ? __uint_as_float(mag) : 0.f;
         }
         total += (double)wave_sum(acc);
-        if (md.aux) {
+        if (dense) {
             // dense masked copy; with absorption the mean of a row group's pruned weights goes to its kept ones
             constexpr size_t ES = DT == kF32 ? 4 : 2;
             if constexpr (!kHoldRaw)
                 cw_load_column<DT, M>(md, p, raw);        // every entry is read and written by the same lane: in place is fine
-            char *orow = (char *)md.aux + ((size_t)p.br * M * md.ld_aux + p.col0) * ES;      // same in every lane
+            char *orow = (char *)dense + ((size_t)p.br * M * md.ld_aux + p.col0) * ES;      // same in every lane
 #pragma unroll
             for (int i = 0; i < M; i++) {
                 const bool k = (keep >> i) & 1u;
@@ -433,6 +440,7 @@ __global__ __launch_bounds__(kCwThreads, M == 32 ? 4 : 1) void cw_mask_kernel(co
             }
         }
     }
+    const Handover out = cw_objective_at_end(args, which);
     if (out.dst)
         hand_over<kCwThreads>(out, total, nullptr);
 }
@@ -501,7 +509,7 @@ __global__ __launch_bounds__(64 * kRowsTiles, 8) void cw_mask32_bf16_kernel(cons
     __shared__ __align__(16) uint32_t lds[kRowsTiles][64 * kPitch];
     const int which = cw_find(args, blockIdx.x);
     const CwMat md = args.m[which];
-    const Handover out = cw_objective<true>(args, md, which);
+    const Handover out = cw_objective<true>(args, md);
     const uint32_t lane = threadIdx.x & 63u, blk = lane >> 5, j = lane & 31u;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     uint32_t *const T = lds[wave];                        // the wavefront's own: no barriers among its lanes
@@ -618,7 +626,6 @@ __global__ __launch_bounds__(kCwThreads, M == 32 ? 3 : 1) void cw_exact_kernel(c
     __shared__ uint32_t PK[NB][M];
     const int which = cw_find(args, blockIdx.x);
     const CwMat md = args.m[which];
-    const Handover out = cw_objective<false>(args, md, which);     // registers are short
     const uint32_t lane = threadIdx.x, blk = lane / M, j = lane % M;
     const uint32_t K = args.K;
     double total = 0.0;
@@ -803,6 +810,7 @@ __global__ __launch_bounds__(kCwThreads, M == 32 ? 3 : 1) void cw_exact_kernel(c
             acc += (p.active && ((keep >> i) & 1u)) ? __uint_as_float(key[i]) : 0.f;
         total += (double)wave_sum(acc);
     }
+    const Handover out = cw_objective_at_end(args, which);
     if (out.dst)
         hand_over<kCwThreads>(out, total, nullptr);
 }
@@ -814,10 +822,8 @@ __global__ __launch_bounds__(kCwThreads, M == 32 ? 3 : 1) void cw_exact_kernel(c
 template <int DT, int M, int FMT>
 __global__ __launch_bounds__(kCwThreads) void cw_score_kernel(const CwArgs args)
 {
-    const int which = cw_find(args, blockIdx.x);
+    int which = cw_find(args, blockIdx.x);
     const CwMat md = args.m[which];
-    const Handover out = handover<sizeof(ScorePartial), 7>(args.partials, args.tags, args.partial0 + blockIdx.x, blockIdx.x - md.wg0, md.n_wg,
-                                                           args.score + which);
     const uint32_t lane = threadIdx.x, blk = lane / M, j = lane % M;
     const uint32_t N = args.N;
     double retained = 0.0, total = 0.0;
@@ -853,6 +859,9 @@ __global__ __launch_bounds__(kCwThreads) void cw_score_kernel(const CwArgs args)
         retained += (double)wave_sum(ret);
         total += (double)wave_sum(tot);
     }
+    asm volatile("" : "+s"(which));                       // read here, as in cw_objective_at_end
+    const Handover out = handover<sizeof(ScorePartial), 7, false>(args.partials, args.tags, args.partial0 + blockIdx.x,
+                                                                  blockIdx.x - args.m[which].wg0, args.m[which].n_wg, args.score + which);
     const ScoreSums own = {retained, total, kept, rowv, colv, rowne, colne};
     hand_over_score<kCwThreads>(out, own);
 }
@@ -1202,6 +1211,7 @@ int cw_run_mask(int solver, const tmask_mat *mats, int n_mats, int dt, int N, in
         const int nb = n_mats - first < kMaxCwBatch ? n_mats - first : kMaxCwBatch;
         CwArgs args;
         memset(&args, 0, sizeof args);
+        double *objective[kMaxCwBatch];
         uint32_t wg0[kMaxCwBatch + 1];
         uint32_t wgs = 0;
         LaunchSums sums;
@@ -1210,7 +1220,8 @@ int cw_run_mask(int solver, const tmask_mat *mats, int n_mats, int dt, int N, in
             cw_fill(args.m[k], t.w, t.rows, t.cols, t.ld, t.mask, t.mask_ld, M, wgs);
             if (by_rows)
                 args.m[k].n_wg = (args.m[k].n_tiles + kRowsTiles - 1) / kRowsTiles;
-            args.objective[k] = t.objective;
+            objective[k] = t.objective;
+            args.m[k].aux = t.objective;
             sums.add(args.m[k].n_wg, t.objective);
             wg0[k] = wgs;
             wgs += args.m[k].n_wg;
@@ -1229,7 +1240,7 @@ int cw_run_mask(int solver, const tmask_mat *mats, int n_mats, int dt, int N, in
         if (e != hipSuccess)
             return hip_fail(e, "column-wise mask kernel launch");
         if (want_obj && !one_launch) {
-            const int rc = launch_objective_reduce(args.objective, wg0, nb, partial0, ws, stream);
+            const int rc = launch_objective_reduce(objective, wg0, nb, partial0, ws, stream);
             if (rc)
                 return rc;
         }

@@ -61,6 +61,15 @@ def _wavefronts(use):
     return min(8, 512 // (-(-use["vgpr"] // 8) * 8))
 
 
+@pytest.mark.parametrize("name,waves", [("cw_exact_kernel<%d, 8, %d>", 6), ("cw_score_kernel<%d, 32, 1>", 7)])
+@pytest.mark.parametrize("dt", [0, 1])
+def test_column_per_lane_kernels_hold_nothing_for_their_end(kernels, name, waves, dt):
+    """Where a workgroup's sum goes is read behind the loop over tiles."""
+    for fmt in (0, 1):
+        use, = kernels[name % ((dt, fmt) if name.count("%") == 2 else dt)]
+        assert _wavefronts(use) >= waves and use["scratch"] == 0, use
+
+
 @pytest.mark.parametrize("fmt", [0, 1])
 def test_16_of_32_by_rows_has_eight_workgroups_on_a_compute_unit(kernels, fmt):
     use, = kernels["cw_mask32_bf16_kernel<%d>" % fmt]
