@@ -1801,7 +1801,8 @@ int tmask_approx_pack(const tmask_fused_desc *descs, int n, tmask_dtype dt, int 
             d.tile0 = tiles;
             rargs.objective[k] = p.objective;
             rargs.tile0[k] = tiles;
-            args.objective[k] = p.objective;
+            if (k < kFewMats)
+                args.objective[k] = p.objective;
             const uint32_t own = d.tiles_x * ((d.rows + kPack4Rows - 1) / kPack4Rows);
             sums.add(own, p.objective);
             tiles += own;
@@ -1809,7 +1810,9 @@ int tmask_approx_pack(const tmask_fused_desc *descs, int n, tmask_dtype dt, int 
         rargs.tile0[nb] = tiles;
         fill_coarse(args.ci, rargs.tile0, nb, tiles);
         args.n = (uint32_t)nb; args.partial0 = partial0; args.partials = want_obj ? workspace : nullptr;
-        const bool one_launch = want_obj && adds_up_itself(sums, kThreads, false) && workspace_bytes >= 2 * partials_bytes(kPack4Rows);
+        // a pointer for each of 224 matrices would be 2 KB of arguments more, which calls without objectives pay for too (512^2
+        // fp32 2:4 6.18 us with them, 6.04 without)
+        const bool one_launch = want_obj && nb <= kFewMats && adds_up_itself(sums, kThreads, false) && workspace_bytes >= 2 * partials_bytes(kPack4Rows);
         if (one_launch)
             args.tags = draw_tags();
         {

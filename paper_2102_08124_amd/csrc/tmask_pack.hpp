@@ -47,11 +47,11 @@ struct FusedArgs {
     CoarseIndex<kCoarse> ci;
     uint32_t n;
     uint32_t partial0;          // index of this launch's first partial in the workspace
-    void *partials;             // one double per workgroup, or null
+    void *partials;             // a record per workgroup (tags given) or a double, or null
     Tags tags;
-    double *objective[kMaxPackBatch];
+    double *objective[kFewMats];        // tags given: of each matrix, in launches of so many at most
 };
-static_assert(sizeof(FusedArgs) <= 16384 + 4096, "descriptor table is sized to stay a small kernel argument");
+static_assert(sizeof(FusedArgs) <= 16384 + 2048, "descriptor table is sized to stay a small kernel argument");
 
 
 // Tile number inside a matrix -> tile coordinates, for the kernels that write W^T in short runs per column.
@@ -90,7 +90,8 @@ __device__ __forceinline__ int find_pack_desc(const Args &args, uint32_t tile)
 template <int TR>
 __device__ __forceinline__ Handover objective_of(const FusedArgs &args, const PackDev &d, int k, uint32_t tile)
 {
-    return handover<8, 2>(args.partials, args.tags, args.partial0 + tile, tile - d.tile0, d.tiles_x * ((d.rows + TR - 1u) / TR), args.objective[k]);
+    return handover<8, 2>(args.partials, args.tags, args.partial0 + tile, tile - d.tile0, d.tiles_x * ((d.rows + TR - 1u) / TR),
+                          args.objective[k % kFewMats]);
 }
 
 template <uint32_t ADJ = 1>

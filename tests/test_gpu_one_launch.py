@@ -145,6 +145,21 @@ def test_how_many_matrices_a_launch_adds_up(shape, dtype, N, M, n, few):
     assert [s["kept"] for s in tm.read_scores(out, n)] == [int((m != 0).sum()) for m in masks]
 
 
+@pytest.mark.parametrize("n", [8, 9, 40, 224, 230])
+@pytest.mark.parametrize("dtype,N,M", [(F32, 2, 4), (BF16, 4, 8)])
+def test_one_pass_over_many_small_matrices(dtype, N, M, n):
+    """One launch has room for the objectives of eight; the rest take the second launch, also past the 224 of a launch."""
+    ws = _weights([(16, 64)] * n, dtype, 37)
+    packed = [tm.alloc_packed(w, N, M) for w in ws]
+    obj, ref = torch.full((n,), -1.0, dtype=torch.float64, device="cuda"), torch.zeros(n, dtype=torch.float64, device="cuda")
+    wsp = tm.alloc_workspace(ws, N, M)
+    tm.tmask_approx_noalloc(ws, tm.alloc_masks(ws), N, M, objective=ref)
+    _garbage(wsp, "random")
+    tm.tmask_approx_pack(ws, None, packed, N, M, objective=obj, workspace=wsp)
+    torch.cuda.synchronize()
+    assert torch.allclose(obj, ref, rtol=2e-6, atol=0.0)
+
+
 def test_replays_with_anything_in_the_workspace_between():
     shapes = [(1024, 1024), (520, 136)]
     ws = _weights(shapes, F32, 19)
