@@ -25,7 +25,7 @@
  *   The workspace (at least tmask_workspace_bytes(), 256-byte aligned) is scratch for the duration
  *   of the enqueued work; calls that overlap on different streams need different workspaces
  *   (calls that share one all the same leave objectives and scores undefined: NaN if a workgroup waits for a partial
- *   result that another call has overwritten, for some seconds at the most).  Its contents before a call do not matter.
+ *   result that another call has overwritten, which it gives up after two to six seconds).  Its contents before a call do not matter.
  *
  * Layout requirements (checked; violations return TMASK_ERR_SHAPE / TMASK_ERR_ALIGN)
  *   rows and cols multiples of M (the paper's only requirement: Sec. 4 speaks of the M x M blocks of a weight

@@ -276,10 +276,10 @@ __device__ __forceinline__ double block_sum_f32(float v, double *lds /* kThreads
 // the same each time it is replayed, finds none of its own.  (Contents of a workspace pass for a result only if they hold both
 // 32-bit tags of a call in the right places, two tags that differ and are drawn anew for each call.)
 // The wait ends: so few workgroups wait at a time that every workgroup finds a place that none of them holds (see kMostWaiting),
-// and those that are waited for wait for nobody.  Should a result never come, the wait gives up after some seconds and the sum
-// is NaN.
+// and those that are waited for wait for nobody.  Should a result never come, a wavefront gives up after kMostReads reads, 1-3 us
+// each, that found something missing, and the sum is NaN.
 
-constexpr uint32_t kMostReads = 1u << 21;     // of one record, a microsecond or more each
+constexpr uint32_t kMostReads = 1u << 21;     // by a wavefront, of all the records that it takes: 2-6 s
 
 __device__ __forceinline__ void put_word(unsigned long long *at, uint32_t value, uint32_t tag)
 {
@@ -291,17 +291,16 @@ __device__ __forceinline__ unsigned long long get_word(const unsigned long long 
     return __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// The words of a record (even ones tagged a, odd ones b), cleared when all of them are there; false if they never came.  A read
-// goes to memory and takes 2-3 us behind what the chip has in flight; four records at a time took
-// registers, and with them a wavefront of occupancy, for no gain.
+// The words of a record (even ones tagged a, odd ones b), cleared when all of them are there.  The lanes of a wavefront read
+// together until each has its record, at most `left` times in vain, a number that they share and that later records have less of;
+// false if the record has not come by then.  (A lane that has its record reads it again: keeping it would take registers.)  A
+// read goes to memory and takes 2-3 us behind what the chip has in flight; four records at a time took registers, and with them a
+// wavefront of occupancy, for no gain.
 template <int W>
-__device__ __forceinline__ bool take_words(unsigned long long *at, const Tags &tags, uint32_t (&v)[W])
+__device__ __forceinline__ bool take_words(unsigned long long *at, const Tags &tags, uint32_t (&v)[W], uint32_t &left)
 {
     bool all;
-    uint32_t reads = 0;
-    do {
-        if (reads)
-            __builtin_amdgcn_s_sleep(1);
+    for (;;) {
         unsigned long long w[W];
 #pragma unroll
         for (int k = 0; k < W; k++)
@@ -313,10 +312,16 @@ __device__ __forceinline__ bool take_words(unsigned long long *at, const Tags &t
             wrong |= (uint32_t)(w[k] >> 32) ^ ((k & 1) ? tags.b : tags.a);
         }
         all = wrong == 0u;
-    } while (!all && ++reads < kMostReads);
+        if (!__any(!all) || left == 0u)
+            break;
+        left--;
+        __builtin_amdgcn_s_sleep(1);
+    }
+    if (all) {
 #pragma unroll
-    for (int k = 0; k < W; k++)
-        __hip_atomic_store(at + k, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (int k = 0; k < W; k++)
+            __hip_atomic_store(at + k, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
     return all;
 }
 
@@ -374,6 +379,7 @@ __device__ __forceinline__ void hand_over(const Handover &h, double t, double *r
     }
     static_assert(THREADS == 64 || THREADS == kThreads, "the order above");
     double total = 0.0;
+    uint32_t left = kMostReads;
 #pragma nounroll
     for (uint32_t q = 0; q < (uint32_t)kThreads; q += THREADS) {
         const uint32_t first = threadIdx.x + q;
@@ -381,7 +387,7 @@ __device__ __forceinline__ void hand_over(const Handover &h, double t, double *r
 #pragma nounroll
         for (uint32_t i = first; i < h.others; i += kThreads) {
             uint32_t v[2];
-            const bool came = take_words<2>(h.records + 2u * i, tags, v);
+            const bool came = take_words<2>(h.records + 2u * i, tags, v, left);
             sum += words_as_double(v[0], v[1], came);
         }
         if (h.others % kThreads == first)
@@ -440,10 +446,11 @@ __device__ __forceinline__ void hand_over_score(const Handover &h, ScoreSums own
     }
     if (threadIdx.x != 0)
         own = ScoreSums{};
+    uint32_t left = kMostReads;
 #pragma nounroll
     for (uint32_t i = threadIdx.x; i < h.others; i += THREADS) {
         uint32_t v[W];
-        const bool came = take_words<W>(h.records + (size_t)W * i, tags, v);
+        const bool came = take_words<W>(h.records + (size_t)W * i, tags, v, left);
         own.retained += words_as_double(v[0], v[1], came);
         own.total += words_as_double(v[2], v[3], came);
         own.kept += v[4] & 0xFFFFu; own.rowv += v[4] >> 16;
