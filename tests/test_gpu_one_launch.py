@@ -33,13 +33,16 @@ def _kept(ws, masks):
 
 # workgroups of a matrix: 256 strips of 16 bytes x M rows each at M <= 16 aligned (fp32 2:4: 4096 weights), tiles of 32 x 64 at M = 32
 # (bf16 16:32: four of them), 64 columns x M rows on unaligned matrices.  One, two, 256 and 257 that report to a last one, the most
-# that do (8 for each thread of it) and one more, the most of a launch (8192) and more, several matrices, ragged ends.
+# that do (8 for each thread of it) and one more, more matrices than may wait in a launch, ragged ends.
 CASES = [
     ([(64, 64)], F32, 2, 4), ([(4, 8)], F32, 1, 4), ([(64, 128)], F32, 3, 4), ([(1024, 1024), (64, 72), (1028, 1024)], F32, 2, 4),
     ([(2048, 4096)], F32, 2, 4), ([(2052, 4096)], F32, 2, 4), ([(1024, 1024)] * 32, F32, 2, 4), ([(1024, 1024)] * 33, F32, 2, 4),
     ([(1000, 2052)], BF16, 2, 4), ([(1024, 2048), (8, 16)], BF16, 4, 8), ([(1024, 1040)], F32, 4, 8), ([(512, 528)], BF16, 8, 16),
     ([(512, 512)], F32, 5, 16), ([(1024, 1024), (32, 32)], BF16, 16, 32), ([(256, 4160)], F32, 16, 32), ([(1024, 1056)], F32, 16, 32),
-    ([(256, 516)], BF16, 1, 4), ([(64, 68)], BF16, 1, 4)]
+    ([(256, 516)], BF16, 1, 4), ([(64, 68)], BF16, 1, 4),
+    # a score adds up 256 workgroups itself and no more: strips, narrow strips, columns
+    ([(1024, 1024)], F32, 2, 4), ([(1024, 1024), (4, 8)], F32, 2, 4), ([(512, 2044)], BF16, 2, 4), ([(512, 2044), (4, 4)], BF16, 2, 4),
+    ([(512, 1024)], BF16, 16, 32), ([(512, 1024), (32, 32)], BF16, 16, 32), ([(256, 512)], F32, 16, 32), ([(64, 64)], F32, 8, 32)]
 
 
 @pytest.mark.parametrize("shapes,dtype,N,M", CASES)
@@ -160,7 +163,80 @@ def test_one_pass_over_many_small_matrices(dtype, N, M, n):
     assert torch.allclose(obj, ref, rtol=2e-6, atol=0.0)
 
 
+# the call, the matrices and, for each of these, the workgroups: workgroup 0 .. n - 2 of a matrix leave records of so many words
+REPLAYS = [("approx", [(1024, 1024), (520, 136)], F32, 4, 8, 2, [128, 9]), ("exact", [(512, 512), (264, 136)], BF16, 4, 8, 2, [32, 5]),
+           ("approx", [(1024, 1024)], BF16, 16, 32, 2, [128]), ("approx", [(256, 512)], F32, 5, 16, 2, [8]), ("prune", [(256, 256)], F32, 2, 4, 2, [16]),
+           ("pack", [(1024, 1024)], F32, 4, 8, 2, None), ("score", [(512, 512), (136, 264)], F32, 2, 4, 7, [64, 9]), ("score", [(256, 256)], F32, 16, 32, 7, [32]),
+           ("score", [(256, 516)], BF16, 2, 4, 7, [33])]
+
+
+@pytest.mark.parametrize("kind,shapes,dtype,N,M,words,workgroups", REPLAYS)
+def test_a_replay_finds_nothing_of_the_one_before(kind, shapes, dtype, N, M, words, workgroups):
+    """One call in a graph, replayed with other weights and nothing else in its workspace in between: records that the last replay
+    left would bear this one's tags, and their sums would be the last weights'.  References come from a second workspace."""
+    ws = _weights(shapes, dtype, 19)
+    masks, wsp, other = tm.alloc_masks(ws), tm.alloc_workspace(ws, N, M).zero_(), tm.alloc_workspace(ws, N, M)
+    packed = [tm.alloc_packed(w, N, M) for w in ws] if kind == "pack" else None
+    obj = torch.zeros(len(ws), dtype=torch.float64, device="cuda")
+    out = torch.zeros(len(ws) * tm.SCORE_OUT_BYTES, dtype=torch.uint8, device="cuda")
+    for m in masks:
+        m.random_(0, 2)
+
+    def call(space):
+        if kind == "score":
+            tm.tmask_score(ws, masks, N, M, out, workspace=space)
+        elif kind == "pack":
+            tm.tmask_approx_pack(ws, None, packed, N, M, objective=obj, workspace=space)
+        else:
+            {"approx": tm.tmask_approx, "exact": tm.tmask_exact, "prune": tm.tmask_prune_1d}[kind](ws, masks, N, M, objective=obj, workspace=space)
+
+    call(other)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=torch.cuda.Stream()):
+        call(wsp)
+    seen = []
+    for turn in range(6):
+        for w in ws:
+            w.mul_(1.25 if turn % 3 else -0.5)
+        call(other)
+        torch.cuda.synchronize()
+        want = (obj.clone(), out.clone())
+        obj.fill_(-1.0)
+        out.fill_(0xA5 if kind == "score" else 0)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(obj if kind != "score" else out, want[kind == "score"]), turn
+        seen.append(want[kind == "score"])
+        assert not bool(wsp.any())                             # one launch, and no record left
+    assert all(not torch.equal(a, b) for a, b in zip(seen, seen[1:]))
+
+
+@pytest.mark.parametrize("kind,shapes,dtype,N,M,words,workgroups", [r for r in REPLAYS if r[6] is not None])
+def test_records_are_cleared_where_they_lie(kind, shapes, dtype, N, M, words, workgroups):
+    """Of a workspace full of ones, a call changes the words of its records, to zero, and no others (the last workgroup of a matrix has
+    no record)."""
+    ws = _weights(shapes, dtype, 41)
+    masks, wsp = tm.alloc_masks(ws), tm.alloc_workspace(ws, N, M)
+    wsp.fill_(0xFF)
+    obj = torch.zeros(len(ws), dtype=torch.float64, device="cuda")
+    if kind == "score":
+        for m in masks:
+            m.fill_(1)
+        tm.tmask_score(ws, masks, N, M, torch.zeros(len(ws) * tm.SCORE_OUT_BYTES, dtype=torch.uint8, device="cuda"), workspace=wsp)
+    else:
+        {"approx": tm.tmask_approx, "exact": tm.tmask_exact, "prune": tm.tmask_prune_1d}[kind](ws, masks, N, M, objective=obj, workspace=wsp)
+    torch.cuda.synchronize()
+    want = [-1] * (wsp.numel() // 8)
+    first = 0
+    for n in workgroups:
+        want[words * first:words * (first + n - 1)] = [0] * (words * (n - 1))
+        first += n
+    assert wsp[:len(want) * 8].view(torch.int64).tolist() == want
+
+
 def test_replays_with_anything_in_the_workspace_between():
+    """Several calls in a graph share a workspace, which eager calls use, and which is overwritten, between the replays."""
     shapes = [(1024, 1024), (520, 136)]
     ws = _weights(shapes, F32, 19)
     masks, wsp = tm.alloc_masks(ws), tm.alloc_workspace(ws, 4, 8)
@@ -191,7 +267,7 @@ def test_replays_with_anything_in_the_workspace_between():
         obj.fill_(-1.0)
         out.fill_(0)
         graph.replay()
-        if turn == 4:                              # twice in a row: the second finds nothing of the first
+        if turn == 4:                              # twice in a row
             graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(obj, want) and torch.equal(out, score)
@@ -227,3 +303,16 @@ def test_matrices_without_an_objective_between_others():
     want = _kept(ws, masks)
     assert float(obj[1]) == -1.0
     assert torch.allclose(obj[[0, 2]], want[[0, 2]], rtol=2e-6, atol=0.0)
+
+
+@pytest.mark.parametrize("shapes,dtype,N,M,itself", [([(1024, 1024)], F32, 2, 4, True), ([(1024, 1024), (4, 8)], F32, 2, 4, False),
+                                                     ([(512, 2044)], BF16, 2, 4, True), ([(512, 2044), (4, 4)], BF16, 2, 4, False),
+                                                     ([(512, 1024)], BF16, 16, 32, True), ([(512, 1024), (32, 32)], BF16, 16, 32, False)])
+def test_a_score_of_256_workgroups_is_one_launch_and_of_257_two(shapes, dtype, N, M, itself):
+    ws = _weights(shapes, dtype, 43)
+    masks, wsp = tm.alloc_masks(ws), tm.alloc_workspace(ws, N, M).zero_()
+    for m in masks:
+        m.fill_(1)
+    tm.tmask_score(ws, masks, N, M, torch.zeros(len(ws) * tm.SCORE_OUT_BYTES, dtype=torch.uint8, device="cuda"), workspace=wsp)
+    torch.cuda.synchronize()
+    assert bool(wsp.any()) != itself
