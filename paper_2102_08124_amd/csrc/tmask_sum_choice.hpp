@@ -28,16 +28,18 @@ struct LaunchSums {
 constexpr uint32_t kQueues = 4, kUnitsOfXcd = 32;
 constexpr uint32_t kMostWaiting = (kUnitsOfXcd - 1) / kQueues;
 
-// Workgroups of `threads`.  Back to back, two launches / one, us: 512^2 .. 1536^2 masks at 2:4 and 4:8 9.3-10.2 / 6.9-7.3, 4096^2
-// bf16 14.6 / 13.0, six matrices fp32 2:4 (3072 workgroups) 15.2 / 13.7.  Eight results per thread of the adding workgroup at most:
-// up to there the second launch has 256 threads, and the order of additions is the same.  A score's record is seven words:
-// 512^2 and 1024^2 mask, compression and score (256 workgroups) 17.1 / 16.7, 1024 x 2048 (512) 18.6 / 19.3, six matrices (3072)
-// 60 / 67.
+// Workgroups of `threads`.  Objectives: whatever seven matrices of at most eight results per thread of the adding workgroup have in
+// all (up to there the second launch has 256 threads, and the order of additions is the same).  Two launches / one, us, fp32 2:4: one
+// matrix of 512 workgroups 4.8 / 4.5, of 2048 11.3 / 10.4, two 17.3 / 16.5, four 30.6 / 29.5, seven (14336) 50.6 / 48.9; bf16 4:8
+// 7.7 / 7.5 ... 119.6 / 117.4; optimal 4:8 17.4 / 17.2 ... 226 / 224.  (With many more that wait the readers slow down what they wait
+// for: 144 matrices, 36864 workgroups, 147 / 153.)
+// Scores: 256 workgroups, whose records are seven words each.  512^2 and 1024^2 mask, compression and score (256 workgroups)
+// 17.1 / 16.7, 1024 x 2048 (512) 18.6 / 19.3, six matrices (3072) 60 / 67; the score alone 384 7.6 / 6.6, 512 7.8 / 7.3, 1024 8.6 / 12.1.
 inline bool adds_up_itself(const LaunchSums &launch, uint32_t threads, bool score)
 {
     if (launch.waiting > kMostWaiting)
         return false;
-    return score ? launch.total <= 256u : launch.total <= 8192u && launch.most <= 8u * threads;
+    return score ? launch.total <= 256u : launch.most <= 8u * threads;
 }
 
 }  // namespace tmask

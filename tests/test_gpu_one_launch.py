@@ -40,6 +40,7 @@ CASES = [
     ([(1000, 2052)], BF16, 2, 4), ([(1024, 2048), (8, 16)], BF16, 4, 8), ([(1024, 1040)], F32, 4, 8), ([(512, 528)], BF16, 8, 16),
     ([(512, 512)], F32, 5, 16), ([(1024, 1024), (32, 32)], BF16, 16, 32), ([(256, 4160)], F32, 16, 32), ([(1024, 1056)], F32, 16, 32),
     ([(256, 516)], BF16, 1, 4), ([(64, 68)], BF16, 1, 4),
+    ([(2048, 4096)] * 7, F32, 2, 4),
     # a score adds up 256 workgroups itself and no more: strips, narrow strips, columns
     ([(1024, 1024)], F32, 2, 4), ([(1024, 1024), (4, 8)], F32, 2, 4), ([(512, 2044)], BF16, 2, 4), ([(512, 2044), (4, 4)], BF16, 2, 4),
     ([(512, 1024)], BF16, 16, 32), ([(512, 1024), (32, 32)], BF16, 16, 32), ([(256, 512)], F32, 16, 32), ([(64, 64)], F32, 8, 32)]

@@ -62,5 +62,5 @@ def test_the_limits(itself):
     assert itself([1] * 200) and itself([1] * 200 + [256] * 7) and not itself([1] * 200 + [256] * 8)
     assert itself([256] * 8, [1] * 7 + [0])                                    # nobody asked for the eighth
     assert itself([2048]) and not itself([2049]) and itself([512], threads=64) and not itself([513], threads=64)
-    assert itself([2048] * 4) and not itself([2048] * 4 + [1])
+    assert itself([2048] * 7) and itself([2048] * 7 + [1] * 200)               # whatever they have in all
     assert itself([256], score=True) and not itself([257], score=True) and not itself([128, 129], score=True)
