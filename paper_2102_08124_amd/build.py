@@ -14,6 +14,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libtmask.so")
 CALLS = os.path.join(HERE, "_calls.so")
 CALLS_SOURCE = os.path.join(CSRC, "tmask_calls.cpp")
+ABI = os.path.join(HERE, "..", "include", "tmask.h")
 SOURCES = ["tmask_kernels.hip", "tmask_colwise.hip", "tmask_spmm.hip", "tmask_extras.hip"]
 HEADERS = ["tmask_device.hpp", "tmask_solvers.hpp", "tmask_pack.hpp", "tmask_approx4.hpp", "tmask_networks.hpp", "tmask_approx_sel.hpp", "tmask_pack4.hpp", "tmask_pack8.hpp", "tmask_exact_balance.hpp", "tmask_fused4.hpp", "tmask_spmm_choice.hpp", "tmask_sum_choice.hpp", "tmask_host.hpp", os.path.join("..", "..", "include", "tmask.h")]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -30,15 +31,31 @@ def _stale() -> bool:
     return any(os.path.getmtime(os.path.join(CSRC, f)) > t for f in SOURCES + HEADERS)
 
 
+def calls_stamp() -> str:
+    """What _calls.so is built for: it uses the layout of this torch's tensors and of this Python's objects."""
+    import torch
+    return "torch %s hip %s python %d.%d" % ((torch.__version__, torch.version.hip) + sys.version_info[:2])
+
+
+def calls_stale() -> bool:
+    """Whether _calls.so is missing, older than its source or the C ABI, or built for another torch or Python."""
+    if not os.path.exists(CALLS):
+        return True
+    if any(os.path.getmtime(f) > os.path.getmtime(CALLS) for f in (CALLS_SOURCE, ABI)):
+        return True
+    with open(CALLS, "rb") as f:
+        return calls_stamp().encode() + b"\0" not in f.read()
+
+
 def build_calls(force: bool = False, verbose: bool = False) -> str:
     """The extension module that turns tensors into arguments; links against the torch that will load it."""
-    if not force and os.path.exists(CALLS) and os.path.getmtime(CALLS) >= os.path.getmtime(CALLS_SOURCE):
+    if not force and not calls_stale():
         return CALLS
     import torch
     root = os.path.dirname(torch.__file__)
     tmp = CALLS + ".tmp%d" % os.getpid()
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
-           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), '-DTMASK_BUILT_FOR="%s"' % calls_stamp(),
            "-I" + os.path.join(root, "include"), "-I" + os.path.join(root, "include", "torch", "csrc", "api", "include"),
            "-I" + sysconfig.get_paths()["include"], "-I/opt/rocm/include", "-L" + os.path.join(root, "lib"), "-o", tmp, CALLS_SOURCE,
            "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]

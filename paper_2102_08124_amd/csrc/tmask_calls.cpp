@@ -14,8 +14,22 @@
 
 #include <climits>
 #include <cstdint>
+#include <type_traits>
+
+#include "../../include/tmask.h"
+
+#ifndef TMASK_BUILT_FOR
+#error "the build names the torch and the Python that the module is for"
+#endif
 
 namespace {
+
+// The C functions come as addresses; their types are those of the header, or this does not compile.
+template <typename Desc>
+using batch_fn = int(const Desc *, int, tmask_dtype, int, int, tmask_mask_fmt, void *, size_t, void *);
+static_assert(std::is_same_v<decltype(tmask_approx), batch_fn<tmask_mat>> && std::is_same_v<decltype(tmask_exact), batch_fn<tmask_mat>> &&
+              std::is_same_v<decltype(tmask_prune_1d), batch_fn<tmask_mat>> && std::is_same_v<decltype(tmask_apply_pack), batch_fn<tmask_pack_desc>> &&
+              std::is_same_v<decltype(tmask_approx_pack), batch_fn<tmask_fused_desc>>, "the functions that batch() is called with");
 
 bool as_int(PyObject *o, int *out)
 {
@@ -131,8 +145,7 @@ PyObject *batch(PyObject *, PyObject *const *a, Py_ssize_t n)
     size_t bytes;
     return run([&] { return as_head(a, &h) && as_workspace(a[7], &ws, &bytes) && as_stream(a[8], &stream); },
                [&] {
-                   typedef int (*fn_t)(const void *, int, int, int, int, int, void *, size_t, void *);
-                   return ((fn_t)h.fn)(h.descs, h.n, h.dt, h.N, h.M, h.fmt, ws, bytes, stream);
+                   return ((batch_fn<void> *)h.fn)(h.descs, h.n, (tmask_dtype)h.dt, h.N, h.M, (tmask_mask_fmt)h.fmt, ws, bytes, stream);
                });
 }
 
@@ -145,8 +158,8 @@ PyObject *dense(PyObject *, PyObject *const *a, Py_ssize_t n)
     void *stream;
     return run([&] { return as_head(a, &h) && as_stream(a[7], &stream); },
                [&] {
-                   typedef int (*fn_t)(const void *, int, int, int, int, int, void *);
-                   return ((fn_t)h.fn)(h.descs, h.n, h.dt, h.N, h.M, h.fmt, stream);
+                   return ((decltype(&tmask_approx_dense))h.fn)((const tmask_mask_dense_desc *)h.descs, h.n, (tmask_dtype)h.dt, h.N, h.M,
+                                                                (tmask_mask_fmt)h.fmt, stream);
                });
 }
 
@@ -175,8 +188,8 @@ PyObject *score(PyObject *, PyObject *const *a, Py_ssize_t n)
             return as_workspace(a[10], &ws, &bytes) && as_stream(a[11], &stream);
         },
         [&] {
-            typedef int (*fn_t)(const void *, int, int, int, int, int, void *, void *, void *, size_t, void *);
-            return ((fn_t)h.fn)(h.descs, h.n, h.dt, h.N, h.M, h.fmt, out, per_block, ws, bytes, stream);
+            return ((decltype(&tmask_score))h.fn)((const tmask_mat *)h.descs, h.n, (tmask_dtype)h.dt, h.N, h.M, (tmask_mask_fmt)h.fmt,
+                                                  (tmask_score_out *)out, (float *)per_block, ws, bytes, stream);
         });
 }
 
@@ -211,8 +224,7 @@ PyObject *spmm24(PyObject *, PyObject *const *a, Py_ssize_t n)
             return as_stream(a[7], &stream);
         },
         [&] {
-            typedef int (*fn_t)(const void *, const void *, int64_t, int64_t, const void *, int64_t, void *, int64_t, int64_t, int, void *);
-            return ((fn_t)fn)(pv, pi, rows, cols, px, ld_x, py, ld_y, tokens, dt, stream);
+            return ((decltype(&tmask_spmm24))fn)(pv, pi, rows, cols, px, ld_x, py, ld_y, tokens, (tmask_dtype)dt, stream);
         });
 }
 
@@ -226,4 +238,12 @@ PyModuleDef kModule = {PyModuleDef_HEAD_INIT, "_calls", nullptr, 0, kMethods, nu
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__calls(void) { return PyModule_Create(&kModule); }
+PyMODINIT_FUNC PyInit__calls(void)
+{
+    PyObject *const m = PyModule_Create(&kModule);
+    if (m && PyModule_AddStringConstant(m, "built_for", TMASK_BUILT_FOR) < 0) {
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
+}

@@ -1,13 +1,14 @@
 """The native half of binding.py takes the usual arguments and leaves every other one to the Python half: it never raises, and on
 the GPU both halves give the same outputs and the same errors."""
 import ctypes
+import os
 import types
 
 import pytest
 
 torch = pytest.importorskip("torch")
 
-from paper_2102_08124_amd import binding as tm   # noqa: E402
+from paper_2102_08124_amd import binding as tm, build   # noqa: E402
 
 NONE = types.SimpleNamespace(**{name: (lambda *a: None) for name in ("batch", "dense", "score", "spmm24")})
 
@@ -84,6 +85,26 @@ def test_host_memory_reaches_no_kernel(monkeypatch):
     assert seen == []
     tm.tmask_spmm24(_Device(64, 64), _Device(64, 16, dtype=torch.uint8), 64, 128, x, y, stream=stream)
     assert len(seen) == 1
+
+
+def test_the_native_half_is_rebuilt_when_what_it_uses_changes(monkeypatch, tmp_path):
+    build.build_calls()
+    assert not build.calls_stale()
+    copy = tmp_path / "_calls.so"
+    copy.write_bytes(open(build.CALLS, "rb").read())
+    monkeypatch.setattr(build, "CALLS", str(copy))
+    assert not build.calls_stale()
+    abi = tmp_path / "tmask.h"
+    abi.write_text("")
+    os.utime(abi, (copy.stat().st_mtime + 10,) * 2)
+    with monkeypatch.context() as m:
+        m.setattr(build, "ABI", str(abi))
+        assert build.calls_stale()
+    with monkeypatch.context() as m:
+        m.setattr(build, "calls_stamp", lambda: "torch 1.0 hip 5 python 3.10")
+        assert build.calls_stale()
+    copy.unlink()
+    assert build.calls_stale()
 
 
 def _outcome(f):
