@@ -10,9 +10,12 @@ from __future__ import annotations
 import ctypes as C
 import importlib
 import os
+import warnings
 from typing import Optional, Sequence
 
 import torch
+
+from .build import calls_stamp
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libtmask.so")
@@ -81,13 +84,35 @@ _lib = None
 _calls = None
 
 
+class _ThroughCtypes:
+    """In the place of _calls: every call is one for the code here."""
+    batch = dense = score = spmm24 = staticmethod(lambda *args: None)
+
+
+def _native_calls():
+    """The module _calls, if it is there and was built for this torch and this Python; the code here makes the same calls of
+    libtmask.so one microsecond slower."""
+    if not os.path.exists(CALLS_PATH):
+        warnings.warn("_calls.so is missing: calls go through ctypes (build it with `python -m paper_2102_08124_amd.build`)")
+        return _ThroughCtypes
+    try:
+        module = importlib.import_module(__package__ + "._calls")
+        if module.built_for == calls_stamp():
+            return module
+        reason = "it was built for " + module.built_for
+    except (ImportError, AttributeError) as e:
+        reason = str(e)
+    warnings.warn("_calls.so does not fit (%s): calls go through ctypes" % reason)
+    return _ThroughCtypes
+
+
 def load_library():
     """Loads libtmask.so; raises if it has not been built (python -m paper_2102_08124_amd.build)."""
     global _lib, _calls
     if _lib is not None:
         return _lib
-    if not os.path.exists(LIB_PATH) or not os.path.exists(CALLS_PATH):
-        raise RuntimeError("libtmask.so or _calls.so is missing: build it with `python -m paper_2102_08124_amd.build` "
+    if not os.path.exists(LIB_PATH):
+        raise RuntimeError("libtmask.so is missing: build it with `python -m paper_2102_08124_amd.build` "
                            "(there is no fallback path)")
     L = C.CDLL(LIB_PATH)
     vp, ci, sz = C.c_void_p, C.c_int, C.c_size_t
@@ -131,7 +156,7 @@ def load_library():
     L.at = {name: C.cast(getattr(L, name), vp).value for name in
             ("tmask_approx", "tmask_exact", "tmask_prune_1d", "tmask_apply_pack", "tmask_approx_pack", "tmask_approx_dense",
              "tmask_score", "tmask_spmm24")}
-    _calls = importlib.import_module(__package__ + "._calls")
+    _calls = _native_calls()
     _lib = L
     return L
 

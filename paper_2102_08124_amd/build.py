@@ -71,8 +71,14 @@ def build_calls(force: bool = False, verbose: bool = False) -> str:
 
 def build(force: bool = False, verbose: bool = False) -> str:
     """Compile what is older than its sources (or everything with force=True).  The translation units are compiled side by
-    side into _build/ (not tracked), then linked."""
-    build_calls(force, verbose)
+    side into _build/ (not tracked), then linked.  Without a g++ or torch's headers there is no _calls.so, and binding.py goes
+    through ctypes."""
+    try:
+        build_calls(force, verbose)
+    except (ImportError, OSError, RuntimeError) as e:
+        if os.path.exists(CALLS):
+            os.remove(CALLS)                      # not one of other sources
+        sys.stderr.write("no _calls.so (%s): calls will go through ctypes\n" % e)
     if not (force or _stale()):
         return LIB
     from concurrent.futures import ThreadPoolExecutor

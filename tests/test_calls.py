@@ -87,6 +87,36 @@ def test_host_memory_reaches_no_kernel(monkeypatch):
     assert len(seen) == 1
 
 
+def test_the_binding_works_without_the_native_half(monkeypatch, tmp_path):
+    """Missing, unloadable, or built for another torch: every call then takes the Python half."""
+    tm.load_library()
+    native = tm._calls
+    assert native is not tm._ThroughCtypes and native.built_for == build.calls_stamp()
+    monkeypatch.setattr(tm, "_calls", native)                  # put back at the end
+    broken = tmp_path / "_calls.so"
+    for path, module in [(tmp_path / "none.so", None), (broken, ImportError("undefined symbol")), (broken, types.SimpleNamespace()),
+                         (broken, types.SimpleNamespace(built_for="torch 1.0"))]:
+        broken.write_bytes(b"")
+        monkeypatch.setattr(tm, "CALLS_PATH", str(path))
+
+        def load(name, module=module):
+            assert name.endswith("._calls")
+            if isinstance(module, Exception):
+                raise module
+            return module
+
+        monkeypatch.setattr(tm.importlib, "import_module", load)
+        monkeypatch.setattr(tm, "_lib", None)
+        with pytest.warns(UserWarning, match="go through ctypes"):
+            L = tm.load_library()
+        assert tm._calls is tm._ThroughCtypes
+        batch = tm.MatBatch.__new__(tm.MatBatch)
+        batch.arr, batch.n, batch.dt = (tm.tmask_mat * 1)(), 1, 0
+        with pytest.raises(tm.TmaskError, match="NULL"):
+            tm.tmask_approx(batch, None, 2, 4, stream=types.SimpleNamespace(cuda_stream=0))
+        assert L.at["tmask_approx"]
+
+
 def test_the_native_half_is_rebuilt_when_what_it_uses_changes(monkeypatch, tmp_path):
     build.build_calls()
     assert not build.calls_stale()
@@ -105,6 +135,20 @@ def test_the_native_half_is_rebuilt_when_what_it_uses_changes(monkeypatch, tmp_p
         assert build.calls_stale()
     copy.unlink()
     assert build.calls_stale()
+
+
+def test_a_build_without_a_compiler_leaves_no_native_half(monkeypatch, tmp_path, capsys):
+    copy = tmp_path / "_calls.so"
+    copy.write_bytes(b"of other sources")
+    monkeypatch.setattr(build, "CALLS", str(copy))
+    monkeypatch.setattr(build, "_stale", lambda: False)
+
+    def run(cmd, **kwargs):
+        raise FileNotFoundError(cmd[0])
+
+    monkeypatch.setattr(build.subprocess, "run", run)
+    assert build.build() == build.LIB and not copy.exists()
+    assert "ctypes" in capsys.readouterr().err
 
 
 def _outcome(f):
