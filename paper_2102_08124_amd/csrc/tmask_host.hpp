@@ -34,6 +34,15 @@ struct ProfileScope {
 
 Tags draw_tags();
 
+// A launch whose arguments HIP copies from where they lie: passed by value, a table of 15 KB is copied to the stack of the kernel's
+// stub first.  An error shows in hipGetLastError.
+template <typename Args>
+inline void launch_kernel(void (*kernel)(const Args), dim3 grid, dim3 block, size_t lds, hipStream_t stream, Args &args)
+{
+    void *params[] = {&args};
+    (void)hipLaunchKernel((const void *)kernel, grid, block, params, lds, stream);
+}
+
 // Second-stage reductions (tmask_kernels.hip) for kernels of other translation units: first0[k] = index, inside the
 // launch, of the first partial result of matrix k; first0[nb] = their number.
 int launch_objective_reduce(double *const *objective, const uint32_t *first0, int nb, uint32_t partial0, const void *partials,

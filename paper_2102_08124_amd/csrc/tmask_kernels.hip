@@ -1372,7 +1372,7 @@ static int run_mask(const tmask_mat *mats, int n_mats, int dt, int N, int M, int
                 args.tags = draw_tags();
             {
                 ProfileScope prof(stream, first + kMaxBatch >= n_mats);
-                hipLaunchKernelGGL(kernel, dim3(tiles), dim3(kThreads), 0, stream, args);
+                launch_kernel(kernel, dim3(tiles), dim3(kThreads), 0, stream, args);
             }
             const hipError_t e = hipGetLastError();
             return e == hipSuccess ? TMASK_OK : hip_fail(e, "mask kernel launch");
@@ -1518,7 +1518,7 @@ int tmask_score(const tmask_mat *mats, int n_mats, tmask_dtype dt, int N, int M,
                 args.tags = draw_tags();
             {
                 ProfileScope prof(stream, first + kMaxBatch >= n_mats);
-                hipLaunchKernelGGL(kernel, dim3(tiles), dim3(kThreads), 0, stream, args);
+                launch_kernel(kernel, dim3(tiles), dim3(kThreads), 0, stream, args);
             }
             const hipError_t e = hipGetLastError();
             return e == hipSuccess ? TMASK_OK : hip_fail(e, "score kernel launch");
@@ -1671,7 +1671,7 @@ int tmask_apply_pack(const tmask_pack_desc *descs, int n, tmask_dtype dt, int N,
             args.n = (uint32_t)nb; args.N = (uint32_t)N;
             {
                 ProfileScope prof(stream, first + kMaxPackBatch >= n);
-                hipLaunchKernelGGL(kernel, dim3(tiles), dim3(threads), lds_reserve, stream, args);
+                launch_kernel(kernel, dim3(tiles), dim3(threads), lds_reserve, stream, args);
             }
             const hipError_t e = hipGetLastError();
             return e == hipSuccess ? TMASK_OK : hip_fail(e, "pack kernel launch");
@@ -1911,7 +1911,7 @@ static int run_mask_dense(const tmask_mask_dense_desc *descs, int n, tmask_dtype
             args.n_mats = (uint32_t)nb; args.K = (uint32_t)(M - N); args.N = (uint32_t)N;
             {
                 ProfileScope prof(stream, first + kMaxBatch >= n);
-                hipLaunchKernelGGL(kernel, dim3(tiles), dim3(kThreads), 0, stream, args);
+                launch_kernel(kernel, dim3(tiles), dim3(kThreads), 0, stream, args);
             }
             const hipError_t e = hipGetLastError();
             return e == hipSuccess ? TMASK_OK : hip_fail(e, "mask + dense copy kernel launch");
