@@ -75,9 +75,11 @@ struct Tags {
 };
 
 // CAP matrices.  The arguments of a launch are copied to where the device reads them, 16 KB in about a microsecond, and a small
-// call has little else to do; so the kernels whose calls can be that short exist with a table of eight too.  Back to back, us: masked
-// copy 256^2 .. 1024^2 5.4 -> 4.2, optimal 2:4 of 512^2 5.4 -> 4.6, masks at 4:8 5.3 -> 5.0, mask, compression and score of
-// 1000 x 2052 22.7 -> 21.1; the slower ones (other N, the optimal masks at M = 8, 16) would gain 0.2 us of 14 or more.
+// call has little else to do; so Algorithm 1, its masked copies and the compressions at N = M/2, the optimal 2:4 and the scores exist
+// with a table of eight too.  Back to back, us: masked copy 256^2 .. 1024^2 5.4 -> 4.2, optimal 2:4 of 512^2 5.4 -> 4.6, masks at 4:8
+// 5.3 -> 5.0, mask, compression and score of 1000 x 2052 22.7 -> 21.1.  The others have the large table alone: the optimal masks at M =
+// 8, 16 would gain 0.2 us of 14 or more; other N, row pruning, the one-pass compression and the column-per-lane kernels are not
+// measured with a small one (a mask of 512^2 fp32 without objective takes 3.3 us at 2:4, 4.2 at 1:4).
 template <int CAP>
 struct BatchArgsOf {
     MatDev m[CAP];

@@ -42,8 +42,8 @@ __device__ __forceinline__ void unpack_row(const u32x4 &r, uint32_t (&a)[C])
 // A bf16 lane takes half a strip, four columns, as an fp32 lane does (the host launches twice the workgroups): eight
 // columns of a block and the prices' state do not fit a lane's registers.
 constexpr bool exact_half_strips(int dt, int M) { return dt == kBF16 && M >= 8; }
-// Workgroups per compute unit, which the registers are held to: 96 at M = 8 (at most two values of a lane in
-// scratch memory), 168 at M = 16 (at most one).
+// Workgroups per compute unit, which the registers are held to: 96 at M = 8 (no value of a lane in
+// scratch memory, at bf16 with bit masks and any N four), 168 at M = 16 (none to two).
 constexpr int exact_workgroups_per_cu(int dt, int M) { return M == 16 ? 3 : 5; }
 
 // GENERAL: any N (K = args.K pruned per line); otherwise N = M/2.

@@ -516,9 +516,10 @@ __global__ __launch_bounds__(256, RT * CT <= 4 ? 2 : 1) void spmm24_tile_kernel(
     // whole (1048576 x 64, 4 tokens: 38 -> 31 us).
     // With p.lines it covers whole lines of 128 bytes of eight tokens, and the stores are streaming ones: as plain stores the
     // results push out of L2 the panels that the next tiles read (8192 tokens, three / four rotating sets of buffers, us: 4096 x
-    // 1024 bf16 52 -> 48 / 57.5 -> 50, fp32 64 -> 55 / 68 -> 59; 1024 x 4096 fp32 63 -> 49; 1024 x 256 bf16 10.0 -> 8.1; one set of
-    // buffers, which stays in the memory-side cache: 4096 x 1024 bf16 50.3 -> 50.5).  Streaming stores of parts of lines lose
-    // (fp32 8192 x 64 54 -> 78), which is where the line lies on the host.
+    // 1024 bf16 52 -> 48 / 57.5 -> 50, fp32 64 -> 55 / 68 -> 59; 1024 x 4096 fp32 63 -> 49; 1024 x 256 bf16 10.0 -> 8.1).  What stays in
+    // the memory-side cache gains nothing: one set of buffers 4096 x 1024 bf16 50.3 -> 50.5, the same product with
+    // new inputs and results for each call 46.9 -> 46.7, fp32 3072 x 64 into the same 100 MB each time 20.1 -> 22.9 (four sets 24.5 -> 23.0).
+    // Streaming stores of parts of lines lose (fp32 8192 x 64 54 -> 78), which is where the line lies on the host.
     auto store_tile = [&](uint32_t j) -> bool {
         uint32_t row0, tok0;
         locate(j, row0, tok0);

@@ -76,6 +76,17 @@ def test_16_of_32_by_rows_has_eight_workgroups_on_a_compute_unit(kernels, fmt):
     assert use["threads"] == 256 and _wavefronts(use) == 8 and 160 * 1024 // use["lds"] >= 8, use
 
 
+@pytest.mark.parametrize("m,waves", [(8, 5), (16, 3)])
+def test_the_exact_kernels_keep_next_to_nothing_in_scratch_memory(kernels, m, waves):
+    """At most four values of a lane at M = 8, two at M = 16 (and 4 bytes); their workgroups are four wavefronts."""
+    for dt in (0, 1):
+        for fmt in (0, 1):
+            for general in ("false", "true"):
+                use, = kernels["exact_balanced_kernel<%d, %d, %d, %s>" % (dt, m, fmt, general)]
+                none = m == 8 and (dt, fmt, general) != (1, 1, "true")
+                assert _wavefronts(use) == waves and use["scratch"] <= (0 if none else 20 if m == 8 else 12), (dt, fmt, general, use)
+
+
 @pytest.mark.parametrize("dt", [0, 1, 2])
 @pytest.mark.parametrize("fmt", [0, 1])
 def test_scores_at_m4_leave_room_for_eight_wavefronts(kernels, dt, fmt):
