@@ -22,9 +22,12 @@ struct LaunchSums {
 // queue starts the workgroups of one launch after the other, and a launch whose workgroups have all started ends by itself, so
 // of each queue the waiting workgroups of one launch count.  Seven each on the four queues that HIP makes hold 28 of the
 // 32 compute units of an XCD at the worst (all on the same one, each on a compute unit of its own): a unit that none of them holds is
-// left, and any workgroup fits there once the others on it are done.  (Queues of other processes come on top; launches would
-// have to fill five or more of them, each with seven waiting workgroups on one XCD.)  Larger batches leave their sums to a second
-// launch, which they hardly notice: 52 matrices of 5724 workgroups 22.8 us in one launch, 23.5 in two.
+// left, and any workgroup fits there once the others on it are done.  With streams of all three priorities, four queues each, it is 84
+// waiting workgroups, of 96 places that an XCD has for the largest of these kernels (three to a compute unit).  A launch alone ends
+// on however few compute units: workgroups start in the order of their numbers on each XCD, and only lower ones are waited for.
+// Beyond that (streams confined to the same few compute units, queues of many processes) the wait is bounded.  Larger
+// batches leave their sums to a second launch, which they hardly notice: 52 matrices of 5724 workgroups 22.8 us in one launch, 23.5
+// in two.
 constexpr uint32_t kQueues = 4, kUnitsOfXcd = 32;
 constexpr uint32_t kMostWaiting = (kUnitsOfXcd - 1) / kQueues;
 

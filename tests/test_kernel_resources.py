@@ -95,3 +95,18 @@ def test_scores_at_m4_leave_room_for_eight_wavefronts(kernels, dt, fmt):
     assert len(uses) == 2                                      # the two sizes of the table
     for use in uses:
         assert _wavefronts(use) == 8 and use["scratch"] == 0, use
+
+
+def test_a_compute_unit_has_three_places_for_each_kernel_that_waits(kernels):
+    """What the number of workgroups that may wait in a launch is reckoned with."""
+    waits = re.compile(r"mask_kernel<|approx24|approx_sel|exact24|exact_balanced|score_kernel<|approx_pack24|pack48_\w+<.*true|cw_mask|cw_exact|cw_score")
+    seen = 0
+    for name, uses in kernels.items():
+        if not waits.match(name) or name.startswith("mask_kernel<0, 1, 16,"):     # the generic form of Algorithm 1, which bf16 8:16 never takes
+            continue
+        for use in uses:
+            lds = use["lds"] + (8192 if name.startswith("approx_pack24_kernel<0") else 0)         # reserved at the launch
+            places = min(_wavefronts(use) * 4 // (use["threads"] // 64), 160 * 1024 // lds if lds else 32)
+            assert places >= 3, (name, use)
+            seen += 1
+    assert seen > 100
