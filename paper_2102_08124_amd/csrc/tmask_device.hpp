@@ -180,10 +180,25 @@ __device__ __forceinline__ void lm_shift_in(uint32_t &r, lanemask_t m)
 // Wavefront sums by DPP, in a fixed order (deterministic): quad, then the four quads of a row of 16
 // lanes by row rotation, then the four rows through scalar reads.  All 64 lanes must be active.
 // The result is uniform.
+constexpr int kRowHalfMirror = 0x141, kRowRor8 = 0x128, kRowNewbcast = 0x150;     // lane l of sixteen reads lane l ^ 7, l ^ 8, the one given
+
 template <int CTRL>
 __device__ __forceinline__ uint32_t dpp_read(uint32_t v)
 {
     return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, 0xF, 0xF, false);
+}
+
+// What lane I of the M = 8 or 16 lanes of a block (an aligned part of sixteen lanes) holds.
+template <int M, int I>
+__device__ __forceinline__ uint32_t of_lane(uint32_t v)
+{
+    static_assert(M == 8 || M == 16, "a row of sixteen lanes or half of one");
+    if constexpr (M == 16) {
+        return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kRowNewbcast + I, 0xF, 0xF, true);
+    } else {
+        const int low = __builtin_amdgcn_update_dpp(0, (int)v, kRowNewbcast + I, 0xF, 0x3, true);
+        return (uint32_t)__builtin_amdgcn_update_dpp(low, (int)v, kRowNewbcast + 8 + I, 0xF, 0xC, false);
+    }
 }
 
 __device__ __forceinline__ float wave_sum(float v)

@@ -388,8 +388,16 @@ __device__ __forceinline__ void exact_costs(const uint32_t (&key)[M][CL], T (&co
         const uint32_t o = quad_xor<1>(kmax);
         kmax = o > kmax ? o : kmax;
     }
-    if constexpr (G == 4) {
+    if constexpr (G >= 4) {
         const uint32_t o = quad_xor<2>(kmax);
+        kmax = o > kmax ? o : kmax;
+    }
+    if constexpr (G >= 8) {                                     // the quads hold one value each by now: any pairing of them will do
+        const uint32_t o = dpp_read<kRowHalfMirror>(kmax);
+        kmax = o > kmax ? o : kmax;
+    }
+    if constexpr (G == 16) {
+        const uint32_t o = dpp_read<kRowRor8>(kmax);
         kmax = o > kmax ? o : kmax;
     }
     const uint32_t emax = (kmax >> 23) ? (kmax >> 23) : 1u;
@@ -489,6 +497,68 @@ struct PriceSchedule<16> {
     static constexpr float window = 0.445f, window_next = 0.703f, step = 0.192f, step_next = 0.736f, momentum = 0.2f;
 };
 
+// A column of a round: x[i] = 0 ... 1 by where key k[i] (a positive float, which compares as its bits) lies in a window of
+// width -1 / slope around the middle between the K-th and the (K+1)-th smallest key.
+template <int M, bool GENERAL>
+__device__ __forceinline__ void price_window(const uint32_t (&k)[M], float slope, uint32_t K, float (&x)[M])
+{
+    constexpr int H = M / 2;
+    float both;                                                 // the two, added
+    if constexpr (GENERAL) {
+        uint32_t srt[M];
+#pragma unroll
+        for (int i = 0; i < M; i++)
+            srt[i] = k[i];
+        sort_asc<M>(srt);
+        both = __uint_as_float(srt[(K - 1u) & (uint32_t)(M - 1)]) + __uint_as_float(srt[K & (uint32_t)(M - 1)]);
+    } else if constexpr (M == 8) {
+        const Eight e = columns_of_8(k);
+        both = __uint_as_float(fourth_of_8(e)) + __uint_as_float(fifth_of_8(e));
+    } else {
+        uint32_t lo[H], hi[H], below = 0u, above = 0xFFFFFFFFu;
+#pragma unroll
+        for (int i = 0; i < H; i++) {
+            lo[i] = k[i];
+            hi[i] = k[H + i];
+        }
+        sort_asc<H>(lo);
+        sort_asc<H>(hi);
+#pragma unroll
+        for (int i = 0; i < H; i += 2) {
+            const uint32_t b0 = lo[i] < hi[H - 1 - i] ? lo[i] : hi[H - 1 - i], b1 = lo[i + 1] < hi[H - 2 - i] ? lo[i + 1] : hi[H - 2 - i];
+            const uint32_t a0 = lo[i] < hi[H - 1 - i] ? hi[H - 1 - i] : lo[i], a1 = lo[i + 1] < hi[H - 2 - i] ? hi[H - 2 - i] : lo[i + 1];
+            below = max3u(below, b0, b1);
+            above = min3u(above, a0, a1);
+        }
+        both = __uint_as_float(below) + __uint_as_float(above);
+    }
+    const float at = 0.5f - (0.5f * slope) * both;              // clamp((middle - key) / w + 1/2)
+#pragma unroll
+    for (int i = 0; i < M; i++)
+        x[i] = fma_clamp01(__uint_as_float(k[i]), slope, at);
+}
+
+// What the rounds of a block start with: the part of the row means that its prices make equal, and slope (of the windows) and step.
+// mean: of the block's costs; spread: of two entries of a column half a block apart, row means taken off; row_dev: sum of what
+// the row means differ from the mean by.
+template <int M>
+struct PriceScale {
+    float part, slope, step;
+
+    __device__ __forceinline__ PriceScale(float mean, float spread, float row_dev)
+    {
+        using Sched = PriceSchedule<M>;
+        // three times what chance makes of the row means of independent entries, against what they are
+        const float chance = 3.f * spread * (M == 16 ? 2.828427f : 2.f) * __builtin_amdgcn_rcpf(row_dev);      // sqrt(M / 2) M / M
+        part = 1.f - 0.25f * (chance < 1.f ? chance : 1.f);
+        float unit = 1.414214f * spread;
+        unit = unit < mean ? unit : mean;
+        unit = unit > 1.f ? unit : 1.f;                         // blocks of zeros, and of costs that rows and columns explain
+        slope = -(1.f / Sched::window) * __builtin_amdgcn_rcpf(unit);
+        step = Sched::step * unit;
+    }
+};
+
 template <int M, int CL, int G, bool GENERAL = false>
 __device__ __forceinline__ uint32_t exact_priced_start(const float (&cost)[M][CL], uint32_t gpos, uint32_t (&xcol)[CL],
                                                        uint32_t k_general = 0)
@@ -537,18 +607,13 @@ __device__ __forceinline__ uint32_t exact_priced_start(const float (&cost)[M][CL
     if constexpr (G == 4)
         spread = quad_xor_sum<2>(spread);
     spread *= 2.f / (M * M);
-    // three times what chance makes of the row means of independent entries, against what they are
-    const float chance = 3.f * spread * (M == 16 ? 2.828427f : 2.f) * __builtin_amdgcn_rcpf(row_dev);      // sqrt(M / 2) M / M
-    const float part = 1.f - 0.25f * (chance < 1.f ? chance : 1.f);
+    const PriceScale<M> scale(mean, spread, row_dev);
 #pragma unroll
     for (int i = 0; i < M; i++) {
-        pr[i] = kOffset + part * pr[i];
+        pr[i] = kOffset + scale.part * pr[i];
         vel[i] = 0.f;
     }
-    float unit = 1.414214f * spread;
-    unit = unit < mean ? unit : mean;
-    unit = unit > 1.f ? unit : 1.f;                             // blocks of zeros, and of costs that rows and columns explain
-    float slope = -(1.f / Sched::window) * __builtin_amdgcn_rcpf(unit), step = Sched::step * unit;
+    float slope = scale.slope, step = scale.step;
     float drift = 0.f;                                          // what K per row and round adds to every price
     float dvel = 0.f;
     constexpr float kCarry = Sched::momentum / Sched::step_next;
@@ -561,41 +626,11 @@ __device__ __forceinline__ uint32_t exact_priced_start(const float (&cost)[M][CL
 #pragma unroll
             for (int i = 0; i < M; i++)
                 k[i] = __float_as_uint(pr[i] + cf[i][c]);
-            float both;                                         // the K-th and the (K+1)-th smallest key, added
-            if constexpr (GENERAL) {
-                uint32_t srt[M];
+            float x[M];
+            price_window<M, GENERAL>(k, slope, (uint32_t)K, x);
 #pragma unroll
-                for (int i = 0; i < M; i++)
-                    srt[i] = k[i];
-                sort_asc<M>(srt);
-                both = __uint_as_float(srt[(uint32_t)(K - 1) & (uint32_t)(M - 1)]) + __uint_as_float(srt[(uint32_t)K & (uint32_t)(M - 1)]);
-            } else if constexpr (M == 8) {
-                const Eight e = columns_of_8(k);
-                both = __uint_as_float(fourth_of_8(e)) + __uint_as_float(fifth_of_8(e));
-            } else {
-                uint32_t lo[H], hi[H], below = 0u, above = 0xFFFFFFFFu;
-#pragma unroll
-                for (int i = 0; i < H; i++) {
-                    lo[i] = k[i];
-                    hi[i] = k[H + i];
-                }
-                sort_asc<H>(lo);
-                sort_asc<H>(hi);
-#pragma unroll
-                for (int i = 0; i < H; i += 2) {
-                    const uint32_t b0 = lo[i] < hi[H - 1 - i] ? lo[i] : hi[H - 1 - i], b1 = lo[i + 1] < hi[H - 2 - i] ? lo[i + 1] : hi[H - 2 - i];
-                    const uint32_t a0 = lo[i] < hi[H - 1 - i] ? hi[H - 1 - i] : lo[i], a1 = lo[i + 1] < hi[H - 2 - i] ? hi[H - 2 - i] : lo[i + 1];
-                    below = max3u(below, b0, b1);
-                    above = min3u(above, a0, a1);
-                }
-                both = __uint_as_float(below) + __uint_as_float(above);
-            }
-            const float at = 0.5f - (0.5f * slope) * both;      // clamp((middle - key) / w + 1/2)
-#pragma unroll
-            for (int i = 0; i < M; i++) {
-                const float x = fma_clamp01(__uint_as_float(k[i]), slope, at);
-                f[i] = c == 0 ? x : f[i] + x;
-            }
+            for (int i = 0; i < M; i++)
+                f[i] = c == 0 ? x[i] : f[i] + x[i];
             if constexpr (CL > 4 || M == 16)
                 __builtin_amdgcn_sched_barrier(0);   // one column at a time: interleaving them costs M registers each
         }
@@ -701,13 +736,22 @@ __device__ __forceinline__ uint32_t exact_priced_start(const float (&cost)[M][CL
     return e2 >> 1;
 }
 
-// LDS of one wavefront's searches: labels and predecessors of the rows and columns of its 64 / M blocks, the chain that each
+// LDS of one wavefront's searches: the predecessors of the rows and columns of its 64 / M blocks, the chain that each
 // row would take and the row it starts from, and the entries that the chains flip.
 struct SearchLds {
-    int drow[64], dcol[64];
     uint32_t prow[64], pcol[64];
     uint32_t chain[64], start[64], flip_row[64], flip_col[64];
 };
+
+// go(std::integral_constant<int, I>) for I = 0 ... M - 1: lane numbers within DPP controls are constants of the instruction.
+template <int M, int I = 0, typename Go>
+__device__ __forceinline__ void each_of(Go &&go)
+{
+    if constexpr (I < M) {
+        go(std::integral_constant<int, I>{});
+        each_of<M, I + 1>(go);
+    }
+}
 
 // Augments until every row of the block has exactly K pruned entries (after at most M*M searches).  M lanes hold a
 // block, a wavefront 64 / M of them: lane j of the block holds column j (ccol, xcol: bit i = entry (i, j) pruned) and row
@@ -715,8 +759,9 @@ struct SearchLds {
 //
 // A search labels the rows from those with excess, alternating a column step (lane j: the cheapest way into column j
 // through a pruned entry of a reached row) and a row step (lane j: the cheapest way into row j out of a column through an
-// unpruned entry); labels travel through LDS, which within a wavefront needs no barrier.  Labels only ever fall, and a
-// predecessor changes only when its label falls strictly: with exact integer sums and no negative cycle the
+// unpruned entry).  Labels pass between the lanes of a block by DPP, and which entries are pruned is a lane mask for each
+// row and column: four vector instructions an entry (eight through LDS with the bits tested in place, and the reads' latency).  Labels only
+// ever fall, and a predecessor changes only when its label falls strictly: with exact integer sums and no negative cycle the
 // predecessor graph is then a forest, also among entries of equal cost.
 //
 // At convergence every predecessor edge is tight (label of the head = label of the tail + edge cost), so flipping along any
@@ -745,43 +790,40 @@ __device__ __forceinline__ void exact_search(const int (&ccol)[M], const int (&c
         if (excess == 0)
             break;
         uint32_t over = mine(excess);
-        int drow = cnt > K ? 0 : kInfDist;
-        uint32_t prow = kNoPred;
-        fence();
-        lds.drow[lane] = drow;
-        lds.prow[lane] = prow;
-        fence();
-        int dcol = kInfDist;
-        uint32_t pcol = 0;
+        int drow = cnt > K ? 0 : kInfDist, dcol = kInfDist;
+        uint32_t prow = kNoPred, pcol = 0;
+        lanemask_t in[M], out[M];                                // entry (i, j) is pruned, entry (j, i) is not
+#pragma unroll
+        for (int i = 0; i < M; i++) {
+            in[i] = lm((xcol >> i) & 1u);
+            out[i] = ~lm((xrow >> i) & 1u);
+        }
 #pragma unroll 1
         for (int it = 0; it <= M; it++) {
-#pragma unroll
-            for (int i = 0; i < M; i++) {
-                const int d = lds.drow[base + i];
-                const int v = d - ccol[i];
-                const bool better = ((xcol >> i) & 1u) && d < kReachable && v < dcol;
+            // from a row that is not reached: above every label, and not a label itself
+            each_of<M>([&](auto c) {
+                constexpr int i = decltype(c)::value;
+                const int v = (int)of_lane<M, i>((uint32_t)drow) - ccol[i];
+                const bool better = lm_test(lm(v < dcol) & in[i]);
                 dcol = better ? v : dcol;
                 pcol = better ? (uint32_t)i : pcol;
-            }
-            lds.dcol[lane] = dcol;
-            lds.pcol[lane] = pcol;
-            fence();
-            bool changed = false;
-#pragma unroll
-            for (int c = 0; c < M; c++) {
-                const int v = lds.dcol[base + c] + crow[c];      // from an unreached column: above every label
-                const bool better = !((xrow >> c) & 1u) && v < drow;
+            });
+            dcol = dcol < kReachable ? dcol : kInfDist;
+            const int before = drow;
+            each_of<M>([&](auto c) {
+                constexpr int i = decltype(c)::value;
+                const int v = (int)of_lane<M, i>((uint32_t)dcol) + crow[i];      // from an unreached column: above every label
+                const bool better = lm_test(lm(v < drow) & out[i]);
                 drow = better ? v : drow;
-                prow = better ? (uint32_t)c : prow;
-                changed = changed || better;
-            }
-            fence();
-            lds.drow[lane] = drow;
-            lds.prow[lane] = prow;
-            fence();
-            if (lm(changed) == 0)
+                prow = better ? (uint32_t)i : prow;
+            });
+            if (lm(drow != before) == 0)
                 break;
         }
+        fence();
+        lds.prow[lane] = prow;
+        lds.pcol[lane] = pcol;
+        fence();
         const bool lacks = cnt < K && drow < kReachable;
         uint32_t cand = mine(lm(lacks));
         if (lm(cand != 0u) == 0)
