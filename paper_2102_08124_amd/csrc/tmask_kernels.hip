@@ -20,6 +20,7 @@
 #include "tmask_pack4.hpp"
 #include "tmask_pack8.hpp"
 #include "tmask_exact_balance.hpp"
+#include "tmask_exact_spread.hpp"
 #include "tmask_fused4.hpp"
 
 namespace tmask {
@@ -1207,6 +1208,13 @@ static int scratch_of_current_device(void **out)
     return TMASK_OK;
 }
 
+// Workgroups per compute unit up to which tmask_exact gives every column of a block a lane of its own: at M = 16 what a compute unit
+// holds of that kernel, at M = 8 less, since a block is an eighth of the work there and the start of a kernel weighs more.  One matrix,
+// four columns / one column to a lane, us: fp32 8:16 464 x 128 28.9 / 14.3, 1024^2 (one workgroup per unit) 34.4 / 20.2, 2048^2 (4) 38.0 / 32.6, 4096 x
+// 2048 (8) 50.4 / 51.6; 13:16 4096 x 2048 55.1 / 55.3; 4:8 464 x 128 12.6 / 8.6, 1024 x 512 (1) 14.1 / 11.9, 1024^2 (2) 15.2 / 14.0, 2048 x
+// 1024 (4) 15.9 / 17.4; bf16 4:8 12.9 / 8.9, 14.4 / 12.0, 14.7 / 13.7, 14.9 / 16.9; 3:8 1024^2 16.7 / 14.0.
+static uint64_t spread_workgroups(int M) { return M == 16 ? 5u : 2u; }
+
 // One launch for at most kWholeMats matrices of at most kWholeThreads strips at 2:4 (checked by the caller, like the rest).
 template <int SOLVER>
 static int run_whole(const tmask_mat *mats, int n_mats, int sdt, int mf, hipStream_t stream)
@@ -1317,7 +1325,25 @@ static int run_mask(const tmask_mat *mats, int n_mats, int dt, int N, int M, int
         else
             kern = mf == kMaskU8 ? TMASK_MANY(exact24_kernel, kBF16, kMaskU8, 3, BatchArgs) : TMASK_MANY(exact24_kernel, kBF16, kMaskBits, 3, BatchArgs);
     }
-    if (SOLVER == kSolveExact && (M == 8 || M == 16)) {
+    bool spread = false;
+    if (SOLVER == kSolveExact && (M == 8 || M == 16) && n_mats <= kFewMats) {
+        uint64_t wgs = 0;
+        for (int i = 0; i < n_mats; i++)
+            wgs += (uint64_t)(mats[i].rows / M * mats[i].cols + kThreads - 1) / kThreads;
+        // Four of its workgroups take the weights that the workspace reserves 56 bytes for, 64 in records.  Where those do not fit, one
+        // matrix leaves its sum to a second launch, and more keep the one launch of the other kernel.
+        const bool room = !want_obj || n_mats == 1 || wgs * 16u <= ws_bytes;
+        spread = room && wgs <= spread_workgroups(M) * (uint64_t)cu_count();
+    }
+    if (spread) {
+#define TMASK_PICK(DT, MM, FM) \
+    if (dt == DT && M == MM && mf == FM) \
+        kern.few = 2 * N == M ? exact_spread_kernel<DT, MM, FM, false> : exact_spread_kernel<DT, MM, FM, true>;
+        TMASK_PICK(kF32, 8, kMaskU8) TMASK_PICK(kF32, 16, kMaskU8) TMASK_PICK(kBF16, 8, kMaskU8)
+        TMASK_PICK(kBF16, 16, kMaskU8) TMASK_PICK(kF32, 8, kMaskBits) TMASK_PICK(kF32, 16, kMaskBits)
+        TMASK_PICK(kBF16, 8, kMaskBits) TMASK_PICK(kBF16, 16, kMaskBits)
+#undef TMASK_PICK
+    } else if (SOLVER == kSolveExact && (M == 8 || M == 16)) {
 #define TMASK_PICK(DT, MM, FM) \
     if (dt == DT && M == MM && mf == FM) \
         kern = 2 * N == M ? TMASK_MANY(exact_balanced_kernel, DT, MM, FM, false) : TMASK_MANY(exact_balanced_kernel, DT, MM, FM, true);
@@ -1340,8 +1366,8 @@ static int run_mask(const tmask_mat *mats, int n_mats, int dt, int N, int M, int
         kern = mf == kMaskU8 ? TMASK_BOTH(approx_sel_bf16_kernel, 16, kMaskU8, false) : TMASK_BOTH(approx_sel_bf16_kernel, 16, kMaskBits, false);
     if (SOLVER == kSolveApprox && dt == kBF16 && M == 8 && N != 4)
         kern = mf == kMaskU8 ? TMASK_MANY(approx_sel_bf16_kernel, 8, kMaskU8, true, BatchArgs) : TMASK_MANY(approx_sel_bf16_kernel, 8, kMaskBits, true, BatchArgs);
-    // the exact kernel for bf16 8:16 gives a lane half a strip: twice the workgroups
-    const uint32_t unit_split = (SOLVER == kSolveExact && exact_half_strips(dt, M)) ? 2u : 1u;
+    // the exact kernels give a lane half a strip of bf16 (twice the workgroups) or a column
+    const uint32_t unit_split = spread ? (uint32_t)strip_cols(sdt) : (SOLVER == kSolveExact && exact_half_strips(dt, M)) ? 2u : 1u;
     hipStream_t stream = (hipStream_t)stream_;
     uint32_t partial0 = 0;
     for (int first = 0; first < n_mats; first += kMaxBatch) {
@@ -1367,7 +1393,8 @@ static int run_mask(const tmask_mat *mats, int n_mats, int dt, int N, int M, int
             args.n_mats = (uint32_t)nb; args.K = (uint32_t)(M - N); args.N = (uint32_t)N;
             args.partial0 = partial0; args.partials = want_obj ? ws : nullptr;
             // the array of tmask_approx_noalloc has room for the sums alone, and calls that overlap share it
-            one_launch = want_obj && !own_scratch && adds_up_itself(sums, kThreads, false);
+            one_launch = want_obj && !own_scratch && adds_up_itself(sums, kThreads, false) &&
+                         (size_t)(partial0 + tiles) * 16u <= ws_bytes;
             if (one_launch)
                 args.tags = draw_tags();
             {

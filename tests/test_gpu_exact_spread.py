@@ -1,0 +1,55 @@
+"""tmask_exact at M = 8 and 16 has two kernels: calls of up to eight matrices that leave the chip idle give each column of a block a
+lane, all others four columns.  Both against the oracle on the same matrices, one by one and nine in a call, and what the
+first leaves to a second launch when the workspace has no room for its records."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2102_08124_amd import workloads as wl
+
+from .test_gpu_parity import _check_exact
+
+pytestmark = pytest.mark.gpu
+
+tm = pytest.importorskip("paper_2102_08124_amd.binding")
+from .gpu_util import run_masks  # noqa: E402
+
+
+def _nine(M, dt):
+    """One block; a workgroup of 256 columns less a block, full and one block more; several block-rows; and blocks that the start
+    leaves unbalanced: tied values, zeros, rows and columns scaled, columns alike."""
+    rng = np.random.default_rng(300 + M)
+    f = lambda r, c, s: wl.gaussian_f32(r, c, seed=301 + M + s)
+    sparse = f(3 * M, 21 * M, 5)
+    sparse[rng.random(sparse.shape) < 0.6] = 0
+    rows = f(2 * M, 33 * M, 6) * np.exp2(rng.integers(-20, 21, size=(2 * M, 1))).astype(np.float32)
+    alike = np.repeat(np.abs(f(2 * M, 17, 7)), M, axis=1) + np.float32(0.001) * np.abs(f(2 * M, 17 * M, 8))
+    ws = [f(M, M, 0), f(M, 256 - M, 1), f(M, 256, 2), f(M, 256 + M, 3), f(5 * M, 7 * M, 4),
+          wl.tie_heavy_f32(3 * M, 21 * M, 302, levels=3), sparse, rows, alike]
+    return [np.ascontiguousarray(w if dt == "f32" else wl.f32_to_bf16_bits(w)) for w in ws]
+
+
+@pytest.mark.parametrize("fmt", [tm.TMASK_MASK_U8, tm.TMASK_MASK_BITS])
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("N,M", [(4, 8), (1, 8), (6, 8), (8, 16), (3, 16), (15, 16)])
+def test_both_kernels_against_the_oracle(N, M, dt, fmt):
+    ws = _nine(M, dt)
+    together, sums = run_masks(tm.tmask_exact, ws, N, M, fmt, ld_pad=16)
+    for k, w in enumerate(ws):
+        (alone,), own = run_masks(tm.tmask_exact, [w], N, M, fmt, ld_pad=16)
+        _, total, per_block = oracle.exact(w, N, M, per_block=True, threads=8)
+        for mask, s in ((alone, own[0]), (together[k], sums[k])):
+            _check_exact(w, mask, N, M, per_block)
+            assert s == pytest.approx(total, rel=1e-5)
+
+
+@pytest.mark.parametrize("N,M,rows,cols", [(8, 16, 512, 1024), (8, 16, 512, 1040), (4, 8, 512, 512), (4, 8, 512, 520)])
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+def test_objective_with_and_without_room_for_the_records(N, M, rows, cols, dt):
+    # 32 workgroups of 256 strips of four columns have room for 128 records of 16 bytes, one more has not
+    w = wl.gaussian_f32(rows, cols, seed=310)
+    w = w if dt == "f32" else wl.f32_to_bf16_bits(w)
+    (mask,), obj = run_masks(tm.tmask_exact, [w], N, M)
+    mag = np.abs(w if dt == "f32" else (w.astype(np.uint32) << 16).view(np.float32)).astype(np.float64)
+    # masks are checked above; a wavefront's 64 columns are added in fp32, at most M + 6 additions deep
+    assert obj[0] == pytest.approx((mag * mask).sum(), rel=(M + 6) * 2.0 ** -24)
