@@ -205,8 +205,8 @@ __device__ __forceinline__ uint32_t exact_spread_start(const float (&cost)[M], u
 }
 
 // GENERAL: any N (K = args.K pruned per line); otherwise N = M/2.
-template <int DT, int M, int FMT, bool GENERAL>
-__global__ __launch_bounds__(kThreads, 4) void exact_spread_kernel(const FewArgs args)
+template <int DT, int M, int FMT, bool GENERAL, typename Args>
+__global__ __launch_bounds__(kThreads, 4) void exact_spread_kernel(const Args args)
 {
     using Ge = Geo<DT, M>;
     constexpr int kWaves = kThreads / 64, NB = 64 / M;

@@ -1326,19 +1326,23 @@ static int run_mask(const tmask_mat *mats, int n_mats, int dt, int N, int M, int
             kern = mf == kMaskU8 ? TMASK_MANY(exact24_kernel, kBF16, kMaskU8, 3, BatchArgs) : TMASK_MANY(exact24_kernel, kBF16, kMaskBits, 3, BatchArgs);
     }
     bool spread = false;
-    if (SOLVER == kSolveExact && (M == 8 || M == 16) && n_mats <= kFewMats) {
+    if (SOLVER == kSolveExact && (M == 8 || M == 16) && n_mats <= kMaxBatch) {
         uint64_t wgs = 0;
-        for (int i = 0; i < n_mats; i++)
-            wgs += (uint64_t)(mats[i].rows / M * mats[i].cols + kThreads - 1) / kThreads;
+        LaunchSums sums;
+        for (int i = 0; i < n_mats; i++) {
+            const uint64_t own = (uint64_t)(mats[i].rows / M * mats[i].cols + kThreads - 1) / kThreads;
+            sums.add((uint32_t)own, mats[i].objective);
+            wgs += own;
+        }
         // Four of its workgroups take the weights that the workspace reserves 56 bytes for, 64 in records.  Where those do not fit, one
-        // matrix leaves its sum to a second launch, and more keep the one launch of the other kernel.
-        const bool room = !want_obj || n_mats == 1 || wgs * 16u <= ws_bytes;
+        // matrix leaves its sum to a second launch, and several keep the one launch that the other kernel has for them.
+        const bool room = !want_obj || n_mats == 1 || sums.waiting > kMostWaiting || wgs * 16u <= ws_bytes;
         spread = room && wgs <= spread_workgroups(M) * (uint64_t)cu_count();
     }
     if (spread) {
 #define TMASK_PICK(DT, MM, FM) \
     if (dt == DT && M == MM && mf == FM) \
-        kern.few = 2 * N == M ? exact_spread_kernel<DT, MM, FM, false> : exact_spread_kernel<DT, MM, FM, true>;
+        kern = 2 * N == M ? TMASK_BOTH(exact_spread_kernel, DT, MM, FM, false) : TMASK_BOTH(exact_spread_kernel, DT, MM, FM, true);
         TMASK_PICK(kF32, 8, kMaskU8) TMASK_PICK(kF32, 16, kMaskU8) TMASK_PICK(kBF16, 8, kMaskU8)
         TMASK_PICK(kBF16, 16, kMaskU8) TMASK_PICK(kF32, 8, kMaskBits) TMASK_PICK(kF32, 16, kMaskBits)
         TMASK_PICK(kBF16, 8, kMaskBits) TMASK_PICK(kBF16, 16, kMaskBits)

@@ -1,6 +1,7 @@
-"""tmask_exact at M = 8 and 16 has two kernels: calls of up to eight matrices that leave the chip idle give each column of a block a
-lane, all others four columns.  Both against the oracle on the same matrices, one by one and nine in a call, and what the
-first leaves to a second launch when the workspace has no room for its records."""
+"""tmask_exact at M = 8 and 16 has two kernels: calls that leave the chip idle give each column of a block a lane, all others four
+columns; so do several matrices that the first kernel would need a second launch for.  Both against the oracle on the same
+matrices, alone and beside a large one, and what the first leaves to a second launch when the workspace has no room for its
+records."""
 import numpy as np
 import pytest
 
@@ -15,7 +16,7 @@ tm = pytest.importorskip("paper_2102_08124_amd.binding")
 from .gpu_util import run_masks  # noqa: E402
 
 
-def _nine(M, dt):
+def _kinds(M, dt):
     """One block; a workgroup of 256 columns less a block, full and one block more; several block-rows; and blocks that the start
     leaves unbalanced: tied values, zeros, rows and columns scaled, columns alike."""
     rng = np.random.default_rng(300 + M)
@@ -33,8 +34,14 @@ def _nine(M, dt):
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
 @pytest.mark.parametrize("N,M", [(4, 8), (1, 8), (6, 8), (8, 16), (3, 16), (15, 16)])
 def test_both_kernels_against_the_oracle(N, M, dt, fmt):
-    ws = _nine(M, dt)
-    together, sums = run_masks(tm.tmask_exact, ws, N, M, fmt, ld_pad=16)
+    ws = _kinds(M, dt)
+    large = wl.gaussian_f32(512, 1040, seed=311)                 # with it the records of a column per lane do not fit
+    large = large if dt == "f32" else wl.f32_to_bf16_bits(large)
+    together, sums = [], []
+    for part in (ws[:5], ws[5:]):
+        masks, obj = run_masks(tm.tmask_exact, part + [large], N, M, fmt, ld_pad=16)
+        together += masks[:-1]
+        sums += list(obj[:-1])
     for k, w in enumerate(ws):
         (alone,), own = run_masks(tm.tmask_exact, [w], N, M, fmt, ld_pad=16)
         _, total, per_block = oracle.exact(w, N, M, per_block=True, threads=8)
