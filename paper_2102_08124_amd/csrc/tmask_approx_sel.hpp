@@ -247,16 +247,54 @@ __device__ __forceinline__ void middle_pair_row16(uint32_t (&s)[4], uint32_t gpo
     u = quad_xor_max<1>(ul, ul);
 }
 
+// The same at any cut: t = the (K+1)-th smallest, u = the K-th smallest.  The two runs of eight are merged into one of sixteen
+// (lane gpos holds its values 4 gpos .. 4 gpos + 3), and the lane that has the value passes it to the other three.
+__device__ __forceinline__ void cut_of_row16(uint32_t (&s)[4], uint32_t gpos, uint32_t K, uint32_t &t, uint32_t &u)
+{
+    sort_asc<4>(s);
+    const bool odd = (gpos & 1u) != 0u, far = (gpos & 2u) != 0u;
+    uint32_t m[4], n[4];
+    auto four = [](uint32_t (&v)[4]) { cmpx(v[0], v[2]); cmpx(v[1], v[3]); cmpx(v[0], v[1]); cmpx(v[2], v[3]); };
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        const uint32_t hi = quad_xor_max<1>(s[i], s[3 - i]), lo = quad_xor_min<1>(s[i], s[3 - i]);
+        m[i] = odd ? hi : lo;
+    }
+    four(m);
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        const uint32_t hi = quad_xor_max<3>(m[i], m[3 - i]), lo = quad_xor_min<3>(m[i], m[3 - i]);
+        n[i] = far ? hi : lo;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        const uint32_t hi = quad_xor_max<1>(n[i], n[i]), lo = quad_xor_min<1>(n[i], n[i]);
+        m[i] = odd ? hi : lo;
+    }
+    four(m);
+    auto value = [&](uint32_t at) {
+        const uint32_t low = (at & 1u) ? m[1] : m[0], high = (at & 1u) ? m[3] : m[2];
+        uint32_t v = gpos == at >> 2 ? ((at & 2u) ? high : low) : 0u;
+        v = quad_xor_max<1>(v, v);
+        return quad_xor_max<2>(v, v);
+    };
+    t = value(K);
+    u = value(K - 1u);
+}
+
 // a[i][c] = magnitude keys of the lane's strip (4 columns).  Fills bits[i] (bit c = keep) and the
 // kept sum; returns true if some line had a tie across its cut (result then invalid).
-// GENERAL (M = 8 only): any number K of pruned entries per line, the same in every lane: the line's eight keys are
+// GENERAL: any number K of pruned entries per line, the same in every lane: the line's keys are
 // sorted, t = the (K+1)-th smallest and u = the K-th smallest are read at a register index that every lane shares.
+// (At M = 16 the column-per-lane kernel, which sorts every row and column in a lane, did this before, with as many workgroups as there
+// are 256 strips: masks 224 x 128 13:16 32.3 -> 8.0 us, 4096 x 2048 3:16 47.5 -> 18.9, 7424 x 1984 13:16 47.5 -> 23.4; masked copies 31.4 -> 8.0,
+// 46.1 -> 20.7, 48.9 -> 27.7.  The copies hold the weights beside the magnitudes, 203 registers; reading them again instead,
+// with 128, is slower: 27.7 -> 35.4.)
 template <int M, bool GENERAL = false>
 __device__ __forceinline__ bool approx_half_f32(const uint32_t (&a)[M][4], uint32_t gpos, uint32_t (&rowbytes)[M],
                                                 float &sum, uint32_t k_general = 0)
 {
-    static_assert(!GENERAL || M == 8, "a line of eight keys: one lane's column, two lanes' row");
-    const uint32_t kidx = GENERAL ? (__builtin_amdgcn_readfirstlane(k_general) & 7u) : 0u;
+    const uint32_t kidx = GENERAL ? (__builtin_amdgcn_readfirstlane(k_general) & (uint32_t)(M - 1)) : 0u;
     constexpr int H = M / 2;
     uint32_t tcol[4];
     bool tie = false;
@@ -269,10 +307,15 @@ __device__ __forceinline__ bool approx_half_f32(const uint32_t (&a)[M][4], uint3
             hi[i] = a[H + i][c];
         }
         if constexpr (GENERAL) {
-            uint32_t srt[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-            sort_asc<8>(srt);
+            uint32_t srt[M];
+#pragma unroll
+            for (int i = 0; i < H; i++) {
+                srt[i] = lo[i];
+                srt[H + i] = hi[i];
+            }
+            sort_asc<M>(srt);
             tcol[c] = srt[kidx];
-            u = srt[(kidx - 1u) & 7u];
+            u = srt[(kidx - 1u) & (uint32_t)(M - 1)];
         } else {
             middle_pair<H>(lo, hi, tcol[c], u);
         }
@@ -284,7 +327,9 @@ __device__ __forceinline__ bool approx_half_f32(const uint32_t (&a)[M][4], uint3
     for (int i = 0; i < M; i++) {
         uint32_t s[4] = {a[i][0], a[i][1], a[i][2], a[i][3]};
         uint32_t trow, u;
-        if constexpr (GENERAL) {
+        if constexpr (GENERAL && M == 16) {
+            cut_of_row16(s, gpos, kidx, trow, u);
+        } else if constexpr (GENERAL) {
             uint32_t srt[8] = {s[0], s[1], s[2], s[3], quad_xor<1>(s[0]), quad_xor<1>(s[1]), quad_xor<1>(s[2]), quad_xor<1>(s[3])};
             sort_asc<8>(srt);
             trow = srt[kidx];

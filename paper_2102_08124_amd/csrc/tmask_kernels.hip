@@ -115,7 +115,7 @@ __global__ __launch_bounds__(kThreads) void approx24_kernel(const Args args)
 
 // tmask_approx for fp32 with N = M/2, M = 8 or 16: thresholds on magnitudes; a wavefront in which some
 // line has a tie across its cut redoes its strips with the form that resolves ties by position (uniform branch).
-// GENERAL (M = 8): any N, thresholds read from the sorted line; ties send the wavefront to the rank form.
+// GENERAL: any N, thresholds read from the sorted line; ties send the wavefront to the rank form.
 template <int M, int FMT, bool GENERAL, typename Args>
 __global__ __launch_bounds__(kThreads, (M == 16 && FMT == kMaskBits) ? 4 : 1) void approx_sel_f32_kernel(const Args args)
 {
@@ -369,15 +369,15 @@ __global__ __launch_bounds__(kThreads) void approx_dense_kernel(const Args args)
                 for (int i = 0; i < 4; i++)
                     bits[i] |= bytes4_to_bits(bytes[i]) << (4 * b);
             }
-        } else if constexpr (HALFN && DT == kF32 && M >= 8) {
+        } else if constexpr ((HALFN && DT == kF32 && M >= 8) || (MODE == kDenseApprox && DT == kF32 && M == 16)) {
             uint32_t rowbytes[M];
             float unused = 0.f;
-            const bool tie = approx_half_f32<M>(a, gpos, rowbytes, unused);
+            const bool tie = approx_half_f32<M, !HALFN>(a, gpos, rowbytes, unused, args.K);
             if (__any(tie)) {
                 if constexpr (M == 8)
                     approx_half_f32_ties<M>(a, gpos, rowbytes, unused);
                 else
-                    approx_keep<kF32, M, false>(a, (uint32_t)(M / 2), gpos, bits);
+                    approx_keep<kF32, M, false>(a, HALFN ? (uint32_t)(M / 2) : args.K, gpos, bits);
             }
             if (M == 8 || !__any(tie)) {
 #pragma unroll
@@ -1274,10 +1274,9 @@ static int run_mask(const tmask_mat *mats, int n_mats, int dt, int N, int M, int
     } else if (want_obj && (rc = check_workspace(mats, n_mats, M, ws, ws_bytes))) {
         return rc;
     }
-    // N != M/2 at M = 16, Algorithm 1 and row pruning: the strip kernels have only their rank form there (except
-    // Algorithm 1 at bf16, where keys are unique and a row lies in two lanes); the column-per-lane kernels take a
+    // N != M/2 at M = 16, row pruning: the strip kernels have only their rank form there; the column-per-lane kernels take a
     // threshold from a sorting network
-    const bool general_n = 2 * N != M && M == 16 && SOLVER != kSolveExact && !(SOLVER == kSolveApprox && dt == kBF16);
+    const bool general_n = 2 * N != M && M == 16 && SOLVER == kSolveRow1D;
     if (fit == kFitColumns || general_n)     // also M = 32, or a matrix that the strips cannot read
         return cw_run_mask(SOLVER == kSolveApprox ? 0 : SOLVER == kSolveExact ? 1 : 2, mats, n_mats, dt, N, M, mf, ws, !own_scratch,
                            (hipStream_t)stream_);
@@ -1360,6 +1359,8 @@ static int run_mask(const tmask_mat *mats, int n_mats, int dt, int N, int M, int
         kern = mf == kMaskU8 ? TMASK_BOTH(approx_sel_f32_kernel, 8, kMaskU8, false) : TMASK_BOTH(approx_sel_f32_kernel, 8, kMaskBits, false);
     if (SOLVER == kSolveApprox && dt == kF32 && M == 16 && N == 8)
         kern = mf == kMaskU8 ? TMASK_BOTH(approx_sel_f32_kernel, 16, kMaskU8, false) : TMASK_BOTH(approx_sel_f32_kernel, 16, kMaskBits, false);
+    if (SOLVER == kSolveApprox && dt == kF32 && M == 16 && N != 8)
+        kern = mf == kMaskU8 ? TMASK_MANY(approx_sel_f32_kernel, 16, kMaskU8, true, BatchArgs) : TMASK_MANY(approx_sel_f32_kernel, 16, kMaskBits, true, BatchArgs);
     if (SOLVER == kSolveApprox && dt == kBF16 && M == 16 && N != 8)
         kern = mf == kMaskU8 ? TMASK_MANY(approx_sel_bf16_kernel, 16, kMaskU8, true, BatchArgs) : TMASK_MANY(approx_sel_bf16_kernel, 16, kMaskBits, true, BatchArgs);
     if (SOLVER == kSolveApprox && dt == kF32 && M == 8 && N != 4)
@@ -1892,9 +1893,7 @@ static int run_mask_dense(const tmask_mask_dense_desc *descs, int n, tmask_dtype
     }
     if (with_mask != 0 && with_mask != n)
         return fail(TMASK_ERR_NULL, "mask must be given for all matrices or for none (%d of %d have one)", with_mask, n);
-    // Algorithm 1 with N != M/2 at M = 16: the strip kernels have only their rank form there (see run_mask); the
-    // row modes are faster on the strips (8192^2 fp32 5:16 with absorption: 101 against 121 us)
-    if (fit == kFitColumns || (2 * N != M && M == 16 && mode == kDenseApprox && dt != kBF16)) {
+    if (fit == kFitColumns) {
         const bool absorb = mode == kDenseRow1DAbsorb || mode == kDenseRow1DHalfAbsorb;
         const bool rows_only = absorb || mode == kDenseRow1D || mode == kDenseRow1DHalf;
         return cw_run_dense(descs, n, (int)dt, N, M, (int)mf, absorb ? 2 : rows_only ? 1 : 0, (hipStream_t)hip_stream);

@@ -1,0 +1,51 @@
+"""Algorithm 1 on fp32 at M = 16 with N != 8: the strip kernels against the oracle, and against the column-per-lane kernels, which take
+the same matrices where their rows start at odd multiples of four bytes."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2102_08124_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+tm = pytest.importorskip("paper_2102_08124_amd.binding")
+from .gpu_util import mask_to_host, run_masks  # noqa: E402
+
+
+def _matrices():
+    """One block, a workgroup's 64 blocks and one more, part-filled workgroups; values with ties across the cut in single lines, in all
+    of them, and zeros, infinities and NaN."""
+    rng = np.random.default_rng(40)
+    plain = [wl.gaussian_f32(r, c, seed=41 + r + c) for r, c in ((16, 16), (16, 1024), (16, 1040), (48, 336))]
+    lines = wl.gaussian_f32(48, 1040, seed=42)
+    lines[5, 16:32], lines[16:32, 40] = 0.25, -0.5
+    odd = wl.gaussian_f32(32, 128, seed=43)
+    odd[rng.random(odd.shape) < 0.1] = np.inf
+    odd[rng.random(odd.shape) < 0.1] = np.nan
+    odd[rng.random(odd.shape) < 0.1] = -0.0
+    return plain + [lines, wl.tie_heavy_f32(32, 272, 44, levels=4), np.zeros((16, 32), np.float32), odd]
+
+
+@pytest.mark.parametrize("fmt", [tm.TMASK_MASK_U8, tm.TMASK_MASK_BITS])
+@pytest.mark.parametrize("N", [1, 2, 5, 7, 9, 12, 14, 15])
+def test_masks_and_masked_copies(N, fmt):
+    ws = _matrices()
+    masks, obj = run_masks(tm.tmask_approx, ws, N, 16, fmt)
+    for k, w in enumerate(ws):
+        want, total = oracle.approx(w, N, 16)
+        assert np.array_equal(masks[k], want), k
+        if np.isfinite(w).all():
+            assert obj[k] == pytest.approx(total, rel=1e-5)
+        for ld in (w.shape[1], w.shape[1] + 1):                  # strips, columns
+            buf = torch.zeros((w.shape[0], ld), device="cuda")
+            dev = buf[:, :w.shape[1]]
+            dev.copy_(torch.from_numpy(w))
+            out, mask = torch.full(w.shape, 7.0, device="cuda"), tm.alloc_masks([dev], fmt)
+            tm.tmask_approx_dense([dev], mask, [out], N, 16, mask_fmt=fmt)
+            other = tm.alloc_masks([dev], fmt)
+            tm.tmask_approx([dev], other, N, 16, mask_fmt=fmt)
+            torch.cuda.synchronize()
+            assert np.array_equal(mask_to_host(mask[0], w.shape[1], fmt), want), (k, ld)
+            assert torch.equal(mask[0], other[0])
+            assert np.array_equal(out.cpu().numpy().view(np.uint32), np.where(want != 0, w, np.float32(0)).view(np.uint32)), (k, ld)
