@@ -1093,13 +1093,15 @@ static BatchKernel pick_score_kernel(int dt, int M, int mf)
 }
 
 // Whether a launch over these matrices has at most `per_cu` tiles of TR x TC for a compute unit, so that tiles of half the
-// height (one or two block-rows per lane instead of two or four) pay.  A launch of a tile or two per compute unit takes
+// height, or width, (one or two block-rows per lane instead of two or four) pay.  A launch of a tile or two per compute unit takes
 // as long as a tile does, and half the work per lane nearly halves that; with more tiles the shorter runs per column of W^T
 // cost more.  Whole tile / half tile in us, graph replays: bf16 4:8 compression 1024^2 10.8 / 7.8, 4096 x 3072 (384 tiles)
 // 18.9 / 18.4, 4096^2 (512) 20.3 / 26.0; in one pass 14.4 / 9.8, 4096^2 21.9 / 20.8, 20 x 1024^2 (640) 28.9 / 26.8, 4096 x
 // 6144 (768) 31.0 / 35.1.  bf16 2:4 the same lines; fp32 2:4 1024^2 8.3 / 6.3, 6 x 1024^2 (384) 15.1 / 13.4, 4096 x 2048
-// (512) 16.7 / 19.0; in one pass 10.0 / 7.0, 512 tiles 14.6 / 13.7, 768 tiles 22.7 / 26.8.
-constexpr double kHalfTilesPack = 1.5, kHalfTilesFusedF32 = 2.0, kHalfTilesFusedBf16 = 2.5;
+// (512) 16.7 / 19.0; in one pass 10.0 / 7.0, 512 tiles 14.6 / 13.7, 768 tiles 22.7 / 26.8.  fp32 4:8 (half the width, one block-row to
+// a lane) 128^2 8.9 / 6.1, 2048^2 (256) 11.7 / 9.7, 3144 x 3192 (650) 28.7 / 34.0; in one pass 128^2 16.9 / 8.3, 2048^2 15.5 / 12.2, 3072^2
+// (576) 24.1 / 20.2, 4096 x 3072 (768) 25.6 / 29.3.
+constexpr double kHalfTilesPack = 1.5, kHalfTilesFusedF32 = 2.0, kHalfTilesFusedF32M8 = 2.5, kHalfTilesFusedBf16 = 2.5;
 
 template <typename DESC>
 static bool few_tiles(const DESC *descs, int n, int64_t TR, int64_t TC, double per_cu)
@@ -1671,12 +1673,17 @@ int tmask_apply_pack(const tmask_pack_desc *descs, int n, tmask_dtype dt, int N,
     for (int i = 0; i < n && fast48f; i++)
         fast48f = (((uintptr_t)descs[i].vals | (uintptr_t)descs[i].valsT) & 7) == 0;
     if (fast48f) {
-        kern = mf == TMASK_MASK_U8 ? pack48_f32_kernel<kMaskU8, kPack8F32Strips, false, false, PackArgs>
-                                   : pack48_f32_kernel<kMaskBits, kPack8F32Strips, false, false, PackArgs>;
-        few = mf == TMASK_MASK_U8 ? pack48_f32_kernel<kMaskU8, kPack8F32Strips, false, false, FewPackArgs>
-                                  : pack48_f32_kernel<kMaskBits, kPack8F32Strips, false, false, FewPackArgs>;
-        TC = Pack8F32Geo<kPack8F32Strips>::TC;
-        TR = Pack8F32Geo<kPack8F32Strips>::TR;
+        constexpr int SW = kPack8F32Strips, SH = kPack8F32Half;
+        const bool small = few_tiles(descs, n, Pack8F32Geo<SW>::TR, Pack8F32Geo<SW>::TC, kHalfTilesPack);
+#define TMASK_PICK(FM, SS, QN) \
+        if ((int)mf == FM && small == (QN == 1)) { \
+            kern = pack48_f32_kernel<FM, SS, false, false, PackArgs, QN>; \
+            few = pack48_f32_kernel<FM, SS, false, false, FewPackArgs, QN>; \
+        }
+        TMASK_PICK(kMaskU8, SH, 1) TMASK_PICK(kMaskU8, SW, 2) TMASK_PICK(kMaskBits, SH, 1) TMASK_PICK(kMaskBits, SW, 2)
+#undef TMASK_PICK
+        TC = small ? Pack8F32Geo<SH, 1>::TC : Pack8F32Geo<SW>::TC;
+        TR = small ? Pack8F32Geo<SH, 1>::TR : Pack8F32Geo<SW>::TR;
     }
     hipStream_t stream = (hipStream_t)hip_stream;
     for (int first = 0; first < n; first += kMaxPackBatch) {
@@ -1771,24 +1778,28 @@ int tmask_approx_pack(const tmask_fused_desc *descs, int n, tmask_dtype dt, int 
     constexpr int SF = 64, SB = 32;
     const uint32_t strips = dt == TMASK_F32 ? SF : SB;
     using G8F = Pack8F32Geo<kPack8F32Strips>;
-    const uint32_t TC = fused48 ? (dt == TMASK_F32 ? (uint32_t)G8F::TC : (uint32_t)Pack8Geo<2>::TC)
+    uint32_t TC = fused48 ? (dt == TMASK_F32 ? (uint32_t)G8F::TC : (uint32_t)Pack8Geo<2>::TC)
                                 : strips * 16 / (uint32_t)elem_size((int)dt);
     uint32_t kPack4Rows = !fused48 ? 4096 / strips : dt == TMASK_F32 ? (uint32_t)G8F::TR : (uint32_t)Pack8Geo<2>::TR;
-    auto partials_bytes = [&](uint32_t tile_rows) {
+    auto partials_bytes = [&](uint32_t tile_rows, uint32_t tile_cols) {
         size_t tiles = 0;
         for (int i = 0; i < n; i++)
-            tiles += (size_t)((descs[i].cols + TC - 1) / TC) * (size_t)((descs[i].rows + tile_rows - 1) / tile_rows);
+            tiles += (size_t)((descs[i].cols + tile_cols - 1) / tile_cols) * (size_t)((descs[i].rows + tile_rows - 1) / tile_rows);
         return tiles * sizeof(double);
     };
     // half tiles leave more partial sums than the workspace was asked to hold: only where it happens to
-    const bool small = !(fused48 && dt == TMASK_F32) && few_tiles(descs, n, kPack4Rows, TC, dt == TMASK_F32 ? kHalfTilesFusedF32 : kHalfTilesFusedBf16) &&
-                       (!want_obj || workspace_bytes >= partials_bytes(kPack4Rows / 2));
-    if (small)
-        kPack4Rows /= 2;
+    const bool f48 = fused48 && dt == TMASK_F32;
+    const uint32_t half_rows = f48 ? (uint32_t)Pack8F32Geo<kPack8F32Half, 1>::TR : kPack4Rows / 2, half_cols = f48 ? (uint32_t)Pack8F32Geo<kPack8F32Half, 1>::TC : TC;
+    const bool small = few_tiles(descs, n, kPack4Rows, TC, f48 ? kHalfTilesFusedF32M8 : dt == TMASK_F32 ? kHalfTilesFusedF32 : kHalfTilesFusedBf16) &&
+                       (!want_obj || workspace_bytes >= partials_bytes(half_rows, half_cols));
+    if (small) {
+        kPack4Rows = half_rows;
+        TC = half_cols;
+    }
     if (want_obj) {
         if (!workspace || ((uintptr_t)workspace & 255))
             return fail(TMASK_ERR_WORKSPACE, "workspace is NULL or not 256-byte aligned");
-        const size_t need = partials_bytes(kPack4Rows);
+        const size_t need = partials_bytes(kPack4Rows, TC);
         if (workspace_bytes < need)
             return fail(TMASK_ERR_WORKSPACE, "workspace has %zu bytes, %zu needed", workspace_bytes, need);
     }
@@ -1800,13 +1811,13 @@ int tmask_approx_pack(const tmask_fused_desc *descs, int n, tmask_dtype dt, int 
     TMASK_PICK(kF32, kMaskU8, SF, 4) TMASK_PICK(kF32, kMaskBits, SF, 4) TMASK_PICK(kBF16, kMaskU8, SB, 4) TMASK_PICK(kBF16, kMaskBits, SB, 4)
     TMASK_PICK(kF32, kMaskU8, SF, 2) TMASK_PICK(kF32, kMaskBits, SF, 2) TMASK_PICK(kBF16, kMaskU8, SB, 2) TMASK_PICK(kBF16, kMaskBits, SB, 2)
 #undef TMASK_PICK
-    if (fused48 && dt == TMASK_F32) {
-        constexpr int S8 = kPack8F32Strips;
-        if (mf == TMASK_MASK_U8)
-            kern = with_mask ? pack48_f32_kernel<kMaskU8, S8, true, true, FusedArgs> : pack48_f32_kernel<kMaskU8, S8, true, false, FusedArgs>;
-        else
-            kern = with_mask ? pack48_f32_kernel<kMaskBits, S8, true, true, FusedArgs>
-                             : pack48_f32_kernel<kMaskBits, S8, true, false, FusedArgs>;
+    if (f48) {
+#define TMASK_PICK(FM, SS, QN) \
+        if ((int)mf == FM && small == (QN == 1)) \
+            kern = with_mask ? pack48_f32_kernel<FM, SS, true, true, FusedArgs, QN> : pack48_f32_kernel<FM, SS, true, false, FusedArgs, QN>;
+        TMASK_PICK(kMaskU8, kPack8F32Half, 1) TMASK_PICK(kMaskU8, kPack8F32Strips, 2)
+        TMASK_PICK(kMaskBits, kPack8F32Half, 1) TMASK_PICK(kMaskBits, kPack8F32Strips, 2)
+#undef TMASK_PICK
     } else if (fused48) {
 #define TMASK_PICK(FM, ST) \
         if ((int)mf == FM && small == (ST == 1)) \
@@ -1844,7 +1855,7 @@ int tmask_approx_pack(const tmask_fused_desc *descs, int n, tmask_dtype dt, int 
         args.n = (uint32_t)nb; args.partial0 = partial0; args.partials = want_obj ? workspace : nullptr;
         // a pointer for each of 224 matrices would be 2 KB of arguments more, which calls without objectives pay for too (512^2
         // fp32 2:4 6.18 us with them, 6.04 without)
-        const bool one_launch = want_obj && nb <= kFewMats && adds_up_itself(sums, kThreads, false) && workspace_bytes >= 2 * partials_bytes(kPack4Rows);
+        const bool one_launch = want_obj && nb <= kFewMats && adds_up_itself(sums, kThreads, false) && workspace_bytes >= 2 * partials_bytes(kPack4Rows, TC);
         if (one_launch)
             args.tags = draw_tags();
         {

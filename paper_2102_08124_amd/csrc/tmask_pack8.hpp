@@ -159,31 +159,6 @@ __global__ __launch_bounds__(kThreads) void pack48_bf16_kernel(const ARGS args)
     __shared__ double red[kThreads / 64];
 
     const uint32_t tid = threadIdx.x, l = tid & 63u;
-    // ---- the table: entry m describes the slots for the set m of kept positions (the kept ones in order, at most
-    //      four; if fewer, the lowest-numbered other positions as fillers: choose_slots, worked out once per entry) ----
-    {
-        uint32_t sel, chosen;
-        choose_slots<8>(tid, 4u, sel, chosen);
-        uint32_t sa0 = 0x0C0C0C0Cu, sa1 = 0x0C0C0C0Cu, sb0 = 0x0C0C0C0Cu, sb1 = 0x0C0C0C0Cu, code = 0, s = 0;
-#pragma unroll
-        for (uint32_t p = 0; p < 8; p++) {
-            if (((chosen >> p) & 1u) && s < 4u) {
-                const uint32_t b = 2u * (p & 3u);
-                const uint32_t pair = (b | ((b + 1u) << 8)) << (16u * (s & 1u));
-                const uint32_t clear = ~(0xFFFFu << (16u * (s & 1u)));
-                if (p < 4) {          // first half of the group: dwords 0 and 1
-                    if (s < 2u) sa0 = (sa0 & clear) | pair; else sa1 = (sa1 & clear) | pair;
-                } else {
-                    if (s < 2u) sb0 = (sb0 & clear) | pair; else sb1 = (sb1 & clear) | pair;
-                }
-                code |= p << (3u * s);
-                s++;
-            }
-        }
-        LUTS[tid] = u32x4{sa0, sb0, sa1, sb1};
-        LUTC[tid] = (uint16_t)code;
-    }
-
     const uint32_t tile = blockIdx.x;
     const int which = find_pack_desc(args, tile);
     const PackDev d = args.d[which];
@@ -205,8 +180,6 @@ __global__ __launch_bounds__(kThreads) void pack48_bf16_kernel(const ARGS args)
     const size_t lane_m = (size_t)sub * (8u * NSTEP) * d.mask_ld + (FMT == kMaskU8 ? tcol : (col >> 3));
     const size_t lane_v = (size_t)sub * (8u * NSTEP) * pitchW * ES + strip * 8u;
     const size_t mcol0 = FMT == kMaskU8 ? col0 : 0;
-    __syncthreads();                                      // the table is complete
-
     // ---- loads: both blocks of the lane first; when the mask is computed here, the second block's rows are
     // requested only after the first block's thresholds are done (they would occupy registers meanwhile) ----
     u32x4 raw[NSTEP][8];
@@ -243,6 +216,33 @@ __global__ __launch_bounds__(kThreads) void pack48_bf16_kernel(const ARGS args)
     if constexpr (!APPROX && NSTEP == 2)
         issue(1);
     static_assert(NSTEP <= 2, "the load schedule above is written for at most two blocks per lane");
+    __builtin_amdgcn_sched_barrier(0);
+
+    // ---- the table, while the loads are under way: entry m describes the slots for the set m of kept positions (the kept ones in order, at most
+    //      four; if fewer, the lowest-numbered other positions as fillers: choose_slots, worked out once per entry) ----
+    {
+        uint32_t sel, chosen;
+        choose_slots<8>(tid, 4u, sel, chosen);
+        uint32_t sa0 = 0x0C0C0C0Cu, sa1 = 0x0C0C0C0Cu, sb0 = 0x0C0C0C0Cu, sb1 = 0x0C0C0C0Cu, code = 0, s = 0;
+#pragma unroll
+        for (uint32_t p = 0; p < 8; p++) {
+            if (((chosen >> p) & 1u) && s < 4u) {
+                const uint32_t b = 2u * (p & 3u);
+                const uint32_t pair = (b | ((b + 1u) << 8)) << (16u * (s & 1u));
+                const uint32_t clear = ~(0xFFFFu << (16u * (s & 1u)));
+                if (p < 4) {          // first half of the group: dwords 0 and 1
+                    if (s < 2u) sa0 = (sa0 & clear) | pair; else sa1 = (sa1 & clear) | pair;
+                } else {
+                    if (s < 2u) sb0 = (sb0 & clear) | pair; else sb1 = (sb1 & clear) | pair;
+                }
+                code |= p << (3u * s);
+                s++;
+            }
+        }
+        LUTS[tid] = u32x4{sa0, sb0, sa1, sb1};
+        LUTC[tid] = (uint16_t)code;
+    }
+    __syncthreads();
 
     float acc = 0.f;
     uint32_t tcode[8];                                    // position bits of the lane's columns, 12 per block-row
@@ -403,6 +403,7 @@ __global__ __launch_bounds__(kThreads) void pack48_bf16_kernel(const ARGS args)
 // Staging and copy-out as in pack48_bf16_kernel.
 // =================================================================================================
 constexpr int kPack8F32Strips = 64;   // tile width in strips (32: 123 against 121 us on 8192 x 8192)
+constexpr int kPack8F32Half = 32;     // of half tiles, one block-row per lane, as high as the others
 
 template <int S, int QN = 2, int NW = 4>
 struct Pack8F32Geo {
@@ -439,11 +440,11 @@ __device__ __forceinline__ uint32_t gather_every_fourth_bit(uint32_t y)
 // FusedArgs): the keep flags come from Algorithm 1 in its threshold form on the lane pair's block
 // (approx_half_f32; a wavefront in which some line has a tie across its cut redoes its blocks with approx_half_f32_ties),
 // the mask is written if WMASK, the kept magnitudes' sum goes to the workgroup's partial.
-template <int FMT, int S, bool APPROX, bool WMASK, typename ARGS>
+template <int FMT, int S, bool APPROX, bool WMASK, typename ARGS, int QN = 2>
 __global__ __launch_bounds__(256) void pack48_f32_kernel(const ARGS args)
 {
-    using PG = Pack8F32Geo<S>;
-    constexpr int ES = 4, QN = 2, LPR = PG::LPR, TR = PG::TR, TC = PG::TC, OTD = PG::OTD, TCP = PG::TCP,
+    using PG = Pack8F32Geo<S, QN>;
+    constexpr int ES = 4, LPR = PG::LPR, TR = PG::TR, TC = PG::TC, OTD = PG::OTD, TCP = PG::TCP,
                   IDXB = PG::IDXB, IDXTB = PG::IDXTB, NT = PG::NT;
     static_assert(NT == 256 && S % 4 == 0, "the table has one entry per thread; two groups share a quad");
 
@@ -454,31 +455,6 @@ __global__ __launch_bounds__(256) void pack48_f32_kernel(const ARGS args)
     __shared__ double red[NT / 64];
 
     const uint32_t tid = threadIdx.x, l = tid & 63u;
-    // ---- the table: entry m = position codes (3 bits per slot) of the four slots for the set m of kept positions ----
-    {
-        uint32_t chosen = 0, cnt = 0;
-#pragma unroll
-        for (uint32_t p = 0; p < 8; p++)
-            if (((tid >> p) & 1u) && cnt < 4u) {
-                chosen |= 1u << p;
-                cnt++;
-            }
-#pragma unroll
-        for (uint32_t p = 0; p < 8; p++)
-            if (!((tid >> p) & 1u) && cnt < 4u) {
-                chosen |= 1u << p;
-                cnt++;
-            }
-        uint32_t code = 0, sl = 0;
-#pragma unroll
-        for (uint32_t p = 0; p < 8; p++)
-            if ((chosen >> p) & 1u) {
-                code |= p << (3u * sl);
-                sl++;
-            }
-        LUT[tid] = (uint16_t)code;
-    }
-
     const uint32_t tile = blockIdx.x;
     const int which = find_pack_desc(args, tile);
     const PackDev d = args.d[which];
@@ -503,8 +479,6 @@ __global__ __launch_bounds__(256) void pack48_f32_kernel(const ARGS args)
     const size_t lane_m = (size_t)sub * (8u * QN) * d.mask_ld + (FMT == kMaskU8 ? tcol : (col >> 3));
     const size_t lane_v = (size_t)sub * (8u * QN) * pitchW * ES + strip * 8u;
     const size_t mcol0 = FMT == kMaskU8 ? col0 : 0;
-    __syncthreads();                                      // the table is complete
-
     u32x4 raw[QN][8];
     uint32_t mk[QN][8];                                   // U8: the row's four mask bytes; BITS: the lane's nibble
     bool okq[QN];
@@ -533,6 +507,33 @@ __global__ __launch_bounds__(256) void pack48_f32_kernel(const ARGS args)
             }
         }
     }
+    __builtin_amdgcn_sched_barrier(0);
+
+    // ---- the table, while the loads are under way: entry m = position codes (3 bits per slot) of the four slots for the set m of kept positions ----
+    {
+        uint32_t chosen = 0, cnt = 0;
+#pragma unroll
+        for (uint32_t p = 0; p < 8; p++)
+            if (((tid >> p) & 1u) && cnt < 4u) {
+                chosen |= 1u << p;
+                cnt++;
+            }
+#pragma unroll
+        for (uint32_t p = 0; p < 8; p++)
+            if (!((tid >> p) & 1u) && cnt < 4u) {
+                chosen |= 1u << p;
+                cnt++;
+            }
+        uint32_t code = 0, sl = 0;
+#pragma unroll
+        for (uint32_t p = 0; p < 8; p++)
+            if ((chosen >> p) & 1u) {
+                code |= p << (3u * sl);
+                sl++;
+            }
+        LUT[tid] = (uint16_t)code;
+    }
+    __syncthreads();
     float acc = 0.f;
 
     uint32_t tcode[4] = {0u, 0u, 0u, 0u};                 // position bits of the lane's columns, 12 per block-row
@@ -659,11 +660,18 @@ __global__ __launch_bounds__(256) void pack48_f32_kernel(const ARGS args)
         for (int sl = 0; sl < 4; sl++)
             *(u32x4 *)&OT[4 * brl + sl][tcol] = u32x4{oc[sl][0], oc[sl][1], oc[sl][2], oc[sl][3]};
     }
-    // the lane's two block-rows are neighbours: 24 position bits = three whole bytes per column
-    static_assert(QN == 2, "three bytes per column and lane");
+    // two block-rows that are neighbours have 24 position bits = three whole bytes per column: the lane's own two, or its
+    // one and that of the lane half a wavefront further (which holds the next block-row)
+    static_assert(QN == 2 || (QN == 1 && LPR == 2), "lanes l and l + 32 hold neighbouring runs");
+    if constexpr (QN == 1) {
+#pragma unroll
+        for (int c = 0; c < 4; c++)
+            tcode[c] |= (uint32_t)__shfl_xor((int)tcode[c], 32, 64) << 12;
+    }
 #pragma unroll
     for (int t = 0; t < 3; t++)
-        *(uint32_t *)&IDXT[3 * q2 + t][tcol] = ((tcode[0] >> (8 * t)) & 0xFFu) | (((tcode[1] >> (8 * t)) & 0xFFu) << 8) |
+        if (QN == 2 || sub == 0)
+            *(uint32_t *)&IDXT[3 * (QN == 1 ? w : q2) + t][tcol] = ((tcode[0] >> (8 * t)) & 0xFFu) | (((tcode[1] >> (8 * t)) & 0xFFu) << 8) |
                                                (((tcode[2] >> (8 * t)) & 0xFFu) << 16) | (((tcode[3] >> (8 * t)) & 0xFFu) << 24);
     __syncthreads();
     pack48_copy_out<ES, TR, TC, TCP, IDXB, IDXTB, NT>(d, row0, col0, OT, IDXT, IDX);
