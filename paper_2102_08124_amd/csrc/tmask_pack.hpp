@@ -116,6 +116,123 @@ __device__ __forceinline__ void tile_coords(uint32_t tl, uint32_t tiles_x, uint3
     }
 }
 
+// ---- finished tiles out of LDS ------------------------------------------------------------------------------------------
+// Lines of position bits, and of values where N and the matrix' height are odd, start at any byte.  What they cost is lines touched
+// per store instruction, so a line leaves in one: neighbouring lanes store its dwords wherever these lie (the memory path takes
+// dwords at any byte), and the last one, of a length that is no multiple of four, overlaps the one before.  (By bytes before, each
+// with a division by the length: bf16 4:8 of 3576 x 3456 29.9 -> 19.0 us, 2:8 of 4096^2 33.0 -> 28.8.  A lane that stores three dwords of a line in a row touches it
+// three times: fp32 3:16 of 4096^2 36.7 -> 39.7.)
+
+// Byte `x` dwords into a line of nb (>= 4) bytes, or four before its end.
+__device__ __forceinline__ uint32_t piece_at(uint32_t x, uint32_t nb) { return min(4u * x, nb - 4u); }
+
+__device__ __forceinline__ void store_anywhere(uint32_t v, unsigned char *p) { __builtin_memcpy(p, &v, 4); }
+
+__device__ __forceinline__ void store_three(uint32_t v, unsigned char *p, uint32_t nb)        // the first nb < 4 bytes
+{
+    if (nb > 0u)
+        p[0] = (unsigned char)v;
+    if (nb > 1u)
+        p[1] = (unsigned char)(v >> 8);
+    if (nb > 2u)
+        p[2] = (unsigned char)(v >> 16);
+}
+
+// Dword x of the first nb bytes of a line of LB in LDS.
+template <int LB>
+__device__ __forceinline__ void copy_piece(const uint8_t *line, unsigned char *dst, uint32_t x, uint32_t nb)
+{
+    const uint32_t *const words = (const uint32_t *)line;
+    if (nb < 4u) {
+        if (x == 0u)
+            store_three(words[0], dst, nb);
+    } else if (4u * x < nb) {
+        const uint32_t at = piece_at(x, nb), w = at / 4u;
+        store_anywhere(__builtin_amdgcn_alignbyte(words[min(w + 1u, (uint32_t)LB / 4u - 1u)], words[w], at & 3u), dst + at);
+    }
+}
+
+// The first nb (<= NB) bytes of `rows` lines of LB in LDS to lines `pitch` bytes apart.
+template <int LB, int NT, int NB = LB>
+__device__ __forceinline__ void copy_lines(const uint8_t (*src)[LB], unsigned char *dst, size_t pitch, uint32_t rows, uint32_t nb)
+{
+    static_assert(LB % 4 == 0 && NB <= LB, "lines of whole dwords");
+    if (NB % 8 == 0 && LB % 8 == 0 && (((uint32_t)(uintptr_t)dst | (uint32_t)pitch | nb) & 7u) == 0u) {
+        constexpr uint32_t P = (NB + 7) / 8;
+        for (uint32_t j = threadIdx.x; j < rows * P; j += NT) {
+            const uint32_t r = j / P, x = j % P;
+            if (8u * x < nb)
+                *(u32x2 *)(dst + (size_t)r * pitch + 8 * x) = ((const u32x2 *)&src[r][0])[x];
+        }
+    } else {
+        constexpr uint32_t P = (NB + 3) / 4;
+        for (uint32_t j = threadIdx.x; j < rows * P; j += NT) {
+            const uint32_t r = j / P;
+            copy_piece<LB>(&src[r][0], dst + (size_t)r * pitch, j % P, nb);
+        }
+    }
+}
+
+// The same for lines that are mostly much shorter than LB: their dwords to the next power of two of lanes.
+template <int LB, int NT>
+__device__ __forceinline__ void copy_short_lines(const uint8_t (*src)[LB], unsigned char *dst, size_t pitch, uint32_t rows, uint32_t nb)
+{
+    static_assert(LB % 4 == 0, "lines of whole dwords");
+    const uint32_t nd = (nb + 3u) / 4u, shift = nd > 1u ? 32u - (uint32_t)__builtin_clz(nd - 1u) : 0u;
+    const uint32_t x = threadIdx.x & ((1u << shift) - 1u);
+    if (x < nd)
+        for (uint32_t r = threadIdx.x >> shift; r < rows; r += (uint32_t)NT >> shift)
+            copy_piece<LB>(&src[r][0], dst + (size_t)r * pitch, x, nb);
+}
+
+// The same of a tile that lies in LDS as [byte of the line][line]: NB bytes of TC lines.  Whole lines of eight-byte pieces go as above;
+// the dwords of others to one lane for each line (side by side they meet in one bank of LDS: 4:8 in one pass 17.9 -> 18.6 us).
+template <int NB, int TC, int NT>
+__device__ __forceinline__ void copy_columns(const uint8_t (*src)[TC], unsigned char *dst, size_t pitch, uint32_t cols, uint32_t nb)
+{
+    static_assert(NB % 4 == 0 && NT % TC == 0, "whole dwords; a thread keeps its line");
+    auto word = [&](uint32_t at, uint32_t c) {
+        return (uint32_t)src[at][c] | ((uint32_t)src[at + 1][c] << 8) | ((uint32_t)src[at + 2][c] << 16) | ((uint32_t)src[at + 3][c] << 24);
+    };
+    if (NB % 8 == 0 && nb == (uint32_t)NB && (((uint32_t)(uintptr_t)dst | (uint32_t)pitch) & 7u) == 0u) {
+        constexpr uint32_t P = (NB + 7) / 8;
+        for (uint32_t j = threadIdx.x; j < cols * P; j += NT) {
+            const uint32_t c = j / P, x = j % P;
+            *(u32x2 *)(dst + (size_t)c * pitch + 8 * x) = u32x2{word(8 * x, c), word(8 * x + 4, c)};
+        }
+        return;
+    }
+    const uint32_t c = threadIdx.x % (uint32_t)TC, first = threadIdx.x / (uint32_t)TC;
+    if (c >= cols)
+        return;
+    unsigned char *const line = dst + (size_t)c * pitch;
+    if (nb < 4u) {
+        if (first == 0u)
+            store_three(word(0, c), line, nb);
+    } else {
+        for (uint32_t x = first; 4u * x < nb; x += NT / TC) {
+            const uint32_t at = piece_at(x, nb);
+            store_anywhere(word(at, c), line + at);
+        }
+    }
+}
+
+// Four dwords of a column of W^T, `left` (> 0) of them valid, to an address that is a multiple of four bytes: where the columns' runs are
+// not whole 16-byte pieces.  Plain stores: with streaming ones the lines that two tiles share are not put together in L2.
+__device__ __forceinline__ void store_dwords(u32x4 v, char *p, uint32_t left)
+{
+    typedef u32x4 dwords __attribute__((aligned(4)));
+    if (left >= 4u) {
+        *(dwords *)p = v;
+    } else {
+        ((uint32_t *)p)[0] = v.x;
+        if (left > 1u)
+            ((uint32_t *)p)[1] = v.y;
+        if (left > 2u)
+            ((uint32_t *)p)[2] = v.z;
+    }
+}
+
 template <int M>
 struct Log2 {
     static constexpr int v = (M == 4) ? 2 : (M == 8) ? 3 : (M == 16) ? 4 : 5;
@@ -399,45 +516,37 @@ __global__ __launch_bounds__(kThreads) void pack_kernel(const PackArgs args)
     }
     __syncthreads();
 
-    // ---- G: stream the staged W^T values and both index arrays out (row-per-lane-group, no divisions) ----
+    // ---- G: stream the staged W^T values and both index arrays out ----
     {
         // valsT: c_valid rows (columns of W), b_valid*N elements each
         const uint32_t run = b_valid * N;
         const size_t pitch = (size_t)(d.rows / M) * N;
         T *dst = (T *)d.valsT + (size_t)col0 * pitch + (size_t)(row0 / M) * N;
         if (ES == 4 || (((run | (uint32_t)pitch | (uint32_t)((row0 / M) * N)) & 1u) == 0)) {
-            // lanes per output row: a run has at most BPT * (M - 1) * ES / 4 dwords, BPT * M / 2 * ES / 4 when N = M/2
-            constexpr uint32_t LWMAX = ES == 4 ? 64 : 32;
-            constexpr uint32_t LW = (NN != 0 && 2 * NN == M) ? LWMAX / 2 : LWMAX;
-            const uint32_t rd = run * ES / 4, x = tid % LW;
+            const uint32_t rd = run * ES / 4, shift = rd > 1u ? 32u - (uint32_t)__builtin_clz(rd - 1u) : 0u;
+            const uint32_t x = tid & ((1u << shift) - 1u);
             if (x < rd)
-                for (uint32_t c = tid / LW; c < c_valid; c += kThreads / LW)
+                for (uint32_t c = tid >> shift; c < c_valid; c += (uint32_t)kThreads >> shift)
                     stream_store(((const uint32_t *)&OT[c][0])[x], (uint32_t *)(dst + (size_t)c * pitch) + x);
         } else {
-            for (uint32_t k = tid; k < c_valid * run; k += kThreads) {
-                const uint32_t c = k / run, x = k - c * run;
-                dst[(size_t)c * pitch + x] = OT[c][x];
-            }
+            copy_short_lines<OTP * ES, kThreads>((const uint8_t (*)[OTP * ES])OT, (unsigned char *)dst, pitch * ES, c_valid, run * ES);
         }
     }
     {
-        // idx: per row, the tile's bit string starts on a byte boundary (GPT*N*IB is a multiple of 8)
-        constexpr uint32_t LW = IDXW * 4 <= 32 ? 32 : 64;
-        const size_t pitch = ((size_t)(d.cols / M) * N * IB + 7) / 8;
-        const uint32_t nbytes = (g_valid * N * IB + 7) / 8, x = tid % LW;
-        unsigned char *dst = (unsigned char *)d.idx + (size_t)row0 * pitch + ((size_t)(col0 / M) * N * IB) / 8;
-        if (x < nbytes)
-            for (uint32_t r = tid / LW; r < r_valid; r += kThreads / LW)
-                dst[(size_t)r * pitch + x] = ((const unsigned char *)&IDX[r][0])[x];
-    }
-    {
-        constexpr uint32_t LW = IDXTW * 4 <= 32 ? 32 : 64;
-        const size_t pitch = ((size_t)(d.rows / M) * N * IB + 7) / 8;
-        const uint32_t nbytes = (b_valid * N * IB + 7) / 8, x = tid % LW;
-        unsigned char *dst = (unsigned char *)d.idxT + (size_t)col0 * pitch + ((size_t)(row0 / M) * N * IB) / 8;
-        if (x < nbytes)
-            for (uint32_t c = tid / LW; c < c_valid; c += kThreads / LW)
-                dst[(size_t)c * pitch + x] = ((const unsigned char *)&IDXT[c][0])[x];
+        // per row, the tile's bit string starts on a byte boundary (GPT*N*IB is a multiple of 8)
+        const size_t pitch = ((size_t)(d.cols / M) * N * IB + 7) / 8, pitchT = ((size_t)(d.rows / M) * N * IB + 7) / 8;
+        unsigned char *const dst = (unsigned char *)d.idx + (size_t)row0 * pitch + ((size_t)(col0 / M) * N * IB) / 8;
+        unsigned char *const dstT = (unsigned char *)d.idxT + (size_t)col0 * pitchT + ((size_t)(row0 / M) * N * IB) / 8;
+        const uint32_t nb = (g_valid * N * IB + 7) / 8, nbT = (b_valid * N * IB + 7) / 8;
+        auto lines = (const uint8_t (*)[IDXW * 4])IDX;
+        auto linesT = (const uint8_t (*)[IDXTW * 4])IDXT;
+        if constexpr (NN != 0) {
+            copy_lines<IDXW * 4, kThreads, GPT * NN * IB / 8>(lines, dst, pitch, r_valid, nb);
+            copy_lines<IDXTW * 4, kThreads, BPT * NN * IB / 8>(linesT, dstT, pitchT, c_valid, nbT);
+        } else {
+            copy_short_lines<IDXW * 4, kThreads>(lines, dst, pitch, r_valid, nb);
+            copy_short_lines<IDXTW * 4, kThreads>(linesT, dstT, pitchT, c_valid, nbT);
+        }
     }
 }
 

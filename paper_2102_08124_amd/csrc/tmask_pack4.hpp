@@ -110,72 +110,36 @@ __device__ __forceinline__ void pack24_copy_out(const PackDev &d, uint32_t row0,
     const size_t pitchT = (size_t)(d.rows / 4) * 2;    // elements per row of valsT
     const uint32_t cols_valid = min((uint32_t)TC, d.cols - col0);
     const uint32_t brs_valid = min((uint32_t)(TR / 4), (d.rows - row0) / 4);
-    const uint32_t rows_valid = brs_valid * 4;
-    // ---- valsT ----
-    {
-        char *dst = (char *)d.valsT + ((size_t)col0 * pitchT + (size_t)(row0 / 4) * 2) * ES;
-        const size_t pitch_b = pitchT * ES;
-        if (brs_valid == TR / 4 && (pitch_b & 15) == 0 && (((uintptr_t)dst) & 15) == 0) {
-            constexpr int CH = OTD / 4;   // 16-byte chunks per column
-            for (uint32_t j = tid; j < cols_valid * CH; j += kNT) {
-                const uint32_t cc = j / CH, part = j % CH;
-                const uint32_t sc = ot_col(4 * part, cc);          // the same for the four rows 4 part .. 4 part + 3
-                const u32x4 v = {OT[4 * part][sc], OT[4 * part + 1][sc], OT[4 * part + 2][sc], OT[4 * part + 3][sc]};
-                stream_store(v, (u32x4 *)(dst + (size_t)cc * pitch_b + 16 * part));
-            }
-        } else {
-            const uint32_t rd = brs_valid * 2 * ES / 4;   // dwords per column
-            for (uint32_t j = tid; j < cols_valid * rd; j += kNT) {
-                const uint32_t cc = j / rd, x = j - cc * rd;
+    const size_t pitch_b = pitchT * ES;
+    char *const dst = (char *)d.valsT + (size_t)col0 * pitch_b + (size_t)(row0 / 4) * 2 * ES;
+    const bool whole = (((uintptr_t)dst | pitch_b) & 15) == 0;
+    constexpr uint32_t CH = OTD / 4;                   // 16-byte pieces per column
+    const uint32_t rd = brs_valid * PG::VPB;           // valid dwords per column
+    if (whole && brs_valid == (uint32_t)TR / 4u) {
+        for (uint32_t j = tid; j < cols_valid * CH; j += kNT) {
+            const uint32_t cc = j / CH, part = j % CH;
+            const uint32_t sc = ot_col(4 * part, cc);  // the same for the four rows 4 part .. 4 part + 3
+            const u32x4 v = {OT[4 * part][sc], OT[4 * part + 1][sc], OT[4 * part + 2][sc], OT[4 * part + 3][sc]};
+            stream_store(v, (u32x4 *)(dst + (size_t)cc * pitch_b + 16 * part));
+        }
+    } else if constexpr (DT == kF32) {                 // a dword to a lane: 2156 x 4992 in one pass 24.1, four 24.8 us
+        for (uint32_t j = tid; j < cols_valid * OTD; j += kNT) {
+            const uint32_t cc = j / OTD, x = j % OTD;
+            if (x < rd)
                 *(uint32_t *)(dst + (size_t)cc * pitch_b + 4 * x) = OT[x][ot_col(x, cc)];
-            }
+        }
+    } else {
+        for (uint32_t j = tid; j < cols_valid * CH; j += kNT) {
+            const uint32_t cc = j / CH, part = j % CH;
+            const uint32_t sc = ot_col(4 * part, cc);
+            const u32x4 v = {OT[4 * part][sc], OT[4 * part + 1][sc], OT[4 * part + 2][sc], OT[4 * part + 3][sc]};
+            if (4u * part < rd)
+                store_dwords(v, dst + (size_t)cc * pitch_b + 16 * part, rd - 4u * part);
         }
     }
-    // ---- idx ----
-    {
-        const size_t pitch = ((size_t)d.cols + 7) / 8;
-        const uint32_t nb = (cols_valid / 4 + 1) / 2;
-        unsigned char *dst = (unsigned char *)d.idx + (size_t)row0 * pitch + col0 / 8;
-        if ((nb & 3) == 0 && (pitch & 3) == 0 && (((uintptr_t)dst) & 3) == 0) {
-            const uint32_t nd = nb / 4;
-            for (uint32_t j = tid; j < rows_valid * nd; j += kNT) {
-                const uint32_t r = j / nd, x = j - r * nd;
-                *(uint32_t *)(dst + (size_t)r * pitch + 4 * x) = ((const uint32_t *)&IDX[r][0])[x];
-            }
-        } else {
-            for (uint32_t j = tid; j < rows_valid * nb; j += kNT) {
-                const uint32_t r = j / nb, x = j - r * nb;
-                dst[(size_t)r * pitch + x] = IDX[r][x];
-            }
-        }
-    }
-    // ---- idxT ----
-    {
-        const size_t pitch = ((size_t)d.rows + 7) / 8;
-        const uint32_t nb = (brs_valid + 1) / 2;
-        unsigned char *dst = (unsigned char *)d.idxT + (size_t)col0 * pitch + row0 / 8;
-        constexpr uint32_t PB = TR % 64 == 0 ? 8 : 4;     // bytes per store
-        if (nb == TR / 8 && (pitch & (PB - 1)) == 0 && (((uintptr_t)dst) & (PB - 1)) == 0) {
-            constexpr uint32_t P = TR / 8 / PB;           // pieces per column
-            for (uint32_t j = tid; j < cols_valid * P; j += kNT) {
-                const uint32_t cc = j / P, x = j % P;
-                uint32_t v[PB / 4];
-#pragma unroll
-                for (uint32_t h = 0; h < PB / 4; h++)
-                    v[h] = (uint32_t)IDXT[PB * x + 4 * h][cc] | ((uint32_t)IDXT[PB * x + 4 * h + 1][cc] << 8) |
-                           ((uint32_t)IDXT[PB * x + 4 * h + 2][cc] << 16) | ((uint32_t)IDXT[PB * x + 4 * h + 3][cc] << 24);
-                if constexpr (PB == 8)
-                    *(u32x2 *)(dst + (size_t)cc * pitch + 8 * x) = u32x2{v[0], v[1]};
-                else
-                    *(uint32_t *)(dst + (size_t)cc * pitch + 4 * x) = v[0];
-            }
-        } else {
-            for (uint32_t j = tid; j < cols_valid * nb; j += kNT) {
-                const uint32_t cc = j / nb, x = j - cc * nb;
-                dst[(size_t)cc * pitch + x] = IDXT[x][cc];
-            }
-        }
-    }
+    const size_t pitch = ((size_t)d.cols + 7) / 8, pitchX = ((size_t)d.rows + 7) / 8;
+    copy_lines<PG::IDXB, kNT>(IDX, (unsigned char *)d.idx + (size_t)row0 * pitch + col0 / 8, pitch, brs_valid * 4, (cols_valid / 4 + 1) / 2);
+    copy_columns<PG::IDXTB, TC, kNT>(IDXT, (unsigned char *)d.idxT + (size_t)col0 * pitchX + row0 / 8, pitchX, cols_valid, (brs_valid + 1) / 2);
 }
 
 template <int DT, int FMT, int S, int NW, int QN, typename Args = PackArgs>

@@ -69,75 +69,29 @@ __device__ __forceinline__ void pack48_copy_out(const PackDev &d, uint32_t row0,
     const uint32_t tid = threadIdx.x;
     const uint32_t cols_valid = min((uint32_t)TC, d.cols - col0);
     const uint32_t brs_valid = min((uint32_t)(TR / 8), (d.rows - row0) / 8);
-    const uint32_t rows_valid = brs_valid * 8;
-    {
-        const size_t pitch_b = (size_t)(d.rows / 8) * 4 * ES;          // bytes per row of valsT
-        char *dst = (char *)d.valsT + (size_t)col0 * pitch_b + (size_t)(row0 / 8) * 4 * ES;
-        if (brs_valid == TR / 8 && (pitch_b & 15) == 0 && (((uintptr_t)dst) & 15) == 0) {
-            constexpr uint32_t CH = OTD / 4;                           // 16-byte pieces per column
-            for (uint32_t j = tid; j < cols_valid * CH; j += NT) {
-                const uint32_t cc = j / CH, part = j % CH;
-                const u32x4 v = {OT[4 * part][cc], OT[4 * part + 1][cc], OT[4 * part + 2][cc], OT[4 * part + 3][cc]};
-                stream_store(v, (u32x4 *)(dst + (size_t)cc * pitch_b + 16 * part));
-            }
-        } else {
-            const uint32_t rd = brs_valid * DPB;                       // dwords per column
-            for (uint32_t j = tid; j < cols_valid * rd; j += NT) {
-                const uint32_t cc = j / rd, x = j - cc * rd;
-                *(uint32_t *)(dst + (size_t)cc * pitch_b + 4 * x) = OT[x][cc];
-            }
+    const size_t pitch_b = (size_t)(d.rows / 8) * 4 * ES;              // bytes per row of valsT
+    char *const dst = (char *)d.valsT + (size_t)col0 * pitch_b + (size_t)(row0 / 8) * 4 * ES;
+    const bool whole = (((uintptr_t)dst | pitch_b) & 15) == 0;
+    constexpr uint32_t CH = OTD / 4;                                   // 16-byte pieces per column
+    if (whole && brs_valid == (uint32_t)TR / 8u) {
+        for (uint32_t j = tid; j < cols_valid * CH; j += NT) {
+            const uint32_t cc = j / CH, part = j % CH;
+            const u32x4 v = {OT[4 * part][cc], OT[4 * part + 1][cc], OT[4 * part + 2][cc], OT[4 * part + 3][cc]};
+            stream_store(v, (u32x4 *)(dst + (size_t)cc * pitch_b + 16 * part));
+        }
+    } else {
+        for (uint32_t j = tid; j < cols_valid * CH; j += NT) {
+            const uint32_t cc = j / CH, part = j % CH;
+            const u32x4 v = {OT[4 * part][cc], OT[4 * part + 1][cc], OT[4 * part + 2][cc], OT[4 * part + 3][cc]};
+            if (4u * part < brs_valid * DPB)
+                store_dwords(v, dst + (size_t)cc * pitch_b + 16 * part, brs_valid * DPB - 4u * part);
         }
     }
-    {
-        const size_t pitch = ((size_t)(d.cols / 8) * 12 + 7) / 8;
-        const uint32_t nb = ((cols_valid / 8) * 12 + 7) / 8;
-        unsigned char *dst = (unsigned char *)d.idx + (size_t)row0 * pitch + (size_t)(col0 / 8) * 12 / 8;
-        if ((nb & 3) == 0 && (pitch & 3) == 0 && (((uintptr_t)dst) & 3) == 0) {
-            const uint32_t nd = nb / 4;
-            for (uint32_t j = tid; j < rows_valid * nd; j += NT) {
-                const uint32_t r = j / nd, x = j - r * nd;
-                *(uint32_t *)(dst + (size_t)r * pitch + 4 * x) = ((const uint32_t *)&IDX[r][0])[x];
-            }
-        } else {
-            for (uint32_t j = tid; j < rows_valid * nb; j += NT) {
-                const uint32_t r = j / nb, x = j - r * nb;
-                dst[(size_t)r * pitch + x] = IDX[r][x];
-            }
-        }
-    }
-    {
-        constexpr uint32_t PB = (IDXTB % 8 == 0) ? 8 : 4;              // bytes per store
-        static_assert(IDXTB % PB == 0, "a tile column's position bytes are whole pieces");
-        const size_t pitch = ((size_t)(d.rows / 8) * 12 + 7) / 8;
-        const uint32_t nb = (brs_valid * 12 + 7) / 8;
-        unsigned char *dst = (unsigned char *)d.idxT + (size_t)col0 * pitch + (size_t)(row0 / 8) * 12 / 8;
-        if (nb == IDXTB && (pitch & (PB - 1)) == 0 && (((uintptr_t)dst) & (PB - 1)) == 0) {
-            for (uint32_t j = tid; j < cols_valid * (IDXTB / PB); j += NT) {
-                const uint32_t piece = j / cols_valid, cc = j - piece * cols_valid;
-                uint32_t v[PB / 4];
-#pragma unroll
-                for (uint32_t h = 0; h < PB / 4; h++) {
-                    v[h] = 0;
-#pragma unroll
-                    for (uint32_t k = 0; k < 4; k++)
-                        v[h] |= (uint32_t)IDXT[PB * piece + 4 * h + k][cc] << (8 * k);
-                }
-                if constexpr (PB == 8) {
-                    u32x2 vv;
-                    vv.x = v[0];
-                    vv.y = v[1];
-                    *(u32x2 *)(dst + (size_t)cc * pitch + 8 * piece) = vv;
-                } else {
-                    *(uint32_t *)(dst + (size_t)cc * pitch + 4 * piece) = v[0];
-                }
-            }
-        } else {
-            for (uint32_t j = tid; j < cols_valid * nb; j += NT) {
-                const uint32_t x = j / cols_valid, cc = j - x * cols_valid;
-                dst[(size_t)cc * pitch + x] = IDXT[x][cc];
-            }
-        }
-    }
+    const size_t pitch = ((size_t)(d.cols / 8) * 12 + 7) / 8, pitchT = ((size_t)(d.rows / 8) * 12 + 7) / 8;
+    copy_lines<IDXB, NT>(IDX, (unsigned char *)d.idx + (size_t)row0 * pitch + (size_t)(col0 / 8) * 12 / 8, pitch, brs_valid * 8,
+                         ((cols_valid / 8) * 12 + 7) / 8);
+    copy_columns<IDXTB, TC, NT>(IDXT, (unsigned char *)d.idxT + (size_t)col0 * pitchT + (size_t)(row0 / 8) * 12 / 8, pitchT, cols_valid,
+                                (brs_valid * 12 + 7) / 8);
 }
 
 // APPROX = false: tmask_apply_pack (ARGS = PackArgs, the mask is read).  APPROX = true: tmask_approx_pack
