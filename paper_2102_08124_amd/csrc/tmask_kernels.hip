@@ -1101,6 +1101,11 @@ static BatchKernel pick_score_kernel(int dt, int M, int mf)
 // (512) 16.7 / 19.0; in one pass 10.0 / 7.0, 512 tiles 14.6 / 13.7, 768 tiles 22.7 / 26.8.  fp32 4:8 (half the width, one block-row to
 // a lane) 128^2 8.9 / 6.1, 2048^2 (256) 11.7 / 9.7, 3144 x 3192 (650) 28.7 / 34.0; in one pass 128^2 16.9 / 8.3, 2048^2 15.5 / 12.2, 3072^2
 // (576) 24.1 / 20.2, 4096 x 3072 (768) 25.6 / 29.3.
+// The kernel for any N:M takes workgroups of 1024 threads instead of 256 up to two tiles for a compute unit, which is what one holds of
+// them: a unit to a thread instead of four to eight one after the other.  256 / 1024, us: fp32 8:16 464 x 128 5.9 / 4.3, 2048 x 1024 (512
+// tiles) 7.0 / 6.2, 2048^2 (1024) 10.5 / 11.9; 7:8 464 x 128 8.2 / 5.3, 2048 x 1024 13.9 / 11.8; bf16 8:16 464 x 128 7.3 / 4.7, 2048^2 (512) 9.8 / 7.9,
+// 1712 x 2752 (594) 12.1 / 12.7; 3:8 9.5 / 5.8, 13.0 / 10.1, 15.3 / 14.8.
+constexpr double kWideTilesPack = 2.0;
 constexpr double kHalfTilesPack = 1.5, kHalfTilesFusedF32 = 2.0, kHalfTilesFusedF32M8 = 2.5, kHalfTilesFusedBf16 = 2.5;
 
 template <typename DESC>
@@ -1468,6 +1473,30 @@ int launch_score_reduce(const uint32_t *first0, int nb, uint32_t partial0, const
     return e == hipSuccess ? TMASK_OK : hip_fail(e, "score reduce launch");
 }
 
+// The kernels for any N:M: with workgroups of 256 and the large table, or of 1024 and the small one.
+template <int NT, typename Args>
+static void (*pick_pack_kernel(int dt, int M, int mf, int N))(const Args)
+{
+    if (2 * N == M) {   // N known at compile time
+#define TMASK_PICK(DT, MM, FM) \
+    if (dt == DT && M == MM && mf == FM) return pack_kernel<DT, MM, FM, MM / 2, NT, Args>;
+        TMASK_PICK(kF32, 4, kMaskU8) TMASK_PICK(kF32, 8, kMaskU8) TMASK_PICK(kF32, 16, kMaskU8)
+        TMASK_PICK(kBF16, 4, kMaskU8) TMASK_PICK(kBF16, 8, kMaskU8) TMASK_PICK(kBF16, 16, kMaskU8)
+        TMASK_PICK(kF32, 4, kMaskBits) TMASK_PICK(kF32, 8, kMaskBits) TMASK_PICK(kF32, 16, kMaskBits)
+        TMASK_PICK(kBF16, 4, kMaskBits) TMASK_PICK(kBF16, 8, kMaskBits) TMASK_PICK(kBF16, 16, kMaskBits)
+        TMASK_PICK(kF32, 32, kMaskU8) TMASK_PICK(kBF16, 32, kMaskU8) TMASK_PICK(kF32, 32, kMaskBits) TMASK_PICK(kBF16, 32, kMaskBits)
+#undef TMASK_PICK
+    }
+#define TMASK_PICK(DT, MM, FM) \
+    if (dt == DT && M == MM && mf == FM) return pack_kernel<DT, MM, FM, 0, NT, Args>;
+    TMASK_PICK(kF32, 4, kMaskU8) TMASK_PICK(kF32, 8, kMaskU8) TMASK_PICK(kF32, 16, kMaskU8)
+    TMASK_PICK(kBF16, 4, kMaskU8) TMASK_PICK(kBF16, 8, kMaskU8) TMASK_PICK(kBF16, 16, kMaskU8)
+    TMASK_PICK(kF32, 4, kMaskBits) TMASK_PICK(kF32, 8, kMaskBits) TMASK_PICK(kF32, 16, kMaskBits)
+    TMASK_PICK(kBF16, 4, kMaskBits) TMASK_PICK(kBF16, 8, kMaskBits) TMASK_PICK(kBF16, 16, kMaskBits)
+#undef TMASK_PICK
+    return nullptr;
+}
+
 }  // namespace tmask
 
 using namespace tmask;
@@ -1569,28 +1598,6 @@ int tmask_score(const tmask_mat *mats, int n_mats, tmask_dtype dt, int N, int M,
 typedef void (*pack_kernel_t)(const PackArgs);
 typedef void (*few_pack_kernel_t)(const FewPackArgs);
 
-static pack_kernel_t pick_pack_kernel(int dt, int M, int mf, int N)
-{
-    if (2 * N == M) {   // N known at compile time
-#define TMASK_PICK(DT, MM, FM) \
-    if (dt == DT && M == MM && mf == FM) return pack_kernel<DT, MM, FM, MM / 2>;
-        TMASK_PICK(kF32, 4, kMaskU8) TMASK_PICK(kF32, 8, kMaskU8) TMASK_PICK(kF32, 16, kMaskU8)
-        TMASK_PICK(kBF16, 4, kMaskU8) TMASK_PICK(kBF16, 8, kMaskU8) TMASK_PICK(kBF16, 16, kMaskU8)
-        TMASK_PICK(kF32, 4, kMaskBits) TMASK_PICK(kF32, 8, kMaskBits) TMASK_PICK(kF32, 16, kMaskBits)
-        TMASK_PICK(kBF16, 4, kMaskBits) TMASK_PICK(kBF16, 8, kMaskBits) TMASK_PICK(kBF16, 16, kMaskBits)
-        TMASK_PICK(kF32, 32, kMaskU8) TMASK_PICK(kBF16, 32, kMaskU8) TMASK_PICK(kF32, 32, kMaskBits) TMASK_PICK(kBF16, 32, kMaskBits)
-#undef TMASK_PICK
-    }
-#define TMASK_PICK(DT, MM, FM) \
-    if (dt == DT && M == MM && mf == FM) return pack_kernel<DT, MM, FM>;
-    TMASK_PICK(kF32, 4, kMaskU8) TMASK_PICK(kF32, 8, kMaskU8) TMASK_PICK(kF32, 16, kMaskU8)
-    TMASK_PICK(kBF16, 4, kMaskU8) TMASK_PICK(kBF16, 8, kMaskU8) TMASK_PICK(kBF16, 16, kMaskU8)
-    TMASK_PICK(kF32, 4, kMaskBits) TMASK_PICK(kF32, 8, kMaskBits) TMASK_PICK(kF32, 16, kMaskBits)
-    TMASK_PICK(kBF16, 4, kMaskBits) TMASK_PICK(kBF16, 8, kMaskBits) TMASK_PICK(kBF16, 16, kMaskBits)
-#undef TMASK_PICK
-    return nullptr;
-}
-
 int tmask_apply_pack(const tmask_pack_desc *descs, int n, tmask_dtype dt, int N, int M, tmask_mask_fmt mf,
                      void *workspace, size_t workspace_bytes, void *hip_stream)
 {
@@ -1617,13 +1624,17 @@ int tmask_apply_pack(const tmask_pack_desc *descs, int n, tmask_dtype dt, int N,
     const bool narrow24 = fit == kFitNarrow && N == 2;           // the only kernel with narrow strips
     if (fit != kFitWide && !narrow24)
         return cw_run_pack(descs, n, (int)dt, N, M, (int)mf, (hipStream_t)hip_stream);
-    pack_kernel_t kern = pick_pack_kernel((int)dt, M, (int)mf, N);
+    pack_kernel_t kern = pick_pack_kernel<kThreads, PackArgs>((int)dt, M, (int)mf, N);
     few_pack_kernel_t few = nullptr;      // of kern, where it has one
     uint32_t TC = 256 / (uint32_t)elem_size((int)dt);
     bool fast24 = (M == 4 && N == 2) && !narrow24;
     for (int i = 0; i < n && fast24; i++)
         fast24 = (((uintptr_t)descs[i].vals | (uintptr_t)descs[i].valsT) & 7) == 0;
     uint32_t TR = kPackTR, lds_reserve = 0, threads = kThreads;
+    if (n <= kFewMats && few_tiles(descs, n, TR, TC, kWideTilesPack)) {
+        few = pick_pack_kernel<kPackThreads, FewPackArgs>((int)dt, M, (int)mf, N);
+        threads = kPackThreads;
+    }
     if (fast24) {
         // tile widths in strips: measured best per element type (bf16: narrower and taller, so the runs written
         // per column of W^T are 128 bytes long)
@@ -1668,6 +1679,7 @@ int tmask_apply_pack(const tmask_pack_desc *descs, int n, tmask_dtype dt, int N,
 #undef TMASK_PICK
         TC = Pack8Geo<2>::TC;
         TR = small ? Pack8Geo<1>::TR : Pack8Geo<2>::TR;
+        threads = kThreads;
     }
     bool fast48f = (M == 8 && N == 4 && dt == TMASK_F32);
     for (int i = 0; i < n && fast48f; i++)
@@ -1684,6 +1696,7 @@ int tmask_apply_pack(const tmask_pack_desc *descs, int n, tmask_dtype dt, int N,
 #undef TMASK_PICK
         TC = small ? Pack8F32Geo<SH, 1>::TC : Pack8F32Geo<SW>::TC;
         TR = small ? Pack8F32Geo<SH, 1>::TR : Pack8F32Geo<SW>::TR;
+        threads = kThreads;
     }
     hipStream_t stream = (hipStream_t)hip_stream;
     for (int first = 0; first < n; first += kMaxPackBatch) {

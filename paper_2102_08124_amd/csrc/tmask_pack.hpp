@@ -5,11 +5,10 @@
 // non-zeros in every M contiguous elements of both.  The storage format is this library's own and
 // is described in include/tmask.h.
 //
-// One workgroup packs a 64-row x 256-byte tile (64 fp32 or 128 bf16 columns):
+// One workgroup, of 256 threads or, in calls of few tiles, of 1024, packs a 64-row x 256-byte tile (64 fp32 or 128 bf16 columns):
 //   A  coalesced 16-byte loads of W and of the mask; masked values and 0/1 flags go to LDS
-//   C  every thread pulls its row-direction units (one row x one group of M columns) and its
-//      column-direction units (one group of M rows x one column) from LDS into registers
-//   E  each unit is compacted (kept entries, then lowest unused positions as +0 fillers, in position
+//   E  every thread takes its row-direction units (one row x one group of M columns) and its column-direction units (one group of M
+//      rows x one column); each is compacted (kept entries, then lowest unused positions as +0 fillers, in position
 //      order) and scattered into LDS staging: values row-major for W, column-major for W^T, index
 //      bits OR-ed into per-row bit strings
 //   G  staging is streamed out with coalesced stores (runs of 128..256 bytes per output row)
@@ -20,6 +19,7 @@ namespace tmask {
 
 constexpr int kMaxPackBatch = 224;  // descriptors of 72 bytes, passed by value as kernel argument (16 KiB)
 constexpr int kPackTR = 64;
+constexpr int kPackThreads = 1024;    // of the kernel for any N:M where a call has few tiles
 
 struct PackDev {
     const void *w;
@@ -289,8 +289,8 @@ __device__ __forceinline__ void put_code(uint32_t *words, uint32_t g, unsigned l
     }
 }
 
-template <int DT, int M, int FMT, int NN = 0>
-__global__ __launch_bounds__(kThreads) void pack_kernel(const PackArgs args)
+template <int DT, int M, int FMT, int NN = 0, int NT = kThreads, typename Args = PackArgs>
+__global__ __launch_bounds__(NT) void pack_kernel(const Args args)
 {
     using T = typename std::conditional<DT == kF32, uint32_t, uint16_t>::type;
     constexpr int ES = sizeof(T);
@@ -305,10 +305,8 @@ __global__ __launch_bounds__(kThreads) void pack_kernel(const PackArgs args)
     constexpr int NMAX = NN ? NN : M - 1;      // slots per group the staging must hold
     constexpr int IDXW = (GPT * NMAX * IB + 31) / 32 + 2;
     constexpr int IDXTW = (BPT * NMAX * IB + 31) / 32 + 2 + 1;
-    constexpr int NRU = (TR * GPT + kThreads - 1) / kThreads;   // row-direction units per thread
-    constexpr int NCU = (BPT * TC + kThreads - 1) / kThreads;   // column-direction units per thread
-    static_assert((TR * GPT % kThreads == 0 || TR * GPT < kThreads) && (BPT * TC % kThreads == 0 || BPT * TC < kThreads),
-                  "units tile the workgroup, or there are fewer of them than threads (fp32 at M = 32)");
+    constexpr int RU = TR * GPT, CU = BPT * TC;                 // row-direction and column-direction units
+    static_assert(RU % 64 == 0, "a wavefront's units are of one direction");
     // Position codes of a group: NN * IB bits.  Beyond 64 bits (16:32: 80) they are kept as two halves of NN / 2 slots,
     // which go into the bit string as groups number 2g and 2g + 1 of half the width.
     constexpr bool SPLIT = NN * IB > 64;
@@ -335,18 +333,18 @@ __global__ __launch_bounds__(kThreads) void pack_kernel(const PackArgs args)
     const uint32_t r_valid = b_valid * M, c_valid = g_valid * M;
 
     // ---- A: load ----
-    for (uint32_t k = tid; k < TR * IDXW; k += kThreads)
+    for (uint32_t k = tid; k < TR * IDXW; k += NT)
         (&IDX[0][0])[k] = 0;
-    for (uint32_t k = tid; k < TC * IDXTW; k += kThreads)
+    for (uint32_t k = tid; k < TC * IDXTW; k += NT)
         (&IDXT[0][0])[k] = 0;
     // all loads of the thread go out before the first is used, none inside a branch (its result would be waited for
     // at the join): chunks outside the matrix read chunk (0, 0) and are dropped
-    constexpr int PASSES = TR / 16;
+    constexpr int PASSES = TR * 16 / NT;
     u32x4 raws[PASSES];
     uint32_t mlo[PASSES], mhi[PASSES];
 #pragma unroll
     for (int pass = 0; pass < PASSES; pass++) {
-        const uint32_t r = pass * 16 + (tid >> 4), ch = tid & 15u;
+        const uint32_t r = pass * (NT / 16) + (tid >> 4), ch = tid & 15u;
         const uint32_t row = row0 + r, col = col0 + ch * C;
         const bool ok = row < d.rows && col < d.cols;
         const uint32_t rowc = ok ? row : 0u, colc = ok ? col : 0u;
@@ -367,7 +365,7 @@ __global__ __launch_bounds__(kThreads) void pack_kernel(const PackArgs args)
     }
 #pragma unroll
     for (int pass = 0; pass < PASSES; pass++) {
-        const uint32_t r = pass * 16 + (tid >> 4), ch = tid & 15u;
+        const uint32_t r = pass * (NT / 16) + (tid >> 4), ch = tid & 15u;
         const uint32_t row = row0 + r, col = col0 + ch * C;
         const bool ok = row < d.rows && col < d.cols;
         u32x4 raw = raws[pass];
@@ -399,13 +397,14 @@ __global__ __launch_bounds__(kThreads) void pack_kernel(const PackArgs args)
 
     // ---- E: compact.  Row units write W's values straight to memory (consecutive threads own
     // consecutive groups of a row); column units park W^T's values in LDS, column-major. ----
-    {
-        const size_t pitch = (size_t)(d.cols / M) * N;            // elements per row of vals
-        const bool pair_ok = ES == 2 && ((N | (uint32_t)pitch) & 1u) == 0;
+    const size_t pitchW = (size_t)(d.cols / M) * N;               // elements per row of vals
+    const bool pair_ok = ES == 2 && ((N | (uint32_t)pitchW) & 1u) == 0;
 #pragma unroll
-        for (int k = 0; k < NRU; k++) {
-            const uint32_t u = tid + k * kThreads, r = u / GPT, g = u % GPT;
-            if (u >= (uint32_t)(TR * GPT) || r >= r_valid || g >= g_valid)
+    for (int k = 0; k < (RU + CU + NT - 1) / NT; k++) {
+        const uint32_t unit = tid + (uint32_t)k * NT;
+        if (unit < (uint32_t)RU) {
+            const uint32_t r = unit / GPT, g = unit % GPT;
+            if (r >= r_valid || g >= g_valid)
                 continue;   // outside the matrix: must not leave index bits in a row's padding
             uint32_t kb = 0;
             if constexpr (M >= C) {
@@ -417,11 +416,11 @@ __global__ __launch_bounds__(kThreads) void pack_kernel(const PackArgs args)
             }
             uint32_t sel, rem;
             choose_slots<M>(kb, N, sel, rem);
-            T *dst = (T *)d.vals + (size_t)(row0 + r) * pitch + (size_t)(col0 / M + g) * N;
+            T *dst = (T *)d.vals + (size_t)(row0 + r) * pitchW + (size_t)(col0 / M + g) * N;
             unsigned long long code = 0, code_hi = 0;
             uint32_t pend = 0;
             if constexpr (NN != 0 && (NN * ES) % 16 == 0) {
-                if ((((uintptr_t)d.vals | (pitch * ES)) & 15) == 0) {
+                if ((((uintptr_t)d.vals | (pitchW * ES)) & 15) == 0) {
                     // the group's NN values as whole 16-byte pieces
                     uint32_t out[NN * ES / 4];
 #pragma unroll
@@ -472,12 +471,10 @@ __global__ __launch_bounds__(kThreads) void pack_kernel(const PackArgs args)
                 code |= (unsigned long long)p << (sl * IB);
             }
             lds_or_bits(IDX[r], g * N * IB, code);
+            continue;
         }
-    }
-#pragma unroll
-    for (int k = 0; k < NCU; k++) {
-        const uint32_t u = tid + k * kThreads, b = u / TC, c = u % TC;
-        if (u >= (uint32_t)(BPT * TC) || b >= b_valid || c >= c_valid)
+        const uint32_t u = unit - (uint32_t)RU, b = u / TC, c = u % TC;
+        if (u >= (uint32_t)CU || b >= b_valid || c >= c_valid)
             continue;
         uint32_t kb = 0;
 #pragma unroll
@@ -526,10 +523,10 @@ __global__ __launch_bounds__(kThreads) void pack_kernel(const PackArgs args)
             const uint32_t rd = run * ES / 4, shift = rd > 1u ? 32u - (uint32_t)__builtin_clz(rd - 1u) : 0u;
             const uint32_t x = tid & ((1u << shift) - 1u);
             if (x < rd)
-                for (uint32_t c = tid >> shift; c < c_valid; c += (uint32_t)kThreads >> shift)
+                for (uint32_t c = tid >> shift; c < c_valid; c += (uint32_t)NT >> shift)
                     stream_store(((const uint32_t *)&OT[c][0])[x], (uint32_t *)(dst + (size_t)c * pitch) + x);
         } else {
-            copy_short_lines<OTP * ES, kThreads>((const uint8_t (*)[OTP * ES])OT, (unsigned char *)dst, pitch * ES, c_valid, run * ES);
+            copy_short_lines<OTP * ES, NT>((const uint8_t (*)[OTP * ES])OT, (unsigned char *)dst, pitch * ES, c_valid, run * ES);
         }
     }
     {
@@ -541,11 +538,11 @@ __global__ __launch_bounds__(kThreads) void pack_kernel(const PackArgs args)
         auto lines = (const uint8_t (*)[IDXW * 4])IDX;
         auto linesT = (const uint8_t (*)[IDXTW * 4])IDXT;
         if constexpr (NN != 0) {
-            copy_lines<IDXW * 4, kThreads, GPT * NN * IB / 8>(lines, dst, pitch, r_valid, nb);
-            copy_lines<IDXTW * 4, kThreads, BPT * NN * IB / 8>(linesT, dstT, pitchT, c_valid, nbT);
+            copy_lines<IDXW * 4, NT, GPT * NN * IB / 8>(lines, dst, pitch, r_valid, nb);
+            copy_lines<IDXTW * 4, NT, BPT * NN * IB / 8>(linesT, dstT, pitchT, c_valid, nbT);
         } else {
-            copy_short_lines<IDXW * 4, kThreads>(lines, dst, pitch, r_valid, nb);
-            copy_short_lines<IDXTW * 4, kThreads>(linesT, dstT, pitchT, c_valid, nbT);
+            copy_short_lines<IDXW * 4, NT>(lines, dst, pitch, r_valid, nb);
+            copy_short_lines<IDXTW * 4, NT>(linesT, dstT, pitchT, c_valid, nbT);
         }
     }
 }

@@ -39,7 +39,8 @@ def _check(flat, views, used, want):
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
 @pytest.mark.parametrize("N,M", [(2, 4), (1, 4), (4, 8), (2, 8), (7, 8), (8, 16), (3, 16), (15, 16), (16, 32)])
 @pytest.mark.parametrize("rows,cols", [(1, 1), (1, 3), (3, 1), (5, 33), (17, 9), (9, 41)])          # in blocks
-def test_lines_at_odd_bytes(N, M, dt, rows, cols):
+@pytest.mark.parametrize("copies", [1, 9])                       # workgroups of 1024 threads, of 256
+def test_lines_at_odd_bytes(N, M, dt, rows, cols, copies):
     if dt == "bf16" and M == 4:
         cols = 2 * cols                                          # the tiled kernels: rows of whole 16 bytes
     w = wl.gaussian_f32(rows * M, cols * M, seed=50 + rows)
@@ -49,9 +50,12 @@ def test_lines_at_odd_bytes(N, M, dt, rows, cols):
     dev, dmask = to_dev(w), mask_to_dev(mask, tm.TMASK_MASK_U8)
     kinds = [dev.dtype, torch.uint8, dev.dtype, torch.uint8]
     flat, views, used = _guarded(tm.packed_shapes(*w.shape, N, M), kinds)
-    tm.tmask_apply_pack([dev], [dmask], [views], N, M)
+    others = [tm.alloc_packed(dev, N, M) for _ in range(copies - 1)]
+    tm.tmask_apply_pack([dev] * copies, [dmask] * copies, [views] + others, N, M)
     torch.cuda.synchronize()
     _check(flat, views, used, want)
+    if copies > 1:
+        return
     flat, views, used = _guarded(tm.packed_shapes(*w.shape, N, M), kinds)
     obj, wsp = torch.zeros(1, dtype=torch.float64, device="cuda"), tm.alloc_workspace([dev], N, M)
     tm.tmask_approx_pack([dev], tm.alloc_masks([dev]), [views], N, M, objective=obj, workspace=wsp)
