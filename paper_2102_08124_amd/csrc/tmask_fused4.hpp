@@ -238,22 +238,28 @@ __global__ __launch_bounds__(kThreads) void approx_pack24_kernel(const FusedArgs
             for (int c = 0; c < C; c++)
                 tnib[c] &= keepmask;
         }
-        // a lane's QN nibbles per column are QN / 2 bytes: as many rows of C bytes each
+        // a lane's QN nibbles per column are QN / 2 bytes, as many rows of C bytes each; one nibble is completed by that of the lane
+        // half a wavefront further, which holds the next block-row
+        if constexpr (QN == 1) {
 #pragma unroll
-        for (int t = 0; t < QN / 2; t++) {
+            for (int c = 0; c < C; c++)
+                tnib[c] |= (uint32_t)__shfl_xor((int)tnib[c], 32, 64) << 4;
+        }
+        constexpr int ROWS = QN == 1 ? 1 : QN / 2;
+#pragma unroll
+        for (int t = 0; t < ROWS; t++) {
             uint32_t b[C / 4];
 #pragma unroll
             for (int h = 0; h < C / 4; h++)
                 b[h] = ((tnib[4 * h] >> (8 * t)) & 0xFFu) | (((tnib[4 * h + 1] >> (8 * t)) & 0xFFu) << 8) |
                        (((tnib[4 * h + 2] >> (8 * t)) & 0xFFu) << 16) | (((tnib[4 * h + 3] >> (8 * t)) & 0xFFu) << 24);
-            if constexpr (C == 4) {
-                *(uint32_t *)&IDXT[(QN / 2) * q4 + t][tcol] = b[0];
-            } else {
-                u32x2 v;
-                v.x = b[0];
-                v.y = b[1];
-                *(u32x2 *)&IDXT[(QN / 2) * q4 + t][tcol] = v;
-            }
+            if (QN == 1 && sub != 0)
+                break;
+            const uint32_t at = QN == 1 ? w : ROWS * q4 + t;
+            if constexpr (C == 4)
+                *(uint32_t *)&IDXT[at][tcol] = b[0];
+            else
+                *(u32x2 *)&IDXT[at][tcol] = u32x2{b[0], b[1]};
         }
     };
     if (row0 + TR <= d.rows && col0 + TC <= d.cols)

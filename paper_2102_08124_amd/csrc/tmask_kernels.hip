@@ -1101,6 +1101,11 @@ static BatchKernel pick_score_kernel(int dt, int M, int mf)
 // (512) 16.7 / 19.0; in one pass 10.0 / 7.0, 512 tiles 14.6 / 13.7, 768 tiles 22.7 / 26.8.  fp32 4:8 (half the width, one block-row to
 // a lane) 128^2 8.9 / 6.1, 2048^2 (256) 11.7 / 9.7, 3144 x 3192 (650) 28.7 / 34.0; in one pass 128^2 16.9 / 8.3, 2048^2 15.5 / 12.2, 3072^2
 // (576) 24.1 / 20.2, 4096 x 3072 (768) 25.6 / 29.3.
+// Quarter tiles of the 2:4 kernels, one block-row to a lane, where there are no more than 0.7 whole tiles (1 in one pass) for a compute unit.  Half
+// / quarter, us: fp32 1024 x 512 5.6 / 4.8, 1948 x 1216 (155 tiles) 10.0 / 8.1, 2048^2 (256) 8.1 / 9.1; in one pass 8.0 / 6.9, 11.9 / 9.8, 10.1 / 10.1,
+// 2048 x 3072 (384) 12.6 / 14.3; bf16 1024 x 512 6.5 / 5.1, 2048^2 (128) 7.5 / 7.1, 2048 x 3072 (192) 9.3 / 9.5; in one pass 9.8 / 7.5, 10.9 / 9.5, 13.2 / 12.1.
+// Narrow strips (tiles of 64 x 128): 1000 x 1028 6.4 / 5.5, 1000 x 2052 (272) 7.5 / 6.6, 2048 x 1540 (416) 7.7 / 7.5, 2048 x 2052 (544) 9.8 / 11.3.
+constexpr double kQuarterTilesPack = 0.7, kQuarterTilesFused = 1.0, kQuarterTilesNarrow = 1.75;
 // The kernel for any N:M takes workgroups of 1024 threads instead of 256 up to two tiles for a compute unit, which is what one holds of
 // them: a unit to a thread instead of four to eight one after the other.  256 / 1024, us: fp32 8:16 464 x 128 5.9 / 4.3, 2048 x 1024 (512
 // tiles) 7.0 / 6.2, 2048^2 (1024) 10.5 / 11.9; 7:8 464 x 128 8.2 / 5.3, 2048 x 1024 13.9 / 11.8; bf16 8:16 464 x 128 7.3 / 4.7, 2048^2 (512) 9.8 / 7.9,
@@ -1654,6 +1659,14 @@ int tmask_apply_pack(const tmask_pack_desc *descs, int n, tmask_dtype dt, int N,
         TR = small ? TR / 2 : TR;
         threads = 64 * NW;
         lds_reserve = dt == TMASK_F32 && !small ? kPack4LdsReservePackF32 : 0;
+        if (n <= kFewMats && few_tiles(descs, n, 2 * TR, TC, kQuarterTilesPack)) {
+#define TMASK_PICK(DT, FM) \
+            if ((int)dt == DT && (int)mf == FM) few = pack24_kernel<DT, FM, kPack4Quarter, NW, 1, FewPackArgs>;
+            TMASK_PICK(kF32, kMaskU8) TMASK_PICK(kF32, kMaskBits) TMASK_PICK(kBF16, kMaskU8) TMASK_PICK(kBF16, kMaskBits)
+#undef TMASK_PICK
+            TC = kPack4Quarter * 16 / (uint32_t)elem_size((int)dt);
+            TR = Pack4Geo<kF32, kPack4Quarter, NW, 1>::TR;
+        }
     }
     if (narrow24) {
         // 8-byte strips, which write 4 bytes per row: tiles of 64 rows x 128 columns, a quarter of the others' bytes, since
@@ -1664,6 +1677,10 @@ int tmask_apply_pack(const tmask_pack_desc *descs, int n, tmask_dtype dt, int N,
         TC = PG::TC;
         TR = PG::TR;
         threads = PG::NT;
+        if (n <= kFewMats && few_tiles(descs, n, TR, TC, kQuarterTilesNarrow)) {
+            few = mf == TMASK_MASK_U8 ? pack24_kernel<kBF16N, kMaskU8, 32, 4, 1, FewPackArgs> : pack24_kernel<kBF16N, kMaskBits, 32, 4, 1, FewPackArgs>;
+            TR = Pack4Geo<kBF16N, 32, 4, 1>::TR;
+        }
     }
     bool fast48 = (M == 8 && N == 4 && dt == TMASK_BF16);
     for (int i = 0; i < n && fast48; i++)
@@ -1805,9 +1822,11 @@ int tmask_approx_pack(const tmask_fused_desc *descs, int n, tmask_dtype dt, int 
     const uint32_t half_rows = f48 ? (uint32_t)Pack8F32Geo<kPack8F32Half, 1>::TR : kPack4Rows / 2, half_cols = f48 ? (uint32_t)Pack8F32Geo<kPack8F32Half, 1>::TC : TC;
     const bool small = few_tiles(descs, n, kPack4Rows, TC, f48 ? kHalfTilesFusedF32M8 : dt == TMASK_F32 ? kHalfTilesFusedF32 : kHalfTilesFusedBf16) &&
                        (!want_obj || workspace_bytes >= partials_bytes(half_rows, half_cols));
+    const uint32_t quarter_rows = Pack4Geo<kF32, kPack4Quarter, 4, 1>::TR, quarter_cols = kPack4Quarter * 16 / (uint32_t)elem_size((int)dt);
+    const bool quarter = fused24 && small && few_tiles(descs, n, kPack4Rows, TC, kQuarterTilesFused) && (!want_obj || workspace_bytes >= partials_bytes(quarter_rows, quarter_cols));
     if (small) {
-        kPack4Rows = half_rows;
-        TC = half_cols;
+        kPack4Rows = quarter ? quarter_rows : half_rows;
+        TC = quarter ? quarter_cols : half_cols;
     }
     if (want_obj) {
         if (!workspace || ((uintptr_t)workspace & 255))
@@ -1823,6 +1842,11 @@ int tmask_approx_pack(const tmask_fused_desc *descs, int n, tmask_dtype dt, int 
         kern = with_mask ? approx_pack24_kernel<DT, FM, true, SS, QN> : approx_pack24_kernel<DT, FM, false, SS, QN>;
     TMASK_PICK(kF32, kMaskU8, SF, 4) TMASK_PICK(kF32, kMaskBits, SF, 4) TMASK_PICK(kBF16, kMaskU8, SB, 4) TMASK_PICK(kBF16, kMaskBits, SB, 4)
     TMASK_PICK(kF32, kMaskU8, SF, 2) TMASK_PICK(kF32, kMaskBits, SF, 2) TMASK_PICK(kBF16, kMaskU8, SB, 2) TMASK_PICK(kBF16, kMaskBits, SB, 2)
+#undef TMASK_PICK
+#define TMASK_PICK(DT, FM) \
+    if (quarter && (int)dt == DT && (int)mf == FM) \
+        kern = with_mask ? approx_pack24_kernel<DT, FM, true, kPack4Quarter, 1> : approx_pack24_kernel<DT, FM, false, kPack4Quarter, 1>;
+    TMASK_PICK(kF32, kMaskU8) TMASK_PICK(kF32, kMaskBits) TMASK_PICK(kBF16, kMaskU8) TMASK_PICK(kBF16, kMaskBits)
 #undef TMASK_PICK
     if (f48) {
 #define TMASK_PICK(FM, SS, QN) \

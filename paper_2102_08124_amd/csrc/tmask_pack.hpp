@@ -185,8 +185,9 @@ __device__ __forceinline__ void copy_short_lines(const uint8_t (*src)[LB], unsig
             copy_piece<LB>(&src[r][0], dst + (size_t)r * pitch, x, nb);
 }
 
-// The same of a tile that lies in LDS as [byte of the line][line]: NB bytes of TC lines.  Whole lines of eight-byte pieces go as above;
-// the dwords of others to one lane for each line (side by side they meet in one bank of LDS: 4:8 in one pass 17.9 -> 18.6 us).
+// The same of a tile that lies in LDS as [byte of the line][line]: NB bytes of TC lines.  Lines of eight bytes, or of aligned pieces of eight,
+// go as above; the dwords of others to one lane for each line (side by side they meet in one bank of LDS: 4:8 in one pass 17.9 -> 18.6 us;
+// two of them do not matter: 3300 x 2468 bf16 2:4 19.0 / 18.6).
 template <int NB, int TC, int NT>
 __device__ __forceinline__ void copy_columns(const uint8_t (*src)[TC], unsigned char *dst, size_t pitch, uint32_t cols, uint32_t nb)
 {
@@ -199,6 +200,13 @@ __device__ __forceinline__ void copy_columns(const uint8_t (*src)[TC], unsigned 
         for (uint32_t j = threadIdx.x; j < cols * P; j += NT) {
             const uint32_t c = j / P, x = j % P;
             *(u32x2 *)(dst + (size_t)c * pitch + 8 * x) = u32x2{word(8 * x, c), word(8 * x + 4, c)};
+        }
+        return;
+    }
+    if (NB == 8 && nb == 8u) {
+        for (uint32_t j = threadIdx.x; j < cols * 2u; j += NT) {
+            const uint32_t c = j / 2u, at = 4u * (j % 2u);
+            store_anywhere(word(at, c), dst + (size_t)c * pitch + at);
         }
         return;
     }

@@ -20,6 +20,7 @@
 namespace tmask {
 
 constexpr int kPack4Strips = 64;   // default tile width in strips of 16 bytes
+constexpr int kPack4Quarter = 32;  // width of quarter tiles, one block-row to a lane
 // Fewer resident tiles per compute unit than would fit run faster at fp32 (a tile stays resident for about 20 us
 // with four of them, half of a short launch; fewer of them finish sooner and leave a shorter tail, and fewer rows of
 // the matrix are open at a time): two for pack24_kernel (41.1 against 42.4 us on the ResNet-50 set, 75 against 72 %
@@ -122,7 +123,7 @@ __device__ __forceinline__ void pack24_copy_out(const PackDev &d, uint32_t row0,
             const u32x4 v = {OT[4 * part][sc], OT[4 * part + 1][sc], OT[4 * part + 2][sc], OT[4 * part + 3][sc]};
             stream_store(v, (u32x4 *)(dst + (size_t)cc * pitch_b + 16 * part));
         }
-    } else if constexpr (DT == kF32) {                 // a dword to a lane: 2156 x 4992 in one pass 24.1, four 24.8 us
+    } else if constexpr (DT != kBF16) {                // a dword to a lane: 2156 x 4992 in one pass 24.1, four 24.8 us
         for (uint32_t j = tid; j < cols_valid * OTD; j += kNT) {
             const uint32_t cc = j / OTD, x = j % OTD;
             if (x < rd)
@@ -145,7 +146,7 @@ __device__ __forceinline__ void pack24_copy_out(const PackDev &d, uint32_t row0,
 template <int DT, int FMT, int S, int NW, int QN, typename Args = PackArgs>
 __global__ __launch_bounds__(64 * NW) void pack24_kernel(const Args args)
 {
-    static_assert(QN == 2 || QN == 4, "a lane works through two or four block-rows");
+    static_assert(QN == 2 || QN == 4 || (QN == 1 && 64 / S == 2), "a lane works through two or four block-rows, or lanes l and l + 32 hold neighbours");
     using PG = Pack4Geo<DT, S, NW, QN>;
     constexpr int ES = PG::ES, C = PG::C, NG = PG::NG, TR = PG::TR, TC = PG::TC, OTD = PG::OTD,
                   TCP = PG::TCP, IDXB = PG::IDXB, LPR = PG::LPR, IDXTB = PG::IDXTB;
@@ -341,23 +342,28 @@ __global__ __launch_bounds__(64 * NW) void pack24_kernel(const Args args)
             for (int c = 0; c < C; c++)
                 tnib[c] &= keepmask;
         }
-        // the lane's columns are neighbours here too: its QN nibbles per column are QN / 2 bytes, written as
-        // QN / 2 rows of C bytes
+        // a lane's QN nibbles per column are QN / 2 bytes, as many rows of C bytes each; one nibble is completed by that of the lane
+        // half a wavefront further, which holds the next block-row
+        if constexpr (QN == 1) {
 #pragma unroll
-        for (int t = 0; t < QN / 2; t++) {
+            for (int c = 0; c < C; c++)
+                tnib[c] |= (uint32_t)__shfl_xor((int)tnib[c], 32, 64) << 4;
+        }
+        constexpr int ROWS = QN == 1 ? 1 : QN / 2;
+#pragma unroll
+        for (int t = 0; t < ROWS; t++) {
             uint32_t b[C / 4];
 #pragma unroll
             for (int h = 0; h < C / 4; h++)
                 b[h] = ((tnib[4 * h] >> (8 * t)) & 0xFFu) | (((tnib[4 * h + 1] >> (8 * t)) & 0xFFu) << 8) |
                        (((tnib[4 * h + 2] >> (8 * t)) & 0xFFu) << 16) | (((tnib[4 * h + 3] >> (8 * t)) & 0xFFu) << 24);
-            if constexpr (C == 4) {
-                *(uint32_t *)&IDXT[(QN / 2) * q4 + t][tcol] = b[0];
-            } else {
-                u32x2 v;
-                v.x = b[0];
-                v.y = b[1];
-                *(u32x2 *)&IDXT[(QN / 2) * q4 + t][tcol] = v;
-            }
+            if (QN == 1 && sub != 0)
+                break;
+            const uint32_t at = QN == 1 ? w : ROWS * q4 + t;
+            if constexpr (C == 4)
+                *(uint32_t *)&IDXT[at][tcol] = b[0];
+            else
+                *(u32x2 *)&IDXT[at][tcol] = u32x2{b[0], b[1]};
         }
     };
     if (row0 + TR <= d.rows && col0 + TC <= d.cols)

@@ -64,18 +64,32 @@ def test_lines_at_odd_bytes(N, M, dt, rows, cols, copies):
     assert float(obj[0]) == pytest.approx(total, rel=1e-5)
 
 
-@pytest.mark.parametrize("copies", [23, 25, 39, 41])             # 16 tiles each: either side of the lines for half tiles
-def test_half_and_whole_tiles_of_fp32_4of8(copies):
+@pytest.mark.parametrize("dt,N,M", [("f32", 4, 8), ("f32", 2, 4), ("bf16", 2, 4), ("bf16", 4, 8)])
+@pytest.mark.parametrize("copies", [3, 8, 9, 15, 17, 23, 25, 31, 33, 39, 41, 79, 81])   # 16 (bf16: 8) tiles each: either side of the lines
+def test_quarter_half_and_whole_tiles(dt, N, M, copies):                                # between quarter, half and whole tiles
     w = wl.gaussian_f32(200, 776, seed=57)
-    mask, total = oracle.approx(w, 4, 8)
-    want = [torch.from_numpy(np.ascontiguousarray(o)).cuda() for o in oracle.apply_pack(w, mask, 4, 8)]
+    w = w if dt == "f32" else wl.f32_to_bf16_bits(w)
+    mask, total = oracle.approx(w, N, M)
+    want = [torch.from_numpy(np.ascontiguousarray(o).view(np.uint8)).cuda() for o in oracle.apply_pack(w, mask, N, M)]
     ws, masks = [to_dev(w)] * copies, [mask_to_dev(mask, tm.TMASK_MASK_U8)] * copies
-    packed, fused = ([tm.alloc_packed(x, 4, 8) for x in ws] for _ in range(2))
-    obj, wsp = torch.zeros(copies, dtype=torch.float64, device="cuda"), tm.alloc_workspace(ws, 4, 8)
-    tm.tmask_apply_pack(ws, masks, packed, 4, 8)
-    tm.tmask_approx_pack(ws, None, fused, 4, 8, objective=obj, workspace=wsp)
+    packed, fused = ([tm.alloc_packed(x, N, M) for x in ws] for _ in range(2))
+    obj, wsp = torch.zeros(copies, dtype=torch.float64, device="cuda"), tm.alloc_workspace(ws, N, M)
+    tm.tmask_apply_pack(ws, masks, packed, N, M)
+    tm.tmask_approx_pack(ws, None, fused, N, M, objective=obj, workspace=wsp)
     torch.cuda.synchronize()
     for p in packed + fused:
         for got, o in zip(p, want):
-            assert torch.equal(got, o)
+            assert torch.equal(got.view(torch.uint8), o)
     assert obj.cpu().numpy() == pytest.approx(np.full(copies, total), rel=1e-5)
+
+
+@pytest.mark.parametrize("rows,cols", [(1000, 1028), (2048, 2052)])                     # quarter and half tiles of narrow strips
+def test_narrow_strips_of_one_matrix(rows, cols):
+    w = wl.f32_to_bf16_bits(wl.gaussian_f32(rows, cols, seed=58))
+    mask, _ = oracle.approx(w, 2, 4)
+    dev = to_dev(w)
+    packed = tm.alloc_packed(dev, 2, 4)
+    tm.tmask_apply_pack([dev], [mask_to_dev(mask, tm.TMASK_MASK_U8)], [packed], 2, 4)
+    torch.cuda.synchronize()
+    for got, o in zip(packed, oracle.apply_pack(w, mask, 2, 4)):
+        assert torch.equal(got.view(torch.uint8), torch.from_numpy(np.ascontiguousarray(o).view(np.uint8)).cuda())
