@@ -268,8 +268,8 @@ __device__ __forceinline__ double wave_kept(float v)
 }
 
 // Workgroup sum of per-thread fp32 values: inside a wavefront as above, fp64 across wavefronts.
-template <int DT = kF32>
-__device__ __forceinline__ double block_sum_f32(float v, double *lds /* kThreads/64 entries */)
+template <int DT = kF32, int NT = kThreads>
+__device__ __forceinline__ double block_sum_f32(float v, double *lds /* NT/64 entries */)
 {
     const double w = wave_kept<DT>(v);
     const int wave = threadIdx.x >> 6;
@@ -278,7 +278,7 @@ __device__ __forceinline__ double block_sum_f32(float v, double *lds /* kThreads
     __syncthreads();
     double r = lds[0];
 #pragma unroll
-    for (int k = 1; k < kThreads / 64; k++)
+    for (int k = 1; k < NT / 64; k++)
         r += lds[k];
     return r;
 }
@@ -376,7 +376,8 @@ __device__ __forceinline__ Handover handover(void *partials, const Tags &tags, u
 
 // Leaves t (the same in every thread) in the workgroup's record, or, as the last workgroup of its matrix, adds all of them to
 // *dst (not null), in the order of objective_reduce_kernel<256>: result i by thread i mod 256, one after the other, then each
-// wavefront, then the four.  red: four doubles of LDS (THREADS = 64: unused, a lane does the work of four).
+// wavefront, then the four.  red: a double of LDS for each wavefront (THREADS = 64: unused, a lane does the work of four; 512: the
+// upper four wavefronts have none to do).
 template <int THREADS>
 __device__ __forceinline__ void hand_over(const Handover &h, double t, double *red)
 {
@@ -394,7 +395,7 @@ __device__ __forceinline__ void hand_over(const Handover &h, double t, double *r
             *(double *)h.dst = t;
         return;
     }
-    static_assert(THREADS == 64 || THREADS == kThreads, "the order above");
+    static_assert(THREADS == 64 || THREADS == kThreads || THREADS == 2 * kThreads, "the order above");
     double total = 0.0;
     uint32_t left = kMostReads;
 #pragma nounroll
@@ -402,7 +403,7 @@ __device__ __forceinline__ void hand_over(const Handover &h, double t, double *r
         const uint32_t first = threadIdx.x + q;
         double sum = 0.0;
 #pragma nounroll
-        for (uint32_t i = first; i < h.others; i += kThreads) {
+        for (uint32_t i = THREADS > kThreads && first >= (uint32_t)kThreads ? h.others : first; i < h.others; i += kThreads) {
             uint32_t v[2];
             const bool came = take_words<2>(h.records + 2u * i, tags, v, left);
             sum += words_as_double(v[0], v[1], came);

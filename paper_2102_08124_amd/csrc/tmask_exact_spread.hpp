@@ -8,6 +8,7 @@
 // sixteen sums over sixteen lanes).  A round takes 150 instructions at M = 16.  The lanes are already those of the searches: no
 // collecting, no second reading of the weights.
 #pragma once
+#include "tmask_column.hpp"
 #include "tmask_device.hpp"
 #include "tmask_exact_balance.hpp"
 #include "tmask_networks.hpp"
@@ -91,24 +92,6 @@ __device__ __forceinline__ float row_sums(const float (&x)[M])
     const float u0 = (odd ? z[1] : z[0]) + read(odd ? z[0] : z[1], pair);
     const float u1 = (odd ? z[3] : z[2]) + read(odd ? z[2] : z[3], pair);
     return (upper ? u1 : u0) + read(upper ? u0 : u1, across);
-}
-
-// An M x M bit matrix held as one word per lane (lane l, bit i) -> its transpose (lane i, bit l): quarters off the diagonal
-// change places at sizes M/2, ..., 1.
-template <int M>
-__device__ __forceinline__ uint32_t transposed_bits(uint32_t w)
-{
-    auto step = [&](auto size, uint32_t other) {
-        constexpr int S = decltype(size)::value;
-        constexpr uint32_t m = S == 8 ? 0x00FFu : S == 4 ? 0x0F0Fu : S == 2 ? 0x3333u : 0x5555u;
-        w = (threadIdx.x & (uint32_t)S) ? ((w & ~m) | ((other >> S) & m)) : ((w & m) | ((other << S) & (m << S)));
-    };
-    if constexpr (M == 16)
-        step(std::integral_constant<int, 8>{}, dpp_read<kRowRor8>(w));
-    step(std::integral_constant<int, 4>{}, dpp_read<0x1B>(dpp_read<kRowHalfMirror>(w)));      // l ^ 7, then ^ 3
-    step(std::integral_constant<int, 2>{}, dpp_read<0x4E>(w));
-    step(std::integral_constant<int, 1>{}, dpp_read<0xB1>(w));
-    return w;
 }
 
 // exact_priced_start for a block in M lanes: cost = the costs of column j, x = its pruned rows, xrow = the pruned columns of row j;
@@ -205,11 +188,11 @@ __device__ __forceinline__ uint32_t exact_spread_start(const float (&cost)[M], u
 }
 
 // GENERAL: any N (K = args.K pruned per line); otherwise N = M/2.
-template <int DT, int M, int FMT, bool GENERAL, typename Args>
-__global__ __launch_bounds__(kThreads, 4) void exact_spread_kernel(const Args args)
+template <int DT, int M, int FMT, bool GENERAL, typename Args, int NT = kThreads>
+__global__ __launch_bounds__(NT, NT > kThreads ? 6 : 4) void exact_spread_kernel(const Args args)
 {
     using Ge = Geo<DT, M>;
-    constexpr int kWaves = kThreads / 64, NB = 64 / M;
+    constexpr int kWaves = NT / 64, NB = 64 / M;
     __shared__ int costs[kWaves][NB][M][M + 1];                   // of a wavefront's blocks, for their rows
     __shared__ SearchLds search_lds[kWaves];
     __shared__ double red[kWaves];
@@ -219,11 +202,9 @@ __global__ __launch_bounds__(kThreads, 4) void exact_spread_kernel(const Args ar
     const MatDev md = args.m[find_matrix(args, tile)];
     const Handover out = objective_of(args, md, tile);
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6, j = lane % M, blk = lane / M;
-    const uint32_t u = (tile - md.tile0) * kThreads + tid;        // columns of the block-rows, one after the other
-    const uint32_t s = u / Ge::C;
-    const bool valid = s < md.n_strips;
-    const StripPos pos = strip_pos(md, s);
-    const size_t col = (size_t)pos.sc * Ge::C + u % Ge::C;
+    const ColumnPos pos = column_pos<Ge::C>(md, (tile - md.tile0) * NT + tid);
+    const bool valid = pos.valid;
+    const size_t col = pos.col;
 
     // Lanes past the matrix' last column hold a filler block that any start balances (see exact_balanced_kernel).
     uint32_t a[M][1];
@@ -271,24 +252,9 @@ __global__ __launch_bounds__(kThreads, 4) void exact_spread_kernel(const Args ar
 #pragma unroll
     for (int i = 0; i < M; i++)
         acc += (kept >> i) & 1u ? __uint_as_float(a[i][0]) : 0.f;
-    if constexpr (FMT == kMaskU8) {
-        if (valid) {
-            unsigned char *row = (unsigned char *)md.mask + (size_t)pos.br * M * md.mask_ld + col;
-#pragma unroll
-            for (int i = 0; i < M; i++)
-                row[(size_t)i * md.mask_ld] = (unsigned char)((kept >> i) & 1u);
-        }
-    } else {
-        unsigned char *row = (unsigned char *)md.mask + (size_t)pos.br * M * md.mask_ld + (col >> 3);
-#pragma unroll
-        for (int i = 0; i < M; i++) {
-            const lanemask_t flags = lm((kept >> i) & 1u);
-            if (valid && (lane & 7u) == 0u)
-                row[(size_t)i * md.mask_ld] = (unsigned char)(flags >> lane);
-        }
-    }
+    store_column<M, FMT>(md, pos, kept);
     if (out.dst)
-        hand_over<kThreads>(out, block_sum_f32(valid ? acc : 0.f, red), red);
+        hand_over<NT>(out, block_sum_f32<kF32, NT>(valid ? acc : 0.f, red), red);
 }
 
 }  // namespace tmask

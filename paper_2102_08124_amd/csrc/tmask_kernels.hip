@@ -16,6 +16,7 @@
 #include "tmask_solvers.hpp"
 #include "tmask_approx4.hpp"
 #include "tmask_approx_sel.hpp"
+#include "tmask_approx_spread.hpp"
 #include "tmask_pack.hpp"
 #include "tmask_pack4.hpp"
 #include "tmask_pack8.hpp"
@@ -1220,12 +1221,15 @@ static int scratch_of_current_device(void **out)
     return TMASK_OK;
 }
 
-// Workgroups per compute unit up to which tmask_exact gives every column of a block a lane of its own: at M = 16 what a compute unit
+// Workgroups per compute unit up to which every column of a block has a lane of its own.  tmask_exact: at M = 16 what a compute unit
 // holds of that kernel, at M = 8 less, since a block is an eighth of the work there and the start of a kernel weighs more.  One matrix,
 // four columns / one column to a lane, us: fp32 8:16 464 x 128 28.9 / 14.3, 1024^2 (one workgroup per unit) 34.4 / 20.2, 2048^2 (4) 38.0 / 32.6, 4096 x
-// 2048 (8) 50.4 / 51.6; 13:16 4096 x 2048 55.1 / 55.3; 4:8 464 x 128 12.6 / 8.6, 1024 x 512 (1) 14.1 / 11.9, 1024^2 (2) 15.2 / 14.0, 2048 x
-// 1024 (4) 15.9 / 17.4; bf16 4:8 12.9 / 8.9, 14.4 / 12.0, 14.7 / 13.7, 14.9 / 16.9; 3:8 1024^2 16.7 / 14.0.
-static uint64_t spread_workgroups(int M) { return M == 16 ? 5u : 2u; }
+// 2048 (8) 50.4 / 51.6; 13:16 4096 x 2048 55.1 / 55.3; 4:8 464 x 128 12.6 / 8.6, 1024 x 512 (1) 14.1 / 11.2, 1024^2 (2) 15.2 / 11.8, 2048 x
+// 1024 (4) 15.9 / 17.4; bf16 4:8 12.9 / 8.9, 14.4 / 11.1, 14.7 / 11.5; 3:8 1024^2 16.7 / 12.4.
+// Algorithm 1 for bf16 at M = 16, eight columns / one: 8:16 1024 x 512 9.0 / 4.8, 1024^2 9.9 / 5.9, 2048^2 (4) 10.7 / 8.0, 3072 x 2048 (6) 10.8 / 10.1, 4096 x
+// 2048 (8) 11.4 / 12.5; 5:16 1024^2 12.8 / 6.0, 4096 x 2048 14.0 / 12.1; masked copies 8:16 1024^2 10.1 / 4.8, 4096 x 2048 12.4 / 10.9, 13:16 15.0 / 10.8.
+static uint64_t spread_exact(int M) { return M == 16 ? 5u : 2u; }
+static uint64_t spread_approx16(bool dense, int N) { return dense || N != 8 ? 8u : 6u; }
 
 // One launch for at most kWholeMats matrices of at most kWholeThreads strips at 2:4 (checked by the caller, like the rest).
 template <int SOLVER>
@@ -1337,7 +1341,9 @@ static int run_mask(const tmask_mat *mats, int n_mats, int dt, int N, int M, int
             kern = mf == kMaskU8 ? TMASK_MANY(exact24_kernel, kBF16, kMaskU8, 3, BatchArgs) : TMASK_MANY(exact24_kernel, kBF16, kMaskBits, 3, BatchArgs);
     }
     bool spread = false;
-    if (SOLVER == kSolveExact && (M == 8 || M == 16) && n_mats <= kMaxBatch) {
+    uint32_t threads = kThreads;
+    const bool can_spread = SOLVER == kSolveExact ? M == 8 || M == 16 : SOLVER == kSolveApprox && M == 16 && dt == kBF16 && !own_scratch;
+    if (can_spread && n_mats <= kMaxBatch) {
         uint64_t wgs = 0;
         LaunchSums sums;
         for (int i = 0; i < n_mats; i++) {
@@ -1345,18 +1351,26 @@ static int run_mask(const tmask_mat *mats, int n_mats, int dt, int N, int M, int
             sums.add((uint32_t)own, mats[i].objective);
             wgs += own;
         }
-        // Four of its workgroups take the weights that the workspace reserves 56 bytes for, 64 in records.  Where those do not fit, one
-        // matrix leaves its sum to a second launch, and several keep the one launch that the other kernel has for them.
-        const bool room = !want_obj || n_mats == 1 || sums.waiting > kMostWaiting || wgs * 16u <= ws_bytes;
-        spread = room && wgs <= spread_workgroups(M) * (uint64_t)cu_count();
+        // Four of its workgroups take the weights that the workspace reserves 56 bytes for, 64 in records.  Where those do not fit,
+        // workgroups of twice the threads leave half of them (8:16 of 1024^2 bf16 8.9 -> 5.9 us against a second launch, 4:8 fp32 14.0 -> 11.8; the
+        // optimal masks at M = 16 are faster with one: 20.2, 22.1); several matrices of tmask_exact keep the one launch of the other kernel.
+        const bool fits = !want_obj || sums.waiting > kMostWaiting || wgs * 16u <= ws_bytes, exact = SOLVER == kSolveExact;
+        spread = (fits || (n_mats <= kFewMats && (n_mats == 1 || !exact))) &&
+                 wgs <= (exact ? spread_exact(M) : spread_approx16(false, N)) * (uint64_t)cu_count();
+        threads = spread && !fits && !(exact && M == 16) ? 2u * kThreads : kThreads;
     }
-    if (spread) {
+    if (spread && SOLVER == kSolveExact) {
 #define TMASK_PICK(DT, MM, FM) \
     if (dt == DT && M == MM && mf == FM) \
         kern = 2 * N == M ? TMASK_BOTH(exact_spread_kernel, DT, MM, FM, false) : TMASK_BOTH(exact_spread_kernel, DT, MM, FM, true);
         TMASK_PICK(kF32, 8, kMaskU8) TMASK_PICK(kF32, 16, kMaskU8) TMASK_PICK(kBF16, 8, kMaskU8)
         TMASK_PICK(kBF16, 16, kMaskU8) TMASK_PICK(kF32, 8, kMaskBits) TMASK_PICK(kF32, 16, kMaskBits)
         TMASK_PICK(kBF16, 8, kMaskBits) TMASK_PICK(kBF16, 16, kMaskBits)
+#undef TMASK_PICK
+#define TMASK_PICK(DT, FM) \
+    if (dt == DT && mf == FM && threads > (uint32_t)kThreads) \
+        kern.few = 2 * N == M ? exact_spread_kernel<DT, 8, FM, false, FewArgs, 2 * kThreads> : exact_spread_kernel<DT, 8, FM, true, FewArgs, 2 * kThreads>;
+        TMASK_PICK(kF32, kMaskU8) TMASK_PICK(kF32, kMaskBits) TMASK_PICK(kBF16, kMaskU8) TMASK_PICK(kBF16, kMaskBits)
 #undef TMASK_PICK
     } else if (SOLVER == kSolveExact && (M == 8 || M == 16)) {
 #define TMASK_PICK(DT, MM, FM) \
@@ -1383,6 +1397,11 @@ static int run_mask(const tmask_mat *mats, int n_mats, int dt, int N, int M, int
         kern = mf == kMaskU8 ? TMASK_BOTH(approx_sel_bf16_kernel, 16, kMaskU8, false) : TMASK_BOTH(approx_sel_bf16_kernel, 16, kMaskBits, false);
     if (SOLVER == kSolveApprox && dt == kBF16 && M == 8 && N != 4)
         kern = mf == kMaskU8 ? TMASK_MANY(approx_sel_bf16_kernel, 8, kMaskU8, true, BatchArgs) : TMASK_MANY(approx_sel_bf16_kernel, 8, kMaskBits, true, BatchArgs);
+    if (spread && SOLVER == kSolveApprox) {
+        kern = mf == kMaskU8 ? TMASK_BOTH(approx_spread16_kernel, kMaskU8, false) : TMASK_BOTH(approx_spread16_kernel, kMaskBits, false);
+        if (threads > (uint32_t)kThreads)
+            kern.few = mf == kMaskU8 ? approx_spread16_kernel<kMaskU8, false, FewArgs, 2 * kThreads> : approx_spread16_kernel<kMaskBits, false, FewArgs, 2 * kThreads>;
+    }
     // the exact kernels give a lane half a strip of bf16 (twice the workgroups) or a column
     const uint32_t unit_split = spread ? (uint32_t)strip_cols(sdt) : (SOLVER == kSolveExact && exact_half_strips(dt, M)) ? 2u : 1u;
     hipStream_t stream = (hipStream_t)stream_;
@@ -1401,7 +1420,7 @@ static int run_mask(const tmask_mat *mats, int n_mats, int dt, int N, int M, int
                 rargs.objective[k] = t.objective;
                 rargs.tile0[k] = tiles;
                 args.m[k].aux = t.objective;
-                args.m[k].pad = tiles_of(args.m[k].n_strips * unit_split);
+                args.m[k].pad = (args.m[k].n_strips * unit_split + threads - 1) / threads;
                 sums.add(args.m[k].pad, t.objective);
                 tiles += args.m[k].pad;
             }
@@ -1416,7 +1435,7 @@ static int run_mask(const tmask_mat *mats, int n_mats, int dt, int N, int M, int
                 args.tags = draw_tags();
             {
                 ProfileScope prof(stream, first + kMaxBatch >= n_mats);
-                launch_kernel(kernel, dim3(tiles), dim3(kThreads), 0, stream, args);
+                launch_kernel(kernel, dim3(tiles), dim3(threads), 0, stream, args);
             }
             const hipError_t e = hipGetLastError();
             return e == hipSuccess ? TMASK_OK : hip_fail(e, "mask kernel launch");
@@ -1966,6 +1985,16 @@ static int run_mask_dense(const tmask_mask_dense_desc *descs, int n, tmask_dtype
                                        : TMASK_MANY(approx_dense_kernel, kBF16, MM, FM, kDenseRow1DHalfAbsorb, BatchArgs);
     TMASK_PICK(8, kMaskU8) TMASK_PICK(16, kMaskU8) TMASK_PICK(8, kMaskBits) TMASK_PICK(16, kMaskBits)
 #undef TMASK_PICK
+    uint32_t unit_split = 1;
+    if (M == 16 && dt == TMASK_BF16 && n <= kFewMats && (mode == kDenseApprox || mode == kDenseApproxHalf)) {
+        uint64_t wgs = 0;
+        for (int i = 0; i < n; i++)
+            wgs += (uint64_t)(descs[i].rows / M * descs[i].cols + kThreads - 1) / kThreads;
+        if (wgs <= spread_approx16(true, N) * (uint64_t)cu_count()) {
+            kern.few = mf == TMASK_MASK_U8 ? approx_spread16_kernel<kMaskU8, true, FewArgs> : approx_spread16_kernel<kMaskBits, true, FewArgs>;
+            unit_split = (uint32_t)strip_cols(sdt);
+        }
+    }
     hipStream_t stream = (hipStream_t)hip_stream;
     for (int first = 0; first < n; first += kMaxBatch) {
         const int nb = n - first < kMaxBatch ? n - first : kMaxBatch;
@@ -1977,7 +2006,7 @@ static int run_mask_dense(const tmask_mask_dense_desc *descs, int n, tmask_dtype
                 fill_desc(args.m[k], h, sdt, M, tiles);
                 args.m[k].aux = p.out;
                 args.m[k].pad = (uint32_t)p.ld_out;
-                tiles += tiles_of(args.m[k].n_strips);
+                tiles += tiles_of(args.m[k].n_strips * unit_split);
             }
             {
                 uint32_t first0[kMaxBatch + 1];

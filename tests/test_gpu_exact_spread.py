@@ -13,7 +13,8 @@ from .test_gpu_parity import _check_exact
 pytestmark = pytest.mark.gpu
 
 tm = pytest.importorskip("paper_2102_08124_amd.binding")
-from .gpu_util import run_masks  # noqa: E402
+torch = pytest.importorskip("torch")
+from .gpu_util import mask_to_host, run_masks, to_dev  # noqa: E402
 
 
 def _kinds(M, dt):
@@ -53,10 +54,39 @@ def test_both_kernels_against_the_oracle(N, M, dt, fmt):
 @pytest.mark.parametrize("N,M,rows,cols", [(8, 16, 512, 1024), (8, 16, 512, 1040), (4, 8, 512, 512), (4, 8, 512, 520)])
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
 def test_objective_with_and_without_room_for_the_records(N, M, rows, cols, dt):
-    # 32 workgroups of 256 strips of four columns have room for 128 records of 16 bytes, one more has not
+    # 32 workgroups of 256 strips of four columns have room for 128 records of 16 bytes, one more has not: a second launch at M =
+    # 16, workgroups of 512 threads at M = 8
     w = wl.gaussian_f32(rows, cols, seed=310)
     w = w if dt == "f32" else wl.f32_to_bf16_bits(w)
     (mask,), obj = run_masks(tm.tmask_exact, [w], N, M)
     mag = np.abs(w if dt == "f32" else (w.astype(np.uint32) << 16).view(np.float32)).astype(np.float64)
     # masks are checked above; a wavefront's 64 columns are added in fp32, at most M + 6 additions deep
     assert obj[0] == pytest.approx((mag * mask).sum(), rel=(M + 6) * 2.0 ** -24)
+
+
+@pytest.mark.parametrize("fmt", [tm.TMASK_MASK_U8, tm.TMASK_MASK_BITS])
+@pytest.mark.parametrize("N", [8, 1, 6, 15])
+def test_algorithm_1_for_bf16_at_m16(N, fmt):
+    """A column per lane up to 512 x 1024 (workgroups of 256 threads), 512 x 1040 (512) and for nine matrices; larger ones on the strips."""
+    ties = wl.f32_to_bf16_bits(wl.tie_heavy_f32(48, 336, 312, levels=3))
+    odd = wl.gaussian_f32(32, 272, seed=313)
+    odd[::5, ::3], odd[1::7], odd[:, 5] = np.inf, np.nan, -0.0
+    odd = wl.f32_to_bf16_bits(odd)
+    plain = [wl.f32_to_bf16_bits(wl.gaussian_f32(r, c, seed=314 + c)) for r, c in ((16, 16), (16, 256), (16, 272), (512, 1024), (512, 1040))]
+    for ws in [[w] for w in plain] + [[ties], [odd], plain[:2] + [ties, odd], plain[:3] * 3 + [ties]]:
+        masks, obj = run_masks(tm.tmask_approx, ws, N, 16, fmt, ld_pad=16)
+        for k, w in enumerate(ws):
+            want, total = oracle.approx(w, N, 16)
+            assert np.array_equal(masks[k], want), k
+            if np.isfinite(total):
+                assert obj[k] == pytest.approx(total, rel=1e-5)
+            dev = to_dev(w, ld=w.shape[1] + 8)
+            out, mask = torch.full(w.shape, 7.0, dtype=torch.bfloat16, device="cuda"), tm.alloc_masks([dev], fmt)
+            tm.tmask_approx_dense([dev], mask, [out], N, 16, mask_fmt=fmt)
+            alone = out.clone().fill_(3.0)
+            tm.tmask_approx_dense([dev], None, [alone], N, 16, mask_fmt=fmt)
+            torch.cuda.synchronize()
+            assert np.array_equal(mask_to_host(mask[0], w.shape[1], fmt), want)
+            bits = np.where(want != 0, w, np.uint16(0)).view(np.int16)
+            for o in (out, alone):
+                assert np.array_equal(o.view(torch.int16).cpu().numpy(), bits)
