@@ -1342,7 +1342,7 @@ static int run_mask(const tmask_mat *mats, int n_mats, int dt, int N, int M, int
     }
     bool spread = false;
     uint32_t threads = kThreads;
-    const bool can_spread = SOLVER == kSolveExact ? M == 8 || M == 16 : SOLVER == kSolveApprox && M == 16 && dt == kBF16 && !own_scratch;
+    const bool can_spread = SOLVER == kSolveExact ? M == 8 || M == 16 : SOLVER == kSolveApprox && M == 16 && dt == kBF16;
     if (can_spread && n_mats <= kMaxBatch) {
         uint64_t wgs = 0;
         LaunchSums sums;
@@ -1354,7 +1354,8 @@ static int run_mask(const tmask_mat *mats, int n_mats, int dt, int N, int M, int
         // Four of its workgroups take the weights that the workspace reserves 56 bytes for, 64 in records.  Where those do not fit,
         // workgroups of twice the threads leave half of them (8:16 of 1024^2 bf16 8.9 -> 5.9 us against a second launch, 4:8 fp32 14.0 -> 11.8; the
         // optimal masks at M = 16 are faster with one: 20.2, 22.1); several matrices of tmask_exact keep the one launch of the other kernel.
-        const bool fits = !want_obj || sums.waiting > kMostWaiting || wgs * 16u <= ws_bytes, exact = SOLVER == kSolveExact;
+        // By the size that a workspace must have, not by what this one has: the order of the additions is the same with any.
+        const bool fits = !want_obj || sums.waiting > kMostWaiting || wgs * 16u <= workspace_need(mats, n_mats, M), exact = SOLVER == kSolveExact;
         spread = (fits || (n_mats <= kFewMats && (n_mats == 1 || !exact))) &&
                  wgs <= (exact ? spread_exact(M) : spread_approx16(false, N)) * (uint64_t)cu_count();
         threads = spread && !fits && !(exact && M == 16) ? 2u * kThreads : kThreads;
