@@ -407,6 +407,15 @@ __global__ __launch_bounds__(NT) void pack_kernel(const Args args)
     // consecutive groups of a row); column units park W^T's values in LDS, column-major. ----
     const size_t pitchW = (size_t)(d.cols / M) * N;               // elements per row of vals
     const bool pair_ok = ES == 2 && ((N | (uint32_t)pitchW) & 1u) == 0;
+    constexpr int MD = M * ES / 4;                                // dwords of a group
+    // Large N: a slot of every lane to a store touches every line of a row N times, so the tile's rows leave whole at the end, through V, which
+    // the column units read until then.  Start / rows whole, us: fp32 13:16 1440^2 17.4 / 13.4, 4096^2 89.9 / 52.5, 8192 x 4096 178 / 121; 7:8
+    // 15.4 / 13.6, 69.7 / 52.0; 12:16 of 8192^2 301 / 183; bf16 13:16 4096^2 55.6 / 44.8, 15:16 66.1 / 47.2.  Small N pay more for the barrier and
+    // LDS than they save (fp32 3:8 4096^2 39.3 / 40.9, 5:16 1440^2 10.9 / 11.2), even N of bf16 leave by pairs (10:16 38.5 / 41.5), 9:16 and 11:16
+    // are even; so do calls for the kernel with 1024 threads (bf16 13:16 464 x 256 6.4 / 7.8).
+    constexpr bool WHOLE = NN == 0 && NT == kThreads && (ES == 4 ? M > 6 : M > 13);
+    const bool whole = WHOLE && (ES == 4 ? N > 5u : (N & 1u) && N > 12u);
+    [[maybe_unused]] uint32_t held[WHOLE ? (RU + NT - 1) / NT : 1][MD] = {};   // values of a row unit
 #pragma unroll
     for (int k = 0; k < (RU + CU + NT - 1) / NT; k++) {
         const uint32_t unit = tid + (uint32_t)k * NT;
@@ -457,6 +466,22 @@ __global__ __launch_bounds__(NT) void pack_kernel(const Args args)
                     } else {
                         put_code<NN * IB>(IDX[r], g, code);
                     }
+                    continue;
+                }
+            }
+            if constexpr (WHOLE) {
+                if (whole) {
+#pragma unroll
+                    for (int sl = 0; sl < M - 1; sl++) {
+                        if ((uint32_t)sl >= N)
+                            break;
+                        const uint32_t p = (uint32_t)__builtin_ctz(rem);
+                        rem &= rem - 1u;
+                        const uint32_t val = ((sel >> p) & 1u) ? (uint32_t)V[r][g * M + p] : 0u;
+                        held[k][sl * ES / 4] |= ES == 4 ? val : val << (16 * (sl & 1));
+                        code |= (unsigned long long)p << (sl * IB);
+                    }
+                    lds_or_bits(IDX[r], g * N * IB, code);
                     continue;
                 }
             }
@@ -520,6 +545,19 @@ __global__ __launch_bounds__(NT) void pack_kernel(const Args args)
         }
     }
     __syncthreads();
+    if (whole) {
+        // dword q of a group of row r in place (q + r) mod MD of the group: the lanes of a store are 64 / GPT rows and meet in no bank
+#pragma unroll
+        for (int k = 0; k < (RU + NT - 1) / NT; k++) {
+            const uint32_t unit = tid + (uint32_t)k * NT, r = unit / GPT, g = unit % GPT;
+            if (unit < (uint32_t)RU) {
+#pragma unroll
+                for (int q = 0; q < MD; q++)
+                    if ((uint32_t)q * (4 / ES) < N)
+                        ((uint32_t *)&V[r][0])[g * MD + (((uint32_t)q + r) & (uint32_t)(MD - 1))] = held[k][q];
+            }
+        }
+    }
 
     // ---- G: stream the staged W^T values and both index arrays out ----
     {
@@ -553,6 +591,28 @@ __global__ __launch_bounds__(NT) void pack_kernel(const Args args)
             copy_short_lines<IDXW * 4, NT>(lines, dst, pitch, r_valid, nb);
             copy_short_lines<IDXTW * 4, NT>(linesT, dstT, pitchT, c_valid, nbT);
         }
+    }
+    if (whole) {
+        __syncthreads();
+        const uint32_t n = g_valid * N, inv = 65535u / N + 1u;           // e / N = e * inv >> 16 for e < 256
+        T *dst = (T *)d.vals + (size_t)row0 * pitchW + (size_t)(col0 / M) * N;
+        auto value = [&](uint32_t r, uint32_t e) {
+            const uint32_t g = (e * inv) >> 16, sl = e - g * N;
+            const uint32_t w = ((const uint32_t *)&V[r][0])[g * MD + ((sl * ES / 4 + r) & (uint32_t)(MD - 1))];
+            return ES == 4 ? w : (w >> (16u * (sl & 1u))) & 0xFFFFu;
+        };
+        const uint32_t nd = (n * ES + 3u) / 4u, shift = nd > 16u ? 6u : nd > 1u ? 32u - (uint32_t)__builtin_clz(nd - 1u) : 0u;
+        const uint32_t x = tid & ((1u << shift) - 1u);
+        if (x < nd)
+            for (uint32_t r = tid >> shift; r < r_valid; r += (uint32_t)NT >> shift) {
+                T *line = dst + (size_t)r * pitchW;
+                if constexpr (ES == 4) {
+                    line[x] = value(r, x);
+                } else {
+                    const uint32_t e = min(2u * x, n - 2u);               // n > 12; the last dword may repeat an entry
+                    store_anywhere(value(r, e) | (value(r, e + 1u) << 16), (unsigned char *)(line + e));
+                }
+            }
     }
 }
 
