@@ -2,9 +2,8 @@
 // matrices excepted: the tiled pack kernel takes it; Algorithm 1 at 16:32 of aligned bf16 matrices has a row-per-lane kernel
 // here), (b) M = 4, 8, 16 when a matrix
 // misses the 16-byte alignment the strip kernels read with (8 bytes for bf16 at M = 4; only the method's own requirement is left: rows and cols
-// multiples of M, the masks being defined per M x M block; arXiv 2102.08124, Sec. 4) and (c) Algorithm 1 and row
-// pruning with N != M/2 at M = 16, where the strip kernels have only their rank form (Algorithm 1 at bf16 excepted: it
-// has a threshold form on the strips).  gfx950 only.
+// multiples of M, the masks being defined per M x M block; arXiv 2102.08124, Sec. 4) and (c) row pruning with N != M/2 at
+// M = 16, where the strip kernels have only their rank form.  gfx950 only.
 //
 // Layout.  A workgroup is one wavefront and works through tiles of M rows x 64 columns: lane l holds column l of the
 // tile, all M rows, in registers, read and written element by element (no alignment needed).  A block is the M
