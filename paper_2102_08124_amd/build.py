@@ -16,7 +16,7 @@ CALLS = os.path.join(HERE, "_calls.so")
 CALLS_SOURCE = os.path.join(CSRC, "tmask_calls.cpp")
 ABI = os.path.join(HERE, "..", "include", "tmask.h")
 SOURCES = ["tmask_kernels.hip", "tmask_colwise.hip", "tmask_spmm.hip", "tmask_extras.hip"]
-HEADERS = ["tmask_device.hpp", "tmask_solvers.hpp", "tmask_pack.hpp", "tmask_approx4.hpp", "tmask_networks.hpp", "tmask_approx_sel.hpp", "tmask_pack4.hpp", "tmask_pack8.hpp", "tmask_exact_balance.hpp", "tmask_exact_spread.hpp", "tmask_column.hpp", "tmask_approx_spread.hpp", "tmask_fused4.hpp", "tmask_spmm_choice.hpp", "tmask_sum_choice.hpp", "tmask_host.hpp", os.path.join("..", "..", "include", "tmask.h")]
+HEADERS = ["tmask_device.hpp", "tmask_solvers.hpp", "tmask_pack.hpp", "tmask_approx4.hpp", "tmask_networks.hpp", "tmask_pruned.hpp", "tmask_approx_sel.hpp", "tmask_pack4.hpp", "tmask_pack8.hpp", "tmask_exact_balance.hpp", "tmask_exact_spread.hpp", "tmask_column.hpp", "tmask_approx_spread.hpp", "tmask_fused4.hpp", "tmask_spmm_choice.hpp", "tmask_sum_choice.hpp", "tmask_host.hpp", os.path.join("..", "..", "include", "tmask.h")]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
          # packed fp32 VALU ops are kept off on the test machines

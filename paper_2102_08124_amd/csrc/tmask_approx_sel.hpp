@@ -13,6 +13,7 @@
 #pragma once
 #include "tmask_device.hpp"
 #include "tmask_networks.hpp"
+#include "tmask_pruned.hpp"
 
 namespace tmask {
 
@@ -247,54 +248,16 @@ __device__ __forceinline__ void middle_pair_row16(uint32_t (&s)[4], uint32_t gpo
     u = quad_xor_max<1>(ul, ul);
 }
 
-// The same at any cut: t = the (K+1)-th smallest, u = the K-th smallest.  The two runs of eight are merged into one of sixteen
-// (lane gpos holds its values 4 gpos .. 4 gpos + 3), and the lane that has the value passes it to the other three.
-__device__ __forceinline__ void cut_of_row16(uint32_t (&s)[4], uint32_t gpos, uint32_t K, uint32_t &t, uint32_t &u)
-{
-    sort_asc<4>(s);
-    const bool odd = (gpos & 1u) != 0u, far = (gpos & 2u) != 0u;
-    uint32_t m[4], n[4];
-    auto four = [](uint32_t (&v)[4]) { cmpx(v[0], v[2]); cmpx(v[1], v[3]); cmpx(v[0], v[1]); cmpx(v[2], v[3]); };
-#pragma unroll
-    for (int i = 0; i < 4; i++) {
-        const uint32_t hi = quad_xor_max<1>(s[i], s[3 - i]), lo = quad_xor_min<1>(s[i], s[3 - i]);
-        m[i] = odd ? hi : lo;
-    }
-    four(m);
-#pragma unroll
-    for (int i = 0; i < 4; i++) {
-        const uint32_t hi = quad_xor_max<3>(m[i], m[3 - i]), lo = quad_xor_min<3>(m[i], m[3 - i]);
-        n[i] = far ? hi : lo;
-    }
-#pragma unroll
-    for (int i = 0; i < 4; i++) {
-        const uint32_t hi = quad_xor_max<1>(n[i], n[i]), lo = quad_xor_min<1>(n[i], n[i]);
-        m[i] = odd ? hi : lo;
-    }
-    four(m);
-    auto value = [&](uint32_t at) {
-        const uint32_t low = (at & 1u) ? m[1] : m[0], high = (at & 1u) ? m[3] : m[2];
-        uint32_t v = gpos == at >> 2 ? ((at & 2u) ? high : low) : 0u;
-        v = quad_xor_max<1>(v, v);
-        return quad_xor_max<2>(v, v);
-    };
-    t = value(K);
-    u = value(K - 1u);
-}
-
 // a[i][c] = magnitude keys of the lane's strip (4 columns).  Fills bits[i] (bit c = keep) and the
 // kept sum; returns true if some line had a tie across its cut (result then invalid).
-// GENERAL: any number K of pruned entries per line, the same in every lane: the line's keys are
+// GENERAL (M = 8 only): any number K of pruned entries per line, the same in every lane: the line's eight keys are
 // sorted, t = the (K+1)-th smallest and u = the K-th smallest are read at a register index that every lane shares.
-// (At M = 16 the column-per-lane kernel, which sorts every row and column in a lane, did this before, with as many workgroups as there
-// are 256 strips: masks 224 x 128 13:16 32.3 -> 8.0 us, 4096 x 2048 3:16 47.5 -> 18.9, 7424 x 1984 13:16 47.5 -> 23.4; masked copies 31.4 -> 8.0,
-// 46.1 -> 20.7, 48.9 -> 27.7.  The copies hold the weights beside the magnitudes, 203 registers; reading them again instead,
-// with 128, is slower: 27.7 -> 35.4.)
 template <int M, bool GENERAL = false>
 __device__ __forceinline__ bool approx_half_f32(const uint32_t (&a)[M][4], uint32_t gpos, uint32_t (&rowbytes)[M],
                                                 float &sum, uint32_t k_general = 0)
 {
-    const uint32_t kidx = GENERAL ? (__builtin_amdgcn_readfirstlane(k_general) & (uint32_t)(M - 1)) : 0u;
+    static_assert(!GENERAL || M == 8, "a line of eight keys: one lane's column, two lanes' row");
+    const uint32_t kidx = GENERAL ? (__builtin_amdgcn_readfirstlane(k_general) & 7u) : 0u;
     constexpr int H = M / 2;
     uint32_t tcol[4];
     bool tie = false;
@@ -307,15 +270,10 @@ __device__ __forceinline__ bool approx_half_f32(const uint32_t (&a)[M][4], uint3
             hi[i] = a[H + i][c];
         }
         if constexpr (GENERAL) {
-            uint32_t srt[M];
-#pragma unroll
-            for (int i = 0; i < H; i++) {
-                srt[i] = lo[i];
-                srt[H + i] = hi[i];
-            }
-            sort_asc<M>(srt);
+            uint32_t srt[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+            sort_asc<8>(srt);
             tcol[c] = srt[kidx];
-            u = srt[(kidx - 1u) & (uint32_t)(M - 1)];
+            u = srt[(kidx - 1u) & 7u];
         } else {
             middle_pair<H>(lo, hi, tcol[c], u);
         }
@@ -327,9 +285,7 @@ __device__ __forceinline__ bool approx_half_f32(const uint32_t (&a)[M][4], uint3
     for (int i = 0; i < M; i++) {
         uint32_t s[4] = {a[i][0], a[i][1], a[i][2], a[i][3]};
         uint32_t trow, u;
-        if constexpr (GENERAL && M == 16) {
-            cut_of_row16(s, gpos, kidx, trow, u);
-        } else if constexpr (GENERAL) {
+        if constexpr (GENERAL) {
             uint32_t srt[8] = {s[0], s[1], s[2], s[3], quad_xor<1>(s[0]), quad_xor<1>(s[1]), quad_xor<1>(s[2]), quad_xor<1>(s[3])};
             sort_asc<8>(srt);
             trow = srt[kidx];
@@ -464,6 +420,59 @@ __device__ __forceinline__ void approx_half_f32_ties(const uint32_t (&a_in)[M][4
         rowbytes[i] = bytes;
         __builtin_amdgcn_sched_barrier(0);
     }
+}
+
+// M = 16 and any N: every line is held by one lane, which settles ties by position in place (pruned_of_line).  The lane has its
+// columns; of the block's rows it takes gpos, gpos + 4, ..., whose other parts the block's four lanes exchange: eight sorts of sixteen keys
+// in all, where thresholds of rows spread over the lanes take sixteen merges.  us, the column-per-lane kernel (a tile of 64 columns to a
+// wavefront) / merges and, behind a tie, the rank form / this, without ties and with zeros on both sides of the cuts: masks 224 x 128 5:16 30.1 /
+// 6.4 / 6.1 and 44.2 / 16.9 / 9.5, 4096 x 2048 42.5 / 12.0 / 10.7 and 58.8 / 28.8 / 15.6, 8192^2 73.3 / 63.9 / 57.3 and 94.1 / 175 / 73.3; masked copies
+// 8192^2 96.1 / 89.6 / 90.4 and 97.7 / 204 / 92.8.
+__device__ __forceinline__ void approx16_f32_by_lines(const u32x4 (&raw)[16], uint32_t gpos, uint32_t K, uint32_t (&rowbytes)[16], float &sum)
+{
+    uint32_t col[2] = {0u, 0u}, row[2] = {0u, 0u};              // pruned entries of the four columns (rows): sixteen bits each
+#pragma unroll
+    for (int c = 0; c < 4; c++) {
+        uint32_t mag[16];
+#pragma unroll
+        for (int i = 0; i < 16; i++)
+            mag[i] = raw[i][c] & 0x7FFFFFFFu;
+        col[c / 2] |= pruned_of_line<kF32, 16>(mag, K) << (16 * (c % 2));
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    const bool odd = (gpos & 1u) != 0u, far = (gpos & 2u) != 0u;
+#pragma unroll
+    for (int k = 0; k < 4; k++) {
+        uint32_t mag[16];
+#pragma unroll
+        for (int c = 0; c < 4; c++) {                           // the four rows' entries of column c in each lane: a 4 x 4 transpose
+            uint32_t v[4] = {raw[4 * k][c], raw[4 * k + 1][c], raw[4 * k + 2][c], raw[4 * k + 3][c]};
+            auto swap = [](bool upper, uint32_t &lo, uint32_t &hi, auto read) {
+                const uint32_t got = read(upper ? lo : hi);
+                lo = upper ? got : lo;
+                hi = upper ? hi : got;
+            };
+            swap(odd, v[0], v[1], quad_xor<1>);
+            swap(odd, v[2], v[3], quad_xor<1>);
+            swap(far, v[0], v[2], quad_xor<2>);
+            swap(far, v[1], v[3], quad_xor<2>);
+#pragma unroll
+            for (int q = 0; q < 4; q++)
+                mag[4 * q + c] = v[q] & 0x7FFFFFFFu;           // not before: the magnitudes would be held beside the weights
+        }
+        row[k / 2] |= pruned_of_line<kF32, 16>(mag, K) << (16 * (k % 2));
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    const uint32_t half[2] = {__builtin_amdgcn_perm(col[1], col[0], 0x06040200u), __builtin_amdgcn_perm(col[1], col[0], 0x07050301u)};
+    sum = 0.f;
+    each_of<16>([&](auto index) {                               // row i: bits of lane i mod 4 of the block
+        constexpr int i = decltype(index)::value;
+        const uint32_t bits = dpp_read<0x55 * (i % 4)>(row[i / 8]) >> (4 * gpos + 16 * (i / 4 % 2));
+        rowbytes[i] = ~(bits_to_bytes4(bits & 0xFu) | half[i / 8] >> (i % 8)) & 0x01010101u;
+#pragma unroll
+        for (int c = 0; c < 4; c++)
+            sum += __builtin_fabsf((rowbytes[i] >> (8 * c)) & 1u ? __uint_as_float(raw[i][c]) : 0.f);
+    });
 }
 
 }  // namespace tmask

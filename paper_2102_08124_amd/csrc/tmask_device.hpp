@@ -188,6 +188,16 @@ __device__ __forceinline__ uint32_t dpp_read(uint32_t v)
     return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, 0xF, 0xF, false);
 }
 
+// go(std::integral_constant<int, I>) for I = 0 ... M - 1: lane numbers within DPP controls are constants of the instruction.
+template <int M, int I = 0, typename Go>
+__device__ __forceinline__ void each_of(Go &&go)
+{
+    if constexpr (I < M) {
+        go(std::integral_constant<int, I>{});
+        each_of<M, I + 1>(go);
+    }
+}
+
 // What lane I of the M = 8 or 16 lanes of a block (an aligned part of sixteen lanes) holds.
 template <int M, int I>
 __device__ __forceinline__ uint32_t of_lane(uint32_t v)

@@ -116,7 +116,7 @@ __global__ __launch_bounds__(kThreads) void approx24_kernel(const Args args)
 
 // tmask_approx for fp32 with N = M/2, M = 8 or 16: thresholds on magnitudes; a wavefront in which some
 // line has a tie across its cut redoes its strips with the form that resolves ties by position (uniform branch).
-// GENERAL: any N, thresholds read from the sorted line; ties send the wavefront to the rank form.
+// GENERAL: any N, thresholds read from the sorted line; at M = 8 ties send the wavefront to the rank form, at M = 16 each line settles its own.
 template <int M, int FMT, bool GENERAL, typename Args>
 __global__ __launch_bounds__(kThreads, (M == 16 && FMT == kMaskBits) ? 4 : 1) void approx_sel_f32_kernel(const Args args)
 {
@@ -134,17 +134,21 @@ __global__ __launch_bounds__(kThreads, (M == 16 && FMT == kMaskBits) ? 4 : 1) vo
         u32x4 raw[M];
         load_strip<kF32, M>(md, pos, a, raw);
         uint32_t rowbytes[M];
-        const bool tie = approx_half_f32<M, GENERAL>(a, gpos, rowbytes, acc, args.K);
+        bool tie = false;
+        if constexpr (M == 16 && GENERAL)
+            approx16_f32_by_lines(raw, gpos, args.K, rowbytes, acc);
+        else
+            tie = approx_half_f32<M, GENERAL>(a, gpos, rowbytes, acc, args.K);
         uint32_t bits[M];
         // Some cut among equal values (a matrix full of zeros, say).  M = 8: the form that sorts them out by position
-        // (8192^2 with 90 % zeros: 80 -> 60 us).  M = 16: the rank form; the other one takes the kernel from 119 to
+        // (8192^2 with 90 % zeros: 80 -> 60 us).  M = 16 at N = 8: the rank form; the other one takes the kernel from 119 to
         // 154-209 registers whichever way it is attached, which costs the common case more (60 -> 69 us) than it
         // saves here (165 -> 118 us).
         bool stored = false;
         if (__any(tie)) {
             if constexpr (M == 8 && !GENERAL) {
                 approx_half_f32_ties<M>(a, gpos, rowbytes, acc);
-            } else {
+            } else if constexpr (M == 8 || !GENERAL) {
                 approx_keep<kF32, M, (M >= 16 && FMT == kMaskBits)>(a, args.K, gpos, bits);
                 acc = kept_sum<M, 4>(a, bits);
                 if constexpr (FMT == kMaskU8)
@@ -308,8 +312,8 @@ __global__ __launch_bounds__(kThreads) void approx_sel_bf16_kernel(const Args ar
 }
 
 // tmask_approx_dense / tmask_prune_1d_dense: a mask and the masked copy W (.) S in one pass.  Same tiling as the
-// kernels above; the keep flags come from the same routines.  MODE: kDenseApprox = Algorithm 1 in the rank form for
-// any N, kDenseApproxHalf = Algorithm 1 at N = M/2 (the lane-mask form at M = 4, the threshold networks at M = 8, 16),
+// kernels above; the keep flags come from the same routines.  MODE: kDenseApprox = Algorithm 1 for any N (fp32 at M = 16: every line
+// in a lane; bf16 at M = 8, 16: thresholds on unique keys; else the rank form), kDenseApproxHalf = Algorithm 1 at N = M/2 (the lane-mask form at M = 4, the threshold networks at M = 8, 16),
 // kDenseRow1D = N:M pruning along rows, kDenseRow1DAbsorb = the same with the mean of every row group's pruned
 // weights added to its kept ones (Sec. 5; fp32 sums inside the lane in position order, then across the lanes of the
 // group pairwise; bf16 results rounded to nearest even).  md.aux = the output matrix, md.pad = its leading dimension
@@ -370,15 +374,24 @@ __global__ __launch_bounds__(kThreads) void approx_dense_kernel(const Args args)
                 for (int i = 0; i < 4; i++)
                     bits[i] |= bytes4_to_bits(bytes[i]) << (4 * b);
             }
-        } else if constexpr ((HALFN && DT == kF32 && M >= 8) || (MODE == kDenseApprox && DT == kF32 && M == 16)) {
+        } else if constexpr (MODE == kDenseApprox && DT == kF32 && M == 16) {
+            uint32_t rowbytes[M];
+            float unused;
+            approx16_f32_by_lines(raw, gpos, args.K, rowbytes, unused);
+#pragma unroll
+            for (int i = 0; i < M; i++) {
+                bits[i] = bytes4_to_bits(rowbytes[i]);
+                asm volatile("" : "+v"(bits[i]));                // else the masked weights are made here and held through the mask's stores
+            }
+        } else if constexpr (HALFN && DT == kF32 && M >= 8) {
             uint32_t rowbytes[M];
             float unused = 0.f;
-            const bool tie = approx_half_f32<M, !HALFN>(a, gpos, rowbytes, unused, args.K);
+            const bool tie = approx_half_f32<M>(a, gpos, rowbytes, unused);
             if (__any(tie)) {
                 if constexpr (M == 8)
                     approx_half_f32_ties<M>(a, gpos, rowbytes, unused);
                 else
-                    approx_keep<kF32, M, false>(a, HALFN ? (uint32_t)(M / 2) : args.K, gpos, bits);
+                    approx_keep<kF32, M, false>(a, (uint32_t)(M / 2), gpos, bits);
             }
             if (M == 8 || !__any(tie)) {
 #pragma unroll

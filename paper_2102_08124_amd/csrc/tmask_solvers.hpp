@@ -743,16 +743,6 @@ struct SearchLds {
     uint32_t chain[64], start[64], flip_row[64], flip_col[64];
 };
 
-// go(std::integral_constant<int, I>) for I = 0 ... M - 1: lane numbers within DPP controls are constants of the instruction.
-template <int M, int I = 0, typename Go>
-__device__ __forceinline__ void each_of(Go &&go)
-{
-    if constexpr (I < M) {
-        go(std::integral_constant<int, I>{});
-        each_of<M, I + 1>(go);
-    }
-}
-
 // Augments until every row of the block has exactly K pruned entries (after at most M*M searches).  M lanes hold a
 // block, a wavefront 64 / M of them: lane j of the block holds column j (ccol, xcol: bit i = entry (i, j) pruned) and row
 // j (crow, xrow: bit c = entry (j, c) pruned).  All lanes of the wavefront take part; lanes with `active` false hold no block.

@@ -49,3 +49,34 @@ def test_masks_and_masked_copies(N, fmt):
             assert np.array_equal(mask_to_host(mask[0], w.shape[1], fmt), want), (k, ld)
             assert torch.equal(mask[0], other[0])
             assert np.array_equal(out.cpu().numpy().view(np.uint32), np.where(want != 0, w, np.float32(0)).view(np.uint32)), (k, ld)
+
+
+def _time(call, n=10):
+    """Best of three, of n calls each."""
+    marks = [torch.cuda.Event(enable_timing=True) for _ in range(4)]
+    call()
+    for k, mark in enumerate(marks):
+        mark.record()
+        for _ in range(n if k < 3 else 0):
+            call()
+    torch.cuda.synchronize()
+    return min(a.elapsed_time(b) for a, b in zip(marks, marks[1:]))
+
+
+@pytest.mark.parametrize("N", [3, 5, 13])
+def test_equal_magnitudes_cost_little(N):
+    """A mask found again for weights that are masked already: zeros on both sides of the cut of nearly every line.  Bound by memory
+    without ties; a form that starts a wavefront again takes two to three times as long."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(60 + N)
+    plain = torch.randn((8192, 8192), device="cuda", generator=gen)
+    masked = torch.empty_like(plain)
+    tm.tmask_approx_dense([plain], None, [masked], N, 16)
+    mask, out = tm.alloc_masks([plain])[0], torch.empty_like(plain)
+    times = []
+    for w in (plain, masked):
+        batch, dense = tm.MatBatch([w], [mask]), tm.DenseBatch([w], None, [out])
+        times.append((_time(lambda: tm.tmask_approx(batch, None, N, 16)), _time(lambda: tm.tmask_approx_dense(dense, None, None, N, 16))))
+    assert torch.equal(out, masked)
+    for before, after in zip(*times):
+        assert after < 1.8 * before, times

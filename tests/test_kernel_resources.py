@@ -87,6 +87,14 @@ def test_the_exact_kernels_keep_next_to_nothing_in_scratch_memory(kernels, m, wa
                 assert _wavefronts(use) == waves and use["scratch"] <= (0 if none else 20 if m == 8 else 12), (dt, fmt, general, use)
 
 
+@pytest.mark.parametrize("name", ["approx_sel_f32_kernel<16, %d, true>", "approx_dense_kernel<0, 16, %d, 0>"])
+@pytest.mark.parametrize("fmt", [0, 1])
+def test_any_n_at_m16_fits_four_wavefronts(kernels, name, fmt):
+    """Algorithm 1 on fp32: the weights are held once, magnitudes are taken where they are needed."""
+    use, = kernels[name % fmt]
+    assert _wavefronts(use) == 4 and use["scratch"] == 0, use
+
+
 @pytest.mark.parametrize("dt", [0, 1, 2])
 @pytest.mark.parametrize("fmt", [0, 1])
 def test_scores_at_m4_leave_room_for_eight_wavefronts(kernels, dt, fmt):
