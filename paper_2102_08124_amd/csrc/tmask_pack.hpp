@@ -566,8 +566,9 @@ __global__ __launch_bounds__(NT) void pack_kernel(const Args args)
         const size_t pitch = (size_t)(d.rows / M) * N;
         T *dst = (T *)d.valsT + (size_t)col0 * pitch + (size_t)(row0 / M) * N;
         if (ES == 4 || (((run | (uint32_t)pitch | (uint32_t)((row0 / M) * N)) & 1u) == 0)) {
-            // fp32 runs of more than 64 bytes: one to a wavefront's store (5:16 of 8192 x 4096 84 -> 75 us, two to a store 81)
-            const uint32_t rd = run * ES / 4, shift = ES == 4 && rd > 16u ? 6u : rd > 1u ? 32u - (uint32_t)__builtin_clz(rd - 1u) : 0u;
+            // fp32 runs of more than 64 bytes: one to a wavefront's store at M = 16 and 32 (5:16 of 8192 x 4096 84 -> 75 us, two to a store 81;
+            // 6:16 87 -> 78), two where they fit at M = 8 (3:8, 96 bytes: 69.8, one to a store 72.1; 8192^2 135, 139)
+            const uint32_t rd = run * ES / 4, shift = ES == 4 && M > 8 && rd > 16u ? 6u : rd > 1u ? 32u - (uint32_t)__builtin_clz(rd - 1u) : 0u;
             const uint32_t x = tid & ((1u << shift) - 1u);
             if (x < rd)
                 for (uint32_t c = tid >> shift; c < c_valid; c += (uint32_t)NT >> shift)

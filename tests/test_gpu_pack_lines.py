@@ -37,7 +37,7 @@ def _check(flat, views, used, want):
 
 
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
-@pytest.mark.parametrize("N,M", [(2, 4), (1, 4), (4, 8), (2, 8), (7, 8), (8, 16), (3, 16), (15, 16), (16, 32)])
+@pytest.mark.parametrize("N,M", [(2, 4), (1, 4), (4, 8), (2, 8), (3, 8), (7, 8), (8, 16), (3, 16), (15, 16), (16, 32)])
 @pytest.mark.parametrize("rows,cols", [(1, 1), (1, 3), (3, 1), (5, 33), (17, 9), (9, 41)])          # in blocks
 @pytest.mark.parametrize("copies", [1, 9])                       # workgroups of 1024 threads, of 256
 def test_lines_at_odd_bytes(N, M, dt, rows, cols, copies):
