@@ -81,7 +81,8 @@ typedef struct {
     int64_t rows, cols, ld;
     void *mask;        /* device; written by tmask_approx/tmask_exact, read by tmask_score */
     int64_t mask_ld;   /* bytes */
-    double *objective; /* device, nullable: [0] <- retained L1 = sum_ij S_ij |W_ij| (Eq. 3's objective) */
+    double *objective; /* device, nullable: [0] <- retained L1 = sum_ij S_ij |W_ij| (Eq. 3's objective).  The same bits whenever the
+                        * same call is made; with other matrices beside this one its parts may be added in another order. */
 } tmask_mat;
 
 /*
@@ -119,7 +120,8 @@ int tmask_approx_noalloc(const tmask_mat *mats, int n_mats, tmask_dtype dt, int 
  * bits below the block maximum, which costs less than M*(M-N)*2^-26 (resp. 2^-25, 2^-24) of the block
  * maximum in retained L1 (below 1e-5 relative for M <= 16; at M = 32 below 6e-5 in the worst case and
  * about 1e-7 on real-valued data).  Among equally good
- * masks the choice is deterministic but unspecified.  Inputs must be finite for optimality; with
+ * masks the choice is deterministic but unspecified; on the streaming kernels (layouts: above) it depends on the matrix alone, not
+ * on the others of the call nor on whether objectives are asked for.  Inputs must be finite for optimality; with
  * NaN/Inf present the mask is still valid (exactly N per row/column).
  */
 int tmask_exact(const tmask_mat *mats, int n_mats, tmask_dtype dt, int N, int M, tmask_mask_fmt mf,

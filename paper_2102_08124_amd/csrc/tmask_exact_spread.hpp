@@ -3,10 +3,15 @@
 // The kernel of tmask_exact_balance.hpp gives a lane four columns of a block, all work of a full chip at the fewest
 // instructions a block; a call of a few hundred blocks takes as long with it as one wavefront does: 13 rounds of 540 instructions
 // and a search at M = 16, 30 us.  Here M lanes hold a block from the loads to the mask, a quarter of the work each.  Lane j
-// holds column j and the price of row j: the prices reach the keys by DPP (an operand of the addition), and the rows' sums come
-// from a sum over lanes that halves the values at each step, so that lane j is left with row j's (33 instructions for
-// sixteen sums over sixteen lanes).  A round takes 150 instructions at M = 16.  The lanes are already those of the searches: no
-// collecting, no second reading of the weights.
+// holds column j and the price of row j: the prices reach the keys by DPP (an operand of the addition), and a round's columns reach the
+// rows' lanes through LDS, sixteen dwords written and four times four read.  A round takes 150 instructions at M = 16.  The lanes are
+// already those of the searches: no collecting, no second reading of the weights.
+//
+// Every sum is taken in the order of that kernel (four columns one after the other, then pairwise), and what a block's start and
+// searches do depends on the block alone: both kernels return the same mask, bit for bit, whatever else is in the call.  (Sums over
+// lanes that halve the values at each step are 33 instructions for sixteen rows and no LDS, but in another order; in this order, with
+// transposes over four lanes, 63.  us, halving / transposes / LDS: fp32 8:16 464 x 128 15.0 / 16.1 / 16.3, 2048^2 30.0 / 33.2 / 29.9, 2048 x
+// 2560 35.7 / 39.6 / 34.7; 4:8 128^2 8.8 / 9.2 / 9.6, 1024^2 11.6 / 12.3 / 11.8.)
 #pragma once
 #include "tmask_column.hpp"
 #include "tmask_device.hpp"
@@ -16,7 +21,7 @@
 
 namespace tmask {
 
-// v summed over the M lanes of a block, in every lane.
+// v summed over the M lanes of a block, in every lane (integers below 2^24: in any order).
 template <int M>
 __device__ __forceinline__ float over_lanes(float v)
 {
@@ -28,96 +33,69 @@ __device__ __forceinline__ float over_lanes(float v)
     return v;
 }
 
-// x[0 .. 8) of sixteen lanes, summed over lanes l, l ^ 7 of each eight: banks (four lanes) 0, 2 keep values 0 ... 3, banks 1, 3
-// values 4 ... 7.  Two additions for two values, each writing the banks that keep its sum.  (The waits: an operand that was just
-// written cannot be read across lanes for two instructions, on either side of the block.)
-__device__ __forceinline__ void halve8(const float (&x)[8], float (&y)[4])
-{
-    asm("s_nop 1\n\t"
-        "v_add_f32_dpp %0, %4, %4 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
-        "v_add_f32_dpp %1, %5, %5 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
-        "v_add_f32_dpp %2, %6, %6 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
-        "v_add_f32_dpp %3, %7, %7 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
-        "v_add_f32_dpp %0, %8, %8 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
-        "v_add_f32_dpp %1, %9, %9 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
-        "v_add_f32_dpp %2, %10, %10 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
-        "v_add_f32_dpp %3, %11, %11 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
-        "s_nop 1"
-        : "=&v"(y[0]), "=&v"(y[1]), "=&v"(y[2]), "=&v"(y[3])
-        : "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "v"(x[4]), "v"(x[5]), "v"(x[6]), "v"(x[7]));
-}
+// Lane I of the block's M.
+template <int M, int I>
+__device__ __forceinline__ float of_lane_f(float v) { return __uint_as_float(of_lane<M, I>(__float_as_uint(v))); }
 
-// The same for sixteen values: over lanes l, l ^ 8; lanes 0 ... 7 keep values 0 ... 7, the others 8 ... 15.
-__device__ __forceinline__ void halve16(const float (&x)[16], float (&y)[8])
-{
-    asm("s_nop 1\n\t"
-        "v_add_f32_dpp %0, %8, %8 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
-        "v_add_f32_dpp %1, %9, %9 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
-        "v_add_f32_dpp %2, %10, %10 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
-        "v_add_f32_dpp %3, %11, %11 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
-        "v_add_f32_dpp %4, %12, %12 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
-        "v_add_f32_dpp %5, %13, %13 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
-        "v_add_f32_dpp %6, %14, %14 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
-        "v_add_f32_dpp %7, %15, %15 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
-        "v_add_f32_dpp %0, %16, %16 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
-        "v_add_f32_dpp %1, %17, %17 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
-        "v_add_f32_dpp %2, %18, %18 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
-        "v_add_f32_dpp %3, %19, %19 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
-        "v_add_f32_dpp %4, %20, %20 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
-        "v_add_f32_dpp %5, %21, %21 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
-        "v_add_f32_dpp %6, %22, %22 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
-        "v_add_f32_dpp %7, %23, %23 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
-        "s_nop 1"
-        : "=&v"(y[0]), "=&v"(y[1]), "=&v"(y[2]), "=&v"(y[3]), "=&v"(y[4]), "=&v"(y[5]), "=&v"(y[6]), "=&v"(y[7])
-        : "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "v"(x[4]), "v"(x[5]), "v"(x[6]), "v"(x[7]),
-          "v"(x[8]), "v"(x[9]), "v"(x[10]), "v"(x[11]), "v"(x[12]), "v"(x[13]), "v"(x[14]), "v"(x[15]));
-}
-
-// x[i] summed over the M lanes of a block; lane j is left with the sum of x[j].
+// A block's values in LDS, row by row; rows are 16-byte pieces, of which those of eight lanes lie in different banks.
 template <int M>
-__device__ __forceinline__ float row_sums(const float (&x)[M])
+using SpreadBlock = uint32_t[M][M + 4];
+
+// LDS accesses of a wavefront happen in program order.
+__device__ __forceinline__ void lds_fence()
 {
-    float z[4];
-    if constexpr (M == 16) {
-        float y[8];
-        halve16(x, y);
-        halve8(y, z);
-    } else {
-        halve8(x, z);
+    __builtin_amdgcn_wave_barrier();
+    asm volatile("" ::: "memory");
+}
+
+// x[i] summed over the M lanes of a block; lane j is left with the sum of x[j].  Four columns one after the other, then these
+// pairwise: the order of lanes that hold four columns.
+template <int M>
+__device__ __forceinline__ float row_sums(const float (&x)[M], uint32_t j, SpreadBlock<M> &block)
+{
+#pragma unroll
+    for (int i = 0; i < M; i++)
+        block[i][j] = __float_as_uint(x[i]);
+    lds_fence();
+    float z[M / 4];
+#pragma unroll
+    for (int q = 0; q < M / 4; q++) {
+        const u32x4 r = *(const u32x4 *)&block[j][4 * q];
+        z[q] = ((__uint_as_float(r.x) + __uint_as_float(r.y)) + __uint_as_float(r.z)) + __uint_as_float(r.w);
     }
-    auto read = [](float v, auto ctrl) { return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), decltype(ctrl)::value, 0xF, 0xF, true)); };
-    constexpr std::integral_constant<int, 0xB1> pair{};
-    constexpr std::integral_constant<int, 0x4E> across{};
-    const bool odd = threadIdx.x & 1u, upper = threadIdx.x & 2u;
-    const float u0 = (odd ? z[1] : z[0]) + read(odd ? z[0] : z[1], pair);
-    const float u1 = (odd ? z[3] : z[2]) + read(odd ? z[2] : z[3], pair);
-    return (upper ? u1 : u0) + read(upper ? u0 : u1, across);
+    lds_fence();
+    if constexpr (M == 16)
+        return (z[0] + z[1]) + (z[2] + z[3]);
+    else
+        return z[0] + z[1];
 }
 
 // exact_priced_start for a block in M lanes: cost = the costs of column j, x = its pruned rows, xrow = the pruned columns of row j;
-// returns the excess.  The same rounds, sums in another order.
+// returns the excess.
 template <int M, bool GENERAL>
-__device__ __forceinline__ uint32_t exact_spread_start(const float (&cost)[M], uint32_t j, uint32_t &xcol, uint32_t &xrow, uint32_t K)
+__device__ __forceinline__ uint32_t exact_spread_start(const float (&cost)[M], uint32_t j, uint32_t &xcol, uint32_t &xrow, uint32_t K,
+                                                       SpreadBlock<M> &block)
 {
     constexpr int H = M / 2;
     constexpr int S = exact_cost_bits(M);
     constexpr float kOffset = (float)(1 << S);
     using Sched = PriceSchedule<M>;
-    const float own = row_sums<M>(cost);
-    const float mean = over_lanes<M>(own) * (1.f / (M * M));
+    const float own = row_sums<M>(cost, j, block);
+    float mean = 0.f, row_dev = 0.f, spread = 0.f;
+    each_of<M>([&](auto c) { mean += of_lane_f<M, decltype(c)::value>(own); });
+    mean = mean * (1.f / (M * M));
     const float dev = mean - own * (1.f / M);
-    float spread = 0.f;
-    {
-        float level[M];
-        each_of<M>([&](auto c) {
-            constexpr int i = decltype(c)::value;
-            level[i] = __uint_as_float(of_lane<M, i>(__float_as_uint(dev))) + cost[i];
-        });
-#pragma unroll
-        for (int i = 0; i < H; i++)
-            spread += __builtin_fabsf(level[i] - level[H + i]);
-    }
-    const PriceScale<M> scale(mean, over_lanes<M>(spread) * (2.f / (M * M)), over_lanes<M>(__builtin_fabsf(dev)));
+    each_of<M>([&](auto c) { row_dev += __builtin_fabsf(of_lane_f<M, decltype(c)::value>(dev)); });
+    each_of<H>([&](auto c) {
+        constexpr int i = decltype(c)::value;
+        const float rows = of_lane_f<M, i>(dev) - of_lane_f<M, H + i>(dev);
+        const float apart = __builtin_fabsf((cost[i] - cost[H + i]) + rows);
+        each_of<4>([&](auto lane) { spread += __uint_as_float(dpp_read<0x55 * decltype(lane)::value>(__float_as_uint(apart))); });
+    });
+    spread += __uint_as_float(dpp_read<kRowHalfMirror>(__float_as_uint(spread)));
+    if constexpr (M == 16)
+        spread += __uint_as_float(dpp_read<kRowRor8>(__float_as_uint(spread)));
+    const PriceScale<M> scale(mean, spread * (2.f / (M * M)), row_dev);
     float price = kOffset + scale.part * dev, vel = 0.f;
     float slope = scale.slope, step = scale.step;
     float drift = 0.f, dvel = 0.f;
@@ -131,7 +109,7 @@ __device__ __forceinline__ uint32_t exact_spread_start(const float (&cost)[M], u
         });
         float f[M];
         price_window<M, GENERAL>(k, slope, K, f);
-        vel = __builtin_fmaf(kCarry, vel, row_sums<M>(f));
+        vel = __builtin_fmaf(kCarry, vel, row_sums<M>(f, j, block));
         price = __builtin_fmaf(step, vel, price);
         dvel = __builtin_fmaf(kCarry, dvel, (float)K);
         drift = __builtin_fmaf(step, dvel, drift);
@@ -179,7 +157,7 @@ __device__ __forceinline__ uint32_t exact_spread_start(const float (&cost)[M], u
     if (__any(e > 2u)) {
         uint32_t x, xr;
         const uint32_t plain = choose(prices[0], x, xr);
-        const bool better = plain < e;
+        const bool better = plain < e && e > 2u;                 // a block's own excess decides, not its neighbours'
         e = better ? plain : e;
         xcol = better ? x : xcol;
         xrow = better ? xr : xrow;
@@ -193,7 +171,7 @@ __global__ __launch_bounds__(NT, NT > kThreads ? 6 : 4) void exact_spread_kernel
 {
     using Ge = Geo<DT, M>;
     constexpr int kWaves = NT / 64, NB = 64 / M;
-    __shared__ int costs[kWaves][NB][M][M + 1];                   // of a wavefront's blocks, for their rows
+    __shared__ __attribute__((aligned(16))) SpreadBlock<M> blocks[kWaves][NB];
     __shared__ SearchLds search_lds[kWaves];
     __shared__ double red[kWaves];
     const uint32_t K = GENERAL ? args.K : (uint32_t)(M / 2);
@@ -230,19 +208,18 @@ __global__ __launch_bounds__(NT, NT > kThreads ? 6 : 4) void exact_spread_kernel
 #pragma unroll
         for (int i = 0; i < M; i++)
             cost[i] = column[i][0];
-        const uint32_t e = exact_spread_start<M, GENERAL>(cost, j, xcol, xrow, K);
+        const uint32_t e = exact_spread_start<M, GENERAL>(cost, j, xcol, xrow, K, blocks[wave][blk]);
         if (__any(e != 0u)) {
             int ccol[M], crow[M];
 #pragma unroll
             for (int i = 0; i < M; i++) {
                 ccol[i] = (int)cost[i];
-                costs[wave][blk][i][j] = ccol[i];
+                blocks[wave][blk][i][j] = (uint32_t)ccol[i];
             }
-            __builtin_amdgcn_wave_barrier();                     // LDS accesses of a wavefront happen in program order
-            asm volatile("" ::: "memory");
+            lds_fence();
 #pragma unroll
             for (int c = 0; c < M; c++)
-                crow[c] = costs[wave][blk][j][c];
+                crow[c] = (int)blocks[wave][blk][j][c];
             exact_search<M>(ccol, crow, xcol, xrow, true, K, search_lds[wave]);
         }
     }

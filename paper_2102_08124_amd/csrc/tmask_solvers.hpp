@@ -727,7 +727,7 @@ __device__ __forceinline__ uint32_t exact_priced_start(const float (&cost)[M][CL
     if (__any(e2 > 4u)) {
         uint32_t x[CL];
         const uint32_t e = choose(std::false_type{}, x);
-        const bool better = e < e2;
+        const bool better = e < e2 && e2 > 4u;      // a block's own excess decides, not its neighbours'
         e2 = better ? e : e2;
 #pragma unroll
         for (int c = 0; c < CL; c++)
@@ -756,16 +756,18 @@ struct SearchLds {
 //
 // At convergence every predecessor edge is tight (label of the head = label of the tail + edge cost), so flipping along any
 // set of chains with no column in common keeps the pruning cheapest for its row counts.  The first reachable row that
-// lacks pruned entries takes its chain; at M = 16, when four or more rows have excess, as in blocks of tied values, every
-// such row does whose chain is still free, as long as that finds more than one.  (2048^2 8:16 with 50 % zeros 242 ->
-// 200 us, three levels 207 -> 172; at M = 8 the second walk costs more than it saves, 70 -> 75 us with 70 % zeros.)
+// lacks pruned entries takes its chain; at M = 16, when three or more rows of the block have excess, as in blocks of tied values, every
+// such row does whose chain is still free.  All of it depends on the block alone, not on those that share the wavefront: among equally
+// good masks it finds the same one in every call.  (2048^2 8:16 with 50 % zeros 242 ->
+// 200 us, three levels 207 -> 172; at M = 8 the second walk costs more than it saves, 70 -> 75 us with 70 % zeros.  Four or more rows of any
+// block of the wavefront, until no block found two / three or more of the block's own: 4096^2 8:16 50 % zeros 307 / 292, three levels
+// 326 / 324, 13:16 273 / 264 and 284 / 269, random values 75.5 / 75.5.)
 template <int M>
 __device__ __forceinline__ void exact_search(const int (&ccol)[M], const int (&crow)[M], uint32_t &xcol, uint32_t xrow,
                                              bool active, uint32_t K, SearchLds &lds)
 {
     static_assert(M <= 16, "a chain's rows and columns share a word");
     constexpr bool SEVERAL = M == 16;
-    bool several = true;
     const uint32_t lane = threadIdx.x & 63u, j = lane % M, base = lane - j;     // base: first lane of the block
     constexpr uint32_t kSeg = (uint32_t)((1ull << M) - 1ull);
     auto mine = [&](lanemask_t m) { return (uint32_t)(m >> base) & kSeg; };     // the block's bits of a ballot
@@ -818,7 +820,8 @@ __device__ __forceinline__ void exact_search(const int (&ccol)[M], const int (&c
         uint32_t cand = mine(lm(lacks));
         if (lm(cand != 0u) == 0)
             break;                      // cannot happen for 0 < K < M; guards against looping on corrupt state
-        if (!SEVERAL || !several || lm(__builtin_popcount(over) >= 4) == 0) {
+        const bool wide = SEVERAL && __builtin_popcount(over) >= 3;
+        if (lm(wide) == 0) {
             // the first reachable row takes its chain
             const uint32_t target = cand != 0u ? (uint32_t)__builtin_ctz(cand) : 0u;
             uint32_t r = target, src = kNoPred;
@@ -864,10 +867,11 @@ __device__ __forceinline__ void exact_search(const int (&ccol)[M], const int (&c
             lds.chain[lane] = chain;
             lds.start[lane] = start;
             fence();
-            // ... the lowest takes it, and so does each after it that shares no row or column with those taken and whose
-            // first row has excess left
-            uint32_t used = 0u, n = 0u;
+            // ... the lowest takes it, and so does, in a wide block, each after it that shares no row or column with those taken and
+            // whose first row has excess left
+            uint32_t used = 0u;
             bool taken = false;
+            cand = wide ? cand : cand & (0u - cand);
 #pragma unroll 1
             while (lm(cand != 0u) != 0) {
                 over = mine(lm(cnt > K));
@@ -875,13 +879,11 @@ __device__ __forceinline__ void exact_search(const int (&ccol)[M], const int (&c
                 const uint32_t ch = lds.chain[base + t], s = lds.start[base + t];
                 if (cand != 0u && s < (uint32_t)M && (ch & used) == 0u && (over >> (s & 31u) & 1u)) {
                     used |= ch;
-                    n++;
                     taken = taken || j == t;
                     cnt += (j == t ? 1u : 0u) - (j == s ? 1u : 0u);
                 }
                 cand &= cand - 1u;
             }
-            several = lm(n > 1u) != 0;                           // else one at a time from now on
             r = j;
 #pragma unroll 1
             for (int step = 0; step <= M && lm(taken) != 0; step++) {

@@ -51,6 +51,46 @@ def test_both_kernels_against_the_oracle(N, M, dt, fmt):
             assert s == pytest.approx(total, rel=1e-5)
 
 
+def _left(call, wsp):
+    """How a call with objectives of one matrix went, by what it changes in a workspace full of ones: ("one launch", workgroups) if
+    records of two words were there and are cleared, ("two", workgroups) if a result of each workgroup is left."""
+    wsp.fill_(0xFF)
+    call()
+    torch.cuda.synchronize()
+    words = wsp[:wsp.numel() // 8 * 8].view(torch.int64)
+    changed = words[words != -1]
+    if bool((changed == 0).all()):
+        return "one launch", changed.numel() // 2 + 1
+    return "two", changed.numel()
+
+
+@pytest.mark.parametrize("fmt", [tm.TMASK_MASK_U8, tm.TMASK_MASK_BITS])
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("N,M", [(4, 8), (3, 8), (8, 16), (5, 16), (15, 16)])
+def test_a_matrix_has_the_same_mask_in_every_call(N, M, dt, fmt):
+    """Where masks are equally good, too, the choice depends neither on the other matrices of the call nor on the objectives: alone with
+    and without one (a column to a lane), and beside a matrix with which the call takes four columns to a lane."""
+    rng = np.random.default_rng(320 + M)
+    f = lambda s: wl.gaussian_f32(12 * M, 33 * M, seed=321 + M + s)
+    sparse = f(0)
+    sparse[rng.random(sparse.shape) < 0.6] = 0
+    mixed = np.where((np.arange(33 * M) // M % 3 == 0)[None, :], wl.tie_heavy_f32(12 * M, 33 * M, 322, levels=2), f(1))
+    ws = [sparse, mixed, f(2), wl.tie_heavy_f32(12 * M, 33 * M, 323, levels=3)]
+    ws = _kinds(M, dt) + [w if dt == "f32" else wl.f32_to_bf16_bits(w) for w in ws]
+    large = wl.gaussian_f32(1024, 1040, seed=324)
+    large = to_dev(large if dt == "f32" else wl.f32_to_bf16_bits(large))
+    for k, w in enumerate(ws):
+        (alone,), _ = run_masks(tm.tmask_exact, [w], N, M, fmt)
+        (bare,), _ = run_masks(tm.tmask_exact, [w], N, M, fmt, with_objective=False)
+        both = [to_dev(w), large]
+        masks, obj, wsp = tm.alloc_masks(both, fmt), torch.zeros(2, dtype=torch.float64, device="cuda"), tm.alloc_workspace(both, N, M)
+        _, workgroups = _left(lambda: tm.tmask_exact(both, masks, N, M, objective=obj, mask_fmt=fmt, workspace=wsp), wsp)
+        # two matrices: one that waits in each that has two workgroups or more, and is counted once
+        assert workgroups <= -(-w.size // (1024 * M)) + -(-1024 * 1040 // (1024 * M)) + 1
+        assert np.array_equal(alone, bare), k
+        assert np.array_equal(alone, mask_to_host(masks[0], w.shape[1], fmt)), k
+
+
 @pytest.mark.parametrize("N,M,rows,cols", [(8, 16, 512, 1024), (8, 16, 512, 1040), (4, 8, 512, 512), (4, 8, 512, 520)])
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
 def test_objective_with_and_without_room_for_the_records(N, M, rows, cols, dt):
