@@ -28,7 +28,7 @@ __device__ __forceinline__ uint32_t kept_of_16(const uint32_t (&mag)[16], uint32
 
 // DENSE: the masked copy to md.aux, of leading dimension md.pad, and a mask if there is one; else the mask, and the kept sum.
 template <int FMT, bool DENSE, typename Args, int NT = kThreads>
-__global__ __launch_bounds__(NT) void approx_spread16_kernel(const Args args)
+__global__ __launch_bounds__(NT, NT > kThreads ? 6 : 1) void approx_spread16_kernel(const Args args)
 {
     constexpr int M = 16, kWaves = NT / 64;
     using Ge = Geo<kBF16, M>;

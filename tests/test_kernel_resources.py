@@ -87,6 +87,15 @@ def test_the_exact_kernels_keep_next_to_nothing_in_scratch_memory(kernels, m, wa
                 assert _wavefronts(use) == waves and use["scratch"] <= (0 if none else 20 if m == 8 else 12), (dt, fmt, general, use)
 
 
+def test_column_per_lane_kernels_of_small_calls_hold_all_in_registers(kernels):
+    uses = [(name, use) for name, found in kernels.items() if re.match("exact_spread|approx_spread16", name) for use in found]
+    assert len(uses) == 48
+    for name, use in uses:
+        assert use["scratch"] == 0, (name, use)
+        if name.startswith("exact_spread_kernel<") and ", 16," in name:
+            assert min(_wavefronts(use), 160 * 1024 // use["lds"]) >= 5, (name, use)     # of 256 threads: up to where they are chosen
+
+
 @pytest.mark.parametrize("name", ["approx_sel_f32_kernel<16, %d, true>", "approx_dense_kernel<0, 16, %d, 0>"])
 @pytest.mark.parametrize("fmt", [0, 1])
 def test_any_n_at_m16_fits_four_wavefronts(kernels, name, fmt):
@@ -107,8 +116,8 @@ def test_scores_at_m4_leave_room_for_eight_wavefronts(kernels, dt, fmt):
 
 def test_a_compute_unit_has_three_places_for_each_kernel_that_waits(kernels):
     """What the number of workgroups that may wait in a launch is reckoned with."""
-    waits = re.compile(r"mask_kernel<|approx24|approx_sel|exact24|exact_balanced|score_kernel<|approx_pack24|pack48_\w+<.*true|cw_mask|cw_exact|cw_score")
-    seen = 0
+    waits = re.compile(r"mask_kernel<|approx24|approx_sel|approx_spread16_kernel<\d, false|exact24|exact_balanced|exact_spread|score_kernel<|approx_pack24|pack48_\w+<.*true|cw_mask|cw_exact|cw_score")
+    seen = wide = 0
     for name, uses in kernels.items():
         if not waits.match(name) or name.startswith("mask_kernel<0, 1, 16,"):     # the generic form of Algorithm 1, which bf16 8:16 never takes
             continue
@@ -117,4 +126,5 @@ def test_a_compute_unit_has_three_places_for_each_kernel_that_waits(kernels):
             places = min(_wavefronts(use) * 4 // (use["threads"] // 64), 160 * 1024 // lds if lds else 32)
             assert places >= 3, (name, use)
             seen += 1
-    assert seen > 100
+            wide += use["threads"] == 512
+    assert seen > 100 and wide == 10              # 512 threads: the optimal masks at M = 8 and Algorithm 1 for bf16 at M = 16, in small calls
