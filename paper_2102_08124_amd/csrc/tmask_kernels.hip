@@ -53,7 +53,7 @@ __global__ __launch_bounds__(kThreads) void mask_kernel(const BatchArgs args)
         load_strip<DT, M>(md, pos, a, raw);
         static_assert(SOLVER == kSolveApprox || SOLVER == kSolveRow1D, "the exact solvers have kernels of their own");
         if constexpr (SOLVER == kSolveApprox) {
-            approx_keep<DT, M, (M >= 16 && FMT == kMaskBits)>(a, args.K, gpos, bits);
+            approx_keep<DT, M>(a, args.K, gpos, bits);
         } else {
             // structured N:M along rows only: an entry is kept iff at least K entries of its group of M
             // precede it in the (magnitude, position) order
@@ -1084,11 +1084,12 @@ static BatchKernel pick_mask_kernel(int dt, int M, int mf)
 {
 #define TMASK_PICK(DT, MM, FM) \
     if (dt == DT && M == MM && mf == FM) return TMASK_MANY(mask_kernel, SOLVER, DT, MM, FM);
-    TMASK_PICK(kF32, 4, kMaskU8) TMASK_PICK(kF32, 8, kMaskU8) TMASK_PICK(kF32, 16, kMaskU8)
-    TMASK_PICK(kBF16, 4, kMaskU8) TMASK_PICK(kBF16, 8, kMaskU8) TMASK_PICK(kBF16, 16, kMaskU8)
-    TMASK_PICK(kF32, 4, kMaskBits) TMASK_PICK(kF32, 8, kMaskBits) TMASK_PICK(kF32, 16, kMaskBits)
-    TMASK_PICK(kBF16, 4, kMaskBits) TMASK_PICK(kBF16, 8, kMaskBits) TMASK_PICK(kBF16, 16, kMaskBits)
-    TMASK_PICK(kBF16N, 4, kMaskU8) TMASK_PICK(kBF16N, 4, kMaskBits)
+    TMASK_PICK(kF32, 4, kMaskU8) TMASK_PICK(kBF16, 4, kMaskU8) TMASK_PICK(kBF16N, 4, kMaskU8)
+    TMASK_PICK(kF32, 4, kMaskBits) TMASK_PICK(kBF16, 4, kMaskBits) TMASK_PICK(kBF16N, 4, kMaskBits)
+    if constexpr (SOLVER == kSolveRow1D) {        // Algorithm 1 at M = 8, 16 has threshold forms for every N
+        TMASK_PICK(kF32, 8, kMaskU8) TMASK_PICK(kF32, 16, kMaskU8) TMASK_PICK(kBF16, 8, kMaskU8) TMASK_PICK(kBF16, 16, kMaskU8)
+        TMASK_PICK(kF32, 8, kMaskBits) TMASK_PICK(kF32, 16, kMaskBits) TMASK_PICK(kBF16, 8, kMaskBits) TMASK_PICK(kBF16, 16, kMaskBits)
+    }
 #undef TMASK_PICK
     return BatchKernel{nullptr, nullptr};
 }

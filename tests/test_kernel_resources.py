@@ -114,12 +114,16 @@ def test_scores_at_m4_leave_room_for_eight_wavefronts(kernels, dt, fmt):
         assert _wavefronts(use) == 8 and use["scratch"] == 0, use
 
 
+def test_no_form_of_algorithm_1_that_nothing_takes(kernels):
+    assert not [name for name in kernels if re.match(r"mask_kernel<0, \d, (8|16),", name)]
+
+
 def test_a_compute_unit_has_three_places_for_each_kernel_that_waits(kernels):
     """What the number of workgroups that may wait in a launch is reckoned with."""
     waits = re.compile(r"mask_kernel<|approx24|approx_sel|approx_spread16_kernel<\d, false|exact24|exact_balanced|exact_spread|score_kernel<|approx_pack24|pack48_\w+<.*true|cw_mask|cw_exact|cw_score")
     seen = wide = 0
     for name, uses in kernels.items():
-        if not waits.match(name) or name.startswith("mask_kernel<0, 1, 16,"):     # the generic form of Algorithm 1, which bf16 8:16 never takes
+        if not waits.match(name):
             continue
         for use in uses:
             lds = use["lds"] + (8192 if name.startswith("approx_pack24_kernel<0") else 0)         # reserved at the launch
