@@ -1,7 +1,7 @@
-"""tmask_exact at M = 8 and 16 has two kernels: calls that leave the chip idle give each column of a block a lane, all others four
-columns; so do several matrices that the first kernel would need a second launch for.  Both against the oracle on the same
-matrices, alone and beside a large one, and what the first leaves to a second launch when the workspace has no room for its
-records."""
+"""tmask_exact at M = 8 and 16, and Algorithm 1 for bf16 at M = 16, have two kernels: calls that leave the chip idle give each column
+of a block a lane, all others four (eight) columns; so do several matrices of tmask_exact that the first kernel would need a
+second launch for.  Both against the oracle on the same matrices, alone and beside a large one; and the first where the workspace has
+no room for its records: a second launch, or workgroups of 512 threads.  What a call changes in its workspace shows which way it went."""
 import numpy as np
 import pytest
 
@@ -31,37 +31,70 @@ def _kinds(M, dt):
     return [np.ascontiguousarray(w if dt == "f32" else wl.f32_to_bf16_bits(w)) for w in ws]
 
 
+def _changed(call, wsp):
+    """Runs a call with objectives on a workspace full of ones.  (True, words): it added up its sums itself, and cleared a record of two
+    words of 64 bits for each workgroup but a matrix' last; (False, words): it left a result of one word for each workgroup."""
+    wsp.fill_(0xFF)
+    call()
+    torch.cuda.synchronize()
+    words = wsp[:wsp.numel() // 8 * 8].view(torch.int64)
+    words = words[words != -1]
+    return not bool(words.any()), words.numel()
+
+
+def _run(find, ws, N, M, fmt, columns, threads=256):
+    """Masks and objectives, and (in one launch, changed words) as they are for workgroups of so many lanes, each holding so many columns."""
+    dev = [to_dev(w, ld=w.shape[1] + 16) for w in ws]
+    masks, obj, wsp = tm.alloc_masks(dev, fmt), torch.full((len(ws),), -1.0, dtype=torch.float64, device="cuda"), tm.alloc_workspace(dev, N, M)
+    for m in masks:
+        m.fill_(0xCD)
+    itself, words = _changed(lambda: find(dev, masks, N, M, objective=obj, mask_fmt=fmt, workspace=wsp), wsp)
+    per = [-(-w.size // (M * columns * threads)) for w in ws]
+    assert words == (sum(2 * (n - 1) for n in per) if itself else sum(per)), (itself, words, per)
+    return [mask_to_host(m, w.shape[1], fmt) for m, w in zip(masks, ws)], obj.cpu().numpy(), itself
+
+
+def _large(dt):
+    """Beside it no small matrix gets a column per lane: its records would not fit (M = 16), or there are too many workgroups (M = 8)."""
+    w = wl.gaussian_f32(1024, 1040, seed=311)
+    return w if dt == "f32" else wl.f32_to_bf16_bits(w)
+
+
 @pytest.mark.parametrize("fmt", [tm.TMASK_MASK_U8, tm.TMASK_MASK_BITS])
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
 @pytest.mark.parametrize("N,M", [(4, 8), (1, 8), (6, 8), (8, 16), (3, 16), (15, 16)])
 def test_both_kernels_against_the_oracle(N, M, dt, fmt):
     ws = _kinds(M, dt)
-    large = wl.gaussian_f32(512, 1040, seed=311)                 # with it the records of a column per lane do not fit
-    large = large if dt == "f32" else wl.f32_to_bf16_bits(large)
     together, sums = [], []
     for part in (ws[:5], ws[5:]):
-        masks, obj = run_masks(tm.tmask_exact, part + [large], N, M, fmt, ld_pad=16)
+        masks, obj, _ = _run(tm.tmask_exact, part + [_large(dt)], N, M, fmt, 4)
         together += masks[:-1]
         sums += list(obj[:-1])
     for k, w in enumerate(ws):
-        (alone,), own = run_masks(tm.tmask_exact, [w], N, M, fmt, ld_pad=16)
+        (alone,), own, _ = _run(tm.tmask_exact, [w], N, M, fmt, 1)
         _, total, per_block = oracle.exact(w, N, M, per_block=True, threads=8)
         for mask, s in ((alone, own[0]), (together[k], sums[k])):
             _check_exact(w, mask, N, M, per_block)
             assert s == pytest.approx(total, rel=1e-5)
 
 
-def _left(call, wsp):
-    """How a call with objectives of one matrix went, by what it changes in a workspace full of ones: ("one launch", workgroups) if
-    records of two words were there and are cleared, ("two", workgroups) if a result of each workgroup is left."""
-    wsp.fill_(0xFF)
-    call()
-    torch.cuda.synchronize()
-    words = wsp[:wsp.numel() // 8 * 8].view(torch.int64)
-    changed = words[words != -1]
-    if bool((changed == 0).all()):
-        return "one launch", changed.numel() // 2 + 1
-    return "two", changed.numel()
+@pytest.mark.parametrize("fmt", [tm.TMASK_MASK_U8, tm.TMASK_MASK_BITS])
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("N,M", [(4, 8), (1, 8), (7, 8), (8, 16), (1, 16), (15, 16)])
+def test_more_unbalanced_blocks_than_search_slots_on_the_strips(N, M, dt, fmt):
+    # 195 blocks (M = 8: 128 to a workgroup of strips, M = 16: 64; 32 and 16 are searched at a time), most of them left unbalanced
+    rng = np.random.default_rng(1700 + N + M)
+    rows, cols = 3 * M, 65 * M
+    base = wl.gaussian_f32(rows, cols, seed=1701 + M)
+    ws = [np.where(rng.random(base.shape) < 0.5, np.float32(0), base), wl.tie_heavy_f32(rows, cols, 1702, levels=3),
+          base * np.exp2(rng.integers(-20, 21, size=(rows, 1))).astype(np.float32)]
+    if dt == "bf16":
+        ws = [wl.f32_to_bf16_bits(w) for w in ws]
+    masks, obj, _ = _run(tm.tmask_exact, ws + [_large(dt)], N, M, fmt, 4)
+    for w, mask, s in zip(ws, masks, obj):
+        _, total, per_block = oracle.exact(w, N, M, per_block=True, threads=8)
+        _check_exact(w, mask, N, M, per_block)
+        assert s == pytest.approx(total, rel=1e-5)
 
 
 @pytest.mark.parametrize("fmt", [tm.TMASK_MASK_U8, tm.TMASK_MASK_BITS])
@@ -77,37 +110,76 @@ def test_a_matrix_has_the_same_mask_in_every_call(N, M, dt, fmt):
     mixed = np.where((np.arange(33 * M) // M % 3 == 0)[None, :], wl.tie_heavy_f32(12 * M, 33 * M, 322, levels=2), f(1))
     ws = [sparse, mixed, f(2), wl.tie_heavy_f32(12 * M, 33 * M, 323, levels=3)]
     ws = _kinds(M, dt) + [w if dt == "f32" else wl.f32_to_bf16_bits(w) for w in ws]
-    large = wl.gaussian_f32(1024, 1040, seed=324)
-    large = to_dev(large if dt == "f32" else wl.f32_to_bf16_bits(large))
     for k, w in enumerate(ws):
-        (alone,), _ = run_masks(tm.tmask_exact, [w], N, M, fmt)
+        (alone,), _, _ = _run(tm.tmask_exact, [w], N, M, fmt, 1)
         (bare,), _ = run_masks(tm.tmask_exact, [w], N, M, fmt, with_objective=False)
-        both = [to_dev(w), large]
-        masks, obj, wsp = tm.alloc_masks(both, fmt), torch.zeros(2, dtype=torch.float64, device="cuda"), tm.alloc_workspace(both, N, M)
-        _, workgroups = _left(lambda: tm.tmask_exact(both, masks, N, M, objective=obj, mask_fmt=fmt, workspace=wsp), wsp)
-        # two matrices: one that waits in each that has two workgroups or more, and is counted once
-        assert workgroups <= -(-w.size // (1024 * M)) + -(-1024 * 1040 // (1024 * M)) + 1
+        (beside, _), _, _ = _run(tm.tmask_exact, [w, _large(dt)], N, M, fmt, 4)
         assert np.array_equal(alone, bare), k
-        assert np.array_equal(alone, mask_to_host(masks[0], w.shape[1], fmt)), k
+        assert np.array_equal(alone, beside), k
 
 
-@pytest.mark.parametrize("N,M,rows,cols", [(8, 16, 512, 1024), (8, 16, 512, 1040), (4, 8, 512, 512), (4, 8, 512, 520)])
-@pytest.mark.parametrize("dt", ["f32", "bf16"])
-def test_objective_with_and_without_room_for_the_records(N, M, rows, cols, dt):
-    # 32 workgroups of 256 strips of four columns have room for 128 records of 16 bytes, one more has not: a second launch at M =
-    # 16, workgroups of 512 threads at M = 8
+def _check(w, mask, total, N, M, exact):
+    want, best, *per_block = oracle.exact(w, N, M, per_block=True, threads=8) if exact else oracle.approx(w, N, M)
+    if exact:
+        _check_exact(w, mask, N, M, per_block[0])
+    else:
+        assert np.array_equal(mask, want)
+    if np.isfinite(best):
+        assert total == pytest.approx(best, rel=1e-5)
+
+
+# The workspace has 56 bytes for 1024 columns of a block-row, and 256, where a column per lane leaves records of 64.
+@pytest.mark.parametrize("fmt", [tm.TMASK_MASK_U8, tm.TMASK_MASK_BITS])
+@pytest.mark.parametrize("find,dt,N,M,rows,cols,threads,itself", [
+    ("exact", "f32", 8, 16, 512, 1024, 256, True), ("exact", "bf16", 5, 16, 512, 1024, 256, True),
+    ("exact", "f32", 8, 16, 512, 1056, 256, False), ("exact", "bf16", 5, 16, 512, 1056, 256, False),
+    ("exact", "f32", 4, 8, 512, 512, 256, True), ("exact", "bf16", 3, 8, 512, 512, 256, True),
+    ("exact", "f32", 4, 8, 512, 528, 512, True), ("exact", "f32", 3, 8, 512, 528, 512, True), ("exact", "bf16", 4, 8, 512, 528, 512, True),
+    ("exact", "bf16", 3, 8, 1024, 512, 512, True), ("exact", "f32", 4, 8, 1024, 1016, 512, True),
+    ("approx", "bf16", 8, 16, 512, 1024, 256, True), ("approx", "bf16", 8, 16, 512, 1056, 512, True),
+    ("approx", "bf16", 5, 16, 512, 1056, 512, True), ("approx", "bf16", 8, 16, 1024, 1024, 512, True)])
+def test_with_and_without_room_for_the_records(find, dt, N, M, rows, cols, threads, itself, fmt):
     w = wl.gaussian_f32(rows, cols, seed=310)
+    w[:M] = wl.tie_heavy_f32(M, cols, 310, levels=3)
     w = w if dt == "f32" else wl.f32_to_bf16_bits(w)
-    (mask,), obj = run_masks(tm.tmask_exact, [w], N, M)
-    mag = np.abs(w if dt == "f32" else (w.astype(np.uint32) << 16).view(np.float32)).astype(np.float64)
-    # masks are checked above; a wavefront's 64 columns are added in fp32, at most M + 6 additions deep
-    assert obj[0] == pytest.approx((mag * mask).sum(), rel=(M + 6) * 2.0 ** -24)
+    (mask,), obj, one = _run(tm.tmask_exact if find == "exact" else tm.tmask_approx, [w], N, M, fmt, 1, threads)
+    assert one == itself
+    _check(w, mask, obj[0], N, M, find == "exact")
+
+
+@pytest.mark.parametrize("fmt", [tm.TMASK_MASK_U8, tm.TMASK_MASK_BITS])
+@pytest.mark.parametrize("N", [8, 13])
+def test_workgroups_of_512_threads_over_several_matrices(N, fmt):
+    ws = [wl.f32_to_bf16_bits(w) for w in (wl.gaussian_f32(512, 1056, seed=330), wl.gaussian_f32(16, 16, seed=331), wl.tie_heavy_f32(48, 336, 332, levels=3),
+                                           wl.gaussian_f32(16, 528, seed=333), wl.gaussian_f32(272, 1024, seed=334))]
+    masks, obj, itself = _run(tm.tmask_approx, ws, N, 16, fmt, 1, 512)
+    assert itself
+    for w, mask, total in zip(ws, masks, obj):
+        _check(w, mask, total, N, 16, False)
+
+
+@pytest.mark.parametrize("fmt", [tm.TMASK_MASK_U8, tm.TMASK_MASK_BITS])
+@pytest.mark.parametrize("N", [8, 5, 15])
+def test_algorithm_1_for_bf16_at_m16_on_the_strips(N, fmt):
+    """4096 x 2064: one workgroup of columns more than eight to each of 256 compute units."""
+    odd = wl.gaussian_f32(32, 272, seed=313)
+    odd[::5, ::3], odd[1::7], odd[:, 5] = np.inf, np.nan, -0.0
+    ws = [wl.f32_to_bf16_bits(w) for w in (wl.tie_heavy_f32(48, 336, 312, levels=3), odd, wl.gaussian_f32(4096, 2064, seed=335))]
+    masks, obj, _ = _run(tm.tmask_approx, ws, N, 16, fmt, 8)
+    dev = [to_dev(w) for w in ws]
+    outs, copies = [torch.full(w.shape, 7.0, dtype=torch.bfloat16, device="cuda") for w in ws], tm.alloc_masks(dev, fmt)
+    tm.tmask_approx_dense(dev, copies, outs, N, 16, mask_fmt=fmt)
+    torch.cuda.synchronize()
+    for w, mask, total, out, copy in zip(ws, masks, obj, outs, copies):
+        _check(w, mask, total, N, 16, False)
+        assert np.array_equal(mask_to_host(copy, w.shape[1], fmt), mask)
+        assert np.array_equal(out.view(torch.int16).cpu().numpy(), np.where(mask != 0, w, np.uint16(0)).view(np.int16))
 
 
 @pytest.mark.parametrize("fmt", [tm.TMASK_MASK_U8, tm.TMASK_MASK_BITS])
 @pytest.mark.parametrize("N", [8, 1, 6, 15])
 def test_algorithm_1_for_bf16_at_m16(N, fmt):
-    """A column per lane up to 512 x 1024 (workgroups of 256 threads), 512 x 1040 (512) and for nine matrices; larger ones on the strips."""
+    """A column per lane, with matrices of one block to 512 x 1040, and for ten of them in a call."""
     ties = wl.f32_to_bf16_bits(wl.tie_heavy_f32(48, 336, 312, levels=3))
     odd = wl.gaussian_f32(32, 272, seed=313)
     odd[::5, ::3], odd[1::7], odd[:, 5] = np.inf, np.nan, -0.0
