@@ -1,5 +1,5 @@
-// Kernels with a column of a block per lane, for calls that leave the chip idle: a workgroup takes 256 columns of the block-rows, one
-// after the other, and M neighbouring lanes hold a block.
+// Kernels with a column of a block per lane, for calls that leave the chip idle: a workgroup takes 256 or 512 columns (its threads) of
+// the block-rows, one after the other, and M neighbouring lanes hold a block.
 #pragma once
 #include <type_traits>
 

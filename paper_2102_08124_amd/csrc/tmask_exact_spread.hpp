@@ -10,8 +10,8 @@
 // Every sum is taken in the order of that kernel (four columns one after the other, then pairwise), and what a block's start and
 // searches do depends on the block alone: both kernels return the same mask, bit for bit, whatever else is in the call.  (Sums over
 // lanes that halve the values at each step are 33 instructions for sixteen rows and no LDS, but in another order; in this order, with
-// transposes over four lanes, 63.  us, halving / transposes / LDS: fp32 8:16 464 x 128 15.0 / 16.1 / 16.3, 2048^2 30.0 / 33.2 / 29.9, 2048 x
-// 2560 35.7 / 39.6 / 34.7; 4:8 128^2 8.8 / 9.2 / 9.6, 1024^2 11.6 / 12.3 / 11.8.)
+// transposes over four lanes, 63.  us, halving / transposes / LDS: fp32 8:16 464 x 128 15.4 / 16.1 / 16.1, 2048^2 30.6 / 33.2 / 30.3, 2048 x
+// 2560 36.8 / 39.6 / 35.7; 4:8 128^2 8.8 / 9.2 / 9.2, 1024^2 11.6 / 12.3 / 11.5.)
 #pragma once
 #include "tmask_column.hpp"
 #include "tmask_device.hpp"
@@ -37,9 +37,15 @@ __device__ __forceinline__ float over_lanes(float v)
 template <int M, int I>
 __device__ __forceinline__ float of_lane_f(float v) { return __uint_as_float(of_lane<M, I>(__float_as_uint(v))); }
 
-// A block's values in LDS, row by row; rows are 16-byte pieces, of which those of eight lanes lie in different banks.
+// A block's values in LDS, row by row.  Rows are M + 4 dwords apart, so that sixteen lanes read four dwords of a row each from
+// different banks, and blocks so that the lanes of a wavefront write a row of each to different ones (blocks without gaps: 4:8 1024^2
+// 11.8 us against 11.5, 8:16 464 x 128 16.8 against 16.1).
 template <int M>
-using SpreadBlock = uint32_t[M][M + 4];
+struct SpreadBlocks {
+    static constexpr int kPitch = M + 4, kBlock = M * kPitch;
+    static constexpr int kDwords = M == 16 ? 4 * (kBlock + 16) : 4 * (2 * kBlock + 8);       // of a wavefront
+    static constexpr __device__ uint32_t first(uint32_t blk) { return M == 16 ? blk * (kBlock + 16) : blk * kBlock + blk / 2u * 8u; }
+};
 
 // LDS accesses of a wavefront happen in program order.
 __device__ __forceinline__ void lds_fence()
@@ -51,16 +57,17 @@ __device__ __forceinline__ void lds_fence()
 // x[i] summed over the M lanes of a block; lane j is left with the sum of x[j].  Four columns one after the other, then these
 // pairwise: the order of lanes that hold four columns.
 template <int M>
-__device__ __forceinline__ float row_sums(const float (&x)[M], uint32_t j, SpreadBlock<M> &block)
+__device__ __forceinline__ float row_sums(const float (&x)[M], uint32_t j, uint32_t *block)
 {
+    constexpr int P = SpreadBlocks<M>::kPitch;
 #pragma unroll
     for (int i = 0; i < M; i++)
-        block[i][j] = __float_as_uint(x[i]);
+        block[i * P + j] = __float_as_uint(x[i]);
     lds_fence();
     float z[M / 4];
 #pragma unroll
     for (int q = 0; q < M / 4; q++) {
-        const u32x4 r = *(const u32x4 *)&block[j][4 * q];
+        const u32x4 r = *(const u32x4 *)&block[j * P + 4 * q];
         z[q] = ((__uint_as_float(r.x) + __uint_as_float(r.y)) + __uint_as_float(r.z)) + __uint_as_float(r.w);
     }
     lds_fence();
@@ -74,7 +81,7 @@ __device__ __forceinline__ float row_sums(const float (&x)[M], uint32_t j, Sprea
 // returns the excess.
 template <int M, bool GENERAL>
 __device__ __forceinline__ uint32_t exact_spread_start(const float (&cost)[M], uint32_t j, uint32_t &xcol, uint32_t &xrow, uint32_t K,
-                                                       SpreadBlock<M> &block)
+                                                       uint32_t *block)
 {
     constexpr int H = M / 2;
     constexpr int S = exact_cost_bits(M);
@@ -170,8 +177,9 @@ template <int DT, int M, int FMT, bool GENERAL, typename Args, int NT = kThreads
 __global__ __launch_bounds__(NT, NT > kThreads ? 6 : 4) void exact_spread_kernel(const Args args)
 {
     using Ge = Geo<DT, M>;
-    constexpr int kWaves = NT / 64, NB = 64 / M;
-    __shared__ __attribute__((aligned(16))) SpreadBlock<M> blocks[kWaves][NB];
+    constexpr int kWaves = NT / 64;
+    constexpr int P = SpreadBlocks<M>::kPitch;
+    __shared__ __attribute__((aligned(16))) uint32_t blocks[kWaves][SpreadBlocks<M>::kDwords];
     __shared__ SearchLds search_lds[kWaves];
     __shared__ double red[kWaves];
     const uint32_t K = GENERAL ? args.K : (uint32_t)(M / 2);
@@ -201,6 +209,7 @@ __global__ __launch_bounds__(NT, NT > kThreads ? 6 : 4) void exact_spread_kernel
         for (int i = 0; i < M; i++)
             a[i][0] = (((uint32_t)i + j) & (uint32_t)(M - 1)) < (uint32_t)M - K ? 0x3F800000u : 0u;
     }
+    uint32_t *const block = &blocks[wave][SpreadBlocks<M>::first(blk)];
     uint32_t xcol, xrow;
     {
         float column[M][1], cost[M];
@@ -208,18 +217,18 @@ __global__ __launch_bounds__(NT, NT > kThreads ? 6 : 4) void exact_spread_kernel
 #pragma unroll
         for (int i = 0; i < M; i++)
             cost[i] = column[i][0];
-        const uint32_t e = exact_spread_start<M, GENERAL>(cost, j, xcol, xrow, K, blocks[wave][blk]);
+        const uint32_t e = exact_spread_start<M, GENERAL>(cost, j, xcol, xrow, K, block);
         if (__any(e != 0u)) {
             int ccol[M], crow[M];
 #pragma unroll
             for (int i = 0; i < M; i++) {
                 ccol[i] = (int)cost[i];
-                blocks[wave][blk][i][j] = (uint32_t)ccol[i];
+                block[i * P + j] = (uint32_t)ccol[i];
             }
             lds_fence();
 #pragma unroll
             for (int c = 0; c < M; c++)
-                crow[c] = (int)blocks[wave][blk][j][c];
+                crow[c] = (int)block[j * P + c];
             exact_search<M>(ccol, crow, xcol, xrow, true, K, search_lds[wave]);
         }
     }
