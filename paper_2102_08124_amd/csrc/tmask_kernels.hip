@@ -1238,8 +1238,9 @@ static int scratch_of_current_device(void **out)
 // Workgroups per compute unit up to which every column of a block has a lane of its own.  tmask_exact: at M = 16 what a compute unit
 // holds of that kernel, at M = 8 less, since a block is an eighth of the work there and the start of a kernel weighs more.  One matrix,
 // four columns / one column to a lane, us: fp32 8:16 464 x 128 34.7 / 16.1, 2048 x 1024 (two workgroups per unit) 38.1 / 23.4, 2048^2 (4) 37.8 /
-// 30.3, 2048 x 2560 (5) 53.6 / 35.7, 4096 x 2048 (8) 50.4 / 51.6; 13:16 2048 x 2560 51.4 / 37.2; 4:8 128^2 13.6 / 9.2, 1024 x 512 (1) 15.9 / 11.1,
-// 1024^2 (2) 16.1 / 11.5, 2048 x 1024 (4) 15.9 / 17.4; bf16 4:8 11.7 / 8.1, 14.5 / 10.4, 15.0 / 11.2; 3:8 1024^2 17.7 / 12.5.
+// 30.3, 2048 x 2560 (5) 53.6 / 35.7, 3072 x 2048 (6) 46.5 / 40.4, 4096 x 2048 (8) 47.4 / 49.2; 13:16 2048 x 2560 51.4 / 37.2, 4096 x 2048 52.3 / 52.7;
+// 4:8 128^2 13.6 / 9.2, 1024 x 512 (1) 15.9 / 11.1, 1024^2 (2) 16.1 / 11.5, 2048 x 1024 (4) 15.5 / 14.4; bf16 4:8 11.7 / 8.1, 14.5 / 10.4, 15.0 / 11.2,
+// 2048 x 1024 14.2 / 14.4; 3:8 1024^2 17.7 / 12.5.  (The lines were swept with sums over lanes, 4:8 2048 x 1024 17.4 then; six and four would do now.)
 // Algorithm 1 for bf16 at M = 16, eight columns / one: 8:16 1024 x 512 9.0 / 4.8, 1024^2 9.9 / 5.9, 2048^2 (4) 10.7 / 8.0, 3072 x 2048 (6) 10.8 / 10.1, 4096 x
 // 2048 (8) 11.4 / 12.5; 5:16 1024^2 12.8 / 6.0, 4096 x 2048 14.0 / 12.1; masked copies 8:16 1024^2 10.1 / 4.8, 4096 x 2048 12.4 / 10.9, 13:16 15.0 / 10.8.
 static uint64_t spread_exact(int M) { return M == 16 ? 5u : 2u; }
